@@ -143,6 +143,33 @@ __device__ __forceinline__ float block_excl_scan_f(float v, float *tmp, float *t
     return base + prev;
 }
 
+// Sum of the values of the threads ABOVE this one, and of all (an exclusive scan from the last thread down).
+template <int THREADS>
+__device__ __forceinline__ float block_above_scan_f(float v, float *tmp, float *total)
+{
+    constexpr int NW = THREADS / NGC_WAVE;
+    float incl = v;   // this lane and those above it
+#pragma unroll
+    for (int o = 1; o < NGC_WAVE; o <<= 1) {
+        const float t = __shfl_down(incl, o, NGC_WAVE);
+        if (lane_id() + o < NGC_WAVE) incl += t;
+    }
+    if (lane_id() == 0) tmp[wave_id()] = incl;
+    __syncthreads();
+    float base = 0.f, all = 0.f;
+#pragma unroll
+    for (int w = NW - 1; w >= 0; --w) {
+        const float t = tmp[w];
+        if (w > wave_id()) base += t;
+        all += t;
+    }
+    __syncthreads();
+    *total = all;
+    float prev = __shfl_down(incl, 1, NGC_WAVE);
+    if (lane_id() == NGC_WAVE - 1) prev = 0.f;
+    return base + prev;
+}
+
 template <int THREADS>
 __device__ __forceinline__ float block_sum_f(float v, float *tmp)
 {

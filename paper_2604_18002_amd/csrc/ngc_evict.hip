@@ -49,14 +49,139 @@ struct LogprobArgs {
     int32_t *status;
     int64_t logit_stride;
     int sigma_stride;
-    int stage_cap;   // floats of dynamic LDS for the picked items' terms
+    int stage_cap;   // floats of dynamic LDS for the picked items' terms (general route)
+    int row_cap;     // floats of dynamic LDS for a segment's row
 };
 
-// One workgroup per segment; LDS bitmap of picked items (65536 bits).
-template <int THREADS>
+// Both kernels below (Eq. 2 for given actions, and its gradient) read a segment's row once into LDS and its
+// sigma once into registers.  Thread i owns PICKS consecutive picks -- thread 0 the LAST ones, so that an ordinary
+// exclusive scan over threads yields the mass of everything picked after a thread's own -- and keeps their terms in
+// registers between the passes.  A pick marks its item in the LDS row (an exchange, which also finds repeated
+// picks); what stays unmarked was never picked.  Rows that do not fit (N > row_cap) and rows whose logits span more
+// than NGC_WIDE_SPREAD take the general route: a bitmap of picked items and re-reads of the row.
+//
+// What bounds them: 3584 segments of ~2970 items and ~2460 picks (84 MB in, for the gradient 43 MB out; ~15 and
+// ~24 us of traffic) took 61 us and 102 us with the general route alone: three reads of the row and up to three
+// gathers per pick, each pass waiting for global memory.  One read of the row: 38 and 47 us; with the logarithm of a
+// product instead of a logarithm per pick and the shorter exponential 35 and 44 us.  What is left is the chain of
+// one workgroup (row, marks, two scans, the way out) over 3.5 rounds of resident workgroups.
+constexpr uint32_t PICKED_MARK = 0x7FFFFFFFu;   // a NaN: the row in LDS holds none (NaN logits become -inf)
+
+template <int THREADS, int PICKS>
+struct PickedTerms {
+    float d[PICKS];     // s - max s of this thread's picks (latest pick last)
+    float e[PICKS];     // exp(d); 0 past the end
+    int t[PICKS];       // item index; -1 past the end, -2 for an index outside the segment
+    float after;        // mass of everything picked after them
+    float unpicked;     // mass never picked (U of Eq. 2)
+    float smax;
+    int j_lo, count;    // picks j_lo .. j_lo + count - 1
+};
+
+// Returns false (workgroup-uniform) when the segment needs the general route; the LDS row is then free for it.
+// lds_row: row_cap floats; with KEEP_ROW it holds exp(s - max s) of the items never picked and -1 for the picked ones
+// on return, otherwise it is scratch.  fmisc: 32 floats.
+template <int THREADS, int PICKS, bool KEEP_ROW>
+__device__ __forceinline__ bool gather_picked(const float *row, const int32_t *sig, int N, int K, int row_cap,
+                                              float *lds_row, float *fmisc, int32_t *status,
+                                              PickedTerms<THREADS, PICKS> &pt)
+{
+    const int tid = threadIdx.x;
+    if (N > row_cap || K > THREADS * PICKS) return false;
+    const int per = (K + THREADS - 1) / THREADS;          // <= PICKS
+    const int owners = (K + per - 1) / per;
+    pt.j_lo = (owners - 1 - tid) * per;
+    pt.count = tid < owners ? (pt.j_lo + per <= K ? per : K - pt.j_lo) : 0;
+    if (tid >= owners) pt.j_lo = 0;
+#pragma unroll
+    for (int i = 0; i < PICKS; ++i) pt.t[i] = i < pt.count ? sig[pt.j_lo + i] : -1;
+    float smax = -INFINITY, neg_smin = -INFINITY;   // over the unmasked entries
+    auto take = [&](float x) {
+        if (x == x) smax = fmaxf(smax, x);
+        if (x > -INFINITY) neg_smin = fmaxf(neg_smin, -x);
+        return (x != x) ? -INFINITY : x;
+    };
+    if ((reinterpret_cast<uintptr_t>(row) & 15u) == 0) {      // workgroup-uniform
+        const int quads = N >> 2;
+        for (int i = tid; i < quads; i += THREADS) {
+            f32x4 v = reinterpret_cast<const f32x4 *>(row)[i];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = take(v[u]);
+            reinterpret_cast<f32x4 *>(lds_row)[i] = v;
+        }
+        for (int i = 4 * quads + tid; i < N; i += THREADS) lds_row[i] = take(row[i]);
+    } else {
+        for (int i = tid; i < N; i += THREADS) lds_row[i] = take(row[i]);
+    }
+    block_max2_f<THREADS>(smax, neg_smin, fmisc);             // its barriers also publish the row
+    if (smax > -INFINITY && smax + neg_smin > NGC_WIDE_SPREAD) return false;
+    if (smax == -INFINITY) smax = 0.f;                        // every entry masked: all weights are 0
+    pt.smax = smax;
+    float mass = 0.f;
+    int bad = 0;
+#pragma unroll
+    for (int i = 0; i < PICKS; ++i) {
+        pt.d[i] = 0.f;
+        pt.e[i] = 0.f;
+        if (i < per) {                                        // uniform
+            if (i < pt.count) {
+                int t = pt.t[i];
+                float x;
+                const bool inside = t >= 0 && t < N;
+                uint32_t bits = PICKED_MARK;
+                if (inside) bits = atomicExch(reinterpret_cast<uint32_t *>(&lds_row[t]), PICKED_MARK);
+                x = __uint_as_float(bits);
+                if (bits == PICKED_MARK) {                    // out of range, or picked before: counted, then read again
+                    bad = 1;
+                    t = t < 0 ? 0 : (t >= N ? N - 1 : t);
+                    x = row[t];
+                    x = (x != x) ? -INFINITY : x;
+                    if (!inside) pt.t[i] = -2;
+                }
+                pt.d[i] = x - smax;
+                pt.e[i] = exp_shifted(pt.d[i]);
+                mass += pt.e[i];
+            }
+        }
+    }
+    if (bad) atomicAdd(&status[NGC_STATUS_BAD_SIGMA], 1);
+    __syncthreads();                                          // every pick has marked its item
+    float unpicked = 0.f;
+    for (int i = tid; i < N; i += THREADS) {
+        const uint32_t bits = __float_as_uint(lds_row[i]);
+        if (bits != PICKED_MARK) {
+            const float e = exp_shifted(__uint_as_float(bits) - smax);
+            unpicked += e;
+            if (KEEP_ROW) lds_row[i] = e;
+        } else if (KEEP_ROW) {
+            lds_row[i] = -1.f;
+        }
+    }
+    // one exchange for the scan of the picked masses and the sum of the others
+    constexpr int NW = THREADS / NGC_WAVE;
+    const float incl = wave_incl_scan_f(mass);
+    const float others = wave_sum_f(unpicked);
+    if (lane_id() == NGC_WAVE - 1) { fmisc[2 * wave_id()] = incl; fmisc[2 * wave_id() + 1] = others; }
+    __syncthreads();
+    float base = 0.f, never = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (w < wave_id()) base += fmisc[2 * w];
+        never += fmisc[2 * w + 1];
+    }
+    __syncthreads();
+    float prev = __shfl_up(incl, 1, NGC_WAVE);                // sum of the lanes below, no subtraction
+    if (lane_id() == 0) prev = 0.f;
+    pt.after = base + prev;
+    pt.unpicked = never;
+    return true;
+}
+
+// One workgroup per segment; on the general route an LDS bitmap of picked items (65536 bits).
+template <int THREADS, int PICKS>
 __global__ __launch_bounds__(THREADS) void subset_logprob_kernel(LogprobArgs a)
 {
-    extern __shared__ float staged[];         // stage_cap floats
+    extern __shared__ __align__(16) float staged[];   // max(row_cap, stage_cap) floats
     __shared__ uint32_t picked[2048];
     __shared__ float fmisc[32];
     const int tid = threadIdx.x;
@@ -74,6 +199,23 @@ __global__ __launch_bounds__(THREADS) void subset_logprob_kernel(LogprobArgs a)
     if (K == 0) {
         if (tid == 0) a.logp_out[seg] = 0.f;
         return;
+    }
+    {
+        PickedTerms<THREADS, PICKS> pt;
+        if (gather_picked<THREADS, PICKS, false>(row, sig, N, K, a.row_cap, staged, fmisc, a.status, pt)) {
+            float acc = 0.f, R = pt.unpicked + pt.after;
+            LogProduct prod;
+#pragma unroll
+            for (int i = PICKS - 1; i >= 0; --i)
+                if (i < pt.count) {
+                    R += pt.e[i];
+                    acc += pt.d[i];                           // a masked pick (logit -inf) makes log p = -inf,
+                    prod.times(R > 0.f ? R : 1.0f);           // also where nothing unmasked is left (R == 0)
+                }
+            const float lp = block_sum_f<THREADS>(acc - prod.log(), fmisc);
+            if (tid == 0) a.logp_out[seg] = lp;
+            return;
+        }
     }
     for (int i = tid; i < 2048; i += THREADS) picked[i] = 0;
     __syncthreads();
@@ -167,12 +309,13 @@ struct LogprobBwdArgs {
     int64_t logit_stride;
     int sigma_stride;
     int keep_cap;
+    int row_cap;
 };
 
-template <int THREADS>
+template <int THREADS, int PICKS>
 __global__ __launch_bounds__(THREADS) void subset_logprob_backward_kernel(LogprobBwdArgs a)
 {
-    extern __shared__ float inv_r[];          // keep_cap floats
+    extern __shared__ __align__(16) float inv_r[];   // max(row_cap, keep_cap) floats
     __shared__ uint32_t picked[2048];
     __shared__ float fmisc[32];
     const int tid = threadIdx.x;
@@ -194,6 +337,51 @@ __global__ __launch_bounds__(THREADS) void subset_logprob_backward_kernel(Logpro
     if (K == 0) {
         for (int t = tid; t < N; t += THREADS) grow[t] = 0.f;
         return;
+    }
+    {
+        PickedTerms<THREADS, PICKS> pt;
+        if (gather_picked<THREADS, PICKS, true>(row, sig, N, K, a.row_cap, inv_r, fmisc, a.status, pt)) {
+            // 1 / R_j from the last pick backwards, then C_j = sum_{i <= j} 1 / R_i: the picks before a thread's own
+            // are those of the threads ABOVE it
+            float inv[PICKS], part = 0.f;
+            {
+                float R = pt.unpicked + pt.after;
+#pragma unroll
+                for (int i = PICKS - 1; i >= 0; --i) {
+                    inv[i] = 0.f;
+                    if (i < pt.count) {
+                        R += pt.e[i];
+                        inv[i] = 1.0f / R;
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < PICKS; ++i) part += inv[i];
+            float c_all;
+            float C = block_above_scan_f<THREADS>(part, fmisc, &c_all);
+            // every item's gradient into the LDS row, then the row goes out in order
+            for (int i = tid; i < N; i += THREADS) {
+                const float e = inv_r[i];
+                if (e != -1.f) inv_r[i] = -g * e * c_all;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < PICKS; ++i)
+                if (i < pt.count) {
+                    C += inv[i];
+                    if (pt.t[i] >= 0) inv_r[pt.t[i]] = g * (1.0f - pt.e[i] * C);
+                }
+            __syncthreads();
+            if ((reinterpret_cast<uintptr_t>(grow) & 15u) == 0) {
+                const int quads = N >> 2;
+                for (int i = tid; i < quads; i += THREADS)
+                    reinterpret_cast<f32x4 *>(grow)[i] = reinterpret_cast<const f32x4 *>(inv_r)[i];
+                for (int i = 4 * quads + tid; i < N; i += THREADS) grow[i] = inv_r[i];
+            } else {
+                for (int i = tid; i < N; i += THREADS) grow[i] = inv_r[i];
+            }
+            return;
+        }
     }
     for (int i = tid; i < 2048; i += THREADS) picked[i] = 0;
     __syncthreads();
@@ -396,13 +584,17 @@ __global__ __launch_bounds__(LMEM_THREADS) void lmem_layer_kernel(LmemArgs a)
     if (tid == 0) a.loss_layer[l] = (float)(-red[0] / (double)a.B);
 }
 
-__global__ void lmem_total_kernel(const float *loss_layer, int L, float *loss)
+// One wave: 64 layers' losses per load, added in layer order.
+__global__ __launch_bounds__(64) void lmem_total_kernel(const float *loss_layer, int L, float *loss)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        double s = 0.0;
-        for (int l = 0; l < L; ++l) s += (double)loss_layer[l];
-        *loss = (float)s;
+    double s = 0.0;
+    for (int l0 = 0; l0 < L; l0 += 64) {
+        const int l = l0 + (int)threadIdx.x;
+        const float x = l < L ? loss_layer[l] : 0.f;
+        const int m = L - l0 < 64 ? L - l0 : 64;
+        for (int i = 0; i < m; ++i) s += (double)__shfl(x, i, 64);
     }
+    if (threadIdx.x == 0) *loss = (float)s;
 }
 
 // --------------------------------------------------------- compaction -----
@@ -1034,6 +1226,32 @@ size_t select_lds_bytes(int threads, int items_cap, int keep_cap)
     return (size_t)items_cap * 4 + (size_t)hist * 4 + 64 * 4 + (size_t)keep_cap * 2 * 2;
 }
 
+// Eq. 2 and its gradient: how much of a row is held in LDS (an upper bound on the items of a segment that keeps to its
+// own row; a longer one takes the general route), and the workgroup that holds a row's picks in registers.  A
+// workgroup has no more threads than its row keeps busy.  Microseconds for two rounds of Eq. 2 and its gradient:
+// 2048 segments of 700-1400 items 53 with 256 threads, 67 with 512; of 1000-2000 items 69 and 76; 3584 segments of
+// 2150-3789 items 174 with 256 threads, 163 with 512, 386 with 1024.
+constexpr int LOGPROB_MAX_ROW = 16384;
+
+int row_capacity(int64_t logit_stride)
+{
+    const int64_t r = logit_stride < LOGPROB_MAX_ROW ? logit_stride : LOGPROB_MAX_ROW;
+    return (int)((r + 3) & ~(int64_t)3);
+}
+
+struct LogprobShape {
+    int threads, picks;
+};
+
+LogprobShape logprob_shape(int row_cap)
+{
+    if (row_cap <= 1024) return {256, 4};
+    if (row_cap <= 2048) return {256, 8};
+    if (row_cap <= 4096) return {512, 8};
+    if (row_cap <= 8192) return {512, 16};
+    return {1024, 16};
+}
+
 }  // namespace
 
 extern "C" int ngc_perturbed_keys(const ngc_cache *c, int32_t layer, const float *logits,
@@ -1175,14 +1393,20 @@ extern "C" int ngc_subset_logprob(const float *logits, const int32_t *n_items,
     if (ws_bytes < STATUS_BYTES) return NGC_ENOSPC;
     if (nseg == 0) return NGC_OK;
     const int stage_cap = sigma_stride < 16384 ? sigma_stride : 16384;     // at most 64 KB of LDS
+    const int row_cap = row_capacity(logit_stride);
     LogprobArgs la{logits, n_items, sigma, keep, logp_out, reinterpret_cast<int32_t *>(ws),
-                   logit_stride, sigma_stride, stage_cap};
-    const size_t lds = (size_t)stage_cap * sizeof(float);
-    const void *fn = reinterpret_cast<const void *>(&subset_logprob_kernel<512>);
+                   logit_stride, sigma_stride, stage_cap, row_cap};
+    const size_t lds = (size_t)(stage_cap > row_cap ? stage_cap : row_cap) * sizeof(float);
+    const LogprobShape shape = logprob_shape(row_cap);
+    const void *fn = shape.picks == 4       ? reinterpret_cast<const void *>(&subset_logprob_kernel<256, 4>)
+                     : shape.threads == 256 ? reinterpret_cast<const void *>(&subset_logprob_kernel<256, 8>)
+                     : shape.picks == 8     ? reinterpret_cast<const void *>(&subset_logprob_kernel<512, 8>)
+                     : shape.threads == 512 ? reinterpret_cast<const void *>(&subset_logprob_kernel<512, 16>)
+                                            : reinterpret_cast<const void *>(&subset_logprob_kernel<1024, 16>);
     if (lds > 48 * 1024)
         NGC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     void *kargs[] = {&la};
-    NGC_HIP_CHECK(hipLaunchKernel(fn, dim3(nseg), dim3(512), kargs, lds, (hipStream_t)stream));
+    NGC_HIP_CHECK(hipLaunchKernel(fn, dim3(nseg), dim3(shape.threads), kargs, lds, (hipStream_t)stream));
     return NGC_OK;
 }
 
@@ -1197,14 +1421,20 @@ extern "C" int ngc_subset_logprob_backward(const float *logits, const int32_t *n
     if (ws_bytes < STATUS_BYTES) return NGC_ENOSPC;
     if (max_keep > 32768) return NGC_EUNSUPPORTED;
     if (nseg == 0) return NGC_OK;
+    const int row_cap = row_capacity(logit_stride);
     LogprobBwdArgs la{logits, n_items, sigma, keep, gout, grad_out, reinterpret_cast<int32_t *>(ws),
-                      logit_stride, sigma_stride, max_keep};
-    const size_t lds = (size_t)max_keep * sizeof(float);
-    const void *fn = reinterpret_cast<const void *>(&subset_logprob_backward_kernel<512>);
+                      logit_stride, sigma_stride, max_keep, row_cap};
+    const size_t lds = (size_t)(max_keep > row_cap ? max_keep : row_cap) * sizeof(float);
+    const LogprobShape shape = logprob_shape(row_cap);
+    const void *fn = shape.picks == 4       ? reinterpret_cast<const void *>(&subset_logprob_backward_kernel<256, 4>)
+                     : shape.threads == 256 ? reinterpret_cast<const void *>(&subset_logprob_backward_kernel<256, 8>)
+                     : shape.picks == 8     ? reinterpret_cast<const void *>(&subset_logprob_backward_kernel<512, 8>)
+                     : shape.threads == 512 ? reinterpret_cast<const void *>(&subset_logprob_backward_kernel<512, 16>)
+                                            : reinterpret_cast<const void *>(&subset_logprob_backward_kernel<1024, 16>);
     if (lds > 48 * 1024)
         NGC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     void *kargs[] = {&la};
-    NGC_HIP_CHECK(hipLaunchKernel(fn, dim3(nseg), dim3(512), kargs, lds, (hipStream_t)stream));
+    NGC_HIP_CHECK(hipLaunchKernel(fn, dim3(nseg), dim3(shape.threads), kargs, lds, (hipStream_t)stream));
     return NGC_OK;
 }
 

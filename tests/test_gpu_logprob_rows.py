@@ -1,0 +1,108 @@
+"""Eq. 2 for given actions and its gradient at the edges of the route that holds a segment's row in LDS: row capacities
+where the workgroup changes (1024, 2048, 4096, 8192, 16384 items), the first length beyond the largest, rows that are
+not 16-byte aligned, keep counts from one pick to all, masked entries, and segments that need the wide-range route in
+between.  Against the fp64 oracle: log-probability 1e-4 relative, gradient 1e-4 of an entry plus 2e-6."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from _harness import oracle_logprob
+
+pytestmark = pytest.mark.gpu
+
+
+def _ngc():
+    from paper_2604_18002_amd import binding
+    binding.load_library()
+    return binding
+
+
+def _segments(rng, stride, kmax):
+    """(items, picks, kind) of the segments of one call."""
+    full = min(stride, kmax)
+    return [(stride, full, "normal"), (stride, 1, "normal"), (stride - 1, max(1, full // 3), "masked"),
+            (max(1, stride // 2), min(full, max(1, stride // 2)), "normal"), (stride, max(1, full // 2), "wide"),
+            (0, 0, "normal"), (min(stride, 5), min(full, 5), "normal"), (stride, max(1, full - 1), "normal")]
+
+
+@pytest.mark.parametrize("stride", [7, 1023, 1024, 1025, 2048, 2051, 4096, 4097, 8192, 8193, 16384, 16385])
+def test_rows_at_the_edges_of_their_capacities(stride):
+    import torch
+    ngc = _ngc()
+    rng = np.random.default_rng(stride)
+    kmax = min(stride, 12000)
+    segs = _segments(rng, stride, kmax)
+    nseg = len(segs)
+    n_items = np.array([s[0] for s in segs], np.int32)
+    keep = np.array([s[1] for s in segs], np.int32)
+    logits = np.full((nseg, stride), np.nan, np.float32)
+    sigma = np.zeros((nseg, kmax), np.int32)
+    gout = rng.standard_normal(nseg).astype(np.float32)
+    for s, (n, k, kind) in enumerate(segs):
+        if n == 0:
+            continue
+        x = rng.standard_normal(n).astype(np.float32)
+        if kind == "wide":
+            x[rng.random(n) < 0.2] -= np.float32(100.0)
+        if kind == "masked" and n > 8:
+            x[rng.choice(n, n // 8, replace=False)] = -np.inf
+        logits[s, :n] = x
+        order = rng.permutation(n)
+        sigma[s, :k] = order[np.isfinite(x[order])][:k]
+        keep[s] = min(k, int(np.isfinite(x).sum()))
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    ws = torch.zeros(ngc.STATUS_WORDS * 4, dtype=torch.uint8, device="cuda")
+    d_n, d_s, d_k, d_g = d(n_items), d(sigma), d(keep), d(gout)
+    for shift in (0, 1):      # the second time every row starts 4 bytes later
+        flat = torch.full((nseg * stride + 4,), float("nan"), device="cuda")
+        x = flat[shift:shift + nseg * stride].view(nseg, stride)
+        x.copy_(d(logits))
+        out = torch.zeros(nseg, device="cuda")
+        flat_g = torch.full((nseg * stride + 4,), float("nan"), device="cuda")
+        grad = flat_g[shift:shift + nseg * stride].view(nseg, stride)
+        print(f"[logprob-rows] stride={stride} shift={shift}", flush=True)
+        ngc.ngc_subset_logprob(x, d_n, d_s, d_k, nseg, stride, kmax, out, ws)
+        ngc.ngc_subset_logprob_backward(x, d_n, d_s, d_k, nseg, stride, kmax, kmax, d_g, grad, ws)
+        torch.cuda.synchronize()
+        lp, g = out.cpu().numpy(), grad.cpu().numpy()
+        for s in range(nseg):
+            n, k = int(n_items[s]), int(keep[s])
+            if k == 0:
+                assert lp[s] == 0.0
+                continue
+            assert lp[s] == pytest.approx(oracle_logprob(logits[s, :n], sigma[s, :k]), rel=1e-4, abs=1e-5), (s, n, k)
+            assert np.isnan(g[s, n:]).all()
+            if n * k <= 3_000_000:      # the oracle's gradient is term by term
+                want = gout[s] * orc.logprob_grad(logits[s, :n], sigma[s, :k])
+                assert np.all(np.abs(g[s, :n] - want) <= 1e-4 * np.abs(want) + 2e-6), (s, n, k)
+            else:                       # what holds at any size: shift invariance, signs
+                assert abs(g[s, :n].sum(dtype=np.float64)) <= 1e-3 * max(1.0, np.abs(g[s, :n]).sum(dtype=np.float64))
+                picked = np.zeros(n, bool)
+                picked[sigma[s, :k]] = True
+                assert (g[s, :n][~picked] * gout[s] <= 0).all()
+    assert all(v == 0 for v in ngc.read_status(ws))
+
+
+def test_repeated_and_outlying_picks_are_counted_and_rows_may_be_shared():
+    import torch
+    ngc = _ngc()
+    rng = np.random.default_rng(3)
+    n, k = 600, 40
+    x = rng.standard_normal(n).astype(np.float32)
+    sg = np.stack([rng.permutation(n)[:k] for _ in range(3)]).astype(np.int32)
+    bad = sg.copy()
+    bad[1, 7], bad[2, 3] = bad[1, 2], n + 5
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    n_items, keep = d(np.full(3, n, np.int32)), d(np.full(3, k, np.int32))
+    out = torch.zeros(3, device="cuda")
+    ws = torch.zeros(ngc.STATUS_WORDS * 4, dtype=torch.uint8, device="cuda")
+    print("[logprob-rows] shared row", flush=True)
+    ngc.ngc_subset_logprob(d(x), n_items, d(sg), keep, 3, 0, k, out, ws)      # stride 0: one row for all three
+    assert all(v == 0 for v in ngc.read_status(ws))
+    for s in range(3):
+        assert float(out[s]) == pytest.approx(oracle_logprob(x, sg[s]), rel=1e-4)
+    rows = d(np.stack([x] * 3))
+    ngc.ngc_subset_logprob(rows, n_items, d(bad), keep, 3, n, k, out, ws)
+    assert ngc.read_status(ws)[ngc.STATUS_BAD_SIGMA] == 2
+    assert float(out[0]) == pytest.approx(oracle_logprob(x, sg[0]), rel=1e-4)
+    assert bool(torch.isfinite(out).all())
