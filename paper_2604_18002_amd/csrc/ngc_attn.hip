@@ -34,9 +34,26 @@
 // ticket -- no cache-wide write-back or invalidate is involved.
 //
 // The same kernel can first append the new token's K/V row (Sec. 4.1: the cache
-// grows by one entry per token): the wave that owns the last tile writes the
-// row before it loads that tile, and the length is stored by whichever
-// workgroup of the segment finishes last, after every other one has read it.
+// grows by one entry per token): every wave requests the new row together with
+// its first tile; the wave that owns the last tile stores it into the cache and
+// puts it in its place in that tile's operands, so no load waits for the store.
+// The length is stored by whichever workgroup of the segment finishes last,
+// after every other one has read it.
+//
+// Which tiles a wave works on does not depend on the segment's length (tile t
+// belongs to wave t % 4 of workgroup (t / 4) % S), so the first tile is
+// requested before the length has arrived: one memory round trip less in front
+// of every launch.  Rows at or beyond the length are switched off when their
+// tile is computed (their scores by the mask, their V values by zeros: what lies
+// there is unspecified and may be NaN).
+//
+// What bounds a launch: at a few segments the chain of memory round trips (first
+// tile; then, if a segment is shared, partial -> ticket -> merge), at several
+// hundred the read rate of the memory.  Per layer, from a HIP graph, before ->
+// after the first tile moved in front of the length, the partials came in one
+// batch and the last tile lost its prefetch: 2 segments x 2000 rows 8.2 -> 6.7 us,
+// 32 x 525 rows (8.6 MB) 9.1 -> 7.0 us, 128 x 1494 rows (98 MB) 22.0 -> 19.7 us,
+// 512 x 2700 rows (0.71 GB) 119 -> 117 us.
 //
 // Paged layout (PAGED = true): a 32-row tile never straddles a page (pages hold
 // a power-of-two number of rows >= 32), so only the tile's base address changes:
@@ -47,6 +64,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "../../include/ngc.h"
 #include "ngc_device.h"
@@ -90,18 +108,8 @@ struct AttnArgs {
     int B;
 };
 
-// Loads and stores that other workgroups' data travels through: relaxed, device scope (served by memory, not by
-// an XCD's own L2).
-__device__ __forceinline__ void st_device(float *p, float v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float ld_device(const float *p)
-{
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// 16-byte versions for the partial O rows (a wave's stores land as whole cache lines instead of one 4-byte
+// Loads and stores that other workgroups' data travels through: device scope (served by memory, not by an XCD's own
+// L2), 16 bytes wide for the partial O rows (a wave's stores land as whole cache lines instead of one 4-byte
 // write-through per lane): raw buffer accesses with the device-scope bit, bounds-checked by the hardware against
 // `bytes` (a load past the end returns 0, a store past the end is dropped).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t device_span(const void *base, uint32_t bytes)
@@ -117,19 +125,18 @@ __device__ __forceinline__ f32x4 ld_device16(__amdgpu_buffer_rsrc_t r, uint32_t 
 {
     return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, AUX_DEVICE_SCOPE));
 }
-
-// Tiles [t_lo, t_hi) of split s when `tiles` tiles are cut into at most S
-// nearly equal runs; s_eff = number of non-empty splits.
-__device__ __forceinline__ void split_range(int tiles, int S, int s, int &t_lo, int &t_hi, int &s_eff)
+__device__ __forceinline__ void st_device8(__amdgpu_buffer_rsrc_t r, uint32_t byte_off, f32x2 v)
 {
-    const int per = (tiles + S - 1) / S;
-    s_eff = per > 0 ? (tiles + per - 1) / per : 0;
-    t_lo = s * per;
-    t_hi = t_lo + per < tiles ? t_lo + per : tiles;
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, byte_off, 0, AUX_DEVICE_SCOPE);
+}
+__device__ __forceinline__ f32x2 ld_device8(__amdgpu_buffer_rsrc_t r, uint32_t byte_off)
+{
+    return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, byte_off, 0, AUX_DEVICE_SCOPE));
 }
 
 template <int D, bool PAGED, bool APPEND>
-__global__ __launch_bounds__(ATT_WAVES * 64) void decode_kernel(AttnArgs a)
+__global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2)))
+void decode_kernel(AttnArgs a)
 {
     constexpr int ROW_BYTES = D * 2;
     constexpr int DPL = D / 16;                 // bf16 per lane in a V row (8 or 4)
@@ -145,6 +152,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) void decode_kernel(AttnArgs a)
     __shared__ float red_l[ATT_WAVES][16];
     __shared__ float fin_l[16];
     __shared__ int is_last;
+    __shared__ __align__(16) unsigned char fresh[APPEND ? 2 * ROW_BYTES : 16];   // the new K row and V row
 
     const int lane = lane_id(), wv = wave_id();
     const int li = lane & 15, kg = lane >> 4;
@@ -157,7 +165,90 @@ __global__ __launch_bounds__(ATT_WAVES * 64) void decode_kernel(AttnArgs a)
     const int seg = a.seg0 + seg_local;
     const int G = a.G;
 
-    int n = a.len[seg];
+    const int n_raw = a.len[seg];
+    const int h = seg % a.Hkv;
+    const int lb = seg / a.Hkv - a.lb0;   // (layer * B + sequence) relative to q / out
+    float *out_seg = a.out + ((size_t)lb * a.Hkv + h) * G * D;   // [G][D] of this KV head
+
+    const unsigned char *kseg = PAGED ? a.k : a.k + (size_t)seg * a.cap * ROW_BYTES;
+    const unsigned char *vseg = PAGED ? a.v : a.v + (size_t)seg * a.cap * ROW_BYTES;
+    const int wv_u = __builtin_amdgcn_readfirstlane(wv);
+    const int step = a.S * ATT_WAVES;                      // tiles between two of a wave's own
+    int tile = split * ATT_WAVES + wv_u;
+    // Byte offset of a tile from the start of the segment's rows or, paged, of the pools (a tile lies inside one
+    // page).  `top`: the last tile that may be looked up, taken in place of later ones.
+    const int32_t *tab = PAGED ? a.table + (size_t)seg * a.max_pages : nullptr;
+    auto tile_base = [&](int t, int top) -> size_t {
+        const int tc = t < top ? t : top;
+        if constexpr (!PAGED) return (size_t)tc * (ATT_TILE * ROW_BYTES);
+        int page = tab[tc >> a.tpp_shift];
+        page = (page < 0 || page >= a.num_pages) ? 0 : page;   // never leave the pool
+        return ((size_t)page << a.tpp_shift) * (ATT_TILE * ROW_BYTES) +
+               (size_t)(tc & ((1 << a.tpp_shift) - 1)) * (ATT_TILE * ROW_BYTES);
+    };
+
+    // rows this lane loads, relative to the tile: K in full-row order, V in the
+    // order its lane group contracts over (matches the layout of the scores)
+    int vrow_rel[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) vrow_rel[e] = (e < 4) ? (4 * kg + e) : (16 + 4 * kg + (e - 4));
+
+    // 32-bit byte offsets inside the segment (a segment is at most cap * ROW_BYTES <= 2^31 bytes)
+    const uint32_t k_col = (uint32_t)(lane % K_PIECES) * 16u;
+    const uint32_t v_col = (uint32_t)li * (DPL * 2);
+    u32x4 kbuf[K_LOADS];
+    auto load_v_piece = [&](const unsigned char *p) -> u32x4 {
+        if constexpr (DPL == 8) {
+            return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+        } else {
+            const u32x2 t = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(p));
+            return u32x4{t[0], t[1], 0u, 0u};
+        }
+    };
+    // Loads of tile t, whose rows start `base` bytes into K and V; rows beyond `last_row` are not touched (the last one
+    // is read in their place).
+    auto issue_loads = [&](int t, int last_row, size_t base, u32x4 (&vb)[8]) {
+        const unsigned char *kt = kseg + base, *vt = vseg + base;      // wave-uniform
+        const int lim = last_row - t * ATT_TILE;
+#pragma unroll
+        for (int r = 0; r < K_LOADS; ++r) {
+            int rel = r * K_ROWS_PER_LOAD + lane / K_PIECES;
+            rel = rel < lim ? rel : lim;
+            kbuf[r] = __builtin_nontemporal_load(
+                reinterpret_cast<const u32x4 *>(kt + ((uint32_t)rel * ROW_BYTES + k_col)));
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int rel = vrow_rel[e] < lim ? vrow_rel[e] : lim;
+            vb[e] = load_v_piece(vt + ((uint32_t)rel * ROW_BYTES + v_col));
+        }
+    };
+
+    // Everything that does not need the length is requested first: the queries, the new row, the first tile (its
+    // rows are clamped to the capacity only; paged: table entries beyond the pages in use hold anything, which
+    // tile_base() turns into some page of the pool).
+    u32x4 new_piece = {0u, 0u, 0u, 0u};      // lanes [0, K_PIECES) hold the new K row, the next K_PIECES the V row
+    if constexpr (APPEND) {
+        const unsigned char *src = (lane / K_PIECES) & 1 ? a.v_new : a.k_new;
+        new_piece = *reinterpret_cast<const u32x4 *>(src + (size_t)seg_local * ROW_BYTES + k_col);
+    }
+    // B operand of the first product: Q[q = li][32c + 8kg .. +7], zero for q >= G
+    bf16x8 qop[KCH];
+    {
+        const unsigned char *qrow = a.q + ((size_t)lb * a.Hkv * G + (size_t)h * G + (li < G ? li : G - 1)) * ROW_BYTES;
+#pragma unroll
+        for (int c = 0; c < KCH; ++c)
+            qop[c] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(qrow + c * 64 + kg * 16));
+    }
+    u32x4 v_a[8], v_b[8];
+    {
+        const int cap_tile = (a.cap - 1) / ATT_TILE;
+        const int t0 = tile < cap_tile ? tile : cap_tile;
+        issue_loads(t0, a.cap - 1, tile_base(t0, cap_tile), v_a);
+    }
+    __asm__ volatile("" ::: "memory");   // the requests stay in front of everything that waits for the length
+
+    int n = n_raw;
     if (n < 0 || n > a.cap) {
         if (threadIdx.x == 0 && split == 0) atomicAdd(&a.status[NGC_STATUS_LEN_CLAMPED], 1);
         n = n < 0 ? 0 : a.cap;
@@ -172,10 +263,6 @@ __global__ __launch_bounds__(ATT_WAVES * 64) void decode_kernel(AttnArgs a)
             atomicAdd(&a.status[NGC_STATUS_APPEND_FULL], 1);
         }
     }
-    const int h = seg % a.Hkv;
-    const int lb = seg / a.Hkv - a.lb0;   // (layer * B + sequence) relative to q / out
-    float *out_seg = a.out + ((size_t)lb * a.Hkv + h) * G * D;   // [G][D] of this KV head
-
     // Every workgroup of a split segment takes a ticket when it is done (right away if its split is empty); the
     // one that takes the last ticket returns true here, all others false.  Whole workgroup calls it.
     auto took_last_ticket = [&]() -> bool {
@@ -205,54 +292,57 @@ __global__ __launch_bounds__(ATT_WAVES * 64) void decode_kernel(AttnArgs a)
         return;
     }
     const int tiles = (n + ATT_TILE - 1) / ATT_TILE;
-    int t_lo, t_hi, s_eff;
-    split_range(tiles, a.S, split, t_lo, t_hi, s_eff);
+    const int groups = (tiles + ATT_WAVES - 1) / ATT_WAVES;
+    const int s_eff = groups < a.S ? groups : a.S;            // workgroups of the segment that have rows
     const float *seg_po = a.part_o + (size_t)seg_local * a.S * G * D;
     const float *seg_pml = a.part_ml + (size_t)seg_local * a.S * G * 2;
-    // Merge of the s_eff partials of this segment: out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M).  Three
-    // rounds of loads in all (the partials' (max, sum) pairs, then the O values four splits at a time), each round
-    // issued as one batch.  Uses the K staging area, which no wave needs any more.
-    auto merge_partials = [&]() {
+    // Merge of the s_eff partials of this segment: out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M).  A thread
+    // owns four values of the output and asks for them and for their (max, sum) pairs of MERGE partials in one batch,
+    // so up to MERGE partials cost one memory round trip (about 1 us).
+    auto merge_batches = [&](auto batch) {
+        constexpr int MERGE = decltype(batch)::value;
         __asm__ volatile("" ::: "memory");
-        float *ml_s = reinterpret_cast<float *>(lds);          // [s_eff][G][2] -> (weight, sum)
-        float *den_s = ml_s + MAX_SPLITS * 16 * 2;             // [G]
-        const int n_ml = s_eff * G * 2;
-        for (int i = threadIdx.x; i < n_ml; i += ATT_WAVES * 64) ml_s[i] = ld_device(&seg_pml[i]);
-        __syncthreads();
-        if ((int)threadIdx.x < G) {
-            const int qi = threadIdx.x;
-            float M = -INFINITY;
-            for (int sp = 0; sp < s_eff; ++sp) M = fmaxf(M, ml_s[(sp * G + qi) * 2]);
-            float den = 0.f;
-            for (int sp = 0; sp < s_eff; ++sp) {
-                const float wgt = fast_exp2(ml_s[(sp * G + qi) * 2] - M);
-                den += ml_s[(sp * G + qi) * 2 + 1] * wgt;
-                ml_s[(sp * G + qi) * 2] = wgt;
-            }
-            den_s[qi] = den;
-            if (a.lse_out) a.lse_out[((size_t)lb * a.Hkv + h) * G + qi] = (M + __log2f(den)) * 0.6931471805599453f;
-        }
-        __syncthreads();
         const __amdgpu_buffer_rsrc_t po = device_span(seg_po, (uint32_t)(s_eff * G * D * sizeof(float)));
+        const __amdgpu_buffer_rsrc_t pml = device_span(seg_pml, (uint32_t)(s_eff * G * 2 * sizeof(float)));
         for (int i4 = threadIdx.x; i4 < G * D / 4; i4 += ATT_WAVES * 64) {
             const int qi = (i4 * 4) / D;
             f32x4 num = {0.f, 0.f, 0.f, 0.f};
-            for (int sp0 = 0; sp0 < s_eff; sp0 += 4) {
-                f32x4 o[4];
+            float M = -INFINITY, den = 0.f;
+            for (int sp0 = 0; sp0 < s_eff; sp0 += MERGE) {
+                f32x4 o[MERGE];
+                f32x2 ml[MERGE];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < MERGE; ++u) {
                     const int sp = (sp0 + u < s_eff) ? sp0 + u : s_eff - 1;
                     o[u] = ld_device16(po, (uint32_t)((sp * G * D + i4 * 4) * sizeof(float)));
+                    ml[u] = ld_device8(pml, (uint32_t)((sp * G + qi) * 2 * sizeof(float)));
                 }
+                float top = M;                       // finite: a partial has at least one row
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (sp0 + u < s_eff) num += o[u] * ml_s[((sp0 + u) * G + qi) * 2];
+                for (int u = 0; u < MERGE; ++u) top = fmaxf(top, ml[u][0]);
+                const float old = fast_exp2(M - top);
+                den *= old;
+                num *= old;
+                M = top;
+#pragma unroll
+                for (int u = 0; u < MERGE; ++u) {
+                    const float wgt = (sp0 + u < s_eff) ? fast_exp2(ml[u][0] - top) : 0.f;
+                    den += ml[u][1] * wgt;
+                    num += o[u] * wgt;
+                }
             }
-            const float inv = 1.0f / den_s[qi];
+            const float inv = 1.0f / den;
             *reinterpret_cast<f32x4 *>(&out_seg[i4 * 4]) = num * inv;
+            if (a.lse_out && i4 * 4 == qi * D)
+                a.lse_out[((size_t)lb * a.Hkv + h) * G + qi] = (M + __log2f(den)) * 0.6931471805599453f;
         }
     };
-    if (t_lo >= t_hi) {   // whole workgroup: no rows for this split
+    auto merge_partials = [&]() {
+        if (s_eff <= 4) merge_batches(std::integral_constant<int, 4>{});
+        else if (s_eff <= 8) merge_batches(std::integral_constant<int, 8>{});
+        else merge_batches(std::integral_constant<int, 16>{});
+    };
+    if (split * ATT_WAVES >= tiles) {   // whole workgroup: no rows for this split
         if (took_last_ticket()) {
             close_segment();
             if (s_eff > 1) merge_partials();
@@ -260,79 +350,17 @@ __global__ __launch_bounds__(ATT_WAVES * 64) void decode_kernel(AttnArgs a)
         return;
     }
 
-    const unsigned char *kseg = PAGED ? a.k : a.k + (size_t)seg * a.cap * ROW_BYTES;
-    const unsigned char *vseg = PAGED ? a.v : a.v + (size_t)seg * a.cap * ROW_BYTES;
-    // paged: byte offset of a tile inside the pools (wave-uniform)
-    const int32_t *tab = PAGED ? a.table + (size_t)seg * a.max_pages : nullptr;
-    const int wv_u = __builtin_amdgcn_readfirstlane(wv);
-    auto tile_base = [&](int tile) -> size_t {
-        const int tc = tile < tiles ? tile : tiles - 1;   // a prefetch past the end re-reads the last tile
-        int page = tab[tc >> a.tpp_shift];
-        page = (page < 0 || page >= a.num_pages) ? 0 : page;   // never leave the pool
-        return ((size_t)page << a.tpp_shift) * (ATT_TILE * ROW_BYTES) +
-               (size_t)(tc & ((1 << a.tpp_shift) - 1)) * (ATT_TILE * ROW_BYTES);
-    };
-
-    // B operand of the first product: Q[q = li][32c + 8kg .. +7], zero for q >= G
-    bf16x8 qop[KCH];
-    {
-        const unsigned char *qrow = a.q + ((size_t)lb * a.Hkv * G + (size_t)h * G + li) * ROW_BYTES;
-#pragma unroll
-        for (int c = 0; c < KCH; ++c) {
-            u32x4 w = {0u, 0u, 0u, 0u};
-            if (li < G) w = *reinterpret_cast<const u32x4 *>(qrow + c * 64 + kg * 16);
-            qop[c] = __builtin_bit_cast(bf16x8, w);
-        }
-    }
-
     f32x4 oacc[DPL];
 #pragma unroll
     for (int c = 0; c < DPL; ++c) oacc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m_run = -INFINITY, l_run = 0.f;
 
+#pragma unroll
+    for (int c = 0; c < KCH; ++c)
+        if (li >= G) qop[c] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});   // (asked for without a branch)
+
     unsigned char *wlds = lds + wv * WAVE_LDS;
     const int last_row = n - 1;
-
-    // rows this lane loads, relative to the tile: K in full-row order, V in the
-    // order its lane group contracts over (matches the layout of the scores)
-    int vrow_rel[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) vrow_rel[e] = (e < 4) ? (4 * kg + e) : (16 + 4 * kg + (e - 4));
-
-    // 32-bit byte offsets inside the segment (a segment is at most cap * ROW_BYTES <= 2^31 bytes)
-    const uint32_t k_col = (uint32_t)(lane % K_PIECES) * 16u;
-    const uint32_t v_col = (uint32_t)li * (DPL * 2);
-    u32x4 kbuf[K_LOADS];
-    // `base`: paged layout only, tile_base() of the tile
-    auto issue_loads = [&](int tile, size_t base, u32x4 (&vb)[8]) {
-        const int row0 = tile * ATT_TILE;
-        const unsigned char *kt = kseg, *vt = vseg;
-        int first = 0;            // row number that offset 0 of kt / vt holds
-        if constexpr (PAGED) {
-            kt = kseg + base;
-            vt = vseg + base;
-            first = (tile < tiles ? tile : tiles - 1) * ATT_TILE;
-        }
-#pragma unroll
-        for (int r = 0; r < K_LOADS; ++r) {
-            int row = row0 + r * K_ROWS_PER_LOAD + lane / K_PIECES;
-            row = row < last_row ? row : last_row;
-            kbuf[r] = __builtin_nontemporal_load(
-                reinterpret_cast<const u32x4 *>(kt + ((uint32_t)(row - first) * ROW_BYTES + k_col)));
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            int row = row0 + vrow_rel[e];
-            row = row < last_row ? row : last_row;
-            const unsigned char *p = vt + ((uint32_t)(row - first) * ROW_BYTES + v_col);
-            if constexpr (DPL == 8) {
-                vb[e] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-            } else {
-                const u32x2 t = __builtin_nontemporal_load(reinterpret_cast<const u32x2 *>(p));
-                vb[e] = u32x4{t[0], t[1], 0u, 0u};
-            }
-        }
-    };
     auto stage_k = [&]() {
 #pragma unroll
         for (int r = 0; r < K_LOADS; ++r) {
@@ -340,8 +368,32 @@ __global__ __launch_bounds__(ATT_WAVES * 64) void decode_kernel(AttnArgs a)
             *reinterpret_cast<u32x4 *>(wlds + rl * LROW + k_col) = kbuf[r];
         }
     };
+    // The segment's last tile: the new row takes its place (K in LDS, V in the operands), V rows past the end are 0.
+    auto finish_last_tile = [&](int t, u32x4 (&vb)[8]) {
+        const int row0 = t * ATT_TILE;
+        if constexpr (APPEND) {
+            if (grew) {
+                if (lane < K_PIECES)
+                    *reinterpret_cast<u32x4 *>(wlds + (last_row - row0) * LROW + k_col) =
+                        *reinterpret_cast<const u32x4 *>(fresh + k_col);
+                u32x4 piece = {0u, 0u, 0u, 0u};
+                if constexpr (DPL == 8) {
+                    piece = *reinterpret_cast<const u32x4 *>(fresh + ROW_BYTES + v_col);
+                } else {
+                    const u32x2 t2 = *reinterpret_cast<const u32x2 *>(fresh + ROW_BYTES + v_col);
+                    piece = u32x4{t2[0], t2[1], 0u, 0u};
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (row0 + vrow_rel[e] == last_row) vb[e] = piece;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (row0 + vrow_rel[e] > last_row) vb[e] = u32x4{0u, 0u, 0u, 0u};
+    };
     // one 32-row tile: K from the wave's LDS area, V from registers
-    auto compute_tile = [&](int tile, const u32x4 (&vcur)[8]) {
+    auto compute_tile = [&](int tile, const u32x4 (&vcur)[8], auto masked) {
         const int row0 = tile * ATT_TILE;
         f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -356,7 +408,7 @@ __global__ __launch_bounds__(ATT_WAVES * 64) void decode_kernel(AttnArgs a)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const float sc = (e < 4) ? s0[e] : s1[e - 4];
-            x[e] = (row0 + vrow_rel[e] < n) ? sc * a.scale_log2e : -INFINITY;
+            x[e] = (!decltype(masked)::value || row0 + vrow_rel[e] < n) ? sc * a.scale_log2e : -INFINITY;
         }
         float tmax = x[0];
 #pragma unroll
@@ -412,58 +464,59 @@ __global__ __launch_bounds__(ATT_WAVES * 64) void decode_kernel(AttnArgs a)
     // Software pipeline, unrolled by two so that the V registers of the tile in
     // flight and of the tile being computed are distinct (no copies): the loads
     // of the next tile are issued before the current tile's math and are only
-    // waited for at the top of the next step.  The prefetch is unconditional (a
-    // tile past the end only re-reads the last row, which every load clamps to)
-    // so that the number of loads in flight is the same on every path and the
-    // wait for the current tile's data does not also wait for the prefetch.
+    // waited for at the top of the next step.  A wave's last tile is a copy of
+    // the step without the loads (a prefetch inside a branch would make the wait
+    // for the current tile wait for the prefetch too, and a prefetch past the
+    // end, clamped to the last row, sends every wave of a segment to the same
+    // two cache lines: 1.4 us of a 9.6 us launch of 16 segments x 12 workgroups);
+    // only there can the segment end, so only there rows are masked.
     if constexpr (APPEND) {
-        // The wave that owns the last tile stores the new row before anything else.  No other wave or workgroup
-        // uses that row (prefetches past a split's end are never computed on).  The wave's loads of that tile
-        // come after the store in program order; they are issued at once only when the last tile is also the
-        // wave's first one -- then the wave waits for the store first.  Otherwise the loads of the last tile are
-        // issued after the wave has waited for an earlier tile's data, and memory operations of a wave complete
-        // in issue order, so the store is done by then.
         const int last_tile = tiles - 1;
-        if (grew && last_tile >= t_lo && last_tile < t_hi && ((last_tile - t_lo) % ATT_WAVES) == wv) {
+        if (grew && last_tile / ATT_WAVES % a.S == split && last_tile % ATT_WAVES == wv_u) {
+            const size_t at = ((size_t)seg * a.cap + last_row) * ROW_BYTES;
             if (lane < 2 * K_PIECES) {
-                const bool is_v = lane >= K_PIECES;
-                const int piece = is_v ? lane - K_PIECES : lane;
-                const size_t src_off = (size_t)seg_local * ROW_BYTES + piece * 16;
-                const size_t dst_off = ((size_t)seg * a.cap + (n - 1)) * ROW_BYTES + piece * 16;
-                const u32x4 row = *reinterpret_cast<const u32x4 *>((is_v ? a.v_new : a.k_new) + src_off);
-                *reinterpret_cast<u32x4 *>((is_v ? a.v_rw : a.k_rw) + dst_off) = row;
+                *reinterpret_cast<u32x4 *>((lane < K_PIECES ? a.k_rw : a.v_rw) + at + k_col) = new_piece;
+                *reinterpret_cast<u32x4 *>(fresh + (lane / K_PIECES) * ROW_BYTES + k_col) = new_piece;
             }
-            if (lane == 0 && a.pos && a.new_pos) a.pos[(size_t)seg * a.cap + (n - 1)] = a.new_pos[(seg / a.Hkv) % a.B];
-            if (last_tile - t_lo < 2 * ATT_WAVES) __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (lane == 0 && a.pos && a.new_pos) a.pos[(size_t)seg * a.cap + last_row] = a.new_pos[(seg / a.Hkv) % a.B];
         }
     }
 
-    u32x4 v_a[8], v_b[8];
-    int tile = t_lo + (PAGED ? wv_u : wv);
-    size_t base1 = 0, base2 = 0;   // paged: bases of the next tile and of the one after it
-    if constexpr (PAGED) {
-        base1 = tile_base(tile + ATT_WAVES);
-        base2 = tile_base(tile + 2 * ATT_WAVES);
-        issue_loads(tile, tile_base(tile), v_a);
-    } else {
-        issue_loads(tile, 0, v_a);
+    // bases of the next tile and of the one after it (paged: looked up before they are needed)
+    size_t base1 = tile_base(tile + step, tiles - 1), base2 = tile_base(tile + 2 * step, tiles - 1);
+    bool staged = false;
+    while (tile + step < tiles) {
+        stage_k();
+        issue_loads(tile + step, last_row, base1, v_b);
+        base1 = base2;
+        base2 = tile_base(tile + 3 * step, tiles - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        compute_tile(tile, v_a, std::false_type{});
+        __builtin_amdgcn_sched_barrier(0);
+        tile += step;
+        if (tile + step >= tiles) {     // the last tile is in v_b: one copy of its step serves both buffers
+            stage_k();
+            staged = true;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v_a[e] = v_b[e];
+            break;
+        }
+        stage_k();
+        issue_loads(tile + step, last_row, base1, v_a);
+        base1 = base2;
+        base2 = tile_base(tile + 3 * step, tiles - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        compute_tile(tile, v_b, std::false_type{});
+        __builtin_amdgcn_sched_barrier(0);
+        tile += step;
     }
-    while (tile < t_hi) {
-        stage_k();
-        issue_loads(tile + ATT_WAVES, base1, v_b);
-        if constexpr (PAGED) { base1 = base2; base2 = tile_base(tile + 3 * ATT_WAVES); }
+    if (tile < tiles) {
+        if (!staged) stage_k();
         __builtin_amdgcn_sched_barrier(0);
-        compute_tile(tile, v_a);
+        if (tile == tiles - 1) finish_last_tile(tile, v_a);
+        compute_tile(tile, v_a, std::true_type{});
         __builtin_amdgcn_sched_barrier(0);
-        tile += ATT_WAVES;
-        if (tile >= t_hi) break;
-        stage_k();
-        issue_loads(tile + ATT_WAVES, base1, v_a);
-        if constexpr (PAGED) { base1 = base2; base2 = tile_base(tile + 3 * ATT_WAVES); }
-        __builtin_amdgcn_sched_barrier(0);
-        compute_tile(tile, v_b);
-        __builtin_amdgcn_sched_barrier(0);
-        tile += ATT_WAVES;
     }
 
     // ---- merge the waves of this workgroup ----------------------------------
@@ -518,9 +571,9 @@ __global__ __launch_bounds__(ATT_WAVES * 64) void decode_kernel(AttnArgs a)
         st_device16(po, (uint32_t)(i4 * 4 * sizeof(float)), acc);
     }
     if (wv == 0 && kg == 0 && li < G) {
-        float *ml = a.part_ml + (((size_t)seg_local * a.S + split) * G + li) * 2;
-        st_device(&ml[0], m_all);
-        st_device(&ml[1], l_all);
+        const __amdgpu_buffer_rsrc_t pml =
+            device_span(a.part_ml + ((size_t)seg_local * a.S + split) * G * 2, (uint32_t)(G * 2 * sizeof(float)));
+        st_device8(pml, (uint32_t)(li * 2 * sizeof(float)), f32x2{m_all, l_all});
     }
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's partial stores have reached memory
     if (took_last_ticket()) {
@@ -538,41 +591,57 @@ using namespace ngc;
 namespace {
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 constexpr size_t STATUS_BYTES = NGC_STATUS_WORDS * sizeof(int32_t);
-// How many workgroups share a segment.  Two measured limits (MI355X, one launch per layer, microseconds per
-// launch against S, best in brackets):
-//     segments x rows      S=1    2     3     4     6     8    12    16    24    32    64
-//         4 x  3-10K                          23.1        16.3  14.8 [14.3] 15.0  16.0  22.0
-//        16 x  3-10K                          26.3        19.7 [18.0] 18.8  23.8  25.1  36.4
-//        32 x  3-10K       80.3  46.3  35.1  29.4  25.7 [25.6] 31.7  30.8
-//        64 x  3-10K       88.7  54.8  44.9 [42.8] 51.0  46.9  50.6  52.2
-//       128 x  3-10K      101.1 [77.6] 91.6  82.1  82.6  84.6  89.2  94.0
-//       256 x  3-10K     [142.1] 149.9 145.5 148.3 151.9 156.3 166.9 178.0
-//         8 x  1.9-2.5K                       12.5       [11.2] 11.5  12.4  14.3  15.7  24.3
-//        32 x  1.9-3.5K    33.2  22.6  19.7  17.0 [16.7] 17.3  20.8  20.8
-//       128 x  1.9-3.5K    40.7 [36.2] 41.7  39.4  43.8  43.7  48.9  52.9
-//       256 x  1.9-3.5K   [60.9] 67.5  71.3  73.2  77.4  81.4  93.2 103.5
-//         8 x  1.5K                           10.5       [10.1] 10.4  11.1  13.7  13.7  20.8
-//        32 x  1.5K        18.0  14.7  13.6  12.3 [12.2] 12.5  15.0  15.4
-//        64 x  1.5K        20.5  16.0 [15.3] 15.5  18.2  17.9  20.9  22.0
-//       128 x  1.5K       [22.1] 22.2  25.6  25.0  27.8  29.5  33.9  36.7
-// (a) the launch should not have more workgroups than the chip has CUs: beyond one workgroup per CU a further cut
-// only adds workgroups, each paying its first-tile wait, its epilogue and the partial -> ticket -> merge chain;
-// (b) with few segments, a run should stay long enough that streaming it (~68 GB/s per workgroup) costs more than
-// what one more partial adds to the merge (~0.16 us): S ~ sqrt(80 x megabytes of the longest segment).
+// How many workgroups share a segment.  Microseconds per launch (MI355X, one launch per layer from a HIP graph, D = 128)
+// against S, best in brackets:
+//     segments x rows      S=1    2     3     4     5     6     8    10    12    16    24    32
+//         2 x  300         6.6   6.6 [ 5.7]  5.7   5.7   5.7   5.7
+//         2 x  525         8.4   7.7   7.2   6.6 [ 5.9]  6.0   6.0
+//         2 x 2000        20.7  13.8  11.4   9.6   9.4   8.6   7.7   8.2   8.2 [ 6.7]  6.7   6.7
+//         4 x 4000        37.6  22.4  17.0  14.2  12.9  11.9  10.2  10.4   9.4 [ 8.5]  9.6   8.9
+//         4 x 3-10K       53.6  30.2  22.4  18.5  16.2  14.5  12.4  11.7  10.9 [ 9.6] 10.0   9.8
+//        16 x 1.5K        17.4  12.5  10.4   9.2   9.2   8.6 [ 8.3]  8.9   9.0   9.0   9.4  10.8
+//        16 x 3-10K       88.3  47.9  34.3  27.7  23.8  20.7  17.8  16.5  15.4 [14.2] 18.0  16.8
+//        32 x  300         7.2   7.3 [ 6.3]  6.3   6.3   6.3   6.7   6.7
+//        32 x  525         9.4   8.5   7.9   7.4 [ 6.8]  6.9   6.8   6.9   6.9   6.9   8.3   9.9
+//        32 x 1.5K        17.9  12.9  10.9   9.6   9.8   9.4 [ 9.4] 11.2   9.9   9.8  11.5  13.0
+//        32 x 3-10K       89.6  49.4  36.2  30.0  26.2  24.0 [22.8] 28.5  27.0  24.1  26.4  26.5
+//        64 x  525        10.0   9.1   8.8 [ 8.5]  8.9   8.9   8.9   9.2  10.0  11.1
+//        64 x 1.5K        20.3  14.8  13.0 [12.3] 14.5  13.5  13.4  13.8  14.6  15.2
+//        64 x 3-10K       93.6  54.7  43.4 [41.2] 52.6  47.9  43.2  45.3  44.9  43.6
+//       128 x  525        11.1 [10.9] 11.3  11.0  12.4  12.4  12.5
+//       128 x 1.5K        22.2 [20.0] 21.8  20.3  21.9  21.0  21.6
+//       128 x 3-10K      106.4 [78.5] 91.5  80.5  87.4  82.2  78.5
+//       256 x 1.5K       [33.8] 35.7  36.2  37.0
+// What they say: a launch should have no more workgroups than the chip has CUs, S <= 256 / segments.  Below that a
+// workgroup works through rounds of four tiles (one per wave), ~0.95 us each (0.58 at D = 64), so only the S that
+// lower the number of rounds are worth their cost: sharing a segment at all costs ~1.2 us (partial, ticket, merge:
+// three memory round trips), every 16 partials more another such trip, and workgroups beyond 128 ~0.01 us each.
 constexpr int COMPUTE_UNITS = 256;
-constexpr int MIN_TILES_PER_SPLIT = 4;
+
+int most_splits(int nseg_launch, int max_len)
+{
+    const int rounds_of_one = ((max_len + ATT_TILE - 1) / ATT_TILE + ATT_WAVES - 1) / ATT_WAVES;
+    int s = COMPUTE_UNITS / (nseg_launch > 0 ? nseg_launch : 1);
+    s = s < rounds_of_one ? s : rounds_of_one;
+    s = s < MAX_SPLITS ? s : MAX_SPLITS;
+    return s > 1 ? s : 1;
+}
 
 int splits_for(int nseg_launch, int max_len, int row_bytes)
 {
+    const int most = most_splits(nseg_launch, max_len);
     const int tiles = (max_len + ATT_TILE - 1) / ATT_TILE;
-    const double seg_mb = 2.0 * row_bytes * max_len * 1e-6;          // K and V
-    int s = COMPUTE_UNITS / (nseg_launch > 0 ? nseg_launch : 1);
-    const int by_merge = (int)sqrt(80.0 * seg_mb);
-    const int by_length = tiles / MIN_TILES_PER_SPLIT;
-    s = s < by_merge ? s : by_merge;
-    s = s < by_length ? s : by_length;
-    s = s < MAX_SPLITS ? s : MAX_SPLITS;
-    return s > 1 ? s : 1;
+    const float per_round = row_bytes == 256 ? 0.95f : 0.58f;
+    int best = 1;
+    float best_us = 3.0e38f;
+    for (int s = most; s >= 1; --s) {
+        const int rounds = (tiles + ATT_WAVES * s - 1) / (ATT_WAVES * s);
+        if (s > 1 && (tiles + ATT_WAVES * (s - 1) - 1) / (ATT_WAVES * (s - 1)) == rounds) continue;   // one fewer does as well
+        const int beyond = s * nseg_launch > 128 ? s * nseg_launch - 128 : 0;
+        const float us = per_round * (float)rounds + (s > 1 ? 1.2f * (float)((s + 15) / 16) + 0.01f * (float)beyond : 0.f);
+        if (us < best_us) { best_us = us; best = s; }
+    }
+    return best;
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -622,13 +691,9 @@ extern "C" size_t ngc_workspace_bytes(const ngc_cache *c, int32_t max_keep)
     const int per_layer = c->B * c->Hkv;
     // the most any launch can ask for: one layer or all layers, any length hint (a launch that finds less
     // workspace than its preferred split needs falls back to fewer splits, so this is a guarantee, not a limit)
-    size_t most = 0;
-    for (int hint = c->cap; hint >= 1; hint = hint / 2) {
-        const size_t one = attn_partial_bytes(c, per_layer, splits_for(per_layer, hint, c->D * 2));
-        const size_t all = attn_partial_bytes(c, per_layer * c->L, splits_for(per_layer * c->L, hint, c->D * 2));
-        most = one > most ? one : most;
-        most = all > most ? all : most;
-    }
+    const size_t one = attn_partial_bytes(c, per_layer, most_splits(per_layer, c->cap));
+    const size_t all = attn_partial_bytes(c, per_layer * c->L, most_splits(per_layer * c->L, c->cap));
+    const size_t most = one > all ? one : all;
     return attn_offset(c) + most;
 }
 

@@ -1,0 +1,142 @@
+"""Decode attention at the edges of its tiles and rounds: lengths around one row, one 32-row tile, one round of four tiles
+per workgroup and the counts where the number of workgroups per segment changes, every unused row of the cache holding
+NaN (a wave asks for its first tile before it knows the length, and the appended row is put into its tile from the
+call's arguments, so none of these rows may reach the result), both head sizes, every entry point.
+
+Against fp64 attention on the CPU, 1e-4 absolute: the probabilities enter the second product with 2^-16 relative error
+against values of at most ~5, the rest is fp32."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-4
+LENGTHS = [1, 2, 31, 32, 33, 63, 64, 65, 127, 128, 129, 160, 161, 255, 256, 257, 383, 385, 511, 512, 513, 700, 1023, 1025]
+
+
+def _ngc():
+    from paper_2604_18002_amd import binding
+    binding.load_library()
+    return binding
+
+
+def _reference(q, k, v, n, scale):
+    """q [Hq, D], k, v [H, N, D] (fp64), n [H] -> [Hq, D], lse [Hq]"""
+    import torch
+    H, N, D = k.shape
+    out, lse = [], []
+    for h in range(H):
+        s = q.view(H, -1, D)[h] @ k[h, :n[h]].t() * scale
+        out.append(torch.softmax(s, -1) @ v[h, :n[h]])
+        lse.append(torch.logsumexp(s, -1))
+    return torch.cat(out), torch.cat(lse)
+
+
+@pytest.mark.parametrize("B", [1, 6, 40])         # 2, 12, 80 segments: up to 64, 21 and 3 workgroups a segment
+@pytest.mark.parametrize("D,Hq", [(64, 8), (128, 12)])
+def test_lengths_around_tiles_and_rounds_with_nan_beyond_them(B, D, Hq):
+    import torch
+    ngc = _ngc()
+    H, cap, scale = 2, 1040, D ** -0.5
+    g = torch.Generator().manual_seed(B * 1000 + D)
+    lens = [LENGTHS[(i * 7 + B) % len(LENGTHS)] for i in range(B * H)]
+    if B == 1:
+        groups = [LENGTHS[i:i + 2] for i in range(0, len(LENGTHS), 2)]
+    else:
+        groups = [lens]
+    for lens in groups:
+        n = torch.tensor(lens, dtype=torch.int32).view(1, B, H)
+        k = torch.randn(1, B, H, cap, D, generator=g).to(torch.bfloat16)
+        v = torch.randn(1, B, H, cap, D, generator=g).to(torch.bfloat16)
+        q = torch.randn(B, Hq, D, generator=g).to(torch.bfloat16)
+        row = torch.arange(cap)
+        for grow in (False, True):
+            used = (n - 1 if grow else n)                     # rows in the cache before the call
+            unused = row[None, None, None] >= used[..., None]
+            dk, dv = k.clone(), v.clone()
+            dk[unused], dv[unused] = float("nan"), float("nan")
+            for hint in (0, int(n.max()), 4 * int(n.max())):
+                c = ngc.Cache(dk.cuda(), dv.cuda(), used.cuda().contiguous(), None, Hq)
+                ws = ngc.allocate_workspace(c, 1)
+                out, lse = torch.zeros(B, Hq, D, device="cuda"), torch.zeros(B, Hq, device="cuda")
+                print(f"[decode-edges] B={B} D={D} grow={grow} hint={hint} n={lens[:4]}", flush=True)
+                if grow:
+                    at = (n[0].long() - 1)[..., None, None].expand(B, H, 1, D)
+                    kn, vn = k[0].gather(2, at)[:, :, 0], v[0].gather(2, at)[:, :, 0]
+                    ngc.ngc_decode_step(c, 0, kn.cuda().contiguous(), vn.cuda().contiguous(), None, q.cuda(), scale,
+                                        hint, out, ws, lse_out=lse)
+                else:
+                    ngc.ngc_decode_attn(c, 0, q.cuda(), scale, hint, out, ws, lse_out=lse)
+                    out2 = torch.zeros_like(out)
+                    ngc.ngc_decode_attn_static(c, 0, q.cuda(), scale, hint, out2)
+                    assert torch.equal(out, out2)
+                assert torch.equal(c.len.cpu(), n)
+                assert ngc.read_status(ws)[:4] == [0, 0, 0, 0]
+                got, got_lse = out.cpu().double(), lse.cpu().double()
+                for b in range(B):
+                    want, want_lse = _reference(q[b].double(), k[0, b].double(), v[0, b].double(), n[0, b].tolist(), scale)
+                    assert (got[b] - want).abs().max() <= TOL, (b, lens[2 * b:2 * b + 2])
+                    assert (got_lse[b] - want_lse).abs().max() <= 2e-5, (b, lens[2 * b:2 * b + 2])
+                if grow:
+                    hk, hv = c.k.cpu()[0], c.v.cpu()[0]
+                    assert torch.equal(hk.gather(2, at)[:, :, 0], kn) and torch.equal(hv.gather(2, at)[:, :, 0], vn)
+
+
+@pytest.mark.parametrize("page", [32, 128])
+def test_paged_lengths_with_nan_beyond_them_and_stale_table_entries(page):
+    import torch
+    ngc = _ngc()
+    B, H, Hq, D, scale = 6, 2, 12, 128, 128 ** -0.5
+    g = torch.Generator().manual_seed(page)
+    lens = [LENGTHS[(i * 5) % len(LENGTHS)] for i in range(B * H)]
+    n = torch.tensor(lens, dtype=torch.int32).view(1, B, H)
+    max_pages = 1040 // page + 2
+    num_pages = B * H * max_pages
+    order = torch.randperm(num_pages, generator=g).to(torch.int32)
+    table = torch.where(torch.rand(1, B, H, max_pages, generator=g) < 0.5, torch.tensor(-7), torch.tensor(1 << 30)).to(torch.int32)
+    kp = torch.full((num_pages, page, D), float("nan"), dtype=torch.bfloat16)
+    vp = kp.clone()
+    k = torch.randn(B, H, 1040, D, generator=g).to(torch.bfloat16)
+    v = torch.randn(B, H, 1040, D, generator=g).to(torch.bfloat16)
+    used = 0
+    for b in range(B):
+        for h in range(H):
+            m = int(n[0, b, h])
+            for j in range((m + page - 1) // page):
+                p = int(order[used])
+                used += 1
+                table[0, b, h, j] = p
+                rows = min(page, m - j * page)
+                kp[p, :rows], vp[p, :rows] = k[b, h, j * page:j * page + rows], v[b, h, j * page:j * page + rows]
+    q = torch.randn(B, Hq, D, generator=g).to(torch.bfloat16)
+    pc = ngc.PagedCache(kp.cuda(), vp.cuda(), None, table.cuda(), n.cuda(), torch.zeros(num_pages, dtype=torch.int32).cuda(),
+                        torch.zeros(1, dtype=torch.int32).cuda(), Hq)
+    ws = ngc.allocate_paged_workspace(pc)
+    for hint in (0, 600, 1040):
+        out, lse = torch.zeros(B, Hq, D, device="cuda"), torch.zeros(B, Hq, device="cuda")
+        print(f"[decode-edges] paged page={page} hint={hint}", flush=True)
+        ngc.ngc_paged_decode_attn(pc, 0, q.cuda(), scale, hint, out, ws, lse_out=lse)
+        for b in range(B):
+            want, want_lse = _reference(q[b].double(), k[b].double(), v[b].double(), n[0, b].tolist(), scale)
+            assert (out.cpu().double()[b] - want).abs().max() <= TOL, b
+            assert (lse.cpu().double()[b] - want_lse).abs().max() <= 2e-5, b
+
+
+def test_split_rule_stays_inside_the_workspace_it_promises():
+    """Whatever the length hint, the partials of a launch fit the workspace (a launch that finds less quietly takes fewer
+    workgroups): results with the promised size and with a far larger one are the same bits."""
+    import torch
+    ngc = _ngc()
+    B, H, Hq, D, cap = 3, 2, 32, 128, 3000
+    g = torch.Generator(device="cuda").manual_seed(5)
+    c = ngc.Cache(torch.randn(1, B, H, cap, D, generator=g, device="cuda").to(torch.bfloat16),
+                  torch.randn(1, B, H, cap, D, generator=g, device="cuda").to(torch.bfloat16),
+                  torch.full((1, B, H), 2900, dtype=torch.int32, device="cuda"), None, Hq)
+    q = torch.randn(B, Hq, D, generator=g, device="cuda").to(torch.bfloat16)
+    ws = ngc.allocate_workspace(c, 1)
+    big = torch.zeros(ws.numel() + (16 << 20), dtype=torch.uint8, device="cuda")
+    for hint in [0] + list(range(100, 3001, 100)):
+        a, b = torch.zeros(B, Hq, D, device="cuda"), torch.zeros(B, Hq, D, device="cuda")
+        ngc.ngc_decode_attn(c, 0, q, D ** -0.5, hint, a, ws)
+        ngc.ngc_decode_attn(c, 0, q, D ** -0.5, hint, b, big)
+        assert torch.equal(a, b), hint
