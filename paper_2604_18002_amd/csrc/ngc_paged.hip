@@ -207,6 +207,81 @@ __global__ __launch_bounds__(64) void paged_append_kernel(PagedAppendArgs a)
     }
 }
 
+// Grant and append in one launch, by one workgroup, for a layer of a small batch.  The two kernels above take 4.6 us
+// together whatever the number of segments (HIP graph; plus a launch on the host); this one 3.1 us at 32 segments, 3.8
+// at 128, 5.2 at 256 of 256-byte rows and 3.0, 3.3, 3.8, 4.5 (384) of 128-byte rows: it is the copy by one workgroup
+// that grows, hence the limit on the rows' bytes.  Segment i belongs to thread i for the grant; then 2 * PIECES
+// consecutive threads copy a segment's K and V row.  The new rows are asked for first: they wait for nothing.
+constexpr int ONE_LAUNCH_BYTES = 48 * 1024;                    // of new K rows
+constexpr int ONE_LAUNCH_SEGMENTS = ONE_LAUNCH_BYTES / 128;    // at the smaller row
+static_assert(ONE_LAUNCH_SEGMENTS <= POOL_SCAN_THREADS, "a thread per segment");
+
+template <int ROW_BYTES>
+__global__ __launch_bounds__(POOL_SCAN_THREADS) void paged_grow_kernel(PagedArgs pa, PagedAppendArgs a)
+{
+    constexpr int PIECES = ROW_BYTES / 16;
+    constexpr int SEGS_PER_STEP = POOL_SCAN_THREADS / (2 * PIECES);
+    constexpr int PREFETCH = 4;                                        // steps whose rows are asked for in advance
+    __shared__ int tmp[32];
+    __shared__ int page_of[ONE_LAUNCH_SEGMENTS];                       // page of the new row, -1: no room
+    __shared__ int len_of[ONE_LAUNCH_SEGMENTS];
+    const int tid = threadIdx.x;
+    const int sub = tid / (2 * PIECES), lane = tid % (2 * PIECES);     // copy role
+    const bool is_v = lane >= PIECES;
+    const int piece = is_v ? lane - PIECES : lane;
+    const unsigned char *src = is_v ? a.v_new : a.k_new;               // row i belongs to the launch's segment i
+    u32x4 rows[PREFETCH];
+#pragma unroll
+    for (int u = 0; u < PREFETCH; ++u) {
+        int i = u * SEGS_PER_STEP + sub;
+        i = i < pa.nseg ? i : pa.nseg - 1;
+        rows[u] = *reinterpret_cast<const u32x4 *>(src + (size_t)i * ROW_BYTES + piece * 16);
+    }
+    const int count_raw = *pa.free_count;
+    const int count = count_raw < 0 ? 0 : (count_raw > pa.num_pages ? pa.num_pages : count_raw);
+    const int cap = pa.page_rows * pa.max_pages;
+    int n = -1;
+    if (tid < pa.nseg) n = pa.len[pa.seg0 + tid];
+    const bool fits = n >= 0 && n < cap;
+    const bool needs = fits && (n & (pa.page_rows - 1)) == 0;
+    int32_t *entry = pa.table + (size_t)(pa.seg0 + (tid < pa.nseg ? tid : 0)) * pa.max_pages + (fits ? n / pa.page_rows : 0);
+    int page = -1;
+    if (fits && !needs) page = *entry;
+    int total;
+    const int rank = block_excl_scan_i<POOL_SCAN_THREADS>(needs ? 1 : 0, tmp, &total);   // every thread has read the count
+    if (needs) {
+        page = rank < count ? pa.free_stack[count - 1 - rank] : -1;
+        *entry = page;
+    }
+    if (tid < pa.nseg) {
+        const bool outside = page < 0 || page >= pa.num_pages;
+        if (outside) {
+            atomicAdd(&pa.status[NGC_STATUS_APPEND_FULL], 1);
+            if (page >= pa.num_pages) atomicAdd(&pa.status[NGC_STATUS_POOL_BOUNDS], 1);
+        } else {
+            pa.len[pa.seg0 + tid] = n + 1;
+            if (a.pos_pool && a.new_pos)
+                a.pos_pool[(size_t)page * pa.page_rows + (n & (pa.page_rows - 1))] = a.new_pos[((pa.seg0 + tid) / a.Hkv) % a.B];
+        }
+        page_of[tid] = outside ? -1 : page;
+        len_of[tid] = n;
+    }
+    if (tid == 0) {
+        if (count != count_raw) atomicAdd(&pa.status[NGC_STATUS_POOL_BOUNDS], 1);
+        *pa.free_count = count > total ? count - total : 0;
+    }
+    __syncthreads();
+    auto store = [&](int i, u32x4 row) {
+        if (i >= pa.nseg || page_of[i] < 0) return;
+        const size_t at = (size_t)page_of[i] * pa.page_rows + (len_of[i] & (pa.page_rows - 1));
+        *reinterpret_cast<u32x4 *>((is_v ? a.v_pool : a.k_pool) + at * ROW_BYTES + piece * 16) = row;
+    };
+#pragma unroll
+    for (int u = 0; u < PREFETCH; ++u) store(u * SEGS_PER_STEP + sub, rows[u]);
+    for (int i = PREFETCH * SEGS_PER_STEP + sub; i < pa.nseg; i += SEGS_PER_STEP)
+        store(i, *reinterpret_cast<const u32x4 *>(src + (size_t)i * ROW_BYTES + piece * 16));
+}
+
 }  // namespace ngc
 
 // ============================================================ host side ====
@@ -349,8 +424,6 @@ extern "C" int ngc_paged_append(const ngc_paged_cache *pc, int32_t layer, const 
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
     PagedArgs pa = paged_args(pc, ws, seg0, nseg);
-    hipLaunchKernelGGL(paged_grant_kernel, dim3(1), dim3(POOL_SCAN_THREADS), 0, st, pa);
-    NGC_HIP_CHECK(hipGetLastError());
     PagedAppendArgs aa;
     aa.k_pool = reinterpret_cast<unsigned char *>(pc->k_pool);
     aa.v_pool = reinterpret_cast<unsigned char *>(pc->v_pool);
@@ -362,6 +435,16 @@ extern "C" int ngc_paged_append(const ngc_paged_cache *pc, int32_t layer, const 
     aa.seg0 = seg0; aa.src_seg0 = seg0;
     aa.B = pc->B; aa.Hkv = pc->Hkv;
     aa.page_rows = pc->page_rows; aa.max_pages = pc->max_pages; aa.num_pages = pc->num_pages;
+    if ((long long)nseg * pc->D * 2 <= ONE_LAUNCH_BYTES) {
+        if (pc->D == 128)
+            hipLaunchKernelGGL(paged_grow_kernel<256>, dim3(1), dim3(POOL_SCAN_THREADS), 0, st, pa, aa);
+        else
+            hipLaunchKernelGGL(paged_grow_kernel<128>, dim3(1), dim3(POOL_SCAN_THREADS), 0, st, pa, aa);
+        NGC_HIP_CHECK(hipGetLastError());
+        return NGC_OK;
+    }
+    hipLaunchKernelGGL(paged_grant_kernel, dim3(1), dim3(POOL_SCAN_THREADS), 0, st, pa);
+    NGC_HIP_CHECK(hipGetLastError());
     if (pc->D == 128)
         hipLaunchKernelGGL(paged_append_kernel<256>, dim3(nseg), dim3(64), 0, st, aa);
     else

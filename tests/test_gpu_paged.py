@@ -603,3 +603,62 @@ def test_large_pages():
     assert_same_state(pc, m, wl, "large pages, appends")
     check_attention(pc, m, wl, ws, -1, 2)
     assert all(x == 0 for x in ngc.read_status(ws))
+
+
+@pytest.mark.parametrize("D,B,H", [(128, 96, 2), (128, 97, 2), (64, 192, 2), (64, 193, 2), (128, 1, 1), (64, 33, 1)])
+def test_append_on_both_sides_of_the_one_launch_limit(D, B, H):
+    """A layer's append as one launch (up to 48 KB of new K rows) and as two: pages, lengths, rows, free stack and status
+    equal the model's, with segments that are full, a pool that runs dry, lengths on page boundaries and positions."""
+    import torch
+    ngc = _ngc()
+    P, max_pages, L = 32, 3, 2
+    rng = np.random.default_rng(B * D)
+    nseg, cap = B * H, P * max_pages
+    num_pages = L * nseg * 2 + 7
+    lens = rng.choice([0, 1, 31, 32, 33, 63, 64, 65, cap - 1, cap], size=(L, B, H)).astype(np.int32)
+    table = np.full((L, B, H, max_pages), -1, np.int32)
+    order = rng.permutation(num_pages).astype(np.int32)
+    used = 0
+    for idx in np.ndindex(L, B, H):
+        m = (lens[idx] + P - 1) // P
+        if used + m > num_pages - 5:
+            lens[idx], m = 0, 0
+        table[idx][:m] = order[used:used + m]
+        used += m
+    stack = np.zeros(num_pages, np.int32)
+    count = min(num_pages - used, nseg // 8 + 1)          # runs dry
+    stack[:count] = order[used:used + count]
+    d = lambda a: torch.from_numpy(a.copy()).cuda()
+    pc = ngc.PagedCache(torch.zeros(num_pages, P, D, dtype=torch.bfloat16, device="cuda"),
+                        torch.zeros(num_pages, P, D, dtype=torch.bfloat16, device="cuda"),
+                        torch.full((num_pages, P), -1, dtype=torch.int32, device="cuda"), d(table), d(lens), d(stack),
+                        d(np.array([count], np.int32)), H)
+    ws = ngc.allocate_paged_workspace(pc)
+    full = 0
+    for layer in (1, 0):
+        kn = torch.randn(B, H, D, device="cuda").to(torch.bfloat16)
+        vn = torch.randn(B, H, D, device="cuda").to(torch.bfloat16)
+        npos = np.arange(B, dtype=np.int32) + 100 * layer
+        print(f"[paged] one-launch append D={D} segments={nseg} layer={layer}", flush=True)
+        ngc.ngc_paged_append(pc, layer, kn, vn, d(npos), ws)
+        hk, hv, hp = pc.k_pool.cpu(), pc.v_pool.cpu(), pc.pos_pool.cpu().numpy()
+        for b in range(B):
+            for h in range(H):
+                n = int(lens[layer, b, h])
+                if n < cap and n % P == 0:
+                    page = -1
+                    if count > 0:
+                        count -= 1
+                        page = int(stack[count])
+                    table[layer, b, h, n // P] = page
+                page = int(table[layer, b, h, n // P]) if n < cap else -1
+                if page < 0:
+                    full += 1
+                    continue
+                assert torch.equal(hk[page, n % P], kn[b, h].cpu()) and torch.equal(hv[page, n % P], vn[b, h].cpu())
+                assert hp[page, n % P] == npos[b]
+                lens[layer, b, h] = n + 1
+        assert (pc.len.cpu().numpy() == lens).all() and (pc.table.cpu().numpy() == table).all()
+        assert int(pc.free_count) == count
+    status = ngc.read_status(ws)
+    assert status[ngc.STATUS_APPEND_FULL] == full and status[ngc.STATUS_POOL_BOUNDS] == 0
