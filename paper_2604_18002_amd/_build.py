@@ -1,15 +1,18 @@
 """Build the HIP libraries in-tree for gfx950: ``paper_2604_18002_amd/libngc.so`` (the method) and
-``paper_2604_18002_amd/libngc_probe.so`` (streaming probes for the measurement harness)."""
+``paper_2604_18002_amd/libngc_probe.so`` (streaming probes for the measurement harness); with the host compiler
+``paper_2604_18002_amd/_ngc_host.so`` (the Python front of the C ABI)."""
 from __future__ import annotations
 
 import os
 import shutil
 import subprocess
+import sysconfig
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _CSRC = os.path.join(_PKG, "csrc")
 LIB_PATH = os.path.join(_PKG, "libngc.so")
 PROBE_LIB_PATH = os.path.join(_PKG, "libngc_probe.so")   # measurement probes, not part of the method
+HOST_LIB_PATH = os.path.join(_PKG, "_ngc_host.so")       # CPython front of the C ABI (no device code)
 
 _COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
            # packed fp32 instructions stay off on the test machines
@@ -55,6 +58,14 @@ def build(verbose: bool = False) -> str:
         r = subprocess.run(cmd, capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"link failed:\n{r.stderr}")
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        raise RuntimeError("no host C++ compiler found; the Python front cannot be built")
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           "-I", sysconfig.get_paths()["include"], os.path.join(_CSRC, "ngc_host.cpp"), "-o", HOST_LIB_PATH, "-ldl"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cxx} failed on ngc_host.cpp:\n{r.stderr}")
     return LIB_PATH
 
 

@@ -1,6 +1,10 @@
-"""Thin ctypes binding of ``libngc.so`` (see ``include/ngc.h``).
+"""Thin binding of ``libngc.so`` (see ``include/ngc.h``).
 
-Argument marshalling only: every step of the path runs in the HIP kernels.
+Argument marshalling only: every step of the path runs in the HIP kernels.  The
+calls that enqueue work go through ``_ngc_host.so`` (``csrc/ngc_host.cpp``),
+which reads the tensors' pointers and calls the C ABI; ``load_library`` also
+gives the library as a ctypes object for callers that prepare the C arguments
+themselves.
 PyTorch tensors are used as device memory and for the current HIP stream; no
 torch operator takes part in the computation.  There is no CPU fallback: a
 missing library raises.
@@ -12,7 +16,7 @@ import os
 from dataclasses import dataclass
 from typing import Optional
 
-from ._build import LIB_PATH
+from ._build import HOST_LIB_PATH, LIB_PATH
 
 NGC_OK = 0
 NGC_EINVAL = -1
@@ -69,11 +73,12 @@ class ngc_evict_params(C.Structure):
 
 
 _lib = None
+_host = None      # the CPython front, opened on the same library
 
 
 def load_library(path: Optional[str] = None) -> C.CDLL:
     """Load the built library.  Raises if it has not been built."""
-    global _lib
+    global _lib, _host
     if _lib is not None and path is None:
         return _lib
     path = path or LIB_PATH
@@ -133,8 +138,21 @@ def load_library(path: Optional[str] = None) -> C.CDLL:
     lib.ngc_keep_counts.argtypes = [vp, i32, i32, i32, i32, i32, i32, i32, vp, vp]
     lib.ngc_keep_counts.restype = C.c_int
     if path == LIB_PATH:
+        if not os.path.exists(HOST_LIB_PATH):
+            raise RuntimeError(f"{HOST_LIB_PATH} is missing: build it first (python -m paper_2604_18002_amd._build); "
+                               "there is no fallback path")
+        from . import _ngc_host
+        _ngc_host.open(path)
+        _host = _ngc_host
         _lib = lib
     return lib
+
+
+def _front():
+    """The CPython front (loads the library on first use)."""
+    if _host is None:
+        load_library()
+    return _host
 
 
 def strerror(code: int) -> str:
@@ -149,11 +167,19 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+_current_raw_stream = None
+
+
 def _stream(stream) -> Optional[int]:
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+    global _current_raw_stream
+    if _current_raw_stream is None:
+        import torch
+        torch.cuda.current_stream()     # initialises the runtime (or says why it cannot)
+        get, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+        _current_raw_stream = lambda: get(device())     # noqa: E731  (the current stream of the current device)
+    return _current_raw_stream()
 
 
 def _check(rc: int, where: str) -> None:
@@ -219,68 +245,60 @@ def _i32():
 
 
 def ngc_perturbed_keys(cache: Cache, layer: int, logits, params: ngc_evict_params, keys_out, ws, stream=None):
-    v = cache.view()
-    _check(load_library().ngc_perturbed_keys(C.byref(v), layer, _ptr(logits), C.byref(params), _ptr(keys_out),
-                                             _ptr(ws), ws.numel(), _stream(stream)), "ngc_perturbed_keys")
+    _check(_front().perturbed_keys(cache, layer, logits, params, keys_out, ws, _stream(stream)),
+           "ngc_perturbed_keys")
 
 
 def ngc_evict(cache: Cache, layer: int, logits, keep, params: ngc_evict_params, max_keep: int,
               kept_out, sigma_out, logp_out, ws, stream=None):
-    v = cache.view()
-    _check(load_library().ngc_evict(C.byref(v), layer, _ptr(logits), _ptr(keep), C.byref(params), max_keep,
-                                    _ptr(kept_out), _ptr(sigma_out), _ptr(logp_out), _ptr(ws), ws.numel(),
-                                    _stream(stream)), "ngc_evict")
+    _check(_front().evict(cache, layer, logits, keep, params, max_keep, kept_out, sigma_out, logp_out, ws,
+                          _stream(stream)),
+           "ngc_evict")
 
 
 def ngc_subset_logprob(logits, n_items, sigma, keep, nseg: int, logit_stride: int, sigma_stride: int,
                        logp_out, ws, stream=None):
-    _check(load_library().ngc_subset_logprob(_ptr(logits), _ptr(n_items), _ptr(sigma), _ptr(keep), nseg,
-                                             logit_stride, sigma_stride, _ptr(logp_out), _ptr(ws), ws.numel(),
-                                             _stream(stream)), "ngc_subset_logprob")
+    _check(_front().subset_logprob(logits, n_items, sigma, keep, nseg, logit_stride, sigma_stride, logp_out, ws,
+                                   _stream(stream)),
+           "ngc_subset_logprob")
 
 
 def ngc_cache_append(cache: Cache, layer: int, k_new, v_new, new_pos, ws, stream=None):
-    v = cache.view()
-    _check(load_library().ngc_cache_append(C.byref(v), layer, _ptr(k_new), _ptr(v_new), _ptr(new_pos),
-                                           _ptr(ws), ws.numel(), _stream(stream)), "ngc_cache_append")
+    _check(_front().cache_append(cache, layer, k_new, v_new, new_pos, ws, _stream(stream)),
+           "ngc_cache_append")
 
 
 def ngc_decode_attn(cache: Cache, layer: int, q, scale: float, max_len_hint: int, out, ws, stream=None,
                     lse_out=None):
-    v = cache.view()
-    _check(load_library().ngc_decode_attn(C.byref(v), layer, _ptr(q), scale, max_len_hint, _ptr(out),
-                                          _ptr(lse_out), _ptr(ws), ws.numel(), _stream(stream)), "ngc_decode_attn")
+    _check(_front().decode_attn(cache, layer, q, scale, max_len_hint, out, lse_out, ws, _stream(stream)),
+           "ngc_decode_attn")
 
 
 def ngc_decode_step(cache: Cache, layer: int, k_new, v_new, new_pos, q, scale: float, max_len_hint: int, out, ws,
                     stream=None, lse_out=None):
-    v = cache.view()
-    _check(load_library().ngc_decode_step(C.byref(v), layer, _ptr(k_new), _ptr(v_new), _ptr(new_pos), _ptr(q), scale,
-                                          max_len_hint, _ptr(out), _ptr(lse_out), _ptr(ws), ws.numel(),
-                                          _stream(stream)), "ngc_decode_step")
+    _check(_front().decode_step(cache, layer, k_new, v_new, new_pos, q, scale, max_len_hint, out, lse_out, ws,
+                                _stream(stream)),
+           "ngc_decode_step")
 
 
 def ngc_decode_attn_static(cache: Cache, layer: int, q, scale: float, max_len_hint: int, out, stream=None,
                            lse_out=None, status=None):
-    v = cache.view()
-    _check(load_library().ngc_decode_attn_static(C.byref(v), layer, _ptr(q), scale, max_len_hint, _ptr(out),
-                                                 _ptr(lse_out), _ptr(status), _stream(stream)),
+    _check(_front().decode_attn_static(cache, layer, q, scale, max_len_hint, out, lse_out, status,
+                                       _stream(stream)),
            "ngc_decode_attn_static")
 
 
 def ngc_score_keys(cache: Cache, layer: int, q_recent, w: int, scale: float, flags: int, block: int,
                    scores_out, ws, stream=None, lse_recent=None):
-    v = cache.view()
-    _check(load_library().ngc_score_keys(C.byref(v), layer, _ptr(q_recent), _ptr(lse_recent), w, scale, flags, block,
-                                         _ptr(scores_out), _ptr(ws), ws.numel(), _stream(stream)),
+    _check(_front().score_keys(cache, layer, q_recent, lse_recent, w, scale, flags, block, scores_out, ws,
+                               _stream(stream)),
            "ngc_score_keys")
 
 
 def ngc_subset_logprob_backward(logits, n_items, sigma, keep, nseg: int, logit_stride: int, sigma_stride: int,
                                 max_keep: int, gout, grad_out, ws, stream=None):
-    _check(load_library().ngc_subset_logprob_backward(_ptr(logits), _ptr(n_items), _ptr(sigma), _ptr(keep), nseg,
-                                                      logit_stride, sigma_stride, max_keep, _ptr(gout),
-                                                      _ptr(grad_out), _ptr(ws), ws.numel(), _stream(stream)),
+    _check(_front().subset_logprob_backward(logits, n_items, sigma, keep, nseg, logit_stride, sigma_stride,
+                                            max_keep, gout, grad_out, ws, _stream(stream)),
            "ngc_subset_logprob_backward")
 
 
@@ -290,9 +308,9 @@ def ngc_replay_workspace_bytes(B: int, T: int, Hkv: int) -> int:
 
 def ngc_replay_attn(q, k, v, death, B: int, T: int, Hq: int, Hkv: int, D: int, death_per_head: bool,
                     scale: float, out, ws, stream=None):
-    _check(load_library().ngc_replay_attn(_ptr(q), _ptr(k), _ptr(v), _ptr(death), B, T, Hq, Hkv, D,
-                                          1 if death_per_head else 0, scale, _ptr(out), _ptr(ws), ws.numel(),
-                                          _stream(stream)), "ngc_replay_attn")
+    _check(_front().replay_attn(q, k, v, death, B, T, Hq, Hkv, D, 1 if death_per_head else 0, scale, out, ws,
+                                _stream(stream)),
+           "ngc_replay_attn")
 
 
 # ------------------------------------------------------------- paged layout ---
@@ -356,41 +374,37 @@ def allocate_paged_workspace(pc: PagedCache):
 
 def ngc_paged_evict(pc: PagedCache, layer: int, logits, logit_stride: int, keep, params: ngc_evict_params,
                     max_keep: int, kept_out, sigma_out, logp_out, ws, stream=None):
-    v = pc.view()
-    _check(load_library().ngc_paged_evict(C.byref(v), layer, _ptr(logits), logit_stride, _ptr(keep),
-                                          C.byref(params), max_keep, _ptr(kept_out), _ptr(sigma_out),
-                                          _ptr(logp_out), _ptr(ws), ws.numel(), _stream(stream)), "ngc_paged_evict")
+    _check(_front().paged_evict(pc, layer, logits, logit_stride, keep, params, max_keep, kept_out, sigma_out,
+                                logp_out, ws, _stream(stream)),
+           "ngc_paged_evict")
 
 
 def ngc_paged_append(pc: PagedCache, layer: int, k_new, v_new, new_pos, ws, stream=None):
-    v = pc.view()
-    _check(load_library().ngc_paged_append(C.byref(v), layer, _ptr(k_new), _ptr(v_new), _ptr(new_pos),
-                                           _ptr(ws), ws.numel(), _stream(stream)), "ngc_paged_append")
+    _check(_front().paged_append(pc, layer, k_new, v_new, new_pos, ws, _stream(stream)),
+           "ngc_paged_append")
 
 
 def ngc_paged_decode_attn(pc: PagedCache, layer: int, q, scale: float, max_len_hint: int, out, ws, stream=None,
                           lse_out=None):
-    v = pc.view()
-    _check(load_library().ngc_paged_decode_attn(C.byref(v), layer, _ptr(q), scale, max_len_hint, _ptr(out),
-                                                _ptr(lse_out), _ptr(ws), ws.numel(), _stream(stream)),
+    _check(_front().paged_decode_attn(pc, layer, q, scale, max_len_hint, out, lse_out, ws, _stream(stream)),
            "ngc_paged_decode_attn")
 
 
 def ngc_paged_score_keys(pc: PagedCache, layer: int, q_recent, w: int, scale: float, flags: int, block: int,
                          scores_out, ws, stream=None, lse_recent=None):
-    v = pc.view()
-    _check(load_library().ngc_paged_score_keys(C.byref(v), layer, _ptr(q_recent), _ptr(lse_recent), w, scale, flags,
-                                               block, _ptr(scores_out), _ptr(ws), ws.numel(), _stream(stream)),
+    _check(_front().paged_score_keys(pc, layer, q_recent, lse_recent, w, scale, flags, block, scores_out, ws,
+                                     _stream(stream)),
            "ngc_paged_score_keys")
 
 
 def ngc_lmem(logp, rounds, reward, R: int, L: int, B: int, Hkv: int, group: int, adv_out, loss_layer, loss,
              gout, stream=None):
-    _check(load_library().ngc_lmem(_ptr(logp), _ptr(rounds), _ptr(reward), R, L, B, Hkv, group, _ptr(adv_out),
-                                   _ptr(loss_layer), _ptr(loss), _ptr(gout), _stream(stream)), "ngc_lmem")
+    _check(_front().lmem(logp, rounds, reward, R, L, B, Hkv, group, adv_out, loss_layer, loss, gout,
+                         _stream(stream)),
+           "ngc_lmem")
 
 
 def ngc_keep_counts(len_t, seg0: int, nseg: int, cap: int, block: int, num: int, den: int, min_keep: int, keep_out,
                     stream=None):
-    _check(load_library().ngc_keep_counts(_ptr(len_t), seg0, nseg, cap, block, num, den, min_keep, _ptr(keep_out),
-                                          _stream(stream)), "ngc_keep_counts")
+    _check(_front().keep_counts(len_t, seg0, nseg, cap, block, num, den, min_keep, keep_out, _stream(stream)),
+           "ngc_keep_counts")
