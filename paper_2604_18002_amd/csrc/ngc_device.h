@@ -15,8 +15,10 @@
 namespace ngc {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -60,6 +62,36 @@ __device__ __forceinline__ float quad_rows_sum(float v)
     u = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
     auto b = __builtin_amdgcn_permlane16_swap(u, u, false, false);
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// The same over the two lanes {l, l ^ 32} (the lane halves that share lane % 32 in 32-wide matrix tiles).
+__device__ __forceinline__ float half_rows_max(float v)
+{
+    const uint32_t u = __float_as_uint(v);
+    auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return max_no_nan(__uint_as_float(a[0]), __uint_as_float(a[1]));
+}
+__device__ __forceinline__ float half_rows_sum(float v)
+{
+    const uint32_t u = __float_as_uint(v);
+    auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return __uint_as_float(a[0]) + __uint_as_float(a[1]);
+}
+
+// 16 bytes per lane from memory straight into LDS, lane l to lds + 16 l (lds wave-uniform); counts as a vector
+// memory load, so a barrier that follows it (__syncthreads) waits for it.
+__device__ __forceinline__ void load_to_lds16(const void *src, void *lds)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t *)(uintptr_t)src,
+                                     (__attribute__((address_space(3))) uint32_t *)lds, 16, 0, 0);
+}
+
+// Four 16-bit values per lane from LDS, transposed within each 16 lanes: lane x gets value x % 4 of the lanes x / 4,
+// 4 + x / 4, 8 + x / 4, 12 + x / 4 (each lane's own address names four consecutive values).
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ u32x2 read_transposed16(const void *lds)
+{
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)lds));
 }
 
 __device__ __forceinline__ int wave_sum_i(int v)

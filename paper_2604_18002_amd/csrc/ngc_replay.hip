@@ -11,11 +11,21 @@
 // retained cache, not the T x T triangle.  The lists are shared by all query
 // heads that share the decisions.
 //
-// Flash-attention forward on the matrix cores, same operand scheme as the
-// decode kernel (S^T = K Q^T, O^T = V^T P, query on lane%16, P as bf16 head +
-// remainder).  A workgroup = 4 waves x 32 query positions of one query head;
-// K/V tiles of 32 keys are loaded cooperatively into double-buffered LDS and
-// shared by the 4 waves.
+// Flash-attention forward on the matrix cores (S^T = K Q^T, O^T = V^T P, mfma 32x32x16: one query per lane % 32, so all
+// soft-max state is lane local and crosses lanes once, between the two halves; P as bf16 head + remainder).  A workgroup
+// = 4 waves x 32 query positions of one query head; tiles of 64 keys go from memory straight into double-buffered LDS
+// (no registers, no LDS store instructions) and are shared by the waves; the V operand is read transposed from LDS.
+//
+// What bounds it: matrix and vector work of two waves per SIMD that overlap only in part, then the output.  B = 8,
+// T = 4096, 28/4 heads, 27 % of the causal pairs visible (the issued products are worth 390 TFLOP): without the tile
+// loads 403 us, without the products 281 us, with neither 113 us (470 MB of output), together 470 us.  Against the
+// version with 16-wide tiles and rows staged through registers (552 us): 32-wide tiles and loads straight to LDS 511 us;
+// a reference for the exponents that moves only when outgrown by 2^8, and transposing reads of V instead of 32 byte
+// permutes a step, 464 us; the output through LDS in whole lines, nontemporal, and the list kernel in one pass 440 us.
+// At B = 16, T = 1050, 12/2 heads 116 -> 83 us.  Measured and not kept: two independent score accumulators (the chain
+// already issues every 32 cycles), two steps per soft-max (spills at 256 registers, 668 us), 32-key tiles with two
+// (+4 %) or three waves per SIMD (spills at 168 registers, +18 %), the remainder of P by a bf16 dot product (4 instead
+// of 6 instructions a pair, no faster), output straight from the registers nontemporal (+20 %: partial lines).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -33,6 +43,16 @@ constexpr int RP_MT = 32;                    // keys per step of the math (and p
 // Start of the running max: finite and below every real score, so that 2^(x - m) is 0 for a masked
 // x = -inf without a special case, and the first rescale factor 2^(m_init - m_new) is 0.
 constexpr float RP_M_INIT = -1.0e30f;
+constexpr float RP_LAZY = 8.0f;
+
+// RP_MT consecutive keys of a list: the first and the last of them and the smallest death position among them
+// (8 bytes, read as one word: first in the lowest 16 bits, min_death in the upper half).  `last` is beyond every key for
+// the list's last step if it has fewer keys: such a step needs the mask.
+constexpr uint16_t STEP_PARTIAL = 0xFFFF;    // T <= 65535
+struct StepInfo {
+    uint16_t first, last;
+    int32_t min_death;
+};
 
 struct ReplayArgs {
     const unsigned char *q;    // bf16 [B][T][Hq][D]
@@ -41,17 +61,30 @@ struct ReplayArgs {
     const int32_t *death;      // [B][Hd][T]
     uint16_t *klist;           // [B*Hd][nqt][T] visible keys per query tile, ascending
     int32_t *kcount;           // [B*Hd][nqt]
-    int32_t *tile_death;       // [B*Hd][nqt][ceil(T/32)] smallest death among each RP_MT keys of a list
+    StepInfo *steps;           // [B*Hd][nqt][ceil(T/32)] what a wave has to know about each RP_MT keys of a list
     float *out;                // fp32 [B][T][Hq][D]
     int B, T, Hq, Hkv, Hd;     // Hd = Hkv (a death row per KV head) or 1 (shared by the heads)
     float scale_log2e;
 };
 
-// Ordered compaction (ballot + prefix over the 4 waves), 256 keys per step.
-__global__ __launch_bounds__(RP_WAVES * 64) void replay_lists_kernel(ReplayArgs a)
+// Ordered compaction, LIST_PASS keys per pass (one pass up to 4096 positions: its keys' death positions are all asked
+// for at once).  Key j0 + 256 i + tid belongs to thread tid's i-th bit: ballots give the counts of every (i, wave),
+// a scan over those 64 numbers their order.  What the attention kernel has to know about each RP_MT keys is gathered
+// in LDS on the way.  (256 keys per pass, and a second walk over the list for the steps: 16 us at 256 lists of 4096
+// positions, 9 us at 144 lists of 1050; now 6.4 and 5.0, most of it launch and two memory round trips.)
+constexpr int LIST_THREADS = 256;
+constexpr int LIST_BITS = 16;
+constexpr int LIST_PASS = LIST_THREADS * LIST_BITS;
+constexpr int LIST_WAVES = LIST_THREADS / NGC_WAVE;
+constexpr int LIST_MAX_STEPS = 65536 / RP_MT;
+
+__global__ __launch_bounds__(LIST_THREADS) void replay_lists_kernel(ReplayArgs a)
 {
-    __shared__ int wave_cnt[RP_WAVES];
-    const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
+    static_assert(LIST_BITS * LIST_WAVES == NGC_WAVE, "a wave scans the counts of a pass");
+    __shared__ int counts[LIST_BITS * LIST_WAVES];
+    __shared__ int min_death[LIST_MAX_STEPS];
+    __shared__ uint16_t first_key[LIST_MAX_STEPS], last_key[LIST_MAX_STEPS];
+    const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
     const int T = a.T;
     const int nqt = (T + RP_QT - 1) / RP_QT;
     const int qt = blockIdx.x, row = blockIdx.y;          // row = b * Hd + hd
@@ -59,38 +92,45 @@ __global__ __launch_bounds__(RP_WAVES * 64) void replay_lists_kernel(ReplayArgs 
     const int last_pos = (i0 + RP_QT - 1 < T - 1) ? i0 + RP_QT - 1 : T - 1;
     const int32_t *death = a.death + (size_t)row * T;
     uint16_t *klist = a.klist + ((size_t)row * nqt + qt) * T;
+    for (int s = tid; s * RP_MT <= last_pos; s += LIST_THREADS) {
+        min_death[s] = 0x7FFFFFFF;
+        last_key[s] = STEP_PARTIAL;
+    }
     int n_list = 0;
-    for (int j0 = 0; j0 <= last_pos; j0 += RP_WAVES * 64) {
-        const int j = j0 + tid;
-        const bool pred = j <= last_pos && death[j] > i0;
-        const uint64_t bal = __ballot(pred);
-        if (lane == 0) wave_cnt[wv] = __popcll(bal);
-        __syncthreads();
-        int before = 0, total = 0;
+    for (int j0 = 0; j0 <= last_pos; j0 += LIST_PASS) {
+        int d[LIST_BITS];
 #pragma unroll
-        for (int x = 0; x < RP_WAVES; ++x) {
-            const int c = wave_cnt[x];
-            if (x < wv) before += c;
-            total += c;
+        for (int i = 0; i < LIST_BITS; ++i) {
+            const int j = j0 + i * LIST_THREADS + tid;
+            d[i] = j <= last_pos ? death[j] : -1;          // (a key no query of the tile sees)
         }
-        if (pred) klist[n_list + before + popc_below(bal)] = (uint16_t)j;
-        n_list += total;
+        uint64_t seen[LIST_BITS];
+#pragma unroll
+        for (int i = 0; i < LIST_BITS; ++i) {
+            seen[i] = __ballot(d[i] > i0);
+            if (lane == 0) counts[i * LIST_WAVES + wv] = __popcll(seen[i]);
+        }
+        __syncthreads();
+        const int mine = counts[lane];
+        const int upto = wave_incl_scan_i(mine);
+#pragma unroll
+        for (int i = 0; i < LIST_BITS; ++i) {
+            const int before = __builtin_amdgcn_readlane(upto - mine, i * LIST_WAVES + wv);
+            if (d[i] > i0) {
+                const int j = j0 + i * LIST_THREADS + tid;
+                const int slot = n_list + before + popc_below(seen[i]);
+                klist[slot] = (uint16_t)j;
+                atomicMin(&min_death[slot / RP_MT], d[i]);
+                if (slot % RP_MT == 0) first_key[slot / RP_MT] = (uint16_t)j;
+                if (slot % RP_MT == RP_MT - 1) last_key[slot / RP_MT] = (uint16_t)j;
+            }
+        }
+        n_list += __builtin_amdgcn_readlane(upto, NGC_WAVE - 1);
         __syncthreads();
     }
     if (tid == 0) a.kcount[(size_t)row * nqt + qt] = n_list;
-    // smallest death per list tile: a tile whose keys all outlive a wave's queries needs no per-element mask
-    // (the list writes above are this workgroup's own and the loop ended on a barrier)
-    const int tiles_max = (T + RP_MT - 1) / RP_MT;
-    int32_t *tmin = a.tile_death + ((size_t)row * nqt + qt) * tiles_max;
-    for (int t = tid; t * RP_MT < n_list; t += RP_WAVES * 64) {
-        const int s1 = (t + 1) * RP_MT < n_list ? (t + 1) * RP_MT : n_list;
-        int m = 0x7FFFFFFF;
-        for (int s = t * RP_MT; s < s1; ++s) {
-            const int d = death[klist[s]];
-            m = d < m ? d : m;
-        }
-        tmin[t] = m;
-    }
+    StepInfo *steps = a.steps + ((size_t)row * nqt + qt) * ((T + RP_MT - 1) / RP_MT);
+    for (int s = tid; s * RP_MT < n_list; s += LIST_THREADS) steps[s] = StepInfo{first_key[s], last_key[s], min_death[s]};
 }
 
 template <int D>
@@ -98,21 +138,20 @@ __global__ __launch_bounds__(RP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2
 void replay_attn_kernel(ReplayArgs a)
 {
     constexpr int ROW_BYTES = D * 2;
-    constexpr int DPL = D / 16;
-    constexpr int KCH = D / 32;
-    constexpr int LROW = ROW_BYTES + 16;
-    constexpr int TILE_LDS = RP_KT * LROW;
+    constexpr int DT = D / 32;                             // 32-wide d tiles of the second product
+    constexpr int KCH = D / 16;                            // 16-wide d chunks of the first product
+    constexpr int TILE_LDS = RP_KT * ROW_BYTES;
     constexpr int PIECES = ROW_BYTES / 16;                 // 16-byte pieces per row
-    constexpr int LOADS = RP_KT * PIECES / (RP_WAVES * 64); // per thread, per tensor
+    constexpr int LOAD_ROWS = 64 / PIECES;                 // rows one wave-wide load brings
+    constexpr int LOADS = RP_KT / (RP_WAVES * LOAD_ROWS);  // per wave, per tensor
+    constexpr int STEPS = RP_KT / RP_MT;
 
-    __shared__ __align__(16) unsigned char lds_k[2][TILE_LDS];
-    __shared__ __align__(16) unsigned char lds_v[2][TILE_LDS];
+    __shared__ __align__(16) unsigned char lds_k0[TILE_LDS], lds_k1[TILE_LDS], lds_v0[TILE_LDS], lds_v1[TILE_LDS];
     __shared__ __align__(16) int32_t lds_death[2][RP_KT];
     __shared__ __align__(16) int32_t lds_kidx[2][RP_KT];
-    __shared__ int32_t lds_tmin[2][RP_KT / RP_MT];
 
-    const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
-    const int li = lane & 15, kg = lane >> 4;
+    const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const int li = lane & 31, half = lane >> 5;
     const int T = a.T;
     const int nqt = (T + RP_QT - 1) / RP_QT;
     // Workgroup -> (query tile, head, trajectory).  The hardware deals consecutive workgroups round-robin to the
@@ -136,280 +175,283 @@ void replay_attn_kernel(ReplayArgs a)
     const uint32_t kv_row = (uint32_t)a.Hkv * ROW_BYTES;
     const unsigned char *kbase = a.k + ((size_t)b * T * a.Hkv + hkv) * ROW_BYTES;
     const unsigned char *vbase = a.v + ((size_t)b * T * a.Hkv + hkv) * ROW_BYTES;
+    const size_t list = ((size_t)b * a.Hd + hd) * nqt + qt;
+    const uint16_t *klist = a.klist + list * T;
+    const StepInfo *info = a.steps + list * ((T + RP_MT - 1) / RP_MT);
+    const int n_list = a.kcount[list];
+    const int t_end = (n_list + RP_KT - 1) / RP_KT;
 
-    // ---- query operands: two tiles of 16 positions per wave ------------------
-    int qpos[2];
-    bf16x8 qop[2][KCH];
-#pragma unroll
-    for (int qa = 0; qa < 2; ++qa) {
-        qpos[qa] = i0 + wv * RP_QW + qa * 16 + li;
-        const int p = qpos[qa] < T ? qpos[qa] : T - 1;
-        const unsigned char *qrow = a.q + (((size_t)b * T + p) * a.Hq + head) * ROW_BYTES;
-#pragma unroll
-        for (int c = 0; c < KCH; ++c)
-            qop[qa][c] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(qrow + c * 64 + kg * 16));
-    }
-
-    f32x4 oacc[2][DPL];
-    float m_run[2], l_run[2];
-#pragma unroll
-    for (int qa = 0; qa < 2; ++qa) {
-        m_run[qa] = RP_M_INIT;
-        l_run[qa] = 0.f;
-#pragma unroll
-        for (int c = 0; c < DPL; ++c) oacc[qa][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-
-    int vrow_rel[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) vrow_rel[e] = (e < 4) ? (4 * kg + e) : (16 + 4 * kg + (e - 4));
-
-    // keys this workgroup needs (list built by replay_lists_kernel)
-    const uint16_t *klist = a.klist + (((size_t)b * a.Hd + hd) * nqt + qt) * T;
-    int n_list = 0;   // length of the list; read after the first list entries have been requested
-    const int32_t *tmin = a.tile_death + (((size_t)b * a.Hd + hd) * nqt + qt) * ((T + RP_MT - 1) / RP_MT);
-    const int wave_q0 = i0 + wv * RP_QW;                               // first query position of this wave
-    const int wave_q1 = (wave_q0 + RP_QW - 1 < T - 1) ? wave_q0 + RP_QW - 1 : T - 1;   // last real one
-
-    // One tile on its way from global memory to LDS, in two steps so that no load waits for another
-    // inside one step: first the list entries (which keys), one step later the rows they name.
+    // Rows of a tile go straight from memory to LDS: a wave-wide load brings LOAD_ROWS whole rows, lane after lane.
+    // The K pieces of row r are stored at slot (piece ^ (r & SWZ)), so that reading one piece of 32 consecutive rows
+    // meets every bank; the V pieces at (piece ^ v_swizzle(r)), so that reading 32 bytes of 4 consecutive rows does.
+    constexpr int SWZ = PIECES - 1;
+    auto v_swizzle = [](int r) { return (2 * r) & (PIECES < 16 ? SWZ : 7) ; };
+    const int lrow = lane / PIECES, lslot = lane % PIECES;
     struct IdxStage {
-        int key[LOADS];   // key index of the rows this thread copies
+        int key[LOADS];   // key index of the rows this lane copies
         int mine;         // the entry of list slot s0 + tid % RP_KT, as stored
     };
-    struct Stage {
-        u32x4 k[LOADS], v[LOADS];
-        int d, i;
-        int tmin;   // threads < RP_KT / RP_MT only
-    };
-    // List entries are fetched without looking at the list's length (slots past its end hold whatever the
-    // workspace held: any value is clamped to a valid key, and such slots are switched off when the tile is
-    // stored), so the first of these loads does not have to wait for the length to arrive.
+    // Slots past the list's end hold whatever the workspace held: any value is clamped to a valid key, and such slots
+    // are switched off by the mask.
     auto load_idx = [&](int t, IdxStage &ix) {
         const int s0 = t * RP_KT;
 #pragma unroll
         for (int r = 0; r < LOADS; ++r) {
-            const int piece_id = r * (RP_WAVES * 64) + tid;
-            int slot = s0 + piece_id / PIECES;
+            int slot = s0 + (wv * LOADS + r) * LOAD_ROWS + lrow;
             slot = slot < T ? slot : T - 1;             // a list row has T slots
-            const int key = (int)klist[slot];
-            ix.key[r] = key < T ? key : T - 1;          // whatever the list holds, stay inside k / v
+            ix.key[r] = (int)klist[slot];
         }
-        // every thread fetches the key of list slot s0 + tid % RP_KT: no branch around a load, so the loads in
-        // flight are the same on every path
         int sl = s0 + (tid & (RP_KT - 1));
         sl = sl < T ? sl : T - 1;
         ix.mine = (int)klist[sl];
     };
-    auto load_rows = [&](int t, const IdxStage &ix, Stage &st) {
+    auto load_rows = [&](const IdxStage &ix, unsigned char *dk, unsigned char *dv) {
 #pragma unroll
         for (int r = 0; r < LOADS; ++r) {
-            const int piece_id = r * (RP_WAVES * 64) + tid;
-            const uint32_t off = (uint32_t)ix.key[r] * kv_row + (uint32_t)(piece_id % PIECES) * 16u;
-            st.k[r] = *reinterpret_cast<const u32x4 *>(kbase + off);
-            st.v[r] = *reinterpret_cast<const u32x4 *>(vbase + off);
+            const int row0 = (wv * LOADS + r) * LOAD_ROWS;                  // wave-uniform
+            const int key = ix.key[r] < T ? ix.key[r] : T - 1;              // whatever the list holds, stay inside k / v
+            const uint32_t at = (uint32_t)key * kv_row;
+            const uint32_t kp = (uint32_t)(lslot ^ ((row0 + lrow) & SWZ)) * 16u;
+            load_to_lds16(kbase + (at + kp), dk + row0 * ROW_BYTES);
+            const uint32_t vp = (uint32_t)(lslot ^ v_swizzle(row0 + lrow)) * 16u;
+            load_to_lds16(vbase + (at + vp), dv + row0 * ROW_BYTES);
         }
-        int ti = t * (RP_KT / RP_MT) + (tid & (RP_KT / RP_MT - 1));
-        const bool t_inside = ti * RP_MT < n_list;
-        ti = t_inside ? ti : 0;
-        const int tm = tmin[ti];
-        st.tmin = t_inside ? tm : 0;
-        // 0x7FFFFFFF = a key no query comes after: slots past the end of the list
-        const bool inside = t * RP_KT + (tid & (RP_KT - 1)) < n_list;
-        const int dkey = ix.mine < T ? ix.mine : T - 1;
-        const int dv = death[dkey];
-        st.i = inside ? ix.mine : 0x7FFFFFFF;
-        st.d = inside ? dv : 0;
     };
-    auto store_tile = [&](int buf, const Stage &st) {
-#pragma unroll
-        for (int r = 0; r < LOADS; ++r) {
-            const int piece_id = r * (RP_WAVES * 64) + tid;
-            const int off = (piece_id / PIECES) * LROW + (piece_id % PIECES) * 16;
-            *reinterpret_cast<u32x4 *>(lds_k[buf] + off) = st.k[r];
-            *reinterpret_cast<u32x4 *>(lds_v[buf] + off) = st.v[r];
-        }
-        if (tid < RP_KT) { lds_death[buf][tid] = st.d; lds_kidx[buf][tid] = st.i; }
-        if (tid < RP_KT / RP_MT) lds_tmin[buf][tid] = st.tmin;
+    // key index and death position of the tile's rows, for the steps that need a mask; 0x7FFFFFFF = a key no query
+    // comes after: slots past the end of the list
+    struct MaskStage {
+        int d, i;
     };
-
-    auto compute_tile = [&](int buf) {
-#pragma unroll
-      for (int half = 0; half < RP_KT / RP_MT; ++half) {
-        // ---- RP_MT keys of this tile, from LDS --------------------------------
-        const unsigned char *lk = lds_k[buf] + half * RP_MT * LROW, *lv = lds_v[buf] + half * RP_MT * LROW;
-        const int32_t *ldeath = &lds_death[buf][half * RP_MT], *lkidx = &lds_kidx[buf][half * RP_MT];
-        // the list ascends: if the first of these keys is after this wave's last query, so are all
-        const bool wave_needs = (lkidx[0] <= i0 + wv * RP_QW + RP_QW - 1);
-        if (wave_needs) {
-            bf16x8 kop[2][KCH];
-#pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-                for (int c = 0; c < KCH; ++c)
-                    kop[mt][c] = __builtin_bit_cast(
-                        bf16x8, *reinterpret_cast<const u32x4 *>(lk + (mt * 16 + li) * LROW + c * 64 + kg * 16));
-            // A tile whose keys all precede this wave's first query and all outlive its last one needs no
-            // mask (wave-uniform, so the branches below do not diverge).
-            const bool full = __builtin_amdgcn_readfirstlane(
-                (lkidx[RP_MT - 1] <= wave_q0 && lds_tmin[buf][half] > wave_q1) ? 1 : 0) != 0;
-            bf16x8 p_hi[2], p_lo[2];
-            f32x4 sc0[2], sc1[2];
-#pragma unroll
-            for (int qa = 0; qa < 2; ++qa) {
-                sc0[qa] = f32x4{0.f, 0.f, 0.f, 0.f};
-                sc1[qa] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-#pragma unroll
-            for (int c = 0; c < KCH; ++c)
-#pragma unroll
-                for (int qa = 0; qa < 2; ++qa) {
-                    sc0[qa] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[0][c], qop[qa][c], sc0[qa], 0, 0, 0);
-                    sc1[qa] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kop[1][c], qop[qa][c], sc1[qa], 0, 0, 0);
-                }
-            // The V rows are requested as soon as the first product has been issued (the K operand registers are
-            // free from here on) and arrive while the soft-max arithmetic runs.
-            __builtin_amdgcn_sched_barrier(0);
-            u32x4 vcur[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                if constexpr (DPL == 8) {
-                    vcur[e] = *reinterpret_cast<const u32x4 *>(lv + vrow_rel[e] * LROW + li * 16);
-                } else {
-                    const u32x2 tt = *reinterpret_cast<const u32x2 *>(lv + vrow_rel[e] * LROW + li * 8);
-                    vcur[e] = u32x4{tt[0], tt[1], 0u, 0u};
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int qa = 0; qa < 2; ++qa) {
-                const f32x4 s0 = sc0[qa], s1 = sc1[qa];
-                // raw scores; the (positive) scale is applied inside the exponent's multiply-add, the running
-                // max lives in the scaled domain
-                float x[8];
-                const int qp = qpos[qa];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] = (e < 4) ? s0[e] : s1[e - 4];
-                if (!full) {
-                    // key indices and death positions of the rows this lane holds (rare path: fetched here, per
-                    // query tile, rather than kept in registers across the common path)
-                    const int4 d0 = *reinterpret_cast<const int4 *>(&ldeath[4 * kg]);
-                    const int4 d1 = *reinterpret_cast<const int4 *>(&ldeath[16 + 4 * kg]);
-                    const int4 j0 = *reinterpret_cast<const int4 *>(&lkidx[4 * kg]);
-                    const int4 j1 = *reinterpret_cast<const int4 *>(&lkidx[16 + 4 * kg]);
-                    const int dk[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
-                    const int jk[8] = {j0.x, j0.y, j0.z, j0.w, j1.x, j1.y, j1.z, j1.w};
-#pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        if (!(jk[e] <= qp && qp < dk[e])) x[e] = -INFINITY;
-                }
-                // scores are finite or -inf, never NaN (finite inputs)
-                float tmx = x[0];
-#pragma unroll
-                for (int e = 1; e < 8; ++e) tmx = max_no_nan(tmx, x[e]);
-                tmx = quad_rows_max(tmx) * a.scale_log2e;
-                const float m_new = max_no_nan(m_run[qa], tmx);
-                if (__ballot(m_new != m_run[qa])) {
-                    // m_new is finite wherever it changed; exp2(-inf - finite) = 0 on a first visible tile
-                    const float alpha = (m_new == m_run[qa]) ? 1.0f : fast_exp2(m_run[qa] - m_new);
-                    l_run[qa] *= alpha;
-#pragma unroll
-                    for (int c = 0; c < DPL; ++c) oacc[qa][c] *= alpha;
-                    m_run[qa] = m_new;
-                }
-                float p[8], psum = 0.f;
-                const float neg_m = -m_run[qa];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    p[e] = fast_exp2(__builtin_fmaf(x[e], a.scale_log2e, neg_m));   // x = -inf gives 0: m_run is finite
-                    psum += p[e];
-                }
-                l_run[qa] += psum;
-                uint32_t ph[4], pl[4];
-#pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2) {
-                    const uint32_t b0 = __float_as_uint(p[2 * e2]), b1 = __float_as_uint(p[2 * e2 + 1]);
-                    const float r0 = p[2 * e2] - __uint_as_float(b0 & 0xFFFF0000u);
-                    const float r1 = p[2 * e2 + 1] - __uint_as_float(b1 & 0xFFFF0000u);
-                    ph[e2] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);                     // upper halves of b0, b1
-                    pl[e2] = __builtin_amdgcn_perm(__float_as_uint(r1), __float_as_uint(r0), 0x07060302u);
-                }
-                p_hi[qa] = __builtin_bit_cast(bf16x8, u32x4{ph[0], ph[1], ph[2], ph[3]});
-                p_lo[qa] = __builtin_bit_cast(bf16x8, u32x4{pl[0], pl[1], pl[2], pl[3]});
-            }
-#pragma unroll
-            for (int c = 0; c < DPL; ++c) {
-                uint32_t va[4];
-#pragma unroll
-                for (int e2 = 0; e2 < 4; ++e2) {
-                    const uint32_t w0 = vcur[2 * e2][c >> 1];
-                    const uint32_t w1 = vcur[2 * e2 + 1][c >> 1];
-                    // 2x2 transpose of 16-bit elements: one byte permute per output word
-                    va[e2] = (c & 1) ? __builtin_amdgcn_perm(w1, w0, 0x07060302u) : __builtin_amdgcn_perm(w1, w0, 0x05040100u);
-                }
-                const bf16x8 vop = __builtin_bit_cast(bf16x8, u32x4{va[0], va[1], va[2], va[3]});
-#pragma unroll
-                for (int qa = 0; qa < 2; ++qa) {
-                    oacc[qa][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop, p_hi[qa], oacc[qa][c], 0, 0, 0);
-                    oacc[qa][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vop, p_lo[qa], oacc[qa][c], 0, 0, 0);
-                }
-            }
+    auto load_mask = [&](const IdxStage &ix, MaskStage &ms) {
+        ms.i = ix.mine;
+        ms.d = death[ix.mine < T ? ix.mine : T - 1];
+    };
+    auto store_mask = [&](int t, int buf, const MaskStage &ms) {
+        const bool inside = t * RP_KT + tid < n_list;
+        if (tid < RP_KT) {
+            lds_death[buf][tid] = inside ? ms.d : 0;
+            lds_kidx[buf][tid] = inside ? ms.i : 0x7FFFFFFF;
         }
-      }
+    };
+    // scalar loads: wave-uniform, from memory an earlier launch wrote
+    struct TileInfo {
+        uint64_t step[STEPS];
+    };
+    const int last_step = (T + RP_MT - 1) / RP_MT - 1;
+    auto load_info = [&](int t) {
+        TileInfo ti;
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            const int at = t * STEPS + st;
+            ti.step[st] = reinterpret_cast<const __attribute__((address_space(4))) uint64_t *>(
+                (uintptr_t)info)[at < last_step ? at : last_step];
+        }
+        return ti;
     };
 
-    // Per step: tile t is computed from LDS while the rows of tile t+1 travel through registers into
-    // the other LDS buffer and the list entries of tile t+2 are fetched.  Unrolled by two so that the two
-    // list-entry stages swap roles without copies; every load is unconditional so the number of loads in
-    // flight is the same on every path.
-    Stage st;
-    IdxStage ix_a, ix_b;
+    IdxStage ix_a, ix_b;   // take turns, so that a stage being filled is never copied
+    MaskStage ms;
     load_idx(0, ix_a);
+
+    // ---- query operands: 32 positions per wave, lane % 32 = position ----------
+    const int wave_q0 = i0 + wv * RP_QW;                                               // first query position of this wave
+    const int wave_q1 = (wave_q0 + RP_QW - 1 < T - 1) ? wave_q0 + RP_QW - 1 : T - 1;   // last real one
+    const int qpos = wave_q0 + li;
+    bf16x8 qop[KCH];
+    {
+        const int p = qpos < T ? qpos : T - 1;
+        const unsigned char *qrow = a.q + (((size_t)b * T + p) * a.Hq + head) * ROW_BYTES;
+#pragma unroll
+        for (int c = 0; c < KCH; ++c)
+            qop[c] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(qrow + c * 32 + half * 16));
+    }
+    load_rows(ix_a, lds_k0, lds_v0);
+    load_mask(ix_a, ms);
     load_idx(1, ix_b);
-    n_list = a.kcount[((size_t)b * a.Hd + hd) * nqt + qt];
-    const int t_end = (n_list + RP_KT - 1) / RP_KT;
-    load_rows(0, ix_a, st);
-    store_tile(0, st);
+    TileInfo here = load_info(0), next = load_info(1);
+
+    f32x16 oacc[DT];
+#pragma unroll
+    for (int c = 0; c < DT; ++c)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[c][r] = 0.f;
+    float m_run = RP_M_INIT, l_run = 0.f;
+
+    // LDS offsets of this lane's operands.  K: piece 2c + half of row li.  V: a transposing read gives lane x of 16 the
+    // column d0 + x of 4 rows if lane x points at the 4 values from d0 + 4 (x % 4) of row x / 4; the rows are the keys
+    // its half contracts over in a 16-key chunk (4 half .. +3 and 8 + 4 half .. +3: the order the scores come in).
+    uint32_t koff[KCH];
+#pragma unroll
+    for (int c = 0; c < KCH; ++c) koff[c] = (uint32_t)(li * ROW_BYTES + (((2 * c + half) ^ (li & SWZ)) * 16));
+    uint32_t vrd[DT];
+    {
+        const int row = 4 * half + (lane & 15) / 4;       // + 16 kc + 8 g: the same row modulo 8 for every g, kc
+#pragma unroll
+        for (int c = 0; c < DT; ++c) {
+            const int d0 = 32 * c + (lane & 16) + 4 * (lane & 3);
+            vrd[c] = (uint32_t)(row * ROW_BYTES + (((d0 / 8) ^ v_swizzle(row)) * 16) + (d0 % 8) * 2);
+        }
+    }
+
+    auto compute_step = [&](const unsigned char *lk, const unsigned char *lv, const int32_t *ldeath, const int32_t *lkidx,
+                            bool full) {
+        f32x16 sc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+        u32x4 kop[KCH];
+#pragma unroll
+        for (int c = 0; c < KCH; ++c) kop[c] = *reinterpret_cast<const u32x4 *>(lk + koff[c]);
+        __builtin_amdgcn_sched_barrier(0);     // all requests first: the products then wait for one after the other
+#pragma unroll
+        for (int c = 0; c < KCH; ++c)
+            sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop[c]), qop[c], sc, 0, 0, 0);
+        // The V rows are requested as soon as the first product has been issued (the K operand registers are free from
+        // here on) and arrive while the soft-max arithmetic runs.
+        __builtin_amdgcn_sched_barrier(0);
+        u32x2 vop[2][DT][2];      // [16-key chunk][d tile][keys 4 half .. +3, 8 + 4 half .. +3]
+#pragma unroll
+        for (int kc = 0; kc < 2; ++kc)
+#pragma unroll
+            for (int c = 0; c < DT; ++c)
+#pragma unroll
+                for (int g = 0; g < 2; ++g)
+                    vop[kc][c][g] = read_transposed16(lv + vrd[c] + (16 * kc + 8 * g) * ROW_BYTES);
+        __builtin_amdgcn_sched_barrier(0);
+        // lane (q = li, half), register r: key 8 (r / 4) + 4 half + r % 4 of this step.  Raw scores; the (positive)
+        // scale is applied inside the exponent's multiply-add, the running max lives in the scaled domain.
+        if (!full) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int4 d = *reinterpret_cast<const int4 *>(&ldeath[8 * g + 4 * half]);
+                const int4 j = *reinterpret_cast<const int4 *>(&lkidx[8 * g + 4 * half]);
+                sc[4 * g + 0] = ((j.x <= qpos) & (qpos < d.x)) ? sc[4 * g + 0] : -INFINITY;
+                sc[4 * g + 1] = ((j.y <= qpos) & (qpos < d.y)) ? sc[4 * g + 1] : -INFINITY;
+                sc[4 * g + 2] = ((j.z <= qpos) & (qpos < d.z)) ? sc[4 * g + 2] : -INFINITY;
+                sc[4 * g + 3] = ((j.w <= qpos) & (qpos < d.w)) ? sc[4 * g + 3] : -INFINITY;
+            }
+        }
+        // scores are finite or -inf, never NaN (finite inputs)
+        float tmx = sc[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) tmx = max_no_nan(tmx, sc[r]);
+        tmx = half_rows_max(tmx) * a.scale_log2e;
+        // The sums are rescaled only when a maximum has outgrown the reference by 2^RP_LAZY: any reference gives the
+        // same quotients, and probabilities up to 2^RP_LAZY lose nothing in fp32 or in two bf16 parts.
+        if (__ballot(tmx > m_run + RP_LAZY)) {
+            // tmx is finite wherever it is larger; exp2(-1e30 - finite) = 0 on a first visible tile
+            const float m_new = max_no_nan(m_run, tmx);
+            const float alpha = (m_new == m_run) ? 1.0f : fast_exp2(m_run - m_new);
+            l_run *= alpha;
+#pragma unroll
+            for (int c = 0; c < DT; ++c) oacc[c] *= alpha;
+            m_run = m_new;
+        }
+        const float neg_m = -m_run;
+        uint32_t ph[8], pl[8];
+        float psum = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float p0 = fast_exp2(__builtin_fmaf(sc[2 * e], a.scale_log2e, neg_m));       // -inf gives 0
+            const float p1 = fast_exp2(__builtin_fmaf(sc[2 * e + 1], a.scale_log2e, neg_m));
+            psum += p0 + p1;
+            const uint32_t b0 = __float_as_uint(p0), b1 = __float_as_uint(p1);
+            const float r0 = p0 - __uint_as_float(b0 & 0xFFFF0000u);
+            const float r1 = p1 - __uint_as_float(b1 & 0xFFFF0000u);
+            ph[e] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);                     // upper halves of b0, b1
+            pl[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{r0, r1}, bf16x2));   // rounded
+        }
+        l_run += psum;
+#pragma unroll
+        for (int kc = 0; kc < 2; ++kc) {
+            const bf16x8 p_hi = __builtin_bit_cast(bf16x8, u32x4{ph[4 * kc], ph[4 * kc + 1], ph[4 * kc + 2], ph[4 * kc + 3]});
+            const bf16x8 p_lo = __builtin_bit_cast(bf16x8, u32x4{pl[4 * kc], pl[4 * kc + 1], pl[4 * kc + 2], pl[4 * kc + 3]});
+            bf16x8 v[DT];
+#pragma unroll
+            for (int c = 0; c < DT; ++c)
+                v[c] = __builtin_bit_cast(bf16x8, u32x4{vop[kc][c][0][0], vop[kc][c][0][1], vop[kc][c][1][0], vop[kc][c][1][1]});
+#pragma unroll
+            for (int c = 0; c < DT; ++c) oacc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[c], p_hi, oacc[c], 0, 0, 0);
+#pragma unroll
+            for (int c = 0; c < DT; ++c) oacc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[c], p_lo, oacc[c], 0, 0, 0);
+        }
+    };
+    auto compute_tile = [&](int t, const TileInfo &ti, const unsigned char *lk, const unsigned char *lv, int buf) {
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st) {
+            const int at = t * STEPS + st;
+            if (at * RP_MT >= n_list) break;
+            const int first = (int)(ti.step[st] & 0xFFFFu), last = (int)((ti.step[st] >> 16) & 0xFFFFu);
+            const int min_death = (int)(ti.step[st] >> 32);
+            // the list ascends: if the first of these keys is after this wave's last query, so are all
+            if (first > wave_q1) break;
+            // A step whose keys all precede this wave's first query and all outlive its last one needs no mask.
+            const bool full = last <= wave_q0 && min_death > wave_q1;
+            compute_step(lk + st * RP_MT * ROW_BYTES, lv + st * RP_MT * ROW_BYTES, &lds_death[buf][st * RP_MT],
+                         &lds_kidx[buf][st * RP_MT], full);
+        }
+    };
+
+    // Per tile: tile t is computed from one pair of LDS buffers while the rows of tile t+1 travel into the other and the
+    // list entries of tile t+2 are fetched.
+    store_mask(0, 0, ms);
     __syncthreads();
-    int t = 0, buf = 0;
+    int t = 0;
     while (t < t_end) {
-        load_idx(t + 2, ix_a);
-        load_rows(t + 1, ix_b, st);
+        if (t + 1 < t_end) {
+            load_rows(ix_b, lds_k1, lds_v1);
+            load_mask(ix_b, ms);
+            load_idx(t + 2, ix_a);
+        }
         __builtin_amdgcn_sched_barrier(0);
-        compute_tile(buf);
+        compute_tile(t, here, lds_k0, lds_v0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        store_tile(buf ^ 1, st);
-        __syncthreads();
-        buf ^= 1;
+        here = next;
+        next = load_info(t + 2);
         if (++t >= t_end) break;
-        load_idx(t + 2, ix_b);
-        load_rows(t + 1, ix_a, st);
-        __builtin_amdgcn_sched_barrier(0);
-        compute_tile(buf);
-        __builtin_amdgcn_sched_barrier(0);
-        store_tile(buf ^ 1, st);
+        store_mask(t, 1, ms);
         __syncthreads();
-        buf ^= 1;
-        ++t;
+        if (t + 1 < t_end) {
+            load_rows(ix_a, lds_k0, lds_v0);
+            load_mask(ix_a, ms);
+            load_idx(t + 2, ix_b);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        compute_tile(t, here, lds_k1, lds_v1, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        here = next;
+        next = load_info(t + 2);
+        if (++t >= t_end) break;
+        store_mask(t, 0, ms);
+        __syncthreads();
     }
 
     // ---- normalise and write -------------------------------------------------
+    const float l = half_rows_sum(l_run);
+    const float inv = l > 0.f ? 1.0f / l : 0.f;
+    // Through LDS, so that a row's D values leave as whole cache lines (a wave's own 32 rows, one of the four tile
+    // buffers each): 16-byte piece p of row r at slot p ^ r.
+    __syncthreads();                                       // every wave is done with the tiles
+    {
+        constexpr int OP = D / 4;                          // 16-byte pieces per output row
+        unsigned char *mine = wv == 0 ? lds_k0 : wv == 1 ? lds_k1 : wv == 2 ? lds_v0 : lds_v1;
+        static_assert(RP_QW * D * 4 == TILE_LDS, "a wave's output rows fill one tile buffer");
 #pragma unroll
-    for (int qa = 0; qa < 2; ++qa) {
-        float l = l_run[qa];
-        l = quad_rows_sum(l);
-        const float inv = l > 0.f ? 1.0f / l : 0.f;
-        if (qpos[qa] < T) {
-            float *orow = a.out + (((size_t)b * T + qpos[qa]) * a.Hq + head) * D;
+        for (int c = 0; c < DT; ++c)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                // lane (q = li, kg), register (c, r) holds d = DPL * (4kg + r) + c
-                float *dst = orow + DPL * (4 * kg + r);
+            for (int g = 0; g < 4; ++g) {   // register (c, 4g + i) holds d = 32 c + 8 g + 4 half + i
+                const int piece = 8 * c + 2 * g + half;
+                *reinterpret_cast<f32x4 *>(mine + li * (D * 4) + ((piece ^ li) & (OP - 1)) * 16) =
+                    f32x4{oacc[c][4 * g] * inv, oacc[c][4 * g + 1] * inv, oacc[c][4 * g + 2] * inv, oacc[c][4 * g + 3] * inv};
+            }
+        constexpr int ROWS = 64 / OP;                      // rows per wave-wide store
+        const int piece = lane % OP;
 #pragma unroll
-                for (int c = 0; c < DPL; c += 4)
-                    *reinterpret_cast<float4 *>(dst + c) =
-                        make_float4(oacc[qa][c][r] * inv, oacc[qa][c + 1][r] * inv, oacc[qa][c + 2][r] * inv,
-                                    oacc[qa][c + 3][r] * inv);
+        for (int r0 = 0; r0 < RP_QW; r0 += ROWS) {
+            const int r = r0 + lane / OP;
+            const f32x4 x = *reinterpret_cast<const f32x4 *>(mine + r * (D * 4) + ((piece ^ r) & (OP - 1)) * 16);
+            if (wave_q0 + r < T) {
+                f32x4 *dst = reinterpret_cast<f32x4 *>(a.out + (((size_t)b * T + wave_q0 + r) * a.Hq + head) * D) + piece;
+                __builtin_nontemporal_store(x, dst);
             }
         }
     }
@@ -428,7 +470,7 @@ extern "C" size_t ngc_replay_workspace_bytes(int32_t B, int32_t T, int32_t Hkv)
     size_t counts = (size_t)B * Hkv * nqt * sizeof(int32_t);
     counts = (counts + 255) & ~(size_t)255;
     const size_t tiles_max = (size_t)(T + RP_MT - 1) / RP_MT;
-    return 256 + lists + counts + (size_t)B * Hkv * nqt * tiles_max * sizeof(int32_t);
+    return 256 + lists + counts + (size_t)B * Hkv * nqt * tiles_max * sizeof(StepInfo);
 }
 
 extern "C" int ngc_replay_attn(const void *q, const void *k, const void *v, const int32_t *death,
@@ -463,8 +505,8 @@ extern "C" int ngc_replay_attn(const void *q, const void *k, const void *v, cons
     ra.kcount = reinterpret_cast<int32_t *>(reinterpret_cast<unsigned char *>(ws) + 256 + lists);
     size_t counts = (size_t)B * ra.Hd * nqt * sizeof(int32_t);
     counts = (counts + 255) & ~(size_t)255;
-    ra.tile_death = reinterpret_cast<int32_t *>(reinterpret_cast<unsigned char *>(ws) + 256 + lists + counts);
-    hipLaunchKernelGGL(replay_lists_kernel, dim3(nqt, B * ra.Hd), dim3(RP_WAVES * 64), 0, st, ra);
+    ra.steps = reinterpret_cast<StepInfo *>(reinterpret_cast<unsigned char *>(ws) + 256 + lists + counts);
+    hipLaunchKernelGGL(replay_lists_kernel, dim3(nqt, B * ra.Hd), dim3(LIST_THREADS), 0, st, ra);
     NGC_HIP_CHECK(hipGetLastError());
     if (D == 128)
         hipLaunchKernelGGL(replay_attn_kernel<128>, dim3((unsigned)(nqt * Hq * B)), dim3(RP_WAVES * 64), 0, st, ra);
