@@ -94,44 +94,66 @@ __device__ __forceinline__ u32x2 read_transposed16(const void *lds)
     return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)lds));
 }
 
-__device__ __forceinline__ int wave_sum_i(int v)
+// Whole-wave reductions and scans inside the vector ALU: lanes exchange within their row of 16 by data-parallel
+// primitives (a shuffle through LDS costs ~60 cycles a step, these ~8), across rows by gfx950's lane-swap instructions.
+namespace dpp {
+constexpr int QUAD_XOR1 = 0xB1, QUAD_XOR2 = 0x4E, HALF_MIRROR = 0x141, MIRROR = 0x140;   // together: xor 1, 2, 4, 8
+constexpr int ROW_SHR = 0x110;                                                           // + n: from n lanes below
+constexpr int BCAST15 = 0x142, BCAST31 = 0x143;                                          // a row's last lane to the next row(s)
+// lane's partner value; lanes without one (or outside ROWS) get `none`
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ uint32_t from(uint32_t v, uint32_t none)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, NGC_WAVE);
-    return v;
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xF, false);
 }
-__device__ __forceinline__ float wave_sum_f(float v)
+}  // namespace dpp
+
+// op(a, b) over all 64 lanes, result in every lane.  T is a 32-bit type.
+template <class T, class Op>
+__device__ __forceinline__ T wave_reduce(T v, Op op)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, NGC_WAVE);
-    return v;
+    uint32_t u = __builtin_bit_cast(uint32_t, v);
+    auto step = [&](uint32_t w) { u = __builtin_bit_cast(uint32_t, op(__builtin_bit_cast(T, u), __builtin_bit_cast(T, w))); };
+    step(dpp::from<dpp::QUAD_XOR1>(u, u));
+    step(dpp::from<dpp::QUAD_XOR2>(u, u));
+    step(dpp::from<dpp::HALF_MIRROR>(u, u));
+    step(dpp::from<dpp::MIRROR>(u, u));
+    auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    u = a[0];
+    step(a[1]);
+    auto b = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    u = b[0];
+    step(b[1]);
+    return __builtin_bit_cast(T, u);
 }
-__device__ __forceinline__ float wave_max_f(float v)
+// op over this lane and those below it (`none`: the neutral element)
+template <class T, class Op>
+__device__ __forceinline__ T wave_incl_scan(T v, T none, Op op)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, NGC_WAVE));
-    return v;
+    uint32_t u = __builtin_bit_cast(uint32_t, v);
+    const uint32_t z = __builtin_bit_cast(uint32_t, none);
+    auto step = [&](uint32_t w) { u = __builtin_bit_cast(uint32_t, op(__builtin_bit_cast(T, w), __builtin_bit_cast(T, u))); };
+    step(dpp::from<dpp::ROW_SHR + 1>(u, z));
+    step(dpp::from<dpp::ROW_SHR + 2>(u, z));
+    step(dpp::from<dpp::ROW_SHR + 4>(u, z));
+    step(dpp::from<dpp::ROW_SHR + 8>(u, z));
+    step(dpp::from<dpp::BCAST15, 0xA>(u, z));     // rows 1 and 3 take the row below's total
+    step(dpp::from<dpp::BCAST31, 0xC>(u, z));     // rows 2 and 3 that of the lower half
+    return __builtin_bit_cast(T, u);
 }
-__device__ __forceinline__ int wave_incl_scan_i(int v)
-{
-    const int lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < NGC_WAVE; o <<= 1) {
-        int t = __shfl_up(v, o, NGC_WAVE);
-        if (lane >= o) v += t;
-    }
-    return v;
-}
-__device__ __forceinline__ float wave_incl_scan_f(float v)
-{
-    const int lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < NGC_WAVE; o <<= 1) {
-        float t = __shfl_up(v, o, NGC_WAVE);
-        if (lane >= o) v += t;
-    }
-    return v;
-}
+struct OpAdd {
+    template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return a + b; }
+};
+struct OpMaxF {
+    __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
+struct OpMaxU {
+    __device__ __forceinline__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; }
+};
+__device__ __forceinline__ float wave_sum_f(float v) { return wave_reduce(v, OpAdd{}); }
+__device__ __forceinline__ float wave_max_f(float v) { return wave_reduce(v, OpMaxF{}); }
+__device__ __forceinline__ int wave_incl_scan_i(int v) { return wave_incl_scan(v, 0, OpAdd{}); }
+__device__ __forceinline__ float wave_incl_scan_f(float v) { return wave_incl_scan(v, 0.f, OpAdd{}); }
 
 // Block-wide exclusive scan of one int per thread.  `tmp` holds one int per
 // wave (+1).  Returns the exclusive prefix; *total receives the block sum.
@@ -254,11 +276,7 @@ template <int THREADS>
 __device__ __forceinline__ uint32_t block_max_u(uint32_t v, uint32_t *tmp)
 {
     constexpr int NW = THREADS / NGC_WAVE;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint32_t t = (uint32_t)__shfl_xor((int)v, o, NGC_WAVE);
-        v = t > v ? t : v;
-    }
+    v = wave_reduce(v, OpMaxU{});
     if (lane_id() == 0) tmp[wave_id()] = v;
     __syncthreads();
     uint32_t all = tmp[0];
