@@ -1219,13 +1219,6 @@ int resident_workgroups(const void *fn, int threads, size_t lds, int items)
     return (int)(slots < items ? slots : items);
 }
 
-size_t select_lds_bytes(int threads, int items_cap, int keep_cap)
-{
-    const int nw = threads / 64;
-    const int hist = (SEL_BINS > SORT_BINS * nw) ? SEL_BINS : SORT_BINS * nw;
-    return (size_t)items_cap * 4 + (size_t)hist * 4 + 64 * 4 + (size_t)keep_cap * 2 * 2;
-}
-
 // Eq. 2 and its gradient: how much of a row is held in LDS (an upper bound on the items of a segment that keeps to its
 // own row; a longer one takes the general route), and the workgroup that holds a row's picks in registers.  A
 // workgroup has no more threads than its row keeps busy.  Microseconds for two rounds of Eq. 2 and its gradient:
@@ -1318,7 +1311,7 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
         const bool move = !(p->flags & NGC_EVICT_SELECT_ONLY);
         sa.k = move ? c->k : nullptr; sa.v = c->v; sa.pos = c->pos; sa.len_out = c->len;
         sa.unordered = 0;
-        sa.seg0 = seg0; sa.max_keep = max_keep; sa.items_cap = 0; sa.keep_cap = keep_cap;
+        sa.seg0 = seg0; sa.max_keep = max_keep; sa.items_cap = 0; sa.keep_cap = keep_cap; sa.rank_cap = 0;
         sa.pool_codes = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(ws) + codes_off);
         sa.g = SegGeom{c->B, c->Hkv, c->cap, 1};
         sa.logit_stride = c->cap;
@@ -1338,18 +1331,22 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
     int keep_cap = max_keep < items_cap ? max_keep : items_cap;
     keep_cap = (keep_cap + 7) & ~7;
     const int items_cap_al = (items_cap + 3) & ~3;
-    // Workgroup size and rows in flight per thread, measured on configs 2-4.  A round that moves rows in order
-    // is a copy with a selection in front: the copy wants as many bytes in flight per compute unit as registers
-    // allow, which is one 1024-thread workgroup per CU from 4097 rows per segment up (the size follows the rows
-    // of a segment, not its items: with blocks of rows as items the selection is small and the copy is all there
-    // is).  A round that only selects, or fills holes (few rows move), is bound by the selection's ~45 workgroup
-    // barriers; two 512-thread workgroups per CU then cover each other's waits, up to the 8192 rows at which two
-    // of them still fit in LDS (config 3, selection only: 1.79 -> 1.14 ms, steady-state 1.46 -> 0.84 ms;
-    // unordered: 4.54 -> 4.18 and 2.17 -> 1.53 ms).
+    // Workgroup size and rows in flight per thread, all measured.  A round that moves rows in order is a copy with a
+    // selection in front: the copy wants as many bytes in flight per compute unit as registers allow, which is one
+    // 1024-thread workgroup per CU from 4097 rows per segment up (2048 segments of 4096-8192 rows: 975 us, 1046 with
+    // 512 threads; the size follows the rows of a segment, not its items: with blocks of rows as items the selection is
+    // small and the copy is all there is), 512 threads from 513 rows up (1024 segments of 1500 rows: 171 us, 177 with
+    // 256; 16 of 1500: 26.7, 30.8) and 256 below (1024 of 300: 42, 47 with 512).  A round that only selects, or fills
+    // holes (few rows move), is bound by the selection's waits; two 512-thread workgroups per CU cover each other's up to
+    // the 8192 rows at which two of them still fit in LDS (1024 segments of 8192: 96 us, 135 with 1024 threads), 256
+    // threads up to 2048 rows (1024 of 1500: 25 us, 28 with 512) unless there are too few segments to fill the chip
+    // that way (16 of 1500: 14.6 us with 512 threads, 17.2 with 256).
     const bool move_rows = !(p->flags & NGC_EVICT_SELECT_ONLY);
     const bool copy_bound = move_rows && !(p->flags & NGC_EVICT_UNORDERED);
-    const int threads = c->cap > (copy_bound ? 4096 : 8192) ? 1024 : (c->cap > 2048 ? 512 : 256);
-    const size_t lds = select_lds_bytes(threads, items_cap_al, keep_cap);
+    const int few = (copy_bound || nseg <= 512) ? 512 : 2048;
+    const int threads = c->cap > (copy_bound ? 4096 : 8192) ? 1024 : (c->cap > few ? 512 : 256);
+    const int rank_cap = rank_capacity(threads, items_cap_al, keep_cap);
+    const size_t lds = select_lds_bytes(threads, items_cap_al, keep_cap, rank_cap);
     if (lds > 160 * 1024) return NGC_EUNSUPPORTED;
 
     int32_t *status = reinterpret_cast<int32_t *>(ws);
@@ -1361,7 +1358,7 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
     sa.k = move_rows ? c->k : nullptr; sa.v = c->v; sa.pos = c->pos; sa.len_out = c->len;
     sa.unordered = (p->flags & NGC_EVICT_UNORDERED) ? 1 : 0;
     sa.pool_codes = nullptr;
-    sa.seg0 = seg0; sa.max_keep = max_keep; sa.items_cap = items_cap_al; sa.keep_cap = keep_cap;
+    sa.seg0 = seg0; sa.max_keep = max_keep; sa.items_cap = items_cap_al; sa.keep_cap = keep_cap; sa.rank_cap = rank_cap;
     sa.g = SegGeom{c->B, c->Hkv, c->cap, p->block};
     sa.logit_stride = c->cap;
     sa.na = NoiseArgs{p->seed, p->round, p->noise_scale, p->share_heads, p->layer_base, p->seq_base};

@@ -318,13 +318,6 @@ int paged_layer_range(const ngc_paged_cache *pc, int layer, int *seg0, int *nseg
     return NGC_OK;
 }
 
-size_t paged_select_lds_bytes(int threads, int items_cap, int keep_cap)
-{
-    const int nw = threads / 64;
-    const int hist = (SEL_BINS > SORT_BINS * nw) ? SEL_BINS : SORT_BINS * nw;
-    return (size_t)items_cap * 4 + (size_t)hist * 4 + 64 * 4 + (size_t)keep_cap * 2 * 2;
-}
-
 PagedArgs paged_args(const ngc_paged_cache *pc, void *ws, int seg0, int nseg)
 {
     PagedArgs pa;
@@ -375,7 +368,8 @@ extern "C" int ngc_paged_evict(const ngc_paged_cache *pc, int32_t layer, const f
     keep_cap = (keep_cap + 7) & ~7;
     const int items_cap_al = (items_cap + 3) & ~3;
     const int threads = items_cap > 8192 ? 1024 : (items_cap > 2048 ? 512 : 256);
-    const size_t lds = paged_select_lds_bytes(threads, items_cap_al, keep_cap);
+    const int rank_cap = rank_capacity(threads, items_cap_al, keep_cap);
+    const size_t lds = select_lds_bytes(threads, items_cap_al, keep_cap, rank_cap);
     if (lds > 160 * 1024) return NGC_EUNSUPPORTED;
 
     SelectArgs sa;
@@ -384,7 +378,7 @@ extern "C" int ngc_paged_evict(const ngc_paged_cache *pc, int32_t layer, const f
     sa.status = reinterpret_cast<int32_t *>(ws);
     sa.k = nullptr; sa.v = nullptr; sa.pos = nullptr; sa.len_out = nullptr;
     sa.unordered = 0;
-    sa.seg0 = seg0; sa.max_keep = max_keep; sa.items_cap = items_cap_al; sa.keep_cap = keep_cap;
+    sa.seg0 = seg0; sa.max_keep = max_keep; sa.items_cap = items_cap_al; sa.keep_cap = keep_cap; sa.rank_cap = rank_cap;
     sa.pool_codes = nullptr;
     sa.logit_stride = logit_stride;
     sa.g = SegGeom{pc->B, pc->Hkv, pc->max_pages * pc->page_rows, pc->page_rows};

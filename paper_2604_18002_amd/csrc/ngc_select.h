@@ -99,6 +99,29 @@ __device__ __forceinline__ void keys_of_quad(const float *row, int n_items, int 
 
 constexpr int SEL_BINS = 2048;
 
+// LDS of the selection: [codes][histogram][misc][sigma / sort buffer: keep_cap u16][sort / bucket buffer: u16][kept bits].
+// The ranking route needs a bucket entry and a bit per item on top of what the radix route takes.
+inline size_t select_lds_bytes(int threads, int items_cap, int keep_cap, int rank_cap)
+{
+    const int nw = threads / 64, hist = (SEL_BINS > 512 * nw) ? SEL_BINS : 512 * nw;
+    const int second = rank_cap > keep_cap ? rank_cap : keep_cap;
+    return (size_t)items_cap * 4 + (size_t)hist * 4 + 64 * 4 + (size_t)keep_cap * 2 + (size_t)second * 2 +
+           (size_t)((rank_cap + 63) / 64) * 8;
+}
+
+// How many items the ranking route gets LDS for: all of them, unless that costs resident workgroups per CU below three
+// (a round's selection needs others beside it) or does not fit at all.
+inline int rank_capacity(int threads, int items_cap, int keep_cap)
+{
+    const size_t cu = 160 * 1024;
+    const size_t plain = select_lds_bytes(threads, items_cap, keep_cap, 0);
+    const int cap = (items_cap + 7) & ~7;
+    const size_t ranked = select_lds_bytes(threads, items_cap, keep_cap, cap);
+    if (ranked > cu) return 0;
+    const size_t before = cu / plain < 3 ? cu / plain : 3;
+    return cu / ranked >= before ? cap : 0;
+}
+
 struct SelectArgs {
     const float *logits;
     const int32_t *len;
@@ -118,6 +141,7 @@ struct SelectArgs {
     int max_keep;
     int items_cap;       // ceil(cap / block): size of the code array in LDS
     int keep_cap;        // size of each index buffer in LDS
+    int rank_cap;        // items the ranking route has LDS for (0: only the radix select; see rank_lds_bytes)
     int64_t logit_stride; // floats between the logit rows of consecutive segments
     uint32_t *pool_codes; // pooled mode: key codes of every item, Hkv * cap per (layer, sequence)
     SegGeom g;
@@ -129,7 +153,8 @@ struct SelectArgs {
 constexpr int WS_QUEUE_NEXT = NGC_STATUS_WORDS - 2;
 constexpr int WS_QUEUE_DONE = NGC_STATUS_WORDS - 1;
 
-constexpr int SMALL_ITEMS = 256;             // at most this many items: selection by ranking
+constexpr int SMALL_ITEMS = 256;             // at most this many items: ranking by comparing all pairs ...
+constexpr int RANK_MIN_ITEMS = 64;           // ... if ranking by buckets does not apply: beyond so many it is faster
 constexpr int SORT_BITS = 9;                 // digit width of the sigma sort
 constexpr int SORT_BINS = 1 << SORT_BITS;
 
@@ -414,6 +439,147 @@ __device__ __forceinline__ uint16_t *sort_by_code_desc(CodeOf code_of, int K, ui
     return cur;
 }
 
+// Ranks of all N items at once (the ranking route): items are dropped into as many buckets as the histogram area holds,
+// equal slices of the VALUE range [smallest finite key, largest key], and every item finds its place among the items of
+// its bucket by counting.  An item of rank < K is kept and sigma[rank] is the item: no select passes, no sort of the kept
+// ones.  Compared with the radix select (3 passes over the items) and the bucket sort of the kept items that the other
+// route runs, this is one counting pass, one prefix sum and one scatter, 5 workgroup barriers instead of ~25.
+//   bucketed   u16[N] scratch;  order   u16[K] out: the kept items by descending code, equal codes by ascending index
+//   kept_bits  one bit per item, zeroed by the caller (before a barrier), out: which items are kept
+//   hist       NB zeroed entries (before a barrier);  tmp  4 * waves entries
+// Returns false (workgroup-uniform) if a bucket holds more than BUCKET_LIMIT items (many equal keys): nothing but hist,
+// bucketed and tmp has been written then.  Whole workgroup; ends on a barrier.
+template <int THREADS>
+__device__ __forceinline__ bool rank_items(const uint32_t *code, int N, int K, uint32_t cmax, uint32_t cmin, uint32_t *hist,
+                                           uint32_t *tmp, uint16_t *bucketed, uint16_t *order, uint32_t *kept_bits)
+{
+    constexpr int NW = THREADS / NGC_WAVE;
+    constexpr int NB = (SEL_BINS > SORT_BINS * NW) ? SEL_BINS : SORT_BINS * NW;
+    constexpr int PER = NB / THREADS;
+    static_assert(PER % 4 == 0, "vector accesses to a thread's own buckets");
+    const int tid = threadIdx.x;
+    const float kmax = code_to_float(cmax), kmin = code_to_float(cmin);
+    const float width = kmax - kmin;
+    if (!(width > 0.f && width < INFINITY)) return false;
+    const float per_value = (float)(NB - 1) / width;
+    // a non-increasing function of the key in IEEE arithmetic: a larger key never lands in a later bucket
+    auto bucket_of = [&](uint32_t c) -> uint32_t {
+        const float x = (kmax - code_to_float(c)) * per_value;     // >= 0; +inf for a masked key
+        return (uint32_t)fminf(x, (float)(NB - 1));
+    };
+    for (int t = tid; t < N; t += THREADS) atomicAdd(&hist[bucket_of(code[t])], 1u);
+    __syncthreads();
+    u32x4 mine[PER / 4];
+    uint32_t sum = 0, biggest = 0;
+#pragma unroll
+    for (int i = 0; i < PER / 4; ++i) {
+        mine[i] = reinterpret_cast<const u32x4 *>(hist)[tid * (PER / 4) + i];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            sum += mine[i][u];
+            biggest = mine[i][u] > biggest ? mine[i][u] : biggest;
+        }
+    }
+    const uint32_t upto = (uint32_t)wave_incl_scan_i((int)sum);
+    biggest = wave_reduce(biggest, OpMaxU{});
+    if (lane_id() == NGC_WAVE - 1) { tmp[2 * wave_id()] = upto; tmp[2 * wave_id() + 1] = biggest; }
+    __syncthreads();
+    uint32_t run = upto - sum;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (w < wave_id()) run += tmp[2 * w];
+        biggest = tmp[2 * w + 1] > biggest ? tmp[2 * w + 1] : biggest;
+    }
+    if (biggest > (uint32_t)BUCKET_LIMIT) return false;
+#pragma unroll
+    for (int i = 0; i < PER / 4; ++i) {
+        u32x4 start;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            start[u] = run;
+            run += mine[i][u];
+        }
+        reinterpret_cast<u32x4 *>(hist)[tid * (PER / 4) + i] = start;
+    }
+    __syncthreads();
+    // unordered scatter: afterwards hist[b] is the END of bucket b (and the start of bucket b + 1)
+    for (int t = tid; t < N; t += THREADS) {
+        const uint32_t pos = atomicAdd(&hist[bucket_of(code[t])], 1u);
+        bucketed[pos] = (uint16_t)t;
+    }
+    __syncthreads();
+    for (int p = tid; p < N; p += THREADS) {
+        const uint32_t h = bucketed[p];
+        const uint32_t c = code[h];
+        const uint32_t b = bucket_of(c);
+        const int start = b ? (int)hist[b - 1] : 0, end = (int)hist[b];
+        if (start >= K) continue;
+        int rank = start;
+        for (int q = start; q < end; ++q) {
+            const uint32_t h2 = bucketed[q];
+            const uint32_t c2 = code[h2];
+            rank += (c2 > c || (c2 == c && h2 < h)) ? 1 : 0;
+        }
+        if (rank < K) {
+            order[rank] = (uint16_t)h;
+            atomicOr(&kept_bits[h >> 5], 1u << (h & 31));
+        }
+    }
+    __syncthreads();
+    return true;
+}
+
+// Log-probability of the kept items in sampled order (Eq. 2) from their logits x(j) (any order of calls, -inf for a masked
+// pick), U = this thread's share of the mass never picked.  stage: K floats of LDS.  Whole workgroup; every thread gets it.
+template <int THREADS, class Logit>
+__device__ __forceinline__ float sigma_logprob(Logit x, int K, float smax, float unpicked, float *stage, float *tmp)
+{
+    constexpr int NW = THREADS / NGC_WAVE;
+    const int tid = threadIdx.x;
+    float acc = 0.f;
+    for (int j = tid; j < K; j += THREADS) {
+        const float d = x(j) - smax;
+        acc += d;                              // a masked pick makes log p = -inf
+        stage[j] = exp_shifted(d);
+    }
+    __syncthreads();
+    const int chunk = (K + THREADS - 1) / THREADS;
+    const int nchunks = (K + chunk - 1) / chunk;
+    // thread 0 owns the LAST chunk, so an ordinary exclusive scan over threads yields the mass of everything picked
+    // after a thread's chunk
+    const int cidx = nchunks - 1 - tid;
+    const int j_lo = cidx * chunk;
+    const int j_hi = (cidx >= 0) ? ((j_lo + chunk < K) ? j_lo + chunk : K) : 0;
+    float mass = 0.f;
+    if (cidx >= 0)
+        for (int j = j_lo; j < j_hi; ++j) mass += stage[j];
+    const float incl = wave_incl_scan_f(mass);
+    const float others = wave_sum_f(unpicked);
+    if (lane_id() == NGC_WAVE - 1) { tmp[2 * wave_id()] = incl; tmp[2 * wave_id() + 1] = others; }
+    __syncthreads();
+    float R = 0.f, never = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (w < wave_id()) R += tmp[2 * w];
+        never += tmp[2 * w + 1];
+    }
+    __syncthreads();
+    float prev = __shfl_up(incl, 1, NGC_WAVE);   // sum of the lanes below, no subtraction
+    if (lane_id() == 0) prev = 0.f;
+    R = never + (R + prev);
+    LogProduct prod;
+    float logs = 0.f;
+    if (cidx >= 0) {
+        int n = 0;
+        for (int j = j_hi - 1; j >= j_lo; --j) {
+            R += stage[j];
+            prod.times(R > 0.f ? R : 1.0f);      // (0 only behind masked picks, where log p is -inf already)
+            if (++n == 64) { logs += prod.log(); prod = LogProduct{}; n = 0; }   // mantissas stay normal numbers
+        }
+    }
+    return block_sum_f<THREADS>(acc - (logs + prod.log()), tmp);
+}
+
 // Slots of the small shared scratch array `misc` that outlive the selection.
 constexpr int MISC_KEPT = 35;   // items kept in this segment
 constexpr int MISC_ROWS = 36;   // rows in use after compaction
@@ -431,7 +597,8 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
     uint32_t *hist = code + a.items_cap;
     int *misc = reinterpret_cast<int *>(hist + HIST);            // 64 ints
     uint16_t *idxA = reinterpret_cast<uint16_t *>(misc + 64);
-    uint16_t *idxB = idxA + a.keep_cap;
+    uint16_t *idxB = idxA + a.keep_cap;                           // max(keep_cap, rank_cap) entries
+    uint32_t *kept_bits = reinterpret_cast<uint32_t *>(idxB + (a.rank_cap > a.keep_cap ? a.rank_cap : a.keep_cap));
     float *fmisc = reinterpret_cast<float *>(misc);
 
     const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
@@ -461,9 +628,16 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
         return;
     }
 
+    const bool try_rank = want_sort && N > RANK_MIN_ITEMS && N <= a.rank_cap;
+    if (try_rank) {   // (published by the barriers of the reduction below)
+        for (int i = tid; i < HIST / 4; i += THREADS) reinterpret_cast<u32x4 *>(hist)[i] = u32x4{0u, 0u, 0u, 0u};
+        for (int i = tid; i < (N + 63) / 64 * 2; i += THREADS) kept_bits[i] = 0;
+    }
+
     // ---- 1. keys ----------------------------------------------------------
     float smax = -INFINITY, neg_smin = -INFINITY;   // over the unmasked entries (a NaN compares false everywhere)
-    uint32_t cmax = 0;
+    uint32_t cmax = 0, neg_cmin = 0;                // largest code; complement of the smallest code of a finite key
+    constexpr uint32_t CODE_MASKED = 0x007FFFFFu;   // of -inf
     for (int quad = tid; 4 * quad < N; quad += THREADS) {
         float s[4], key[4];
         keys_of_quad(row, N, quad, a.na, l, b, h, s, key);
@@ -473,6 +647,7 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
                 const uint32_t c = ordered_code(key[i]);
                 code[4 * quad + i] = c;
                 cmax = c > cmax ? c : cmax;
+                if (c > CODE_MASKED) neg_cmin = ~c > neg_cmin ? ~c : neg_cmin;
                 smax = fmaxf(smax, s[i]);
                 if (s[i] > -INFINITY) neg_smin = fmaxf(neg_smin, -s[i]);
             }
@@ -480,19 +655,85 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
     // Logits that span more than NGC_WIDE_SPREAD take the wide-range arithmetic of ngc_logsum.h for Eq. 2
     // (workgroup-uniform).
     bool wide = false;
-    if (want_logp) {
-        block_max2_f<THREADS>(smax, neg_smin, fmisc);   // has barriers
-        wide = smax > -INFINITY && smax + neg_smin > NGC_WIDE_SPREAD;
-        if (smax == -INFINITY) smax = 0.f;          // every entry masked: all weights are 0 (log p = -inf below)
+    if (want_sort) {   // all four maxima in one exchange
+        smax = wave_max_f(smax);
+        neg_smin = wave_max_f(neg_smin);
+        cmax = wave_reduce(cmax, OpMaxU{});
+        neg_cmin = wave_reduce(neg_cmin, OpMaxU{});
+        uint32_t *umisc = reinterpret_cast<uint32_t *>(misc);
+        if (lane == 0)
+            reinterpret_cast<u32x4 *>(umisc)[wv] = u32x4{__float_as_uint(smax), __float_as_uint(neg_smin), cmax, neg_cmin};
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const u32x4 m = reinterpret_cast<const u32x4 *>(umisc)[w];
+            smax = fmaxf(smax, __uint_as_float(m[0]));
+            neg_smin = fmaxf(neg_smin, __uint_as_float(m[1]));
+            cmax = m[2] > cmax ? m[2] : cmax;
+            neg_cmin = m[3] > neg_cmin ? m[3] : neg_cmin;
+        }
+        __syncthreads();
+        if (want_logp) {
+            wide = smax > -INFINITY && smax + neg_smin > NGC_WIDE_SPREAD;
+            if (smax == -INFINITY) smax = 0.f;          // every entry masked: all weights are 0 (log p = -inf below)
+        }
     }
-    if (want_sort) cmax = block_max_u<THREADS>(cmax, reinterpret_cast<uint32_t *>(misc));
 
-    // Large segments: radix select, ballot compaction, radix sort (steps 2-4).  Segments of at most
-    // SMALL_ITEMS items (blocks or pages as items, the paper's own sizes): ranking by counting instead.
+    // Ranking by buckets where it applies (steps 2''-4'').  Otherwise -- many equal keys, sigma not wanted, no room in
+    // LDS -- radix select, ballot compaction, sort (steps 2-4), or up to SMALL_ITEMS items ranking by all pairs (2'-4').
+    // Selection only, 896 segments, microseconds with (without) the buckets: 64 items 11.6 (11.6), 128: 11.7 (13.5),
+    // 256: 12.0 (19.8), 300: 13.4 (21.2), 700: 17.2 (22.2); 3584 segments of 4096: 119 (148).
     uint16_t *src = idxA;   // the kept items in sampled order, once known
     float unpicked = 0.f;   // sum of exp(s - smax) over items not kept (for logp)
     LogSum unpicked_w = ls_empty();   // the same sum on the wide-range route
-    if (N > SMALL_ITEMS) {
+    if (try_rank && rank_items<THREADS>(code, N, K, cmax, ~neg_cmin, hist, reinterpret_cast<uint32_t *>(misc), idxB, idxA,
+                                        kept_bits)) {
+        // ---- 2''-4''. ranks by buckets: idxA holds sigma, kept_bits the kept set -------
+        // Kept list, ascending: each wave owns a contiguous range of items; the kept items below it are counted from
+        // the bits, those of a 64-item step by its own word.
+        const int words = (N + 63) / 64;
+        const int per_wave = (words + NW - 1) / NW;
+        const int w_begin = wv * per_wave;
+        const int w_end = (w_begin + per_wave < words) ? (w_begin + per_wave) : words;
+        const u32x2 *bits = reinterpret_cast<const u32x2 *>(kept_bits);
+        int base = 0;
+        for (int w = lane; w < w_begin; w += NGC_WAVE) base += __popc(bits[w][0]) + __popc(bits[w][1]);
+        base = wave_reduce(base, OpAdd{});
+        int32_t *kept_row = a.kept_out + (size_t)seg * a.max_keep;
+        uint16_t *ascending = idxB;      // (every wave is done with the buckets)
+        for (int w = w_begin; w < w_end; ++w) {
+            const u32x2 m = bits[w];
+            const uint64_t sel_bits = ((uint64_t)m[1] << 32) | m[0];
+            const int t = w * 64 + lane;
+            const bool sel = (sel_bits >> lane) & 1u;
+            if (sel) {
+                const int slot = base + popc_below(sel_bits);
+                kept_row[slot] = t;
+                if (fill_holes) ascending[slot] = (uint16_t)t;
+                if (slot == K - 1) misc[34] = t;   // highest kept index
+            } else if (t < N && want_logp) {
+                float x = row[t];
+                if (x != x) x = -INFINITY;
+                if (wide) unpicked_w = ls_add_term(unpicked_w, x);
+                else unpicked += exp_shifted(x - smax);
+            }
+            base += __popcll(sel_bits);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            const int last_item = misc[34];
+            const int last_rows = (last_item == N - 1) ? (n - (N - 1) * a.g.block) : a.g.block;
+            misc[MISC_KEPT] = K;
+            misc[MISC_ROWS] = (K - 1) * a.g.block + last_rows;
+        }
+        if (fill_holes) {
+            const size_t seg_off = (size_t)seg * a.g.cap * ROW_BYTES;
+            fill_holes_inplace<ROW_BYTES, THREADS, 4>(reinterpret_cast<unsigned char *>(a.k) + seg_off,
+                                                      reinterpret_cast<unsigned char *>(a.v) + seg_off,
+                                                      a.pos ? a.pos + (size_t)seg * a.g.cap : nullptr, ascending, K);
+        }
+        src = idxA;
+    } else if (N > SMALL_ITEMS) {
         // ---- 2. radix select of the K-th largest code -------------------------
         int need;   // items equal to the threshold that are kept
         const uint32_t thr = radix_select_kth<THREADS>([&](int t) { return code[t]; }, N, K, hist, misc, need, false);
@@ -534,7 +775,7 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
                 float x = row[t];
                 if (x != x) x = -INFINITY;
                 if (wide) unpicked_w = ls_add_term(unpicked_w, x);
-                else unpicked += expf(x - smax);
+                else unpicked += exp_shifted(x - smax);
             }
             gt_base += __popcll(bgt);
             eq_base += __popcll(beq);
@@ -599,7 +840,7 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
                 float x = row[t];
                 if (x != x) x = -INFINITY;
                 if (wide) unpicked_w = ls_add_term(unpicked_w, x);
-                else unpicked += expf(x - smax);
+                else unpicked += exp_shifted(x - smax);
             }
             kept_so_far += total;
             __syncthreads();
@@ -627,46 +868,22 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
     if (!want_logp) return;
 
     // ---- 5. log-probability of sigma (Eq. 2) -------------------------------
-    // The logits of the picked items, minus the maximum, are gathered into LDS first (over the key codes,
-    // which are no longer needed), all loads in flight at once: the serial chunk loops below then never wait
-    // for a gather.
+    // The terms of the picked items are gathered into LDS first (over the key codes, which are no longer needed), all
+    // loads in flight at once: the serial chunk loops then never wait for a gather.
     float *ds = reinterpret_cast<float *>(code);
-    for (int j = tid; j < K; j += THREADS) {
-        float x = row[src[j]];
-        if (x != x) x = -INFINITY;
-        ds[j] = wide ? x : x - smax;   // the wide-range route works on the logits as they came
-    }
-    __syncthreads();
-    if (wide) {
+    auto logit = [&](int j) {
+        const float x = row[src[j]];
+        return (x != x) ? -INFINITY : x;
+    };
+    if (wide) {                          // that route works on the logits as they came
+        for (int j = tid; j < K; j += THREADS) ds[j] = logit(j);
+        __syncthreads();
         const LogSum Uw = block_sum_ls<THREADS>(unpicked_w, fmisc);
         const float lpw = sigma_logprob_wide<THREADS>([&](int j) { return ds[j]; }, K, Uw, fmisc);
         if (tid == 0) a.logp_out[seg] = lpw;
         return;
     }
-    const float U = block_sum_f<THREADS>(unpicked, fmisc);
-    const int chunk = (K + THREADS - 1) / THREADS;
-    const int nchunks = (K + chunk - 1) / chunk;
-    // thread 0 owns the LAST chunk, so an ordinary exclusive scan over threads
-    // yields the mass of everything picked after a thread's chunk
-    const int cidx = nchunks - 1 - tid;
-    const int j_lo = cidx * chunk;
-    const int j_hi = (cidx >= 0) ? ((j_lo + chunk < K) ? j_lo + chunk : K) : 0;
-    float mass = 0.f;
-    if (cidx >= 0)
-        for (int j = j_lo; j < j_hi; ++j) mass += expf(ds[j]);
-    float total_mass;
-    const float after = block_excl_scan_f<THREADS>(mass, fmisc, &total_mass);
-    float acc = 0.f;
-    if (cidx >= 0) {
-        float R = U + after;
-        for (int j = j_hi - 1; j >= j_lo; --j) {
-            const float d = ds[j];
-            R += expf(d);
-            // a masked pick (logit -inf) has probability 0: log p = -inf, also where nothing unmasked is left (R == 0)
-            acc += (d == -INFINITY) ? -INFINITY : d - logf(R);
-        }
-    }
-    const float lp = block_sum_f<THREADS>(acc, fmisc);
+    const float lp = sigma_logprob<THREADS>(logit, K, smax, unpicked, ds, fmisc);
     if (tid == 0) a.logp_out[seg] = lp;
 }
 

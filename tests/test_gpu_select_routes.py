@@ -1,0 +1,94 @@
+"""The selection's routes (ranking by buckets, radix select, ranking by all pairs) at the item counts where they change and
+on keys that send a segment from one to another: many equal keys, masked entries, infinities, ranges that overflow, every
+keep count from one to all, with and without noise, at the three workgroup sizes.  Kept lists and sampled orders are the
+oracle's, bit for bit; log-probabilities 1e-4 relative."""
+import numpy as np
+import pytest
+
+import oracle as orc
+from _harness import oracle_logprob
+
+pytestmark = pytest.mark.gpu
+
+
+def _ngc():
+    from paper_2604_18002_amd import binding
+    binding.load_library()
+    return binding
+
+
+def _logits(rng, n, kind):
+    x = rng.standard_normal(n).astype(np.float32)
+    if kind == "equal":            # one bucket holds more than any ranking by buckets takes
+        x[:] = np.float32(0.25)
+    elif kind == "quantised":
+        x = (np.round(x * 2) / 2).astype(np.float32)
+    elif kind == "masked":         # two thirds masked
+        x[rng.random(n) < 0.67] = -np.inf
+    elif kind == "few-masked":
+        x[rng.choice(n, min(n - 1, 20), replace=False)] = -np.inf
+    elif kind == "all-masked":
+        x[:] = -np.inf
+    elif kind == "infinite":
+        x[rng.integers(n)] = np.inf
+    elif kind == "huge":           # the value range of the keys is infinite in fp32
+        x[rng.integers(n)] = np.float32(3e38)
+        x[rng.integers(n)] = np.float32(-3e38)
+    elif kind == "outlier":        # nearly everything in one bucket
+        x[rng.integers(n)] = np.float32(1e6)
+    elif kind == "signed-zero":
+        x = np.where(rng.random(n) < 0.5, np.float32(-0.0), np.float32(0.0)).astype(np.float32)
+        x[: n // 2] += rng.standard_normal(n // 2).astype(np.float32)
+    return x
+
+
+KINDS = ["normal", "equal", "quantised", "masked", "few-masked", "all-masked", "infinite", "huge", "outlier", "signed-zero"]
+
+
+@pytest.mark.parametrize("tau", [0.0, 1.0])
+@pytest.mark.parametrize("cap", [64, 65, 96, 127, 128, 129, 255, 256, 257, 513, 700, 2048, 2049, 4099, 8200])
+def test_routes_agree_with_the_oracle(cap, tau):
+    import torch
+    ngc = _ngc()
+    rng = np.random.default_rng(cap)
+    B, D, seed, rnd = len(KINDS), 64, 99, 3
+    lens = np.array([cap - (i % 3) for i in range(B)], np.int32)
+    keeps = np.array([max(1, n // 2) for n in lens], np.int32)
+    keeps[0], keeps[2], keeps[4], keeps[9] = lens[0], 1, lens[4] - 1, lens[9]
+    logits = np.zeros((1, B, 1, cap), np.float32)
+    for b, kind in enumerate(KINDS):
+        logits[0, b, 0, :lens[b]] = _logits(rng, lens[b], kind)
+    mk = int(keeps.max())
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    for flags in (ngc.EVICT_SELECT_ONLY, 0, ngc.EVICT_UNORDERED):
+        c = ngc.Cache.allocate(1, B, 1, 1, D, cap)
+        rows = torch.arange(cap, device="cuda").remainder(251).to(torch.bfloat16)
+        c.k.copy_(rows.view(1, 1, 1, cap, 1).expand_as(c.k))
+        c.v.copy_(c.k)
+        c.len.copy_(d(lens.reshape(1, B, 1)))
+        ws = ngc.allocate_workspace(c, mk)
+        kept = torch.full((1, B, 1, mk), -1, dtype=torch.int32, device="cuda")
+        sigma, logp = torch.full_like(kept, -1), torch.full((1, B, 1), float("nan"), device="cuda")
+        p = ngc.make_params(noise_scale=tau, round=rnd, seed=seed, flags=flags)
+        print(f"[select-routes] cap={cap} tau={tau} flags={flags}", flush=True)
+        ngc.ngc_evict(c, -1, d(logits), d(keeps.reshape(1, B, 1)), p, mk, kept, sigma, logp, ws)
+        torch.cuda.synchronize()
+        hk, hs, hl = kept.cpu().numpy()[0, :, 0], sigma.cpu().numpy()[0, :, 0], logp.cpu().numpy()[0, :, 0]
+        for b, kind in enumerate(KINDS):
+            n, K = int(lens[b]), int(keeps[b])
+            x = logits[0, b, 0, :n]
+            want_k, want_s = orc.evict_select(x, K, tau, seed, rnd, 0, b, 0)
+            assert (hk[b, :K] == want_k).all(), (kind, n, K)
+            assert (hs[b, :K] == want_s).all(), (kind, n, K)
+            assert (hk[b, K:] == -1).all() and (hs[b, K:] == -1).all()
+            if kind == "infinite":
+                continue                              # Eq. 2 is not defined there
+            # (the short form of the oracle leaves the range of fp64 beyond spans of ~745)
+            want = orc.logprob_literal(x, want_s) if kind in ("huge", "outlier") else oracle_logprob(x, want_s)
+            if np.isinf(want):
+                assert hl[b] == want, (kind, n, K)
+            else:
+                assert hl[b] == pytest.approx(want, rel=1e-4, abs=1e-5), (kind, n, K)
+            if flags == 0:
+                assert torch.equal(c.k[0, b, 0, :K, 0], rows[torch.from_numpy(want_k).long().cuda()])
+        assert all(v == 0 for v in ngc.read_status(ws))
