@@ -3,7 +3,8 @@
 // averaged over the query heads of a KV head and over the w queries, then
 // (optionally) averaged over KV heads and over blocks of consecutive keys.
 //
-// One workgroup of 4 waves per (layer, sequence, KV head).  The w*G query rows
+// One workgroup of 4 waves per (layer, sequence, KV head), several where there are
+// few of those and the normalisers are given.  The w*G query rows
 // are padded to QT tiles of 16 and both passes run on the matrix cores:
 //   pass 1  S^T = K Q^T   (queries on lane%16): running max / sum per query row
 //   pass 2  S   = Q K^T   (keys on lane%16):    p = 2^(x - m) / l, summed over
@@ -30,7 +31,8 @@ struct ScoreArgs {
     const float *lse;         // optional fp32 [lb][w][Hq]: log-sum-exp of every query's scaled scores
     float *psi_out;           // fp32 [seg][cap], one value per key
     int32_t *status;
-    int seg0, lb0;
+    int seg0, nseg, lb0;
+    int S;                    // workgroups per segment (1 unless lse is given)
     int w, G, Hkv, cap, causal;
     float scale_log2e;
     // paged layout: k is the pool and a tile's base comes from the page table
@@ -60,14 +62,18 @@ void score_keys_kernel(ScoreArgs a)
 
     const int lane = lane_id(), wv = wave_id();
     const int li = lane & 15, kg = lane >> 4;
-    const int seg = a.seg0 + blockIdx.x;
+    // Workgroup -> (segment, share): the first shares of all segments come first.  Tile t of a segment belongs to wave t % 4
+    // of share (t / 4) % S.
+    const int share = (int)(blockIdx.x / a.nseg);
+    const int seg = a.seg0 + (int)(blockIdx.x - share * a.nseg);
+    const int first_tile = share * SC_WAVES, tile_step = a.S * SC_WAVES;
     const int G = a.G, w = a.w, R = w * G;
     int n = a.len[seg];
     if (n < 0 || n > a.cap) {
-        if (threadIdx.x == 0) atomicAdd(&a.status[NGC_STATUS_LEN_CLAMPED], 1);
+        if (threadIdx.x == 0 && share == 0) atomicAdd(&a.status[NGC_STATUS_LEN_CLAMPED], 1);
         n = n < 0 ? 0 : a.cap;
     }
-    if (n == 0) return;
+    if (first_tile * SC_TILE >= n) return;
     const int h = seg % a.Hkv;
     const int lb = seg / a.Hkv - a.lb0;
     const int Hq = a.Hkv * G;
@@ -236,12 +242,12 @@ void score_keys_kernel(ScoreArgs a)
         }
     const float inv_rows = 1.0f / (float)R;
     {
-        int tile = wv;
+        int tile = first_tile + wv;
         load_tile(tile);
-        for (; tile < tiles; tile += SC_WAVES) {
+        for (; tile < tiles; tile += tile_step) {
             stage_tile();
             const int row0 = tile * SC_TILE;
-            load_tile(tile + SC_WAVES);
+            load_tile(tile + tile_step);
             __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_wave_barrier();
             bf16x8 kop[2][KCH];
@@ -341,6 +347,27 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(ReduceArgs a)
 using namespace ngc;
 
 namespace {
+// Workgroups per segment.  With the normalisers given, a key's score needs nothing from the other keys, so a segment can be
+// shared freely; without them every workgroup would first have to read all of K.  Microseconds against the number S of
+// workgroups per segment (D = 128, w = 5, 6 heads per KV head):
+//     segments x keys     S=1     2     4     8    16    32
+//         8 x 2000       17.6  10.8   7.5   6.5   5.8   5.9
+//         8 x 8000       55.7  30.7  17.7  11.1   7.9   6.4
+//        32 x 8000       74.8  40.3  23.5  15.7  13.7  16.6
+//       128 x 2000       23.8  16.1  13.7  16.5  19.1  19.2
+//       128 x 8000       85.2  52.5  46.2  48.8  49.3  52.5
+//       400 x 2000       38.7  43.6  41.7  43.7  54.6  54.4
+//      2048 x 2150-3789   284   282   294   327   382   470
+// i.e. about two workgroups per CU, four at D = 64 (512 x 2000-6000: 64.9, 55.7 with two each).
+int score_shares(int nseg, int cap, int D, bool have_lse)
+{
+    if (!have_lse) return 1;
+    const int rounds = (cap + SC_TILE * SC_WAVES - 1) / (SC_TILE * SC_WAVES);
+    const int fill = (D == 128 ? 512 : 1024) / nseg;
+    const int s = rounds < fill ? rounds : fill;
+    return s > 1 ? s : 1;
+}
+
 int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, const void *q_recent,
                  const float *lse_recent, int32_t w, float scale, uint32_t flags, int32_t block,
                  float *scores_out, void *ws, size_t ws_bytes, void *stream)
@@ -369,7 +396,8 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     sa.lse = lse_recent;
     sa.psi_out = scores_out;
     sa.status = reinterpret_cast<int32_t *>(ws);
-    sa.seg0 = seg0;
+    sa.seg0 = seg0; sa.nseg = nseg;
+    sa.S = score_shares(nseg, c->cap, c->D, lse_recent != nullptr);   // nseg * S <= max(nseg, 1024)
     sa.lb0 = layer < 0 ? 0 : layer * c->B;
     sa.w = w; sa.G = G; sa.Hkv = c->Hkv; sa.cap = c->cap;
     sa.causal = (flags & NGC_SCORE_NO_CAUSAL) ? 0 : 1;
@@ -384,7 +412,7 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     hipStream_t st = (hipStream_t)stream;
     const int qt = (R + 15) / 16;
 #define NGC_LAUNCH_SCORE(DD, QQ) \
-    hipLaunchKernelGGL((score_keys_kernel<DD, QQ>), dim3(nseg), dim3(SC_WAVES * 64), 0, st, sa)
+    hipLaunchKernelGGL((score_keys_kernel<DD, QQ>), dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), 0, st, sa)
     if (c->D == 128) {
         if (qt == 1) NGC_LAUNCH_SCORE(128, 1); else if (qt == 2) NGC_LAUNCH_SCORE(128, 2);
         else if (qt == 3) NGC_LAUNCH_SCORE(128, 3); else NGC_LAUNCH_SCORE(128, 4);
