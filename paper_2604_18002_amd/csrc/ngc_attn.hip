@@ -668,6 +668,32 @@ size_t attn_partial_bytes(const ngc_cache *c, int nseg_launch, int S)
 {
     return S > 1 ? partial_o_bytes(c, nseg_launch, S) + partial_ml_bytes(c, nseg_launch, S) : 0;
 }
+
+// Whether ngc_decode_attn_static takes a call is decided by this number of workgroups per segment, not by the one that is
+// launched, so that a better split never turns a call away (nor lets one in).  It differs from "always" only for 16 query
+// heads per KV head at D = 128.
+int static_limit_splits(int nseg_launch, int max_len, int row_bytes)
+{
+    const double seg_mb = 2.0 * row_bytes * max_len * 1e-6;          // K and V of a segment
+    int s = COMPUTE_UNITS / (nseg_launch > 0 ? nseg_launch : 1);
+    const int by_merge = (int)sqrt(80.0 * seg_mb);
+    const int by_length = (max_len + ATT_TILE - 1) / ATT_TILE / 4;
+    s = s < by_merge ? s : by_merge;
+    s = s < by_length ? s : by_length;
+    s = s < MAX_SPLITS ? s : MAX_SPLITS;
+    return s > 1 ? s : 1;
+}
+
+// `fixed_layout`: the scratch is not a workspace sized for this cache but the library's own fixed array, which
+// serves caches of any geometry one after the other: tickets and partials then sit at offsets that do not depend
+// on the geometry (a ticket region that moved with the geometry would land on an earlier call's partials).
+constexpr size_t FIXED_TICKET_OFFSET = STATUS_BYTES;      // COMPUTE_UNITS tickets: only launches of at most
+constexpr size_t FIXED_PARTIAL_OFFSET = 4096;             // COMPUTE_UNITS / 2 segments are ever split
+
+bool fits_static(const ngc_cache *c, int nseg_launch, int S)
+{
+    return FIXED_PARTIAL_OFFSET + attn_partial_bytes(c, nseg_launch, S) <= NGC_STATIC_SCRATCH_BYTES;
+}
 }  // namespace
 
 extern "C" int ngc_version(void) { return 220; }
@@ -706,12 +732,6 @@ struct NewRows {            // fused append: the new token's rows, or all null
     const int32_t *new_pos;
 };
 
-// `fixed_layout`: the scratch is not a workspace sized for this cache but the library's own fixed array, which
-// serves caches of any geometry one after the other: tickets and partials then sit at offsets that do not depend
-// on the geometry (a ticket region that moved with the geometry would land on an earlier call's partials).
-constexpr size_t FIXED_TICKET_OFFSET = STATUS_BYTES;      // COMPUTE_UNITS tickets: only launches of at most
-constexpr size_t FIXED_PARTIAL_OFFSET = 4096;             // COMPUTE_UNITS / 2 segments are ever split
-
 int launch_decode(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, const NewRows *nr, const void *q,
                   float scale, int32_t max_len_hint, float *out, float *lse_out, int32_t *status, void *ws,
                   size_t ws_bytes, void *stream, bool fixed_layout = false)
@@ -731,13 +751,13 @@ int launch_decode(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, 
     const int max_len = (max_len_hint > 0 && max_len_hint < c->cap) ? max_len_hint : c->cap;
     int S = splits_for(nseg, max_len, c->D * 2);
     if (nseg > COMPUTE_UNITS) S = 1;   // (what splits_for() returns anyway: the fixed ticket region relies on it)
+    // A call that the fixed array serves is split the same way with a workspace: both return the same bits.
+    const bool static_ok = fits_static(c, nseg, static_limit_splits(nseg, max_len, c->D * 2));
+    if (fixed_layout && !static_ok) return NGC_ENOSPC;
+    while (static_ok && S > 1 && !fits_static(c, nseg, S)) --S;
     const size_t off = fixed_layout ? FIXED_PARTIAL_OFFSET : attn_offset(c);
     if (ws_bytes < off) return NGC_ENOSPC;
-    if (fixed_layout) {   // the fixed array either holds what the launch wants or the call is refused
-        if (ws_bytes < off + attn_partial_bytes(c, nseg, S)) return NGC_ENOSPC;
-    } else {
-        while (S > 1 && ws_bytes < off + attn_partial_bytes(c, nseg, S)) --S;   // fewer splits: same result, less scratch
-    }
+    while (S > 1 && ws_bytes < off + attn_partial_bytes(c, nseg, S)) --S;   // fewer splits: same result, less scratch
     if ((long long)nseg * S > 0x7FFFFFFFLL) return NGC_EUNSUPPORTED;
 
     AttnArgs aa;
