@@ -17,7 +17,7 @@
 // (no registers, no LDS store instructions) and are shared by the waves; the V operand is read transposed from LDS.
 //
 // What bounds it: matrix and vector work of two waves per SIMD that overlap only in part, then the output.  B = 8,
-// T = 4096, 28/4 heads, 27 % of the causal pairs visible (the issued products are worth 390 TFLOP): without the tile
+// T = 4096, 28/4 heads, 27 % of the causal pairs visible (the issued products are worth 390 GFLOP): without the tile
 // loads 403 us, without the products 281 us, with neither 113 us (470 MB of output), together 470 us.  Against the
 // version with 16-wide tiles and rows staged through registers (552 us): 32-wide tiles and loads straight to LDS 511 us;
 // a reference for the exponents that moves only when outgrown by 2^8, and transposing reads of V instead of 32 byte

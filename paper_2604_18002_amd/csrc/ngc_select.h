@@ -85,6 +85,8 @@ __device__ __forceinline__ void keys_of_quad(const float *row, int n_items, int 
 // items (2 B per kept item each) and a histogram area.
 //
 //   1. keys:    4 items per thread per step, one Philox call per 4 items.
+//   2''.-4''. ranking (rank_items), where it has LDS and no bucket overflows: every item's place in the total order
+//               from equal slices of the value range; the kept list from a bitmap.  Otherwise:
 //   2. select:  the K-th largest code by a 3-pass radix select (11+11+10 bits)
 //               over LDS histograms.
 //   3. kept:    each wave owns a contiguous range of items; ballots and lane
@@ -141,7 +143,7 @@ struct SelectArgs {
     int max_keep;
     int items_cap;       // ceil(cap / block): size of the code array in LDS
     int keep_cap;        // size of each index buffer in LDS
-    int rank_cap;        // items the ranking route has LDS for (0: only the radix select; see rank_lds_bytes)
+    int rank_cap;        // items the ranking route has LDS for (0: only the radix select; see rank_capacity)
     int64_t logit_stride; // floats between the logit rows of consecutive segments
     uint32_t *pool_codes; // pooled mode: key codes of every item, Hkv * cap per (layer, sequence)
     SegGeom g;
