@@ -78,12 +78,18 @@ __device__ __forceinline__ float half_rows_sum(float v)
     return __uint_as_float(a[0]) + __uint_as_float(a[1]);
 }
 
-// 16 bytes per lane from memory straight into LDS, lane l to lds + 16 l (lds wave-uniform); counts as a vector
-// memory load, so a barrier that follows it (__syncthreads) waits for it.
+// 16 bytes per lane from memory straight into LDS, lane l to lds + 16 l (lds wave-uniform).  Counts as a vector memory
+// load; lds_loads_done() stands between it and the first use by any wave.
 __device__ __forceinline__ void load_to_lds16(const void *src, void *lds)
 {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) uint32_t *)(uintptr_t)src,
                                      (__attribute__((address_space(3))) uint32_t *)lds, 16, 0, 0);
+}
+
+__device__ __forceinline__ void lds_loads_done()
+{
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's; the barrier makes it every wave's
+    __syncthreads();
 }
 
 // Four 16-bit values per lane from LDS, transposed within each 16 lanes: lane x gets value x % 4 of the lanes x / 4,

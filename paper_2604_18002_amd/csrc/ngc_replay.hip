@@ -394,7 +394,7 @@ void replay_attn_kernel(ReplayArgs a)
     // Per tile: tile t is computed from one pair of LDS buffers while the rows of tile t+1 travel into the other and the
     // list entries of tile t+2 are fetched.
     store_mask(0, 0, ms);
-    __syncthreads();
+    lds_loads_done();
     int t = 0;
     while (t < t_end) {
         if (t + 1 < t_end) {
@@ -409,7 +409,7 @@ void replay_attn_kernel(ReplayArgs a)
         next = load_info(t + 2);
         if (++t >= t_end) break;
         store_mask(t, 1, ms);
-        __syncthreads();
+        lds_loads_done();
         if (t + 1 < t_end) {
             load_rows(ix_a, lds_k0, lds_v0);
             load_mask(ix_a, ms);
@@ -422,7 +422,7 @@ void replay_attn_kernel(ReplayArgs a)
         next = load_info(t + 2);
         if (++t >= t_end) break;
         store_mask(t, 0, ms);
-        __syncthreads();
+        lds_loads_done();
     }
 
     // ---- normalise and write -------------------------------------------------
