@@ -170,6 +170,15 @@ def _ptr(t) -> Optional[int]:
 _current_raw_stream = None
 
 
+def _forget_stream_reader() -> None:
+    """A forked child asks torch again, which refuses there if the parent had initialised the GPU."""
+    global _current_raw_stream
+    _current_raw_stream = None
+
+
+os.register_at_fork(after_in_child=_forget_stream_reader)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream

@@ -106,3 +106,13 @@ def test_unreadable_arguments_raise_and_call_nothing():
         front.decode_attn(c, 0)
     with pytest.raises(RuntimeError):
         front.open("/nonexistent/libngc.so")
+
+
+def test_a_forked_child_asks_torch_for_the_stream_again(monkeypatch):
+    import os
+    from paper_2604_18002_amd import binding
+    monkeypatch.setattr(binding, "_current_raw_stream", lambda: 0)
+    pid = os.fork()
+    if pid == 0:
+        os._exit(0 if binding._current_raw_stream is None else 1)
+    assert os.waitpid(pid, 0)[1] == 0 and binding._current_raw_stream is not None
