@@ -32,9 +32,9 @@ __device__ __forceinline__ float exp_shifted(float d)
     return __builtin_fmaf(r, lo * LN2, r);
 }
 
-// A sum of logarithms taken as the logarithm of a product: mantissas multiply (at most a few dozen before value() is
-// called: each is in [1/2, 1)), exponents add.  Four instructions per term instead of a logarithm, and a smaller
-// error: the product of n mantissas is off by n * 2^-24, n logarithms of ~7 by about 2^-22 each.
+// A sum of logarithms taken as the logarithm of a product: mantissas multiply (at most a few dozen before log() is
+// called: each is in [1/2, 1)), exponents add.  Four instructions per term instead of a logarithm; the product of n
+// mantissas is off by n * 2^-24, n logarithms of ~7 by about 2^-22 each.
 struct LogProduct {
     float mant = 1.0f;
     int exponent = 0;
@@ -44,6 +44,25 @@ struct LogProduct {
         exponent += __builtin_amdgcn_frexp_expf(x);
     }
     __device__ __forceinline__ float log() const { return __builtin_fmaf((float)exponent, 0.693147181f, logf(mant)); }
+};
+
+// Sum of log(e_j / R_j) over a few picks, taken as one logarithm: the mantissas of the e_j and of the R_j multiply, the
+// difference of their exponents is an integer.  A pick that is nearly certain (e_j close to R_j) adds an error of a few
+// 2^-24 whatever its logit; d_j - log R_j, two numbers of up to 80 that cancel, adds 80 * 2^-24, and sums of the d_j and of
+// the logarithms that belong to different picks add that many times over.  e_j = 0 (a masked pick) makes it -inf.  At
+// most MAX_PICKS picks before log(): each mantissa is in [1/2, 1).
+struct LogRatio {
+    static constexpr int MAX_PICKS = 64;
+    float num = 1.0f, den = 1.0f;
+    int exponent = 0;
+    __device__ __forceinline__ void times(float e, float r)
+    {
+        r = r > 0.f ? r : 1.0f;      // 0 only where e is
+        num *= __builtin_amdgcn_frexp_mantf(e);
+        den *= __builtin_amdgcn_frexp_mantf(r);
+        exponent += __builtin_amdgcn_frexp_expf(e) - __builtin_amdgcn_frexp_expf(r);
+    }
+    __device__ __forceinline__ float log() const { return __builtin_fmaf((float)exponent, 0.693147181f, logf(num / den)); }
 };
 
 struct LogSum {

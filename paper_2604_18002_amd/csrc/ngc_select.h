@@ -538,12 +538,7 @@ __device__ __forceinline__ float sigma_logprob(Logit x, int K, float smax, float
 {
     constexpr int NW = THREADS / NGC_WAVE;
     const int tid = threadIdx.x;
-    float acc = 0.f;
-    for (int j = tid; j < K; j += THREADS) {
-        const float d = x(j) - smax;
-        acc += d;                              // a masked pick makes log p = -inf
-        stage[j] = exp_shifted(d);
-    }
+    for (int j = tid; j < K; j += THREADS) stage[j] = exp_shifted(x(j) - smax);
     __syncthreads();
     const int chunk = (K + THREADS - 1) / THREADS;
     const int nchunks = (K + chunk - 1) / chunk;
@@ -569,17 +564,17 @@ __device__ __forceinline__ float sigma_logprob(Logit x, int K, float smax, float
     float prev = __shfl_up(incl, 1, NGC_WAVE);   // sum of the lanes below, no subtraction
     if (lane_id() == 0) prev = 0.f;
     R = never + (R + prev);
-    LogProduct prod;
+    LogRatio ratio;
     float logs = 0.f;
     if (cidx >= 0) {
         int n = 0;
         for (int j = j_hi - 1; j >= j_lo; --j) {
             R += stage[j];
-            prod.times(R > 0.f ? R : 1.0f);      // (0 only behind masked picks, where log p is -inf already)
-            if (++n == 64) { logs += prod.log(); prod = LogProduct{}; n = 0; }   // mantissas stay normal numbers
+            ratio.times(stage[j], R);            // a masked pick makes log p = -inf
+            if (++n == LogRatio::MAX_PICKS) { logs += ratio.log(); ratio = LogRatio{}; n = 0; }
         }
     }
-    return block_sum_f<THREADS>(acc - (logs + prod.log()), tmp);
+    return block_sum_f<THREADS>(logs + ratio.log(), tmp);
 }
 
 // Slots of the small shared scratch array `misc` that outlive the selection.

@@ -92,3 +92,53 @@ def test_routes_agree_with_the_oracle(cap, tau):
             if flags == 0:
                 assert torch.equal(c.k[0, b, 0, :K, 0], rows[torch.from_numpy(want_k).long().cuda()])
         assert all(v == 0 for v in ngc.read_status(ws))
+
+
+@pytest.mark.parametrize("tail", ["spread", "equal"])      # ranking by buckets; too many equal keys: the other routes
+@pytest.mark.parametrize("n", [0, 70, 256, 700, 2100, 9000])
+def test_logprob_of_nearly_certain_picks(n, tail):
+    """A ladder of picks, each far likelier than all that come after it: log p is a small sum of differences of large
+    numbers (logits up to 80 below the largest).  A pick's term in a round's log-probability is log(e_j / R_j) of two fp32
+    numbers: e_j and R_j are rounded (2 x 2^-24), so are the two mantissa products and their quotient (3 x 2^-24): 2^-21.6
+    in all.  Eq. 2 for given picks subtracts log R_j from d_j = x_j - max x instead, each rounded to 2^-24 of its size at
+    most.  Beyond that the 1e-4 relative that holds everywhere."""
+    import torch
+    ngc = _ngc()
+    rng = np.random.default_rng(n)
+    ladders = [(17, 4.9), (12, 6.6), (30, 2.7), (9, 9.7)]
+    cap = max(n, 30)
+    lens = np.array([n or k for k, _ in ladders], np.int32)
+    keeps = np.array([k for k, _ in ladders], np.int32)
+    if n:
+        keeps[:2] -= 2                                     # what lies lowest is the tail, never picked
+    B, mk = len(ladders), int(keeps.max())
+    logits = np.zeros((1, B, 1, cap), np.float32)
+    for b, (k, step) in enumerate(ladders):
+        x = np.full(lens[b], -79.9, np.float32)            # a span of just under 80: no wide-range route
+        if tail == "spread":
+            x += rng.random(lens[b]).astype(np.float32)
+        x[rng.permutation(lens[b])[:k]] = -step * np.arange(k) + 0.01 * rng.random(k)
+        logits[0, b, 0, :lens[b]] = x - x.max() + np.float32(3.0)
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    d_x, d_keep, d_len = d(logits), d(keeps.reshape(1, B, 1)), d(lens.reshape(1, B, 1))
+    for flags in (ngc.EVICT_SELECT_ONLY, 0):
+        c = ngc.Cache.allocate(1, B, 1, 1, 64, cap)
+        c.len.copy_(d_len)
+        ws = ngc.allocate_workspace(c, mk)
+        kept = torch.zeros((1, B, 1, mk), dtype=torch.int32, device="cuda")
+        sigma, logp = torch.zeros_like(kept), torch.zeros((1, B, 1), device="cuda")
+        given = torch.zeros(B, device="cuda")
+        print(f"[select-routes] ladder n={n} tail={tail} flags={flags}", flush=True)
+        ngc.ngc_evict(c, -1, d_x, d_keep, ngc.make_params(noise_scale=0.0, flags=flags), mk, kept, sigma, logp, ws)
+        ngc.ngc_subset_logprob(d_x, d_len, sigma, d_keep, B, cap, mk, given, ws)
+        torch.cuda.synchronize()
+        hs = sigma.cpu().numpy()[0, :, 0]
+        for b in range(B):
+            x, K = logits[0, b, 0, :lens[b]], int(keeps[b])
+            _, want_s = orc.evict_select(x, K, 0.0, 0, 0, 0, b, 0)
+            assert (hs[b, :K] == want_s).all()
+            want = oracle_logprob(x, want_s)
+            for got, rounding in ((float(logp[0, b, 0]), K * 2.0 ** -21.6),
+                                  (float(given[b]), 2.0 ** -23 * float((x.max() - x[want_s]).sum()))):
+                assert abs(got - want) <= 1e-4 * abs(want) + rounding, (n, tail, b, got, want)
+        assert all(v == 0 for v in ngc.read_status(ws))
