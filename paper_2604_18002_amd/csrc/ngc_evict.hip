@@ -1061,9 +1061,11 @@ __global__ __launch_bounds__(THREADS) void evict_kernel(SelectArgs a)
     if constexpr (THREADS != PERSISTENT_THREADS) {
         evict_segment<THREADS, ROW_BYTES, UNROLL>(a, a.seg0 + (int)blockIdx.x, smem_raw, misc);
     } else {
-        __shared__ int next_item;
-        for (int item = next_segment<THREADS>(a, &next_item); item < a.nseg;
-             item = next_segment<THREADS>(a, &next_item))
+        // The item index travels through the start of the sort buffer behind misc[], which a segment's selection writes
+        // only after its first barrier: a word of static LDS would make the largest selections (all of a CU's 160 KB)
+        // unlaunchable.
+        int *next_item = misc + 64;
+        for (int item = next_segment<THREADS>(a, next_item); item < a.nseg; item = next_segment<THREADS>(a, next_item))
             evict_segment<THREADS, ROW_BYTES, UNROLL>(a, a.seg0 + item, smem_raw, misc);
         if (threadIdx.x == 0) {
             const int done = atomicAdd(&a.status[WS_QUEUE_DONE], 1);

@@ -142,3 +142,39 @@ def test_logprob_of_nearly_certain_picks(n, tail):
                                   (float(given[b]), 2.0 ** -23 * float((x.max() - x[want_s]).sum()))):
                 assert abs(got - want) <= 1e-4 * abs(want) + rounding, (n, tail, b, got, want)
         assert all(v == 0 for v in ngc.read_status(ws))
+
+
+@pytest.mark.parametrize("cap,max_keep,fits", [(16384, 15225, True), (16384, 15232, True), (16384, 15233, True),
+                                               (16104, 16088, True), (16352, 16352, True), (16384, 16320, True),
+                                               (16384, 16321, False)])
+def test_selections_that_fill_the_lds(cap, max_keep, fits):
+    """Up to the documented limit, and just beyond it; with buckets and index buffers the first four ask for 160 KB or a
+    few bytes less."""
+    import torch
+    ngc = _ngc()
+    rng = np.random.default_rng(max_keep)
+    x = rng.standard_normal((1, 1, 2, cap)).astype(np.float32)
+    keeps = np.array([max_keep, cap // 3], np.int32)
+    for flags in (ngc.EVICT_SELECT_ONLY, 0):
+        c = ngc.Cache.allocate(1, 1, 2, 2, 64, cap)
+        c.len.fill_(cap)
+        ws = ngc.allocate_workspace(c, max_keep)
+        kept = torch.zeros((1, 1, 2, max_keep), dtype=torch.int32, device="cuda")
+        sigma, logp = torch.zeros_like(kept), torch.zeros((1, 1, 2), device="cuda")
+        args = (c, -1, torch.from_numpy(x).cuda(), torch.from_numpy(keeps.reshape(1, 1, 2)).cuda(),
+                ngc.make_params(seed=5, flags=flags), max_keep, kept, sigma, logp, ws)
+        print(f"[select-routes] lds cap={cap} max_keep={max_keep} flags={flags}", flush=True)
+        if not fits:
+            with pytest.raises(ngc.NgcError) as e:
+                ngc.ngc_evict(*args)
+            assert e.value.code == ngc.NGC_EUNSUPPORTED
+            continue
+        ngc.ngc_evict(*args)
+        torch.cuda.synchronize()
+        for h in range(2):
+            want_k, want_s = orc.evict_select(x[0, 0, h], int(keeps[h]), 1.0, 5, 0, 0, 0, h)
+            assert (kept[0, 0, h, :keeps[h]].cpu().numpy() == want_k).all()
+            assert (sigma[0, 0, h, :keeps[h]].cpu().numpy() == want_s).all()
+            assert float(logp[0, 0, h]) == pytest.approx(oracle_logprob(x[0, 0, h], want_s), rel=1e-4)
+        assert c.len.flatten().tolist() == ([cap, cap] if flags else keeps.tolist())
+        assert all(v == 0 for v in ngc.read_status(ws))
