@@ -574,20 +574,14 @@ __device__ __forceinline__ float sigma_logprob(Logit x, int K, float smax, float
             if (++n == LogRatio::MAX_PICKS) { logs += ratio.log(); ratio = LogRatio{}; n = 0; }
         }
     }
-    // Whole and fractional parts of the threads' shares add up separately, the whole ones exactly (below 2^24): the total,
-    // thousands for a long sequence, is rounded once.
-    const float mine = logs + ratio.log(), whole = rintf(mine);
-    const float wholes = wave_sum_f(whole), parts = wave_sum_f(mine == whole ? 0.f : mine - whole);
-    if (lane_id() == 0) { tmp[2 * wave_id()] = wholes; tmp[2 * wave_id() + 1] = parts; }
+    const float share = wave_sum_f(logs + ratio.log());
+    if (lane_id() == 0) tmp[wave_id()] = share;
     __syncthreads();
-    float all = 0.f, rest = 0.f;
+    double total = 0.0;      // thousands for a long sequence: rounded once
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        all += tmp[2 * w];
-        rest += tmp[2 * w + 1];
-    }
+    for (int w = 0; w < NW; ++w) total += (double)tmp[w];
     __syncthreads();
-    return all + rest;
+    return (float)total;
 }
 
 // Slots of the small shared scratch array `misc` that outlive the selection.
