@@ -41,17 +41,17 @@
 // after every other one has read it.
 //
 // Which tiles a wave works on does not depend on the segment's length (tile t
-// belongs to wave t % 4 of workgroup (t / 4) % S), so the first tile is
-// requested before the length has arrived: one memory round trip less in front
-// of every launch.  Rows at or beyond the length are switched off when their
+// belongs to wave t % 4 of workgroup (t / 4) % S), so in launches that fill no
+// more than the chip the first tile is requested before the length has arrived
+// (first_tile_early() has the rule and its figures).  Rows at or beyond the length are switched off when their
 // tile is computed (their scores by the mask, their V values by zeros: what lies
 // there is unspecified and may be NaN).
 //
 // What bounds a launch: at a few segments the chain of memory round trips (first
 // tile; then, if a segment is shared, partial -> ticket -> merge), at several
 // hundred the read rate of the memory.  Per layer, from a HIP graph, before ->
-// after the first tile moved in front of the length, the partials came in one
-// batch and the last tile lost its prefetch: 2 segments x 2000 rows 8.2 -> 6.7 us,
+// after the tiles were interleaved over the workgroups, the partials came in one
+// batch, the last tile lost its prefetch and small launches asked early: 2 segments x 2000 rows 8.2 -> 6.7 us,
 // 32 x 525 rows (8.6 MB) 9.1 -> 7.0 us, 128 x 1494 rows (98 MB) 22.0 -> 19.7 us,
 // 512 x 2700 rows (0.71 GB) 119 -> 117 us.
 //
@@ -134,7 +134,8 @@ __device__ __forceinline__ f32x2 ld_device8(__amdgpu_buffer_rsrc_t r, uint32_t b
     return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, byte_off, 0, AUX_DEVICE_SCOPE));
 }
 
-template <int D, bool PAGED, bool APPEND>
+// EARLY: a wave's first tile is requested before the length has arrived (see first_tile_early()).
+template <int D, bool PAGED, bool APPEND, bool EARLY>
 __global__ __launch_bounds__(ATT_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void decode_kernel(AttnArgs a)
 {
@@ -224,9 +225,9 @@ void decode_kernel(AttnArgs a)
         }
     };
 
-    // Everything that does not need the length is requested first: the queries, the new row, the first tile (its
-    // rows are clamped to the capacity only; paged: table entries beyond the pages in use hold anything, which
-    // tile_base() turns into some page of the pool).
+    // Everything that does not need the length is requested first: the queries, the new row and, in launches that fill
+    // no more than the chip (EARLY), the first tile (its rows are clamped to the capacity only; paged: table entries
+    // beyond the pages in use hold anything, which tile_base() turns into some page of the pool).
     u32x4 new_piece = {0u, 0u, 0u, 0u};      // lanes [0, K_PIECES) hold the new K row, the next K_PIECES the V row
     if constexpr (APPEND) {
         const unsigned char *src = (lane / K_PIECES) & 1 ? a.v_new : a.k_new;
@@ -241,12 +242,12 @@ void decode_kernel(AttnArgs a)
             qop[c] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(qrow + c * 64 + kg * 16));
     }
     u32x4 v_a[8], v_b[8];
-    {
+    if constexpr (EARLY) {
         const int cap_tile = (a.cap - 1) / ATT_TILE;
         const int t0 = tile < cap_tile ? tile : cap_tile;
         issue_loads(t0, a.cap - 1, tile_base(t0, cap_tile), v_a);
+        __asm__ volatile("" ::: "memory");   // the requests stay in front of everything that waits for the length
     }
-    __asm__ volatile("" ::: "memory");   // the requests stay in front of everything that waits for the length
 
     int n = n_raw;
     if (n < 0 || n > a.cap) {
@@ -482,6 +483,9 @@ void decode_kernel(AttnArgs a)
         }
     }
 
+    if constexpr (!EARLY) {
+        if (tile < tiles) issue_loads(tile, last_row, tile_base(tile, tiles - 1), v_a);
+    }
     // bases of the next tile and of the one after it (paged: looked up before they are needed)
     size_t base1 = tile_base(tile + step, tiles - 1), base2 = tile_base(tile + 2 * step, tiles - 1);
     bool staged = false;
@@ -644,6 +648,25 @@ int splits_for(int nseg_launch, int max_len, int row_bytes)
     return best;
 }
 
+// Whether a wave asks for its first tile before the length has arrived.  It saves part of a memory round trip in front of
+// the launch, and reads rows nobody uses where a segment is shorter than the workgroup's four tiles.  Microseconds
+// without -> with (D = 128, one kernel that takes the choice as an argument; the argument itself costs small launches
+// up to 0.6 us, hence two kernels):
+//     segments x rows        20-32          100-128        500-550        2000-3000
+//           2             4.06 -> 4.25    4.53 -> 4.48    6.02 -> 5.83    7.74 -> 7.71
+//          64             4.27 -> 4.47    4.72 -> 4.71    8.62 -> 8.49    17.9 -> 17.7
+//         256             4.92 -> 5.84    6.38 -> 6.25    13.9 -> 13.8    53.5 -> 52.5
+//         512             5.77 -> 8.45    8.04 -> 8.21    23.3 -> 23.5    103.6 -> 102.3
+//        1024             9.83 -> 14.9    15.0 -> 15.6    44.6 -> 44.6    204.9 -> 203.9
+//        8192             60.2 -> 108     102 -> 108      367 -> 366
+// So it is done where every workgroup has a CU to itself (at most 16 MB are read in vain there) and the longest segment
+// has more rows than two tiles; beyond, the other workgroups of a CU cover the wait.  With the two kernels 1024 segments
+// of 20-32 rows take 8.5 us, 13.7 if all ask early; 512 segments of 2700 rows take the same time either way (0.2 %).
+bool first_tile_early(int nseg_launch, int S, int max_len)
+{
+    return nseg_launch * S <= COMPUTE_UNITS && max_len > 2 * ATT_TILE;
+}
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // workspace layout: [status][per segment of the cache: 2 int32 of the paged layout's pool bookkeeping]
@@ -795,16 +818,23 @@ int launch_decode(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, 
     }
     hipStream_t st = (hipStream_t)stream;
     const dim3 grid(nseg * S), block(ATT_WAVES * 64);
-    if (pc) {
-        if (c->D == 128) hipLaunchKernelGGL((decode_kernel<128, true, false>), grid, block, 0, st, aa);
-        else             hipLaunchKernelGGL((decode_kernel<64, true, false>), grid, block, 0, st, aa);
-    } else if (nr) {
-        if (c->D == 128) hipLaunchKernelGGL((decode_kernel<128, false, true>), grid, block, 0, st, aa);
-        else             hipLaunchKernelGGL((decode_kernel<64, false, true>), grid, block, 0, st, aa);
-    } else {
-        if (c->D == 128) hipLaunchKernelGGL((decode_kernel<128, false, false>), grid, block, 0, st, aa);
-        else             hipLaunchKernelGGL((decode_kernel<64, false, false>), grid, block, 0, st, aa);
+    const bool early = first_tile_early(nseg, S, max_len);
+#define NGC_LAUNCH_DECODE(PAGED, APPEND) \
+    if (c->D == 128) { \
+        if (early) hipLaunchKernelGGL((decode_kernel<128, PAGED, APPEND, true>), grid, block, 0, st, aa); \
+        else       hipLaunchKernelGGL((decode_kernel<128, PAGED, APPEND, false>), grid, block, 0, st, aa); \
+    } else { \
+        if (early) hipLaunchKernelGGL((decode_kernel<64, PAGED, APPEND, true>), grid, block, 0, st, aa); \
+        else       hipLaunchKernelGGL((decode_kernel<64, PAGED, APPEND, false>), grid, block, 0, st, aa); \
     }
+    if (pc) {
+        NGC_LAUNCH_DECODE(true, false)
+    } else if (nr) {
+        NGC_LAUNCH_DECODE(false, true)
+    } else {
+        NGC_LAUNCH_DECODE(false, false)
+    }
+#undef NGC_LAUNCH_DECODE
     NGC_HIP_CHECK(hipGetLastError());
     return NGC_OK;
 }

@@ -140,3 +140,70 @@ def test_split_rule_stays_inside_the_workspace_it_promises():
         ngc.ngc_decode_attn(c, 0, q, D ** -0.5, hint, a, ws)
         ngc.ngc_decode_attn(c, 0, q, D ** -0.5, hint, b, big)
         assert torch.equal(a, b), hint
+
+
+@pytest.mark.parametrize("D,Hq", [(64, 8), (128, 12)])
+@pytest.mark.parametrize("B,hint", [(128, 65), (128, 64), (129, 0)])      # the first tile before the length, and after it (twice)
+def test_first_tile_before_and_after_the_length(B, hint, D, Hq):
+    """256 segments of one workgroup each are the most for which a wave asks for its first tile before it knows the length,
+    and only if the longest may have more than two tiles: both sides of either limit, empty and full segments among them,
+    NaN in every unused row, contiguous (with and without the append) and paged."""
+    import torch
+    ngc = _ngc()
+    H, scale = 2, D ** -0.5
+    cap = hint or 160
+    g = torch.Generator().manual_seed(B + hint + D)
+    edges = [x for x in (0, 1, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 159, 160) if x <= cap] + [cap]
+    n = torch.tensor([edges[(i * 5) % len(edges)] for i in range(B * H)], dtype=torch.int32).view(1, B, H)
+    k = torch.randn(1, B, H, cap, D, generator=g).to(torch.bfloat16)
+    v = torch.randn(1, B, H, cap, D, generator=g).to(torch.bfloat16)
+    q = torch.randn(B, Hq, D, generator=g).to(torch.bfloat16)
+    kn, vn = (torch.randn(B, H, D, generator=g).to(torch.bfloat16) for _ in range(2))
+    unused = torch.arange(cap)[None, None, None] >= n[..., None]
+    k[unused], v[unused] = float("nan"), float("nan")
+
+    def check(out, lse, kk, vv, m, what):
+        for b in range(B):
+            for h in range(H):
+                rows, got = int(m[0, b, h]), out[b].view(H, -1, D)[h].cpu().double()
+                if rows == 0:
+                    assert (got == 0).all() and torch.isneginf(lse[b].view(H, -1)[h]).all(), (what, b, h)
+                    continue
+                s = q[b].double().view(H, -1, D)[h] @ kk[0, b, h, :rows].double().t() * scale
+                assert (got - torch.softmax(s, -1) @ vv[0, b, h, :rows].double()).abs().max() <= TOL, (what, b, h, rows)
+                assert (lse[b].view(H, -1)[h].cpu().double() - torch.logsumexp(s, -1)).abs().max() <= 2e-5, (what, b, h, rows)
+
+    out, lse = torch.zeros(B, Hq, D, device="cuda"), torch.zeros(B, Hq, device="cuda")
+    c = ngc.Cache(k.cuda(), v.cuda(), n.cuda(), None, Hq)
+    ws = ngc.allocate_workspace(c, 1)
+    print(f"[decode-edges] early B={B} hint={hint} D={D}", flush=True)
+    ngc.ngc_decode_attn(c, 0, q.cuda(), scale, hint, out, ws, lse_out=lse)
+    check(out, lse, k, v, n, "attn")
+    ngc.ngc_decode_step(c, 0, kn.cuda(), vn.cuda(), None, q.cuda(), scale, hint, out, ws, lse_out=lse)
+    grown = torch.minimum(n + 1, torch.tensor(cap, dtype=torch.int32))
+    assert torch.equal(c.len.cpu(), grown)
+    k2, v2 = k.clone(), v.clone()
+    for b in range(B):
+        for h in range(H):
+            if n[0, b, h] < cap:
+                k2[0, b, h, n[0, b, h]], v2[0, b, h, n[0, b, h]] = kn[b, h], vn[b, h]
+    check(out, lse, k2, v2, grown, "step")
+    assert ngc.read_status(ws)[:4] == [0, 0, int((n == 0).sum()), int((n == cap).sum())]
+
+    pages = (cap + 31) // 32
+    table = torch.randperm(B * H * pages, generator=g).to(torch.int32).view(1, B, H, pages)
+    pad = torch.full((1, B, H, pages * 32, D), float("nan"), dtype=torch.bfloat16)
+    pools = []
+    for x in (k, v):
+        p = pad.clone()
+        p[:, :, :, :cap] = x
+        pool = torch.empty(B * H * pages, 32, D, dtype=torch.bfloat16)
+        pool[table.flatten().long()] = p.view(-1, 32, D)
+        pools.append(pool.cuda())
+    stale = torch.arange(pages)[None, None, None] * 32 >= n[..., None]
+    table[stale] = 1 << 30
+    pc = ngc.PagedCache(pools[0], pools[1], None, table.cuda(), n.cuda(), torch.zeros(B * H * pages, dtype=torch.int32).cuda(),
+                        torch.zeros(1, dtype=torch.int32).cuda(), Hq)
+    print(f"[decode-edges] early paged B={B} hint={hint} D={D}", flush=True)
+    ngc.ngc_paged_decode_attn(pc, 0, q.cuda(), scale, hint, out, ngc.allocate_paged_workspace(pc), lse_out=lse)
+    check(out, lse, k, v, n, "paged")
