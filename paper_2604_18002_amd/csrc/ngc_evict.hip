@@ -1221,31 +1221,65 @@ int resident_workgroups(const void *fn, int threads, size_t lds, int items)
     return (int)(slots < items ? slots : items);
 }
 
-// Eq. 2 and its gradient: how much of a row is held in LDS (an upper bound on the items of a segment that keeps to its
-// own row; a longer one takes the general route), and the workgroup that holds a row's picks in registers.  A
-// workgroup has no more threads than its row keeps busy.  Microseconds for two rounds of Eq. 2 and its gradient:
-// 2048 segments of 700-1400 items 53 with 256 threads, 67 with 512; of 1000-2000 items 69 and 76; 3584 segments of
-// 2150-3789 items 174 with 256 threads, 163 with 512, 386 with 1024.
+// Eq. 2 and its gradient: the workgroup of a segment and how much of its row it holds in LDS.  The host knows the stride
+// of the rows (no row that keeps to its own is longer), an upper bound on the picks, and the number of segments; a row or
+// a sequence too long for the choice takes the general route.
+//   - Strides up to 8192: by the stride.  Two rounds of Eq. 2 and its gradient, us: 2048 segments of 700-1400 items 53
+//     with 256 threads, 67 with 512; of 1000-2000 items 69 and 76; 3584 segments of 2150-3789 items 174 with 256 threads,
+//     163 with 512.
+//   - Strides up to 16384, as in a cache of that capacity: the rows in it are often far shorter, and with a whole stride in
+//     LDS only two workgroups share a CU, so the picks decide.  Eq. 2 / gradient at a stride of 16384, us (one of 512
+//     threads on the general route alone, then threads x picks per thread):
+//         segments x items, picks       general     256 x 4/8     512 x 8/16    1024 x 16
+//         3584 x 150-300,    240       21.7 / 24.6  19.4 / 24.4   22.7 / 28.8       -
+//         2048 x 700-1400,   1120      19.5 / 26.5  18.2 / 23.9   17.1 / 22.8   37.8 / 49.2
+//         896 x 12000-16000, 1919      40.6 / 85.3  34.0 / 48.5   24.1 / 35.6   33.3 / 48.6
+//         3584 x 2150-3789,  3144      58.5 / 97        -         39.3 / 53.1   76.8 / 104
+//         896 x 6000-7000,   5599      38.6 / 92        -         21.0 / 28.7   29.2 / 40.6
+//         16 x 12000-16000,  7128      26.6 / 40.8      -         12.7 / 17.3   11.3 / 14.6
+//     Up to 2048 picks 256 threads are never the slowest; up to 512 segments, all resident at once, the larger
+//     workgroup is faster: it works through a row in fewer steps.
+//   - Longer strides, or one row for all segments (stride 0): rows may be longer than any LDS row or far shorter (blocks of
+//     rows as items).  LOGPROB_ROW_OF_FOUR items leave room for four workgroups of 512 threads, what the general route
+//     wants: 896 x 18000-20000 items, 1999 picks: 49 / 110 us, with 16384 items in LDS 73 / 125 (1024 threads 67 / 106);
+//     3584 x 2150-3789: 33 / 44 and 77 / 104.  Beyond 4096 picks the gradient's general route takes 1024 threads
+//     (5999 picks: 161 us, 220 with 512), Eq. 2 does not (87 and 85).
 constexpr int LOGPROB_MAX_ROW = 16384;
-
-int row_capacity(int64_t logit_stride)
-{
-    const int64_t r = logit_stride < LOGPROB_MAX_ROW ? logit_stride : LOGPROB_MAX_ROW;
-    return (int)((r + 3) & ~(int64_t)3);
-}
+constexpr int LOGPROB_ROW_OF_FOUR = 8064;
+constexpr int LOGPROB_FEW = 512;
 
 struct LogprobShape {
-    int threads, picks;
+    int threads, picks, row_cap;
 };
 
-LogprobShape logprob_shape(int row_cap)
+LogprobShape logprob_shape(int64_t stride, int64_t most_picks, int nseg, bool gradient)
 {
-    if (row_cap <= 1024) return {256, 4};
-    if (row_cap <= 2048) return {256, 8};
-    if (row_cap <= 4096) return {512, 8};
-    if (row_cap <= 8192) return {512, 16};
-    return {1024, 16};
+    if (stride <= 0 || stride > LOGPROB_MAX_ROW) {
+        if (most_picks <= 4096) return {512, 8, LOGPROB_ROW_OF_FOUR};
+        if (most_picks <= 8192 && !gradient) return {512, 16, LOGPROB_ROW_OF_FOUR};
+        return {1024, 16, LOGPROB_MAX_ROW};
+    }
+    const int row_cap = (int)((stride + 3) & ~(int64_t)3);
+    most_picks = most_picks < stride ? most_picks : stride;
+    if (row_cap <= 1024) return {256, 4, row_cap};
+    if (row_cap <= 2048) return {256, 8, row_cap};
+    if (row_cap <= 8192) return {512, most_picks <= 4096 ? 8 : 16, row_cap};
+    if (nseg > LOGPROB_FEW) {
+        if (most_picks <= 1024) return {256, 4, row_cap};
+        if (most_picks <= 2048) return {256, 8, row_cap};
+    }
+    if (most_picks <= 4096) return {512, 8, row_cap};
+    if (most_picks <= 8192 && nseg > LOGPROB_FEW) return {512, 16, row_cap};
+    return {1024, 16, row_cap};
 }
+
+// One of the five instantiations of a kernel by its workgroup.
+#define NGC_PICK_SHAPE(KERNEL, shape) \
+    ((shape).picks == 4       ? reinterpret_cast<const void *>(&KERNEL<256, 4>) \
+     : (shape).threads == 256 ? reinterpret_cast<const void *>(&KERNEL<256, 8>) \
+     : (shape).picks == 8     ? reinterpret_cast<const void *>(&KERNEL<512, 8>) \
+     : (shape).threads == 512 ? reinterpret_cast<const void *>(&KERNEL<512, 16>) \
+                              : reinterpret_cast<const void *>(&KERNEL<1024, 16>))
 
 }  // namespace
 
@@ -1392,16 +1426,12 @@ extern "C" int ngc_subset_logprob(const float *logits, const int32_t *n_items,
     if (ws_bytes < STATUS_BYTES) return NGC_ENOSPC;
     if (nseg == 0) return NGC_OK;
     const int stage_cap = sigma_stride < 16384 ? sigma_stride : 16384;     // at most 64 KB of LDS
-    const int row_cap = row_capacity(logit_stride);
+    // (sigma_stride 0: one sequence for all segments, of any length)
+    const LogprobShape shape = logprob_shape(logit_stride, sigma_stride > 0 ? sigma_stride : 65536, nseg, false);
     LogprobArgs la{logits, n_items, sigma, keep, logp_out, reinterpret_cast<int32_t *>(ws),
-                   logit_stride, sigma_stride, stage_cap, row_cap};
-    const size_t lds = (size_t)(stage_cap > row_cap ? stage_cap : row_cap) * sizeof(float);
-    const LogprobShape shape = logprob_shape(row_cap);
-    const void *fn = shape.picks == 4       ? reinterpret_cast<const void *>(&subset_logprob_kernel<256, 4>)
-                     : shape.threads == 256 ? reinterpret_cast<const void *>(&subset_logprob_kernel<256, 8>)
-                     : shape.picks == 8     ? reinterpret_cast<const void *>(&subset_logprob_kernel<512, 8>)
-                     : shape.threads == 512 ? reinterpret_cast<const void *>(&subset_logprob_kernel<512, 16>)
-                                            : reinterpret_cast<const void *>(&subset_logprob_kernel<1024, 16>);
+                   logit_stride, sigma_stride, stage_cap, shape.row_cap};
+    const size_t lds = (size_t)(stage_cap > shape.row_cap ? stage_cap : shape.row_cap) * sizeof(float);
+    const void *fn = NGC_PICK_SHAPE(subset_logprob_kernel, shape);
     if (lds > 48 * 1024)
         NGC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     void *kargs[] = {&la};
@@ -1420,16 +1450,11 @@ extern "C" int ngc_subset_logprob_backward(const float *logits, const int32_t *n
     if (ws_bytes < STATUS_BYTES) return NGC_ENOSPC;
     if (max_keep > 32768) return NGC_EUNSUPPORTED;
     if (nseg == 0) return NGC_OK;
-    const int row_cap = row_capacity(logit_stride);
+    const LogprobShape shape = logprob_shape(logit_stride, max_keep, nseg, true);
     LogprobBwdArgs la{logits, n_items, sigma, keep, gout, grad_out, reinterpret_cast<int32_t *>(ws),
-                      logit_stride, sigma_stride, max_keep, row_cap};
-    const size_t lds = (size_t)(max_keep > row_cap ? max_keep : row_cap) * sizeof(float);
-    const LogprobShape shape = logprob_shape(row_cap);
-    const void *fn = shape.picks == 4       ? reinterpret_cast<const void *>(&subset_logprob_backward_kernel<256, 4>)
-                     : shape.threads == 256 ? reinterpret_cast<const void *>(&subset_logprob_backward_kernel<256, 8>)
-                     : shape.picks == 8     ? reinterpret_cast<const void *>(&subset_logprob_backward_kernel<512, 8>)
-                     : shape.threads == 512 ? reinterpret_cast<const void *>(&subset_logprob_backward_kernel<512, 16>)
-                                            : reinterpret_cast<const void *>(&subset_logprob_backward_kernel<1024, 16>);
+                      logit_stride, sigma_stride, max_keep, shape.row_cap};
+    const size_t lds = (size_t)(max_keep > shape.row_cap ? max_keep : shape.row_cap) * sizeof(float);
+    const void *fn = NGC_PICK_SHAPE(subset_logprob_backward_kernel, shape);
     if (lds > 48 * 1024)
         NGC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     void *kargs[] = {&la};

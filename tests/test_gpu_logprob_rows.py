@@ -1,5 +1,5 @@
 """Eq. 2 for given actions and its gradient at the edges of the route that holds a segment's row in LDS: row capacities
-where the workgroup changes (1024, 2048, 4096, 8192, 16384 items), the first length beyond the largest, rows that are
+where the workgroup changes (1024, 2048, 8192, 16384 items), the pick bounds where it changes, the first length beyond the largest, rows that are
 not 16-byte aligned, keep counts from one pick to all, masked entries, and segments that need the wide-range route in
 between.  Against the fp64 oracle: log-probability 1e-4 relative, gradient 1e-4 of an entry plus 2e-6."""
 import numpy as np
@@ -106,3 +106,57 @@ def test_repeated_and_outlying_picks_are_counted_and_rows_may_be_shared():
     assert ngc.read_status(ws)[ngc.STATUS_BAD_SIGMA] == 2
     assert float(out[0]) == pytest.approx(oracle_logprob(x, sg[0]), rel=1e-4)
     assert bool(torch.isfinite(out).all())
+
+
+@pytest.mark.parametrize("stride,kmax,nseg", [(16384, 1024, 513), (16384, 1025, 513), (16384, 2049, 513), (16384, 4097, 513),
+                                              (16384, 4096, 512), (16384, 8193, 513), (8193, 1024, 513), (8192, 4097, 3),
+                                              (16385, 4096, 3), (16388, 4097, 3), (16385, 8193, 3), (40000, 2048, 3),
+                                              (0, 2048, 3), (0, 5000, 3)])
+def test_workgroups_chosen_by_the_picks(stride, kmax, nseg):
+    """Either side of every bound that decides about the workgroup beside the stride: picks and number of segments.  All
+    segments but the last three are empty; of those, one fills the bound, one is short, one is as long as the stride (or, in
+    longer strides, one item longer than what is held of a row in LDS)."""
+    import torch
+    ngc = _ngc()
+    rng = np.random.default_rng(stride + kmax)
+    width = stride or 9000
+    longest = width if stride and stride <= 16384 else 8065
+    n_items, keep = np.zeros(nseg, np.int32), np.zeros(nseg, np.int32)
+    n_items[-3:] = (min(width, kmax + 5), 37, longest) if stride else (8065, 8065, 8065)
+    keep[-3:] = (min(kmax, n_items[-3]), 30, min(kmax, longest) - 1)
+    logits = np.full((nseg if stride else 1, width), np.nan, np.float32)
+    sigma = np.zeros((nseg, kmax), np.int32)
+    row = lambda s: logits[s if stride else 0]
+    for s in range(nseg - 3, nseg):
+        if stride or s == nseg - 3:
+            row(s)[:n_items[s]] = rng.standard_normal(n_items[s]).astype(np.float32)
+        sigma[s, :keep[s]] = rng.permutation(n_items[s])[:keep[s]]
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    x, d_n, d_s, d_k, out = d(logits), d(n_items), d(sigma), d(keep), torch.full((nseg,), float("nan"), device="cuda")
+    gout = rng.standard_normal(nseg).astype(np.float32)
+    ws = torch.zeros(ngc.STATUS_WORDS * 4, dtype=torch.uint8, device="cuda")
+    print(f"[logprob-rows] stride={stride} kmax={kmax} nseg={nseg}", flush=True)
+    ngc.ngc_subset_logprob(x, d_n, d_s, d_k, nseg, stride, kmax, out, ws)
+    lp = out.cpu().numpy()
+    assert (lp[:-3] == 0).all()
+    for s in range(nseg - 3, nseg):
+        assert lp[s] == pytest.approx(oracle_logprob(row(s)[:n_items[s]], sigma[s, :keep[s]]), rel=1e-4, abs=1e-5), s
+    if stride:
+        grad = torch.full((nseg, stride), float("nan"), device="cuda")
+        ngc.ngc_subset_logprob_backward(x, d_n, d_s, d_k, nseg, stride, kmax, kmax, d(gout), grad, ws)
+        g = grad.cpu().numpy()
+        assert np.isnan(g[:-3]).all()
+        for s in range(nseg - 3, nseg):
+            n, k = int(n_items[s]), int(keep[s])
+            # the oracle's gradient is term by term; its cumulative form in fp64 serves where that takes too long
+            if n * k <= 3_000_000:
+                want = orc.logprob_grad(logits[s, :n], sigma[s, :k])
+            else:
+                e = np.exp(logits[s, :n].astype(np.float64) - logits[s, :n].max())
+                picked = e[sigma[s, :k]]
+                inv = np.cumsum(1.0 / (e.sum() - np.concatenate([[0.0], np.cumsum(picked)[:-1]])))
+                want = -e * inv[-1]
+                want[sigma[s, :k]] = 1.0 - picked * inv
+            assert np.all(np.abs(g[s, :n] - gout[s] * want) <= 1e-4 * np.abs(gout[s] * want) + 2e-6 * max(1.0, abs(gout[s]))), (s, n, k)
+            assert np.isnan(g[s, n:]).all()
+    assert all(v == 0 for v in ngc.read_status(ws))
