@@ -45,14 +45,10 @@ constexpr int RP_MT = 32;                    // keys per step of the math (and p
 constexpr float RP_M_INIT = -1.0e30f;
 constexpr float RP_LAZY = 8.0f;
 
-// RP_MT consecutive keys of a list: the first and the last of them and the smallest death position among them
-// (8 bytes, read as one word: first in the lowest 16 bits, min_death in the upper half).  `last` is beyond every key for
-// the list's last step if it has fewer keys: such a step needs the mask.
-constexpr uint16_t STEP_PARTIAL = 0xFFFF;    // T <= 65535
-struct StepInfo {
-    uint16_t first, last;
-    int32_t min_death;
-};
+// What the waves of a query tile have to know about RP_MT consecutive keys of its list, in terms of the wave index:
+// waves below `after` have all their queries before the first of these keys; waves from `from` to `until` - 1 see all of
+// the keys with all of their queries.  One word: after in the lowest byte, then from, then until.
+constexpr uint32_t step_word(uint32_t after, uint32_t from, uint32_t until) { return after | from << 8 | until << 16; }
 
 struct ReplayArgs {
     const unsigned char *q;    // bf16 [B][T][Hq][D]
@@ -61,7 +57,7 @@ struct ReplayArgs {
     const int32_t *death;      // [B][Hd][T]
     uint16_t *klist;           // [B*Hd][nqt][T] visible keys per query tile, ascending
     int32_t *kcount;           // [B*Hd][nqt]
-    StepInfo *steps;           // [B*Hd][nqt][ceil(T/32)] what a wave has to know about each RP_MT keys of a list
+    uint32_t *steps;           // [B*Hd][nqt][ceil(T/32)] what the waves have to know about each RP_MT keys of a list
     float *out;                // fp32 [B][T][Hq][D]
     int B, T, Hq, Hkv, Hd;     // Hd = Hkv (a death row per KV head) or 1 (shared by the heads)
     float scale_log2e;
@@ -77,6 +73,7 @@ constexpr int LIST_BITS = 16;
 constexpr int LIST_PASS = LIST_THREADS * LIST_BITS;
 constexpr int LIST_WAVES = LIST_THREADS / NGC_WAVE;
 constexpr int LIST_MAX_STEPS = 65536 / RP_MT;
+constexpr uint16_t NO_KEY = 0xFFFF;          // beyond every key (T <= 65535): a last step of fewer keys needs the mask
 
 __global__ __launch_bounds__(LIST_THREADS) void replay_lists_kernel(ReplayArgs a)
 {
@@ -94,7 +91,7 @@ __global__ __launch_bounds__(LIST_THREADS) void replay_lists_kernel(ReplayArgs a
     uint16_t *klist = a.klist + ((size_t)row * nqt + qt) * T;
     for (int s = tid; s * RP_MT <= last_pos; s += LIST_THREADS) {
         min_death[s] = 0x7FFFFFFF;
-        last_key[s] = STEP_PARTIAL;
+        last_key[s] = NO_KEY;
     }
     int n_list = 0;
     for (int j0 = 0; j0 <= last_pos; j0 += LIST_PASS) {
@@ -129,8 +126,20 @@ __global__ __launch_bounds__(LIST_THREADS) void replay_lists_kernel(ReplayArgs a
         __syncthreads();
     }
     if (tid == 0) a.kcount[(size_t)row * nqt + qt] = n_list;
-    StepInfo *steps = a.steps + ((size_t)row * nqt + qt) * ((T + RP_MT - 1) / RP_MT);
-    for (int s = tid; s * RP_MT < n_list; s += LIST_THREADS) steps[s] = StepInfo{first_key[s], last_key[s], min_death[s]};
+    uint32_t *steps = a.steps + ((size_t)row * nqt + qt) * ((T + RP_MT - 1) / RP_MT);
+    for (int s = tid; s * RP_MT < n_list; s += LIST_THREADS) {
+        const int first = first_key[s], last = last_key[s], lives_until = min_death[s];
+        int after = 0, from = 0, until = 0;
+#pragma unroll
+        for (int w = 0; w < RP_WAVES; ++w) {
+            const int q0 = i0 + w * RP_QW;                                   // the wave's first query and its last real one
+            const int q1 = q0 + RP_QW - 1 < T - 1 ? q0 + RP_QW - 1 : T - 1;
+            after += first > q1;
+            from += last > q0;
+            until += lives_until > q1;
+        }
+        steps[s] = step_word(after, from, until);
+    }
 }
 
 template <int D>
@@ -177,7 +186,7 @@ void replay_attn_kernel(ReplayArgs a)
     const unsigned char *vbase = a.v + ((size_t)b * T * a.Hkv + hkv) * ROW_BYTES;
     const size_t list = ((size_t)b * a.Hd + hd) * nqt + qt;
     const uint16_t *klist = a.klist + list * T;
-    const StepInfo *info = a.steps + list * ((T + RP_MT - 1) / RP_MT);
+    const uint32_t *info = a.steps + list * ((T + RP_MT - 1) / RP_MT);
     const int n_list = a.kcount[list];
     const int t_end = (n_list + RP_KT - 1) / RP_KT;
 
@@ -235,7 +244,7 @@ void replay_attn_kernel(ReplayArgs a)
     };
     // scalar loads: wave-uniform, from memory an earlier launch wrote
     struct TileInfo {
-        uint64_t step[STEPS];
+        uint32_t step[STEPS];
     };
     const int last_step = (T + RP_MT - 1) / RP_MT - 1;
     auto load_info = [&](int t) {
@@ -243,7 +252,7 @@ void replay_attn_kernel(ReplayArgs a)
 #pragma unroll
         for (int st = 0; st < STEPS; ++st) {
             const int at = t * STEPS + st;
-            ti.step[st] = reinterpret_cast<const __attribute__((address_space(4))) uint64_t *>(
+            ti.step[st] = reinterpret_cast<const __attribute__((address_space(4))) uint32_t *>(
                 (uintptr_t)info)[at < last_step ? at : last_step];
         }
         return ti;
@@ -254,8 +263,7 @@ void replay_attn_kernel(ReplayArgs a)
     load_idx(0, ix_a);
 
     // ---- query operands: 32 positions per wave, lane % 32 = position ----------
-    const int wave_q0 = i0 + wv * RP_QW;                                               // first query position of this wave
-    const int wave_q1 = (wave_q0 + RP_QW - 1 < T - 1) ? wave_q0 + RP_QW - 1 : T - 1;   // last real one
+    const int wave_q0 = i0 + wv * RP_QW;               // first query position of this wave
     const int qpos = wave_q0 + li;
     bf16x8 qop[KCH];
     {
@@ -380,12 +388,10 @@ void replay_attn_kernel(ReplayArgs a)
         for (int st = 0; st < STEPS; ++st) {
             const int at = t * STEPS + st;
             if (at * RP_MT >= n_list) break;
-            const int first = (int)(ti.step[st] & 0xFFFFu), last = (int)((ti.step[st] >> 16) & 0xFFFFu);
-            const int min_death = (int)(ti.step[st] >> 32);
-            // the list ascends: if the first of these keys is after this wave's last query, so are all
-            if (first > wave_q1) break;
-            // A step whose keys all precede this wave's first query and all outlive its last one needs no mask.
-            const bool full = last <= wave_q0 && min_death > wave_q1;
+            const int after = (int)(ti.step[st] & 0xFFu), from = (int)((ti.step[st] >> 8) & 0xFFu);
+            const int until = (int)(ti.step[st] >> 16);
+            if (wv < after) break;                                 // the list ascends: all later keys come after them too
+            const bool full = wv >= from && wv < until;            // no mask
             compute_step(lk + st * RP_MT * ROW_BYTES, lv + st * RP_MT * ROW_BYTES, &lds_death[buf][st * RP_MT],
                          &lds_kidx[buf][st * RP_MT], full);
         }
@@ -470,7 +476,7 @@ extern "C" size_t ngc_replay_workspace_bytes(int32_t B, int32_t T, int32_t Hkv)
     size_t counts = (size_t)B * Hkv * nqt * sizeof(int32_t);
     counts = (counts + 255) & ~(size_t)255;
     const size_t tiles_max = (size_t)(T + RP_MT - 1) / RP_MT;
-    return 256 + lists + counts + (size_t)B * Hkv * nqt * tiles_max * sizeof(StepInfo);
+    return 256 + lists + counts + (size_t)B * Hkv * nqt * tiles_max * sizeof(uint32_t);
 }
 
 extern "C" int ngc_replay_attn(const void *q, const void *k, const void *v, const int32_t *death,
@@ -505,7 +511,7 @@ extern "C" int ngc_replay_attn(const void *q, const void *k, const void *v, cons
     ra.kcount = reinterpret_cast<int32_t *>(reinterpret_cast<unsigned char *>(ws) + 256 + lists);
     size_t counts = (size_t)B * ra.Hd * nqt * sizeof(int32_t);
     counts = (counts + 255) & ~(size_t)255;
-    ra.steps = reinterpret_cast<StepInfo *>(reinterpret_cast<unsigned char *>(ws) + 256 + lists + counts);
+    ra.steps = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(ws) + 256 + lists + counts);
     hipLaunchKernelGGL(replay_lists_kernel, dim3(nqt, B * ra.Hd), dim3(LIST_THREADS), 0, st, ra);
     NGC_HIP_CHECK(hipGetLastError());
     if (D == 128)

@@ -218,3 +218,13 @@ def test_missing_library_is_an_error_not_a_fallback(tmp_path):
     from paper_2604_18002_amd import binding
     with pytest.raises(RuntimeError, match="missing"):
         binding.load_library(str(tmp_path / "no_such_libngc.so"))
+
+
+@pytest.mark.parametrize("B,T,H", [(1, 1, 1), (1, 32, 1), (2, 33, 3), (16, 1050, 2), (8, 4096, 4), (3, 65535, 2)])
+def test_replay_workspace_is_what_callers_already_have(B, T, H):
+    """A workspace that was sized once stays large enough: key lists (2 bytes a key and query tile), their lengths, and four
+    bytes per 32 keys of a list."""
+    tiles, up = (T + 127) // 128, lambda x: (x + 255) // 256 * 256
+    lists, counts, steps = 2 * B * H * tiles * T, 4 * B * H * tiles, 4 * B * H * tiles * ((T + 31) // 32)
+    from paper_2604_18002_amd import binding
+    assert binding.ngc_replay_workspace_bytes(B, T, H) == 256 + up(lists) + up(counts) + steps
