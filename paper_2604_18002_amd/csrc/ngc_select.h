@@ -449,8 +449,11 @@ __device__ __forceinline__ uint16_t *sort_by_code_desc(CodeOf code_of, int K, ui
 //   bucketed   u16[N] scratch;  order   u16[K] out: the kept items by descending code, equal codes by ascending index
 //   kept_bits  one bit per item, zeroed by the caller (before a barrier), out: which items are kept
 //   hist       NB zeroed entries (before a barrier);  tmp  4 * waves entries
-// Returns false (workgroup-uniform) if a bucket holds more than BUCKET_LIMIT items (many equal keys): nothing but hist,
-// bucketed and tmp has been written then.  Whole workgroup; ends on a barrier.
+// Masked items stay out of the buckets: they rank behind all others.  Returns false (workgroup-uniform) if a bucket holds
+// more than BUCKET_LIMIT items (many equal keys) or if masked items are kept: nothing but hist, bucketed and tmp has been
+// written then.  Whole workgroup; ends on a barrier.
+constexpr uint32_t CODE_MASKED = 0x007FFFFFu;   // of -inf, below every other
+
 template <int THREADS>
 __device__ __forceinline__ bool rank_items(const uint32_t *code, int N, int K, uint32_t cmax, uint32_t cmin, uint32_t *hist,
                                            uint32_t *tmp, uint16_t *bucketed, uint16_t *order, uint32_t *kept_bits)
@@ -466,10 +469,13 @@ __device__ __forceinline__ bool rank_items(const uint32_t *code, int N, int K, u
     const float per_value = (float)(NB - 1) / width;
     // a non-increasing function of the key in IEEE arithmetic: a larger key never lands in a later bucket
     auto bucket_of = [&](uint32_t c) -> uint32_t {
-        const float x = (kmax - code_to_float(c)) * per_value;     // >= 0; +inf for a masked key
+        const float x = (kmax - code_to_float(c)) * per_value;     // >= 0
         return (uint32_t)fminf(x, (float)(NB - 1));
     };
-    for (int t = tid; t < N; t += THREADS) atomicAdd(&hist[bucket_of(code[t])], 1u);
+    for (int t = tid; t < N; t += THREADS) {
+        const uint32_t c = code[t];
+        if (c > CODE_MASKED) atomicAdd(&hist[bucket_of(c)], 1u);
+    }
     __syncthreads();
     u32x4 mine[PER / 4];
     uint32_t sum = 0, biggest = 0;
@@ -486,13 +492,14 @@ __device__ __forceinline__ bool rank_items(const uint32_t *code, int N, int K, u
     biggest = wave_reduce(biggest, OpMaxU{});
     if (lane_id() == NGC_WAVE - 1) { tmp[2 * wave_id()] = upto; tmp[2 * wave_id() + 1] = biggest; }
     __syncthreads();
-    uint32_t run = upto - sum;
+    uint32_t run = upto - sum, unmasked = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
         if (w < wave_id()) run += tmp[2 * w];
+        unmasked += tmp[2 * w];
         biggest = tmp[2 * w + 1] > biggest ? tmp[2 * w + 1] : biggest;
     }
-    if (biggest > (uint32_t)BUCKET_LIMIT) return false;
+    if (biggest > (uint32_t)BUCKET_LIMIT || (uint32_t)K > unmasked) return false;
 #pragma unroll
     for (int i = 0; i < PER / 4; ++i) {
         u32x4 start;
@@ -506,11 +513,13 @@ __device__ __forceinline__ bool rank_items(const uint32_t *code, int N, int K, u
     __syncthreads();
     // unordered scatter: afterwards hist[b] is the END of bucket b (and the start of bucket b + 1)
     for (int t = tid; t < N; t += THREADS) {
-        const uint32_t pos = atomicAdd(&hist[bucket_of(code[t])], 1u);
+        const uint32_t c = code[t];
+        if (c <= CODE_MASKED) continue;
+        const uint32_t pos = atomicAdd(&hist[bucket_of(c)], 1u);
         bucketed[pos] = (uint16_t)t;
     }
     __syncthreads();
-    for (int p = tid; p < N; p += THREADS) {
+    for (int p = tid; p < (int)unmasked; p += THREADS) {
         const uint32_t h = bucketed[p];
         const uint32_t c = code[h];
         const uint32_t b = bucket_of(c);
@@ -641,7 +650,6 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
     // ---- 1. keys ----------------------------------------------------------
     float smax = -INFINITY, neg_smin = -INFINITY;   // over the unmasked entries (a NaN compares false everywhere)
     uint32_t cmax = 0, neg_cmin = 0;                // largest code; complement of the smallest code of a finite key
-    constexpr uint32_t CODE_MASKED = 0x007FFFFFu;   // of -inf
     for (int quad = tid; 4 * quad < N; quad += THREADS) {
         float s[4], key[4];
         keys_of_quad(row, N, quad, a.na, l, b, h, s, key);

@@ -178,3 +178,48 @@ def test_selections_that_fill_the_lds(cap, max_keep, fits):
             assert float(logp[0, 0, h]) == pytest.approx(oracle_logprob(x[0, 0, h], want_s), rel=1e-4)
         assert c.len.flatten().tolist() == ([cap, cap] if flags else keeps.tolist())
         assert all(v == 0 for v in ngc.read_status(ws))
+
+
+@pytest.mark.parametrize("tau", [0.0, 1.0])
+@pytest.mark.parametrize("cap", [65, 200, 700, 2100, 8200])
+def test_masked_items_rank_behind_all_others(cap, tau):
+    """Many masked items (-inf and NaN), keep counts below, at and above the number of unmasked ones: the ranking by buckets
+    takes the first two, the others the rest; a single unmasked item, and none."""
+    import torch
+    ngc = _ngc()
+    rng = np.random.default_rng(cap)
+    shares = [0.3, 0.5, 0.5, 0.5, 0.9, 0.98, None, 1.0]         # masked share; None: one unmasked item
+    extra = [-1, -1, 0, 1, -1, 0, 0, 3]                         # keep count minus the unmasked ones
+    B = len(shares)
+    logits, lens = np.zeros((1, B, 1, cap), np.float32), np.full(B, cap, np.int32)
+    keeps = np.zeros(B, np.int32)
+    for b, share in enumerate(shares):
+        x = rng.standard_normal(cap).astype(np.float32)
+        x[rng.random(cap) < (1.0 if share is None else share)] = -np.inf
+        if share is None:
+            x[cap // 2] = 1.0
+        unmasked = int(np.isfinite(x).sum())
+        x[np.isinf(x) & (rng.random(cap) < 0.2)] = np.nan
+        logits[0, b, 0], keeps[b] = x, max(1, unmasked + extra[b])
+    mk = int(keeps.max())
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    c = ngc.Cache.allocate(1, B, 1, 1, 64, cap)
+    c.len.copy_(d(lens.reshape(1, B, 1)))
+    ws = ngc.allocate_workspace(c, mk)
+    kept = torch.full((1, B, 1, mk), -1, dtype=torch.int32, device="cuda")
+    sigma, logp = torch.full_like(kept, -1), torch.full((1, B, 1), float("nan"), device="cuda")
+    print(f"[select-routes] masked cap={cap} tau={tau}", flush=True)
+    ngc.ngc_evict(c, -1, d(logits), d(keeps.reshape(1, B, 1)), ngc.make_params(noise_scale=tau, seed=7, round=1), mk, kept,
+                  sigma, logp, ws)
+    torch.cuda.synchronize()
+    for b in range(B):
+        x, K = np.where(np.isnan(logits[0, b, 0]), np.float32(-np.inf), logits[0, b, 0]), int(keeps[b])
+        want_k, want_s = orc.evict_select(x, K, tau, 7, 1, 0, b, 0)
+        assert (kept[0, b, 0, :K].cpu().numpy() == want_k).all(), (b, K)
+        assert (sigma[0, b, 0, :K].cpu().numpy() == want_s).all(), (b, K)
+        got = float(logp[0, b, 0])
+        if np.isneginf(x[want_s]).any():
+            assert got == -np.inf, (b, K)
+        else:
+            assert got == pytest.approx(oracle_logprob(x, want_s), rel=1e-4, abs=1e-5), (b, K)
+    assert all(v == 0 for v in ngc.read_status(ws))
