@@ -52,6 +52,10 @@ class NgcError(RuntimeError):
         super().__init__(f"{where}: {strerror(code)} ({code})")
 
 
+class ArgumentError(C.ArgumentError, TypeError):
+    """An argument of the wrong type."""
+
+
 class ngc_cache(C.Structure):
     _fields_ = [("k", C.c_void_p), ("v", C.c_void_p), ("len", C.c_void_p), ("pos", C.c_void_p),
                 ("L", C.c_int32), ("B", C.c_int32), ("Hkv", C.c_int32), ("Hq", C.c_int32),
@@ -143,6 +147,8 @@ def load_library(path: Optional[str] = None) -> C.CDLL:
                                "there is no fallback path")
         from . import _ngc_host
         _ngc_host.open(path)
+        _ngc_host.types(ArgumentError, Cache.view, PagedCache.view, ngc_cache, ngc_paged_cache, ngc_evict_params,
+                        C._SimpleCData)
         _host = _ngc_host
         _lib = lib
     return lib
@@ -186,8 +192,12 @@ def _stream(stream) -> Optional[int]:
     if _current_raw_stream is None:
         import torch
         torch.cuda.current_stream()     # initialises the runtime (or says why it cannot)
-        get, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
-        _current_raw_stream = lambda: get(device())     # noqa: E731  (the current stream of the current device)
+        # the current stream of the current device, without the Stream object where torch has its own way to that
+        get, device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        if get and device:
+            _current_raw_stream = lambda: get(device())     # noqa: E731
+        else:
+            _current_raw_stream = lambda: torch.cuda.current_stream().cuda_stream     # noqa: E731
     return _current_raw_stream()
 
 

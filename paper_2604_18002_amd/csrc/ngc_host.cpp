@@ -3,7 +3,8 @@
 // The Python binding used ctypes for this: building an ngc_cache out of a dozen attribute reads and converting a dozen
 // arguments took ~6 us of the 8.5 us a decode step cost on the host, more than the kernel runs for a small cache.  Here
 // it takes ~1.5 us.  Marshalling only: no state is kept between calls, nothing is remembered about a tensor, and every
-// check is the C ABI's own (plus the contiguity the binding always asked for).
+// check is the C ABI's own (plus the contiguity the binding always asked for).  What it takes is what ctypes took: a cache
+// with a view() of its own is asked for it, a structure must be of its type, a number may be a ctypes one.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <dlfcn.h>
@@ -28,8 +29,16 @@ struct Entries {
 // attribute and method names, interned once
 struct Names {
     PyObject *k, *v, *len, *pos, *Hq, *k_pool, *v_pool, *pos_pool, *table, *free_stack, *free_count, *shape, *data_ptr,
-        *numel, *is_contiguous;
+        *numel, *is_contiguous, *view, *value;
 } names;
+
+// what types() was given: the binding's own classes and functions
+struct Types {
+    PyObject *argument_error;             // raised for an argument of the wrong type
+    PyObject *cache_view, *paged_view;    // Cache.view and PagedCache.view: what the front reads in their place
+    PyObject *cache, *paged, *params;     // the ctypes structures
+    PyObject *simple;                     // base of ctypes' numbers
+} types;
 
 struct Ref {   // a new reference, released at the end of the scope
     PyObject *o;
@@ -47,9 +56,33 @@ void *ptr(PyObject *t)
     const Ref r(PyObject_CallMethodNoArgs(t, names.data_ptr));
     return r.o ? PyLong_AsVoidPtr(r.o) : nullptr;
 }
-int64_t i64(PyObject *o) { return PyErr_Occurred() ? 0 : (int64_t)PyLong_AsUnsignedLongLongMask(o); }
+void wrong_type(PyObject *o, const char *wanted)
+{
+    PyErr_Clear();
+    PyErr_Format(types.argument_error ? types.argument_error : PyExc_TypeError, "%s expected instead of %s instance", wanted,
+                 Py_TYPE(o)->tp_name);
+}
+// Numbers as ctypes takes them: anything with __index__ (__float__), or a ctypes number.
+template <class T, class Read>
+T number(PyObject *o, const char *wanted, Read read)
+{
+    if (PyErr_Occurred()) return 0;
+    T x = (T)read(o);
+    if (x != (T)-1 || !PyErr_Occurred()) return x;
+    PyErr_Clear();
+    if (types.simple && PyObject_IsInstance(o, types.simple) == 1) {
+        const Ref v(PyObject_GetAttr(o, names.value));
+        if (v.o) {
+            x = (T)read(v.o);
+            if (x != (T)-1 || !PyErr_Occurred()) return x;
+        }
+    }
+    wrong_type(o, wanted);
+    return 0;
+}
+int64_t i64(PyObject *o) { return number<int64_t>(o, "int", PyLong_AsUnsignedLongLongMask); }
 int32_t i32(PyObject *o) { return (int32_t)i64(o); }
-float f32(PyObject *o) { return PyErr_Occurred() ? 0.f : (float)PyFloat_AsDouble(o); }
+float f32(PyObject *o) { return number<float>(o, "float", PyFloat_AsDouble); }
 size_t bytes(PyObject *t)   // elements of a uint8 workspace tensor
 {
     if (PyErr_Occurred()) return 0;
@@ -96,9 +129,37 @@ int32_t attr_i32(PyObject *o, PyObject *name)
     return v.o ? i32(v.o) : 0;
 }
 
+// Copies a ctypes structure; an object of another type raises.
+template <class T>
+void copy_struct(PyObject *o, PyObject *type, const char *wanted, T *to)
+{
+    const int is = type ? PyObject_IsInstance(o, type) : 1;
+    if (is < 0) return;
+    Py_buffer b;
+    if (!is || PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) return wrong_type(o, wanted);
+    if (b.len == (Py_ssize_t)sizeof(T)) __builtin_memcpy(to, b.buf, sizeof(T));
+    else wrong_type(o, wanted);
+    PyBuffer_Release(&b);
+}
+
+// Whether o.view() is the binding's own method, whose reading of the tensors is done here.  Anything else is called and
+// its structure copied.
+template <class T>
+bool own_view(PyObject *o, PyObject *own, PyObject *type, const char *wanted, T *v)
+{
+    if (PyErr_Occurred()) return false;
+    const Ref m(PyObject_GetAttr(o, names.view));
+    if (!m.o) return false;
+    if (PyMethod_Check(m.o) && PyMethod_GET_SELF(m.o) == o && PyMethod_GET_FUNCTION(m.o) == own) return true;
+    const Ref r(PyObject_CallNoArgs(m.o));
+    if (r.o) copy_struct(r.o, type, wanted, v);
+    return false;
+}
+
 ngc_cache cache_of(PyObject *c)
 {
     ngc_cache v{};
+    if (!own_view(c, types.cache_view, types.cache, "ngc_cache", &v)) return v;
     int32_t d[5] = {};
     sizes(c, names.k, d, 5);
     v.L = d[0]; v.B = d[1]; v.Hkv = d[2]; v.cap = d[3]; v.D = d[4];
@@ -113,6 +174,7 @@ ngc_cache cache_of(PyObject *c)
 ngc_paged_cache paged_of(PyObject *c)
 {
     ngc_paged_cache v{};
+    if (!own_view(c, types.paged_view, types.paged, "ngc_paged_cache", &v)) return v;
     int32_t d[3] = {}, t[4] = {};
     sizes(c, names.k_pool, d, 3);
     sizes(c, names.table, t, 4);
@@ -133,12 +195,7 @@ ngc_paged_cache paged_of(PyObject *c)
 ngc_evict_params params_of(PyObject *p)
 {
     ngc_evict_params v{};
-    if (PyErr_Occurred()) return v;
-    Py_buffer b;
-    if (PyObject_GetBuffer(p, &b, PyBUF_SIMPLE) != 0) return v;
-    if (b.len == (Py_ssize_t)sizeof(v)) __builtin_memcpy(&v, b.buf, sizeof(v));
-    else PyErr_SetString(PyExc_TypeError, "params must be an ngc_evict_params");
-    PyBuffer_Release(&b);
+    if (!PyErr_Occurred()) copy_struct(p, types.params, "ngc_evict_params", &v);
     return v;
 }
 
@@ -267,9 +324,20 @@ PyObject *open_(PyObject *, PyObject *path)
     Py_RETURN_NONE;
 }
 
+// types(ArgumentError, Cache.view, PagedCache.view, ngc_cache, ngc_paged_cache, ngc_evict_params, _SimpleCData)
+ENTRY(types, 7)
+    PyObject **const to[] = {&types.argument_error, &types.cache_view, &types.paged_view, &types.cache, &types.paged,
+                             &types.params, &types.simple};
+    for (int i = 0; i < 7; ++i) {
+        Py_INCREF(a[i]);
+        Py_XSETREF(*to[i], a[i]);
+    }
+    Py_RETURN_NONE;
+END
+
 #define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(&name##_)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
-    {"open", open_, METH_O, nullptr},
+    {"open", open_, METH_O, nullptr}, FAST(types),
     FAST(perturbed_keys), FAST(keep_counts), FAST(evict), FAST(subset_logprob), FAST(subset_logprob_backward), FAST(lmem),
     FAST(cache_append), FAST(decode_attn), FAST(decode_step), FAST(decode_attn_static), FAST(score_keys),
     FAST(replay_attn), FAST(paged_evict), FAST(paged_append), FAST(paged_decode_attn), FAST(paged_score_keys),
@@ -284,7 +352,8 @@ PyMODINIT_FUNC PyInit__ngc_host(void)
         {&names.k, "k"}, {&names.v, "v"}, {&names.len, "len"}, {&names.pos, "pos"}, {&names.Hq, "Hq"},
         {&names.k_pool, "k_pool"}, {&names.v_pool, "v_pool"}, {&names.pos_pool, "pos_pool"}, {&names.table, "table"},
         {&names.free_stack, "free_stack"}, {&names.free_count, "free_count"}, {&names.shape, "shape"},
-        {&names.data_ptr, "data_ptr"}, {&names.numel, "numel"}, {&names.is_contiguous, "is_contiguous"}};
+        {&names.data_ptr, "data_ptr"}, {&names.numel, "numel"}, {&names.is_contiguous, "is_contiguous"},
+        {&names.view, "view"}, {&names.value, "value"}};
     for (const auto &x : all)
         if (!(*x.at = PyUnicode_InternFromString(x.name))) return nullptr;
     return PyModule_Create(&module);

@@ -116,3 +116,69 @@ def test_a_forked_child_asks_torch_for_the_stream_again(monkeypatch):
     if pid == 0:
         os._exit(0 if binding._current_raw_stream is None else 1)
     assert os.waitpid(pid, 0)[1] == 0 and binding._current_raw_stream is not None
+
+
+def test_arguments_of_a_wrong_type_raise_what_ctypes_raises():
+    c = _cache()
+    q, out, ws = torch.zeros(3, 12, 128, dtype=torch.bfloat16), torch.zeros(3, 12, 128), torch.zeros(1 << 20, dtype=torch.uint8)
+    for layer, scale, hint in (("0", 0.1, 0), (0.0, 0.1, 0), (0, "0.1", 0), (0, None, 0), (0, 0.1, [1]), (C.c_char(b"0"), 0.1, 0)):
+        with pytest.raises(C.ArgumentError):
+            ngc.ngc_decode_attn(c, layer, q, scale, hint, out, ws, stream=0)
+    x, keep = torch.zeros(2, 3, 2, 64), torch.zeros(2, 3, 2, dtype=torch.int32)
+    kept = torch.zeros(2, 3, 2, 8, dtype=torch.int32)
+
+    class Other(C.Structure):
+        _fields_ = [("bytes", C.c_char * C.sizeof(ngc.ngc_evict_params))]
+    for params in (Other(), bytearray(C.sizeof(Other)), bytes(C.sizeof(Other)), None):
+        with pytest.raises((C.ArgumentError, TypeError)):
+            ngc.ngc_evict(c, 0, x, keep, params, 8, kept, None, None, ws, stream=0)
+
+    class Params(ngc.ngc_evict_params):
+        pass
+    assert _code(ngc.ngc_evict, c, 0, x, keep, Params(block=0), 8, kept, None, None, ws) == ngc.NGC_EINVAL
+    # numbers that ctypes takes: its own, and whatever has __index__ or __float__
+    for layer in (C.c_int32(2), torch.tensor(2), True + 1):
+        assert _code(ngc.ngc_decode_attn, c, layer, q, C.c_float(0.1), 0, out, ws) == ngc.NGC_EINVAL
+    assert _code(ngc.ngc_decode_attn, c, 0, q, C.c_float(float("nan")), 0, out, ws) == ngc.NGC_EINVAL
+
+
+def test_a_cache_with_a_view_of_its_own_is_asked_for_it():
+    q, out, ws = torch.zeros(3, 12, 128, dtype=torch.bfloat16), torch.zeros(3, 12, 128), torch.zeros(1 << 20, dtype=torch.uint8)
+    asked = []
+
+    class Narrow(ngc.Cache):
+        def view(self):
+            asked.append(1)
+            v = ngc.Cache.view(self)
+            v.D = 96                                         # a head size the library refuses
+            return v
+    c = _cache()
+    c = Narrow(c.k, c.v, c.len, c.pos, c.Hq)
+    assert _code(ngc.ngc_decode_attn, c, 0, q, 0.1, 0, out, ws) == ngc.NGC_EINVAL and asked == [1]
+
+    class Plain:                                             # nothing but a view
+        def __init__(self, v):
+            self.view = lambda: v
+    good = _cache()
+    assert _code(ngc.ngc_decode_attn, Plain(good.view()), 2, q, 0.1, 0, out, ws) == ngc.NGC_EINVAL      # no layer 2
+    assert _code(ngc.ngc_decode_attn, Plain(good.view()), 0, q, 0.1, 0, out, ws[:16]) == ngc.NGC_ENOSPC
+    with pytest.raises(C.ArgumentError):
+        ngc.ngc_decode_attn(Plain(ngc.make_params()), 0, q, 0.1, 0, out, ws, stream=0)
+    with pytest.raises(ZeroDivisionError):
+        ngc.ngc_decode_attn(type("Broken", (), {"view": lambda self: 1 // 0})(), 0, q, 0.1, 0, out, ws, stream=0)
+
+    class NarrowPaged(ngc.PagedCache):
+        def view(self):
+            v = ngc.PagedCache.view(self)
+            v.page_rows = 48
+            return v
+    pc = ngc.PagedCache.allocate(2, 3, 2, 12, 128, 32, 4, 40, device="cpu")
+    pc = NarrowPaged(pc.k_pool, pc.v_pool, pc.pos_pool, pc.table, pc.len, pc.free_stack, pc.free_count, pc.Hq)
+    assert _code(ngc.ngc_paged_decode_attn, pc, 0, q, 0.1, 0, out, ws) == ngc.NGC_EINVAL
+
+
+def test_the_stream_is_found_without_the_private_way_to_it(monkeypatch):
+    monkeypatch.setattr(ngc, "_current_raw_stream", None)
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 77})())
+    assert ngc._stream(None) == 77 and ngc._stream(None) == 77
