@@ -41,19 +41,19 @@
 // after every other one has read it.
 //
 // Which tiles a wave works on does not depend on the segment's length (tile t
-// belongs to wave t % 4 of workgroup (t / 4) % S), so in launches that fill no
-// more than the chip the first tile is requested before the length has arrived
-// (first_tile_early() has the rule and its figures).  Rows at or beyond the length are switched off when their
-// tile is computed (their scores by the mask, their V values by zeros: what lies
-// there is unspecified and may be NaN).
+// belongs to wave t % 4 of workgroup (t / 4) % S), so in small launches and in
+// those over long segments the first tile is requested before the length has
+// arrived (first_tile_early() has the rule and its figures).  Rows at or beyond
+// the length are switched off when their tile is computed (their scores by the
+// mask, their V values by zeros: what lies there is unspecified and may be NaN).
 //
 // What bounds a launch: at a few segments the chain of memory round trips (first
 // tile; then, if a segment is shared, partial -> ticket -> merge), at several
 // hundred the read rate of the memory.  Per layer, from a HIP graph, before ->
 // after the tiles were interleaved over the workgroups, the partials came in one
-// batch, the last tile lost its prefetch and small launches asked early: 2 segments x 2000 rows 8.2 -> 6.7 us,
-// 32 x 525 rows (8.6 MB) 9.1 -> 7.0 us, 128 x 1494 rows (98 MB) 22.0 -> 19.7 us,
-// 512 x 2700 rows (0.71 GB) 119 -> 117 us.
+// batch, the last tile lost its prefetch and the first was asked for early:
+// 2 segments x 2000 rows 8.2 -> 6.7 us, 32 x 525 rows (8.6 MB) 9.1 -> 7.0 us,
+// 128 x 1494 rows (98 MB) 22.0 -> 19.7 us, 512 x 2700 rows (0.71 GB) 119 -> 117 us.
 //
 // Paged layout (PAGED = true): a 32-row tile never straddles a page (pages hold
 // a power-of-two number of rows >= 32), so only the tile's base address changes:
@@ -167,6 +167,7 @@ void decode_kernel(AttnArgs a)
     const int G = a.G;
 
     const int n_raw = a.len[seg];
+    if constexpr (!EARLY) __builtin_amdgcn_sched_barrier(0);   // asked for before anything else: the tile waits for it
     const int h = seg % a.Hkv;
     const int lb = seg / a.Hkv - a.lb0;   // (layer * B + sequence) relative to q / out
     float *out_seg = a.out + ((size_t)lb * a.Hkv + h) * G * D;   // [G][D] of this KV head
@@ -225,8 +226,8 @@ void decode_kernel(AttnArgs a)
         }
     };
 
-    // Everything that does not need the length is requested first: the queries, the new row and, in launches that fill
-    // no more than the chip (EARLY), the first tile (its rows are clamped to the capacity only; paged: table entries
+    // Everything that does not need the length is requested first: the queries, the new row and, in small launches and
+    // those over long segments (EARLY), the first tile (its rows are clamped to the capacity only; paged: table entries
     // beyond the pages in use hold anything, which tile_base() turns into some page of the pool).
     u32x4 new_piece = {0u, 0u, 0u, 0u};      // lanes [0, K_PIECES) hold the new K row, the next K_PIECES the V row
     if constexpr (APPEND) {
@@ -242,10 +243,18 @@ void decode_kernel(AttnArgs a)
             qop[c] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(qrow + c * 64 + kg * 16));
     }
     u32x4 v_a[8], v_b[8];
+    const int cap_tile = (a.cap - 1) / ATT_TILE;
+    // Bases of the first tile and of the two after it.  Paged: looked up before they are needed, and without the length
+    // (a page that turns out not to be in use is not read from): with all three lookups after it 28.9 -> 29.9 us at 896
+    // segments of 350 rows.  (Small launches would rather have the first tile on its way than the others' bases.)
+    const size_t base0 = tile_base(tile, cap_tile);
+    size_t base1 = 0, base2 = 0;
+    if constexpr (!EARLY) {
+        base1 = tile_base(tile + step, cap_tile);
+        base2 = tile_base(tile + 2 * step, cap_tile);
+    }
     if constexpr (EARLY) {
-        const int cap_tile = (a.cap - 1) / ATT_TILE;
-        const int t0 = tile < cap_tile ? tile : cap_tile;
-        issue_loads(t0, a.cap - 1, tile_base(t0, cap_tile), v_a);
+        issue_loads(tile < cap_tile ? tile : cap_tile, a.cap - 1, base0, v_a);
         __asm__ volatile("" ::: "memory");   // the requests stay in front of everything that waits for the length
     }
 
@@ -484,10 +493,11 @@ void decode_kernel(AttnArgs a)
     }
 
     if constexpr (!EARLY) {
-        if (tile < tiles) issue_loads(tile, last_row, tile_base(tile, tiles - 1), v_a);
+        if (tile < tiles) issue_loads(tile, last_row, base0, v_a);
+    } else {
+        base1 = tile_base(tile + step, tiles - 1);
+        base2 = tile_base(tile + 2 * step, tiles - 1);
     }
-    // bases of the next tile and of the one after it (paged: looked up before they are needed)
-    size_t base1 = tile_base(tile + step, tiles - 1), base2 = tile_base(tile + 2 * step, tiles - 1);
     bool staged = false;
     while (tile + step < tiles) {
         stage_k();
@@ -660,11 +670,14 @@ int splits_for(int nseg_launch, int max_len, int row_bytes)
 //        1024             9.83 -> 14.9    15.0 -> 15.6    44.6 -> 44.6    204.9 -> 203.9
 //        8192             60.2 -> 108     102 -> 108      367 -> 366
 // So it is done where every workgroup has a CU to itself (at most 16 MB are read in vain there) and the longest segment
-// has more rows than two tiles; beyond, the other workgroups of a CU cover the wait.  With the two kernels 1024 segments
-// of 20-32 rows take 8.5 us, 13.7 if all ask early; 512 segments of 2700 rows take the same time either way (0.2 %).
-bool first_tile_early(int nseg_launch, int S, int max_len)
+// has more rows than two tiles; beyond, the other workgroups of a CU cover the wait, and it is done only if the caller
+// knows the longest segment to have more than one round of tiles (the capacity alone says nothing about that).  With the
+// two kernels 1024 segments of 20-32 rows take 8.6 us, 13.3 if all ask early; 384 of 100-200 rows 8.9 us if they ask early,
+// 9.6 if not; 1792 of 700-1366 rows at D = 64 147 and 151 us.
+bool first_tile_early(int nseg_launch, int S, int max_len, int max_len_hint)
 {
-    return nseg_launch * S <= COMPUTE_UNITS && max_len > 2 * ATT_TILE;
+    if (nseg_launch * S <= COMPUTE_UNITS) return max_len > 2 * ATT_TILE;
+    return max_len_hint > ATT_WAVES * ATT_TILE;
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -818,7 +831,7 @@ int launch_decode(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, 
     }
     hipStream_t st = (hipStream_t)stream;
     const dim3 grid(nseg * S), block(ATT_WAVES * 64);
-    const bool early = first_tile_early(nseg, S, max_len);
+    const bool early = first_tile_early(nseg, S, max_len, max_len_hint);
 #define NGC_LAUNCH_DECODE(PAGED, APPEND) \
     if (c->D == 128) { \
         if (early) hipLaunchKernelGGL((decode_kernel<128, PAGED, APPEND, true>), grid, block, 0, st, aa); \

@@ -143,17 +143,19 @@ def test_split_rule_stays_inside_the_workspace_it_promises():
 
 
 @pytest.mark.parametrize("D,Hq", [(64, 8), (128, 12)])
-@pytest.mark.parametrize("B,hint", [(128, 65), (128, 64), (129, 0)])      # the first tile before the length, and after it (twice)
+# the first tile before the length, after it (three times), and before it again
+@pytest.mark.parametrize("B,hint", [(128, 65), (128, 64), (129, 0), (129, 128), (129, 129)])
 def test_first_tile_before_and_after_the_length(B, hint, D, Hq):
-    """256 segments of one workgroup each are the most for which a wave asks for its first tile before it knows the length,
-    and only if the longest may have more than two tiles: both sides of either limit, empty and full segments among them,
+    """256 segments of one workgroup each are the most for which a wave asks for its first tile before it knows the length
+    whatever the caller knows, and only if the longest may have more than two tiles; beyond, the caller has to know that the
+    longest has more than 128 rows.  Both sides of each limit, empty and full segments among them,
     NaN in every unused row, contiguous (with and without the append) and paged."""
     import torch
     ngc = _ngc()
     H, scale = 2, D ** -0.5
     cap = hint or 160
     g = torch.Generator().manual_seed(B + hint + D)
-    edges = [x for x in (0, 1, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 159, 160) if x <= cap] + [cap]
+    edges = [x for x in (0, 1, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 159, 160, 255) if x <= cap] + [cap]
     n = torch.tensor([edges[(i * 5) % len(edges)] for i in range(B * H)], dtype=torch.int32).view(1, B, H)
     k = torch.randn(1, B, H, cap, D, generator=g).to(torch.bfloat16)
     v = torch.randn(1, B, H, cap, D, generator=g).to(torch.bfloat16)
