@@ -147,8 +147,7 @@ def load_library(path: Optional[str] = None) -> C.CDLL:
                                "there is no fallback path")
         from . import _ngc_host
         _ngc_host.open(path)
-        _ngc_host.types(ArgumentError, Cache.view, PagedCache.view, ngc_cache, ngc_paged_cache, ngc_evict_params,
-                        C._SimpleCData)
+        _ngc_host.types(ArgumentError, Cache, PagedCache, ngc_cache, ngc_paged_cache, ngc_evict_params, C._SimpleCData)
         _host = _ngc_host
         _lib = lib
     return lib

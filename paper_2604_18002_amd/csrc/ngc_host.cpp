@@ -34,10 +34,11 @@ struct Names {
 
 // what types() was given: the binding's own classes and functions
 struct Types {
-    PyObject *argument_error;             // raised for an argument of the wrong type
-    PyObject *cache_view, *paged_view;    // Cache.view and PagedCache.view: what the front reads in their place
-    PyObject *cache, *paged, *params;     // the ctypes structures
-    PyObject *simple;                     // base of ctypes' numbers
+    PyObject *argument_error;               // raised for an argument of the wrong type
+    PyObject *cache_class, *paged_class;    // Cache and PagedCache, and their view(): what the front reads in its place
+    PyObject *cache, *paged, *params;       // the ctypes structures
+    PyObject *simple;                       // base of ctypes' numbers
+    PyObject *cache_view, *paged_view;
 } types;
 
 struct Ref {   // a new reference, released at the end of the scope
@@ -91,10 +92,22 @@ size_t bytes(PyObject *t)   // elements of a uint8 workspace tensor
 }
 void *stream(PyObject *o) { return o == Py_None || PyErr_Occurred() ? nullptr : PyLong_AsVoidPtr(o); }
 
-void *attr_ptr(PyObject *o, PyObject *name, bool contiguous)
+// The attributes of a cache.  `dict`: where they are if the object is of the binding's own class, else null.
+struct Object {
+    PyObject *o, *dict = nullptr;
+    ~Object() { Py_XDECREF(dict); }
+    PyObject *get(PyObject *name) const      // a new reference
+    {
+        PyObject *v = dict ? PyDict_GetItemWithError(dict, name) : nullptr;
+        Py_XINCREF(v);
+        return v || PyErr_Occurred() ? v : PyObject_GetAttr(o, name);
+    }
+};
+
+void *attr_ptr(const Object &o, PyObject *name, bool contiguous)
 {
     if (PyErr_Occurred()) return nullptr;
-    const Ref t(PyObject_GetAttr(o, name));
+    const Ref t(o.get(name));
     if (!t.o) return nullptr;
     if (contiguous) {
         const Ref c(PyObject_CallMethodNoArgs(t.o, names.is_contiguous));
@@ -108,10 +121,10 @@ void *attr_ptr(PyObject *o, PyObject *name, bool contiguous)
 }
 
 // The first `count` sizes of o.name into d; the tensor must have exactly that many dimensions.
-void sizes(PyObject *o, PyObject *name, int32_t *d, Py_ssize_t count)
+void sizes(const Object &o, PyObject *name, int32_t *d, Py_ssize_t count)
 {
     if (PyErr_Occurred()) return;
-    const Ref t(PyObject_GetAttr(o, name));
+    const Ref t(o.get(name));
     if (!t.o) return;
     const Ref s(PyObject_GetAttr(t.o, names.shape));
     if (!s.o) return;
@@ -122,10 +135,10 @@ void sizes(PyObject *o, PyObject *name, int32_t *d, Py_ssize_t count)
     for (Py_ssize_t i = 0; i < count; ++i) d[i] = i32(PyTuple_GET_ITEM(s.o, i));
 }
 
-int32_t attr_i32(PyObject *o, PyObject *name)
+int32_t attr_i32(const Object &o, PyObject *name)
 {
     if (PyErr_Occurred()) return 0;
-    const Ref v(PyObject_GetAttr(o, name));
+    const Ref v(o.get(name));
     return v.o ? i32(v.o) : 0;
 }
 
@@ -142,24 +155,32 @@ void copy_struct(PyObject *o, PyObject *type, const char *wanted, T *to)
     PyBuffer_Release(&b);
 }
 
-// Whether o.view() is the binding's own method, whose reading of the tensors is done here.  Anything else is called and
+// Whether c.o.view() is the binding's own method, whose reading of the tensors is done here.  Anything else is called and
 // its structure copied.
 template <class T>
-bool own_view(PyObject *o, PyObject *own, PyObject *type, const char *wanted, T *v)
+bool own_view(Object &c, PyObject *own_class, PyObject *own, PyObject *type, const char *wanted, T *v)
 {
     if (PyErr_Occurred()) return false;
-    const Ref m(PyObject_GetAttr(o, names.view));
+    PyTypeObject *const t = Py_TYPE(c.o);
+    if (reinterpret_cast<PyObject *>(t) == own_class && PyDict_GetItemWithError(t->tp_dict, names.view) == own) {
+        c.dict = PyObject_GenericGetDict(c.o, nullptr);
+        if (!c.dict) return false;
+        if (!PyDict_GetItemWithError(c.dict, names.view)) return !PyErr_Occurred();
+        Py_CLEAR(c.dict);
+    }
+    const Ref m(PyObject_GetAttr(c.o, names.view));
     if (!m.o) return false;
-    if (PyMethod_Check(m.o) && PyMethod_GET_SELF(m.o) == o && PyMethod_GET_FUNCTION(m.o) == own) return true;
+    if (PyMethod_Check(m.o) && PyMethod_GET_SELF(m.o) == c.o && PyMethod_GET_FUNCTION(m.o) == own) return true;
     const Ref r(PyObject_CallNoArgs(m.o));
     if (r.o) copy_struct(r.o, type, wanted, v);
     return false;
 }
 
-ngc_cache cache_of(PyObject *c)
+ngc_cache cache_of(PyObject *o)
 {
     ngc_cache v{};
-    if (!own_view(c, types.cache_view, types.cache, "ngc_cache", &v)) return v;
+    Object c{o};
+    if (!own_view(c, types.cache_class, types.cache_view, types.cache, "ngc_cache", &v)) return v;
     int32_t d[5] = {};
     sizes(c, names.k, d, 5);
     v.L = d[0]; v.B = d[1]; v.Hkv = d[2]; v.cap = d[3]; v.D = d[4];
@@ -171,10 +192,11 @@ ngc_cache cache_of(PyObject *c)
     return v;
 }
 
-ngc_paged_cache paged_of(PyObject *c)
+ngc_paged_cache paged_of(PyObject *o)
 {
     ngc_paged_cache v{};
-    if (!own_view(c, types.paged_view, types.paged, "ngc_paged_cache", &v)) return v;
+    Object c{o};
+    if (!own_view(c, types.paged_class, types.paged_view, types.paged, "ngc_paged_cache", &v)) return v;
     int32_t d[3] = {}, t[4] = {};
     sizes(c, names.k_pool, d, 3);
     sizes(c, names.table, t, 4);
@@ -324,14 +346,17 @@ PyObject *open_(PyObject *, PyObject *path)
     Py_RETURN_NONE;
 }
 
-// types(ArgumentError, Cache.view, PagedCache.view, ngc_cache, ngc_paged_cache, ngc_evict_params, _SimpleCData)
+// types(ArgumentError, Cache, PagedCache, ngc_cache, ngc_paged_cache, ngc_evict_params, _SimpleCData)
 ENTRY(types, 7)
-    PyObject **const to[] = {&types.argument_error, &types.cache_view, &types.paged_view, &types.cache, &types.paged,
+    PyObject **const to[] = {&types.argument_error, &types.cache_class, &types.paged_class, &types.cache, &types.paged,
                              &types.params, &types.simple};
     for (int i = 0; i < 7; ++i) {
         Py_INCREF(a[i]);
         Py_XSETREF(*to[i], a[i]);
     }
+    Py_XSETREF(types.cache_view, PyObject_GetAttr(a[1], names.view));
+    Py_XSETREF(types.paged_view, PyObject_GetAttr(a[2], names.view));
+    if (!types.cache_view || !types.paged_view) return nullptr;
     Py_RETURN_NONE;
 END
 

@@ -142,7 +142,7 @@ def test_arguments_of_a_wrong_type_raise_what_ctypes_raises():
     assert _code(ngc.ngc_decode_attn, c, 0, q, C.c_float(float("nan")), 0, out, ws) == ngc.NGC_EINVAL
 
 
-def test_a_cache_with_a_view_of_its_own_is_asked_for_it():
+def test_a_cache_with_a_view_of_its_own_is_asked_for_it(monkeypatch):
     q, out, ws = torch.zeros(3, 12, 128, dtype=torch.bfloat16), torch.zeros(3, 12, 128), torch.zeros(1 << 20, dtype=torch.uint8)
     asked = []
 
@@ -155,6 +155,21 @@ def test_a_cache_with_a_view_of_its_own_is_asked_for_it():
     c = _cache()
     c = Narrow(c.k, c.v, c.len, c.pos, c.Hq)
     assert _code(ngc.ngc_decode_attn, c, 0, q, 0.1, 0, out, ws) == ngc.NGC_EINVAL and asked == [1]
+
+    c = _cache()                                             # overridden on the object, and on the class
+    narrow = c.view()
+    narrow.D = 96
+    assert _code(ngc.ngc_decode_attn, c, 0, q, 0.1, 0, out, ws[:16]) == ngc.NGC_ENOSPC
+    c.view = lambda: narrow
+    assert _code(ngc.ngc_decode_attn, c, 0, q, 0.1, 0, out, ws[:16]) == ngc.NGC_EINVAL
+    with monkeypatch.context() as m:
+        m.setattr(ngc.Cache, "view", lambda self: narrow)
+        assert _code(ngc.ngc_decode_attn, _cache(), 0, q, 0.1, 0, out, ws[:16]) == ngc.NGC_EINVAL
+
+    class Inherits(ngc.Cache):                               # its own class, the binding's view
+        pass
+    c = _cache()
+    assert _code(ngc.ngc_decode_attn, Inherits(c.k, c.v, c.len, c.pos, c.Hq), 0, q, 0.1, 0, out, ws[:16]) == ngc.NGC_ENOSPC
 
     class Plain:                                             # nothing but a view
         def __init__(self, v):
