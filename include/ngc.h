@@ -297,7 +297,8 @@ int ngc_cache_append(const ngc_cache *c, int32_t layer, const void *k_new,
  *   out  fp32 same shape
  *   scale          usually 1 / sqrt(D)
  *   max_len_hint   an upper bound on len the caller knows (0 = use cap); it
- *                  only steers how the work is split, never the result.
+ *                  only steers how the work is split and how much of it is
+ *                  read ahead, never the result.
  *   lse_out        optional fp32 [B][Hq] (or [L][B][Hq]): log sum_j exp(scale *
  *                  <q, K[j]>) per query head (natural log; -inf for n == 0), or
  *                  NULL.  ngc_score_keys can reuse it.
@@ -332,11 +333,12 @@ int ngc_decode_step(const ngc_cache *c, int32_t layer, const void *k_new, const 
  * Returns NGC_ENOSPC, and enqueues nothing, when the call would need more than
  * the fixed array: 4096 bytes of status words and tickets plus
  *     S * nseg * (Hq / Hkv) * (D + 2) * 4 bytes (plus alignment) of partials,
- *     nseg = segments of the launch, S = workgroups per segment as
- *     ngc_decode_attn chooses them (1 for more than 128 segments, else at most
- *     min(256 / nseg, 64)) -- i.e. only 16 query heads per KV head at D = 128
- *     over 240 or more workgroups exceed it; ngc_decode_attn with a workspace
- *     takes those.
+ *     nseg = segments of the launch, n = max_len_hint (or cap),
+ *     S = max(1, min(256 / nseg, sqrt(320e-6 * D * n), ceil(n / 32) / 4, 64)),
+ *     divisions and root rounded down -- i.e. only 16 query heads per KV head
+ *     at D = 128 over more than 251 such workgroups exceed it; ngc_decode_attn
+ *     with a workspace takes those.  S decides only which calls are taken; a
+ *     launch may use fewer or more workgroups per segment.
  * The layout inside the array does not depend on the cache's geometry, so caches
  * of different shapes can be served one after the other.
  * The call itself allocates nothing and calls no allocating routine; the first

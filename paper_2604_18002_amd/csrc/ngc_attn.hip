@@ -705,9 +705,9 @@ size_t attn_partial_bytes(const ngc_cache *c, int nseg_launch, int S)
     return S > 1 ? partial_o_bytes(c, nseg_launch, S) + partial_ml_bytes(c, nseg_launch, S) : 0;
 }
 
-// Whether ngc_decode_attn_static takes a call is decided by this number of workgroups per segment, not by the one that is
-// launched, so that a better split never turns a call away (nor lets one in).  It differs from "always" only for 16 query
-// heads per KV head at D = 128.
+// Whether ngc_decode_attn_static takes a call is decided by this number of workgroups per segment, the one that ngc.h
+// states, not by the one that is launched, so that a better split never turns a call away (nor lets one in).  It differs
+// from "always" only for 16 query heads per KV head at D = 128.
 int static_limit_splits(int nseg_launch, int max_len, int row_bytes)
 {
     const double seg_mb = 2.0 * row_bytes * max_len * 1e-6;          // K and V of a segment

@@ -245,20 +245,6 @@ __device__ __forceinline__ float block_sum_f(float v, float *tmp)
     return all;
 }
 
-template <int THREADS>
-__device__ __forceinline__ float block_max_f(float v, float *tmp)
-{
-    constexpr int NW = THREADS / NGC_WAVE;
-    v = wave_max_f(v);
-    if (lane_id() == 0) tmp[wave_id()] = v;
-    __syncthreads();
-    float all = tmp[0];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) all = fmaxf(all, tmp[w]);
-    __syncthreads();
-    return all;
-}
-
 // Two maxima in one pass (same barriers as one).  `tmp` holds two floats per wave.
 template <int THREADS>
 __device__ __forceinline__ void block_max2_f(float &a, float &b, float *tmp)

@@ -691,8 +691,8 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
         }
     }
 
-    // Ranking by buckets where it applies (steps 2''-4'').  Otherwise -- many equal keys, sigma not wanted, no room in
-    // LDS -- radix select, ballot compaction, sort (steps 2-4), or up to SMALL_ITEMS items ranking by all pairs (2'-4').
+    // Ranking by buckets where it applies (steps 2''-4'').  Otherwise -- many equal keys, masked items kept, sigma not
+    // wanted, no room in LDS -- radix select, ballot compaction, sort (steps 2-4), or up to SMALL_ITEMS items ranking by all pairs (2'-4').
     // Selection only, 896 segments, microseconds with (without) the buckets: 64 items 11.6 (11.6), 128: 11.7 (13.5),
     // 256: 12.0 (19.8), 300: 13.4 (21.2), 700: 17.2 (22.2); 3584 segments of 4096: 119 (148).
     uint16_t *src = idxA;   // the kept items in sampled order, once known
