@@ -228,6 +228,18 @@ __device__ __forceinline__ void fill_holes_inplace(unsigned char *kbase, unsigne
         for (int i = threadIdx.x; i < movers; i += THREADS) pos[hole_of(i)] = pos[kept[jstar + i]];
 }
 
+// The thread's index as a value the compiler does not connect with that of the previous segment.  In the persistent
+// kernel (128 registers a thread) what follows from it would otherwise be computed once, before the loop over the
+// segments, and kept in scratch, to be read again for every segment while rows stream through the caches: 18 registers,
+// 1.2 % of the bytes of a round; 2048 segments of up to 8192 rows took 1005 us with 37 such registers, 988 with none.
+template <int THREADS>
+__device__ __forceinline__ int fresh_thread_index()
+{
+    int tid = threadIdx.x;
+    if constexpr (THREADS == 1024) __asm__ volatile("" : "+v"(tid));
+    return tid;
+}
+
 // ------------------------------------------------- shared building blocks --
 //
 // The two steps every variant of the selection shares (segments of one head in
@@ -312,7 +324,7 @@ __device__ __forceinline__ uint16_t *sort_by_code_desc(CodeOf code_of, int K, ui
     constexpr int NW = THREADS / NGC_WAVE;
     constexpr int NB = (SEL_BINS > SORT_BINS * NW) ? SEL_BINS : SORT_BINS * NW;   // buckets = entries of hist
     static_assert(NB % THREADS == 0, "every thread owns the same number of buckets");
-    const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
+    const int tid = fresh_thread_index<THREADS>(), lane = tid & (NGC_WAVE - 1), wv = tid >> 6;
     const uint32_t range = cmax - thr;
     const int range_bits = range ? 32 - __clz(range) : 0;
     if (range_bits == 0) return idxA;   // all codes equal: the ascending start order is the answer
@@ -462,7 +474,7 @@ __device__ __forceinline__ bool rank_items(const uint32_t *code, int N, int K, u
     constexpr int NB = (SEL_BINS > SORT_BINS * NW) ? SEL_BINS : SORT_BINS * NW;
     constexpr int PER = NB / THREADS;
     static_assert(PER % 4 == 0, "vector accesses to a thread's own buckets");
-    const int tid = threadIdx.x;
+    const int tid = fresh_thread_index<THREADS>();
     const float kmax = code_to_float(cmax), kmin = code_to_float(cmin);
     const float width = kmax - kmin;
     if (!(width > 0.f && width < INFINITY)) return false;
@@ -546,7 +558,7 @@ template <int THREADS, class Logit>
 __device__ __forceinline__ float sigma_logprob(Logit x, int K, float smax, float unpicked, float *stage, float *tmp)
 {
     constexpr int NW = THREADS / NGC_WAVE;
-    const int tid = threadIdx.x;
+    const int tid = fresh_thread_index<THREADS>();
     for (int j = tid; j < K; j += THREADS) stage[j] = exp_shifted(x(j) - smax);
     __syncthreads();
     const int chunk = (K + THREADS - 1) / THREADS;
@@ -614,7 +626,7 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
     uint32_t *kept_bits = reinterpret_cast<uint32_t *>(idxB + (a.rank_cap > a.keep_cap ? a.rank_cap : a.keep_cap));
     float *fmisc = reinterpret_cast<float *>(misc);
 
-    const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
+    const int tid = fresh_thread_index<THREADS>(), lane = tid & (NGC_WAVE - 1), wv = tid >> 6;
     int l, b, h;
     seg_coords(seg, a.g, l, b, h);
     const int n = seg_rows(a.len, seg, a.g.cap, a.status);
