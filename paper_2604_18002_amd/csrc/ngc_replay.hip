@@ -17,9 +17,9 @@
 // (no registers, no LDS store instructions) and are shared by the waves; the V operand is read transposed from LDS.
 //
 // What bounds it: matrix and vector work of two waves per SIMD that overlap only in part, then the output.  B = 8,
-// T = 4096, 28/4 heads, 27 % of the causal pairs visible (the issued products are worth 390 GFLOP): 557 us with 16-wide
-// tiles and rows staged through registers, now 456 us; B = 16, T = 1050, 12/2 heads 124 -> 84 us.  On the way, at the
-// first shape on the box of that day (552 us before): 32-wide tiles and loads straight to LDS 511 us; a reference for the
+// T = 4096, 28/4 heads, 27 % of the causal pairs visible (the issued products are worth 390 GFLOP): 546-557 us with
+// 16-wide tiles and rows staged through registers, now 440-460 us; B = 16, T = 1050, 12/2 heads 123 -> 81-84 us.  On the
+// way, at the first shape (552 us before): 32-wide tiles and loads straight to LDS 511 us; a reference for the
 // exponents that moves only when outgrown by 2^8, and transposing reads of V instead of 32 byte permutes a step, 464 us;
 // the output through LDS in whole lines, nontemporal, and the list kernel in one pass 440 us.  The version before the last
 // of these took 470 us there, 403 without its tile loads, 281 without its products, 113 with neither (470 MB of output).
