@@ -47,6 +47,9 @@ __device__ __forceinline__ float max_no_nan(float a, float b)
 {
     return __builtin_amdgcn_fmed3f(a, b, __builtin_inff());
 }
+// IEEE maximum and minimum: NaN if an operand is one; two of them on the way to a third value are one instruction.
+__device__ __forceinline__ float max_or_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+__device__ __forceinline__ float min_or_nan(float a, float b) { return __builtin_elementwise_minimum(a, b); }
 __device__ __forceinline__ float quad_rows_max(float v)
 {
     uint32_t u = __float_as_uint(v);
@@ -104,13 +107,26 @@ __device__ __forceinline__ u32x2 read_transposed16(const void *lds)
 // primitives (a shuffle through LDS costs ~60 cycles a step, these ~8), across rows by gfx950's lane-swap instructions.
 namespace dpp {
 constexpr int QUAD_XOR1 = 0xB1, QUAD_XOR2 = 0x4E, HALF_MIRROR = 0x141, MIRROR = 0x140;   // together: xor 1, 2, 4, 8
-constexpr int ROW_SHR = 0x110;                                                           // + n: from n lanes below
+constexpr int ROW_SHR = 0x110, ROW_SHL = 0x100;                                          // + n: from n lanes below, above
+constexpr int WAVE_SHR1 = 0x138, WAVE_SHL1 = 0x130;                                      // from the lane below, above
 constexpr int BCAST15 = 0x142, BCAST31 = 0x143;                                          // a row's last lane to the next row(s)
-// lane's partner value; lanes without one (or outside ROWS) get `none`
-template <int CTRL, int ROWS = 0xF>
-__device__ __forceinline__ uint32_t from(uint32_t v, uint32_t none)
+// the partner's value, for exchanges in which every lane has one (the compiler folds them into the operation that follows)
+template <int CTRL>
+__device__ __forceinline__ uint32_t swapped(uint32_t v)
 {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xF, false);
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
+}
+// the value of the lane that CTRL names, 0 where there is none (likewise)
+template <int CTRL>
+__device__ __forceinline__ uint32_t shifted(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
+}
+// the same for lanes of the rows in ROWS; the others get 0
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t broadcast(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
 }
 }  // namespace dpp
 
@@ -120,10 +136,10 @@ __device__ __forceinline__ T wave_reduce(T v, Op op)
 {
     uint32_t u = __builtin_bit_cast(uint32_t, v);
     auto step = [&](uint32_t w) { u = __builtin_bit_cast(uint32_t, op(__builtin_bit_cast(T, u), __builtin_bit_cast(T, w))); };
-    step(dpp::from<dpp::QUAD_XOR1>(u, u));
-    step(dpp::from<dpp::QUAD_XOR2>(u, u));
-    step(dpp::from<dpp::HALF_MIRROR>(u, u));
-    step(dpp::from<dpp::MIRROR>(u, u));
+    step(dpp::swapped<dpp::QUAD_XOR1>(u));
+    step(dpp::swapped<dpp::QUAD_XOR2>(u));
+    step(dpp::swapped<dpp::HALF_MIRROR>(u));
+    step(dpp::swapped<dpp::MIRROR>(u));
     auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
     u = a[0];
     step(a[1]);
@@ -132,20 +148,18 @@ __device__ __forceinline__ T wave_reduce(T v, Op op)
     step(b[1]);
     return __builtin_bit_cast(T, u);
 }
-// op over this lane and those below it (`none`: the neutral element)
-template <class T, class Op>
-__device__ __forceinline__ T wave_incl_scan(T v, T none, Op op)
+// Sum over this lane and those below it.
+template <class T>
+__device__ __forceinline__ T wave_incl_scan(T v)
 {
-    uint32_t u = __builtin_bit_cast(uint32_t, v);
-    const uint32_t z = __builtin_bit_cast(uint32_t, none);
-    auto step = [&](uint32_t w) { u = __builtin_bit_cast(uint32_t, op(__builtin_bit_cast(T, w), __builtin_bit_cast(T, u))); };
-    step(dpp::from<dpp::ROW_SHR + 1>(u, z));
-    step(dpp::from<dpp::ROW_SHR + 2>(u, z));
-    step(dpp::from<dpp::ROW_SHR + 4>(u, z));
-    step(dpp::from<dpp::ROW_SHR + 8>(u, z));
-    step(dpp::from<dpp::BCAST15, 0xA>(u, z));     // rows 1 and 3 take the row below's total
-    step(dpp::from<dpp::BCAST31, 0xC>(u, z));     // rows 2 and 3 that of the lower half
-    return __builtin_bit_cast(T, u);
+    auto bits = [](T x) { return __builtin_bit_cast(uint32_t, x); };
+    v += __builtin_bit_cast(T, dpp::shifted<dpp::ROW_SHR + 1>(bits(v)));
+    v += __builtin_bit_cast(T, dpp::shifted<dpp::ROW_SHR + 2>(bits(v)));
+    v += __builtin_bit_cast(T, dpp::shifted<dpp::ROW_SHR + 4>(bits(v)));
+    v += __builtin_bit_cast(T, dpp::shifted<dpp::ROW_SHR + 8>(bits(v)));
+    v += __builtin_bit_cast(T, dpp::broadcast<dpp::BCAST15, 0xA>(bits(v)));   // rows 1 and 3 take the row below's total
+    v += __builtin_bit_cast(T, dpp::broadcast<dpp::BCAST31, 0xC>(bits(v)));   // rows 2 and 3 that of the lower half
+    return v;
 }
 struct OpAdd {
     template <class T> __device__ __forceinline__ T operator()(T a, T b) const { return a + b; }
@@ -158,8 +172,85 @@ struct OpMaxU {
 };
 __device__ __forceinline__ float wave_sum_f(float v) { return wave_reduce(v, OpAdd{}); }
 __device__ __forceinline__ float wave_max_f(float v) { return wave_reduce(v, OpMaxF{}); }
-__device__ __forceinline__ int wave_incl_scan_i(int v) { return wave_incl_scan(v, 0, OpAdd{}); }
-__device__ __forceinline__ float wave_incl_scan_f(float v) { return wave_incl_scan(v, 0.f, OpAdd{}); }
+__device__ __forceinline__ int wave_incl_scan_i(int v) { return wave_incl_scan(v); }
+__device__ __forceinline__ float wave_incl_scan_f(float v) { return wave_incl_scan(v); }
+// The same sum in 64 bits (both words travel).
+__device__ __forceinline__ double wave_sum_d(double v)
+{
+    auto pair = [](uint32_t lo, uint32_t hi) { return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo); };
+    uint32_t lo, hi;
+    auto halves = [&] {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        lo = (uint32_t)b;
+        hi = (uint32_t)(b >> 32);
+    };
+    halves(); v += pair(dpp::swapped<dpp::QUAD_XOR1>(lo), dpp::swapped<dpp::QUAD_XOR1>(hi));
+    halves(); v += pair(dpp::swapped<dpp::QUAD_XOR2>(lo), dpp::swapped<dpp::QUAD_XOR2>(hi));
+    halves(); v += pair(dpp::swapped<dpp::HALF_MIRROR>(lo), dpp::swapped<dpp::HALF_MIRROR>(hi));
+    halves(); v += pair(dpp::swapped<dpp::MIRROR>(lo), dpp::swapped<dpp::MIRROR>(hi));
+    halves();
+    auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = pair(a[0], b[0]) + pair(a[1], b[1]);
+    halves();
+    a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return pair(a[0], b[0]) + pair(a[1], b[1]);
+}
+// The value of the lane below (above); 0 for the first (last).
+__device__ __forceinline__ float lane_below_f(float v)
+{
+    return __uint_as_float(dpp::shifted<dpp::WAVE_SHR1>(__float_as_uint(v)));
+}
+__device__ __forceinline__ float lane_above_f(float v)
+{
+    return __uint_as_float(dpp::shifted<dpp::WAVE_SHL1>(__float_as_uint(v)));
+}
+// Sum over this lane and those above it.
+__device__ __forceinline__ float wave_above_scan_f(float v)
+{
+    v += __uint_as_float(dpp::shifted<dpp::ROW_SHL + 1>(__float_as_uint(v)));
+    v += __uint_as_float(dpp::shifted<dpp::ROW_SHL + 2>(__float_as_uint(v)));
+    v += __uint_as_float(dpp::shifted<dpp::ROW_SHL + 4>(__float_as_uint(v)));
+    v += __uint_as_float(dpp::shifted<dpp::ROW_SHL + 8>(__float_as_uint(v)));
+    // the rows above: their sums stand in their first lanes
+    auto first_of = [&](int lane) { return __uint_as_float((uint32_t)__builtin_amdgcn_readlane(__float_as_uint(v), lane)); };
+    const float r3 = first_of(48), r2 = first_of(32) + r3, r1 = first_of(16) + r2;
+    const int row = lane_id() >> 4;
+    return v + (row == 0 ? r1 : row == 1 ? r2 : row == 2 ? r3 : 0.f);
+}
+
+// What the NW <= 16 waves of a workgroup have left in tmp[0], tmp[STRIDE], ... combined by every wave: a lane takes one
+// of the values, data-parallel steps within the row of 16 do the rest (2 to 4 of them; a loop over the values costs
+// every wave two or three instructions for each).
+template <int NW, int STRIDE, class T, class Op>
+__device__ __forceinline__ T across_waves(const T *tmp, Op op)
+{
+    static_assert(NW == 4 || NW == 8 || NW == 16, "whole rows of lanes");
+    uint32_t u = __builtin_bit_cast(uint32_t, tmp[(lane_id() & (NW - 1)) * STRIDE]);
+    auto step = [&](uint32_t w) { u = __builtin_bit_cast(uint32_t, op(__builtin_bit_cast(T, u), __builtin_bit_cast(T, w))); };
+    step(dpp::swapped<dpp::QUAD_XOR1>(u));
+    step(dpp::swapped<dpp::QUAD_XOR2>(u));
+    if constexpr (NW > 4) step(dpp::swapped<dpp::HALF_MIRROR>(u));
+    if constexpr (NW > 8) step(dpp::swapped<dpp::MIRROR>(u));
+    return __builtin_bit_cast(T, u);
+}
+// The sum of the values of the waves below this one, *total: of all.  ABOVE: of the waves above this one.
+template <int NW, int STRIDE, bool ABOVE = false, class T>
+__device__ __forceinline__ T below_waves(const T *tmp, T *total)
+{
+    static_assert(NW == 4 || NW == 8 || NW == 16, "whole rows of lanes");
+    const int lane = lane_id() & (NW - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(wave_id());
+    T v = tmp[(ABOVE ? NW - 1 - lane : lane) * STRIDE];
+    auto bits = [](T x) { return __builtin_bit_cast(uint32_t, x); };
+    v += __builtin_bit_cast(T, dpp::shifted<dpp::ROW_SHR + 1>(bits(v)));
+    v += __builtin_bit_cast(T, dpp::shifted<dpp::ROW_SHR + 2>(bits(v)));
+    if constexpr (NW > 4) v += __builtin_bit_cast(T, dpp::shifted<dpp::ROW_SHR + 4>(bits(v)));
+    if constexpr (NW > 8) v += __builtin_bit_cast(T, dpp::shifted<dpp::ROW_SHR + 8>(bits(v)));
+    const uint32_t before = dpp::shifted<dpp::ROW_SHR + 1>(bits(v));
+    *total = __builtin_bit_cast(T, (uint32_t)__builtin_amdgcn_readlane((int)bits(v), NW - 1));
+    return __builtin_bit_cast(T, (uint32_t)__builtin_amdgcn_readlane((int)before, ABOVE ? NW - 1 - wv : wv));
+}
 
 // Block-wide exclusive scan of one int per thread.  `tmp` holds one int per
 // wave (+1).  Returns the exclusive prefix; *total receives the block sum.
@@ -167,80 +258,44 @@ __device__ __forceinline__ float wave_incl_scan_f(float v) { return wave_incl_sc
 template <int THREADS>
 __device__ __forceinline__ int block_excl_scan_i(int v, int *tmp, int *total)
 {
-    constexpr int NW = THREADS / NGC_WAVE;
     const int incl = wave_incl_scan_i(v);
     if (lane_id() == NGC_WAVE - 1) tmp[wave_id()] = incl;
     __syncthreads();
-    int base = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        int t = tmp[w];
-        if (w < wave_id()) base += t;
-        all += t;
-    }
+    const int base = below_waves<THREADS / NGC_WAVE, 1>(tmp, total);
     __syncthreads();
-    *total = all;
     return base + incl - v;
 }
 
 template <int THREADS>
 __device__ __forceinline__ float block_excl_scan_f(float v, float *tmp, float *total)
 {
-    constexpr int NW = THREADS / NGC_WAVE;
     const float incl = wave_incl_scan_f(v);
     if (lane_id() == NGC_WAVE - 1) tmp[wave_id()] = incl;
     __syncthreads();
-    float base = 0.f, all = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        float t = tmp[w];
-        if (w < wave_id()) base += t;
-        all += t;
-    }
+    const float base = below_waves<THREADS / NGC_WAVE, 1>(tmp, total);
     __syncthreads();
-    *total = all;
-    float prev = __shfl_up(incl, 1, NGC_WAVE);   // sum of the lanes below, no subtraction
-    if (lane_id() == 0) prev = 0.f;
-    return base + prev;
+    return base + lane_below_f(incl);            // sum of the lanes below, no subtraction
 }
 
 // Sum of the values of the threads ABOVE this one, and of all (an exclusive scan from the last thread down).
 template <int THREADS>
 __device__ __forceinline__ float block_above_scan_f(float v, float *tmp, float *total)
 {
-    constexpr int NW = THREADS / NGC_WAVE;
-    float incl = v;   // this lane and those above it
-#pragma unroll
-    for (int o = 1; o < NGC_WAVE; o <<= 1) {
-        const float t = __shfl_down(incl, o, NGC_WAVE);
-        if (lane_id() + o < NGC_WAVE) incl += t;
-    }
+    const float incl = wave_above_scan_f(v);     // this lane and those above it
     if (lane_id() == 0) tmp[wave_id()] = incl;
     __syncthreads();
-    float base = 0.f, all = 0.f;
-#pragma unroll
-    for (int w = NW - 1; w >= 0; --w) {
-        const float t = tmp[w];
-        if (w > wave_id()) base += t;
-        all += t;
-    }
+    const float base = below_waves<THREADS / NGC_WAVE, 1, true>(tmp, total);
     __syncthreads();
-    *total = all;
-    float prev = __shfl_down(incl, 1, NGC_WAVE);
-    if (lane_id() == NGC_WAVE - 1) prev = 0.f;
-    return base + prev;
+    return base + lane_above_f(incl);
 }
 
 template <int THREADS>
 __device__ __forceinline__ float block_sum_f(float v, float *tmp)
 {
-    constexpr int NW = THREADS / NGC_WAVE;
     v = wave_sum_f(v);
     if (lane_id() == 0) tmp[wave_id()] = v;
     __syncthreads();
-    float all = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) all += tmp[w];
+    const float all = across_waves<THREADS / NGC_WAVE, 1>(tmp, OpAdd{});
     __syncthreads();
     return all;
 }
@@ -254,26 +309,34 @@ __device__ __forceinline__ void block_max2_f(float &a, float &b, float *tmp)
     b = wave_max_f(b);
     if (lane_id() == 0) { tmp[2 * wave_id()] = a; tmp[2 * wave_id() + 1] = b; }
     __syncthreads();
-    a = tmp[0];
-    b = tmp[1];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) {
-        a = fmaxf(a, tmp[2 * w]);
-        b = fmaxf(b, tmp[2 * w + 1]);
-    }
+    a = across_waves<NW, 2>(tmp, OpMaxF{});
+    b = across_waves<NW, 2>(tmp + 1, OpMaxF{});
+    __syncthreads();
+}
+
+// Largest of the first and smallest of the second over all threads, NaN if one of them is.  `tmp` as above.
+template <int THREADS>
+__device__ __forceinline__ void block_max_min(float &a, float &b, float *tmp)
+{
+    constexpr int NW = THREADS / NGC_WAVE;
+    const auto larger = [](float x, float y) { return max_or_nan(x, y); };
+    const auto smaller = [](float x, float y) { return min_or_nan(x, y); };
+    a = wave_reduce(a, larger);
+    b = wave_reduce(b, smaller);
+    if (lane_id() == 0) { tmp[2 * wave_id()] = a; tmp[2 * wave_id() + 1] = b; }
+    __syncthreads();
+    a = across_waves<NW, 2>(tmp, larger);
+    b = across_waves<NW, 2>(tmp + 1, smaller);
     __syncthreads();
 }
 
 template <int THREADS>
 __device__ __forceinline__ uint32_t block_max_u(uint32_t v, uint32_t *tmp)
 {
-    constexpr int NW = THREADS / NGC_WAVE;
     v = wave_reduce(v, OpMaxU{});
     if (lane_id() == 0) tmp[wave_id()] = v;
     __syncthreads();
-    uint32_t all = tmp[0];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) all = tmp[w] > all ? tmp[w] : all;
+    const uint32_t all = across_waves<THREADS / NGC_WAVE, 1>(tmp, OpMaxU{});
     __syncthreads();
     return all;
 }

@@ -53,137 +53,250 @@ struct LogprobArgs {
     int row_cap;     // floats of dynamic LDS for a segment's row
 };
 
-// Both kernels below (Eq. 2 for given actions, and its gradient) read a segment's row once into LDS and its
-// sigma once into registers.  Thread i owns PICKS consecutive picks -- thread 0 the LAST ones, so that an ordinary
-// exclusive scan over threads yields the mass of everything picked after a thread's own -- and keeps their terms in
-// registers between the passes.  A pick marks its item in the LDS row (an exchange, which also finds repeated
-// picks); what stays unmarked was never picked.  Rows that do not fit (N > row_cap) and rows whose logits span more
-// than NGC_WIDE_SPREAD take the general route: a bitmap of picked items and re-reads of the row.
+// Both kernels below (Eq. 2 for given actions, and its gradient) read a segment's row and its sigma once.  The row's
+// weights exp(s - max s) are computed once, by the threads that read the row, and stand in LDS; a pick takes its item's
+// weight from there and leaves a mark (an exchange, which also finds repeated picks); what stays unmarked was never
+// picked, and the marks tell the thread that read an item whether its logit belongs to the sum over the picks.
+// Thread i owns PICKS consecutive picks -- thread 0 the LAST ones, so that an ordinary exclusive scan over threads yields
+// the mass of everything picked after a thread's own -- and keeps their weights in registers between the passes.  Rows
+// that do not fit (N > row_cap) and rows whose logits span more than NGC_WIDE_SPREAD take the general route: a bitmap of
+// picked items and re-reads of the row.
 //
-// What bounds them: 3584 segments of ~2970 items and ~2460 picks (84 MB in, for the gradient 43 MB out; ~15 and
-// ~24 us of traffic) took 61 us and 102 us with the general route alone: three reads of the row and up to three
-// gathers per pick, each pass waiting for global memory.  One read of the row: 38 and 47 us; with the logarithm of a
-// product instead of a logarithm per pick and the shorter exponential 35 and 44 us.  What is left is the chain of
-// one workgroup (row, marks, two scans, the way out) over 3.5 rounds of resident workgroups.
-constexpr uint32_t PICKED_MARK = 0x7FFFFFFFu;   // a NaN: the row in LDS holds none (NaN logits become -inf)
+// What bounds them: the vector ALU, three quarters busy.  3584 segments of ~2970 items and ~2460 picks (84 MB in, for
+// the gradient 43 MB out; ~15 and ~24 us of traffic): three reads of the row and up to three gathers per pick 61 and
+// 102 us; one read of the row 35 and 44 (570 and 726 instructions a wave); one exponential per item instead of one per pick
+// and one per item and whatever the lanes of a wave disagree about, maxima of three, reductions that fold into their
+// additions, a reciprocal instead of a division: 24 and 29 us.  log p is added up in 64 bits from the threads on (error
+// against 64 bits 5.0e-8 -> 2.7e-8: it is a sum of thousands).
+constexpr float PICKED = -1.0f;      // in the LDS row, where every weight is >= 0
+constexpr int PICKED_WORDS = 2048;   // general route: a bit per item
+constexpr int SPARE_ITEMS = 64;      // LDS words behind the row for lanes without a pick to mark (one each)
+typedef f32x4 f32x4_any __attribute__((aligned(4)));    // rows start anywhere: 16-byte accesses need 4-byte alignment only
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef i32x4 i32x4_any __attribute__((aligned(4)));
 
-template <int THREADS, int PICKS>
+// a value that is the same in every lane, as a scalar: what is decided by it is a branch
+__device__ __forceinline__ float scalar(float x)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x)));
+}
+
+// QUADS: a thread holds the items 4 (i THREADS + tid) .. + 3 of a row of up to 4 QUADS THREADS items in registers.
+template <int THREADS, int PICKS, int QUADS>
 struct PickedTerms {
-    float d[PICKS];     // s - max s of this thread's picks (latest pick last)
-    float e[PICKS];     // exp(d); 0 past the end
+    f32x4 row[QUADS];   // held rows: s - max s of those items and, once the picks are marked, exp(s - max s) or PICKED
+    bool held;
+    float e[PICKS];     // exp(s - max s) of this thread's picks (latest pick last); 0 past the end
     int t[PICKS];       // item index; -1 past the end, -2 for an index outside the segment
     float after;        // mass of everything picked after them
     float unpicked;     // mass never picked (U of Eq. 2)
-    float smax;
-    int j_lo, count;    // picks j_lo .. j_lo + count - 1
+    float logits;       // this thread's share of the sum of s - max s over all picks (not with KEEP_ROW)
+    int count;          // picks of this thread
+    int per;            // the most any thread has
 };
 
-// Returns false (workgroup-uniform) when the segment needs the general route; the LDS row is then free for it.
-// lds_row: row_cap floats; with KEEP_ROW it holds exp(s - max s) of the items never picked and -1 for the picked ones
-// on return, otherwise it is scratch.  fmisc: 32 floats.
-template <int THREADS, int PICKS, bool KEEP_ROW>
+// Returns false (workgroup-uniform) when the segment needs the general route; LDS is then free for it.
+// lds_row: row_cap + SPARE_ITEMS floats; on return exp(s - max s) of the items never picked and PICKED for the others.
+// fmisc: 32 floats.
+template <int THREADS, int PICKS, int QUADS, bool KEEP_ROW>
 __device__ __forceinline__ bool gather_picked(const float *row, const int32_t *sig, int N, int K, int row_cap,
                                               float *lds_row, float *fmisc, int32_t *status,
-                                              PickedTerms<THREADS, PICKS> &pt)
+                                              PickedTerms<THREADS, PICKS, QUADS> &pt)
 {
+    constexpr int NW = THREADS / NGC_WAVE;
     const int tid = threadIdx.x;
     if (N > row_cap || K > THREADS * PICKS) return false;
+    pt.held = N <= 4 * QUADS * THREADS;
     const int per = (K + THREADS - 1) / THREADS;          // <= PICKS
     const int owners = (K + per - 1) / per;
-    pt.j_lo = (owners - 1 - tid) * per;
-    pt.count = tid < owners ? (pt.j_lo + per <= K ? per : K - pt.j_lo) : 0;
-    if (tid >= owners) pt.j_lo = 0;
+    const int j_lo = tid < owners ? (owners - 1 - tid) * per : 0;
+    pt.per = per;
+    pt.count = tid < owners ? (j_lo + per <= K ? per : K - j_lo) : 0;
 #pragma unroll
-    for (int i = 0; i < PICKS; ++i) pt.t[i] = i < pt.count ? sig[pt.j_lo + i] : -1;
-    float smax = -INFINITY, neg_smin = -INFINITY;   // over the unmasked entries
-    auto take = [&](float x) {
-        if (x == x) smax = fmaxf(smax, x);
-        if (x > -INFINITY) neg_smin = fmaxf(neg_smin, -x);
-        return (x != x) ? -INFINITY : x;
-    };
-    if ((reinterpret_cast<uintptr_t>(row) & 15u) == 0) {      // workgroup-uniform
-        const int quads = N >> 2;
-        for (int i = tid; i < quads; i += THREADS) {
-            f32x4 v = reinterpret_cast<const f32x4 *>(row)[i];
+    for (int i = 0; i < PICKS; i += 4) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = take(v[u]);
-            reinterpret_cast<f32x4 *>(lds_row)[i] = v;
-        }
-        for (int i = 4 * quads + tid; i < N; i += THREADS) lds_row[i] = take(row[i]);
-    } else {
-        for (int i = tid; i < N; i += THREADS) lds_row[i] = take(row[i]);
-    }
-    block_max2_f<THREADS>(smax, neg_smin, fmisc);             // its barriers also publish the row
-    if (smax > -INFINITY && smax + neg_smin > NGC_WIDE_SPREAD) return false;
-    if (smax == -INFINITY) smax = 0.f;                        // every entry masked: all weights are 0
-    pt.smax = smax;
-    float mass = 0.f;
-    int bad = 0;
+        for (int u = 0; u < 4; ++u) pt.t[i + u] = -1;
+        if (i < per && tid < owners) {
+            if (j_lo + i + 4 <= K) {
+                const i32x4 v = *reinterpret_cast<const i32x4_any *>(sig + j_lo + i);
 #pragma unroll
-    for (int i = 0; i < PICKS; ++i) {
-        pt.d[i] = 0.f;
-        pt.e[i] = 0.f;
-        if (i < per) {                                        // uniform
-            if (i < pt.count) {
-                int t = pt.t[i];
-                float x;
-                const bool inside = t >= 0 && t < N;
-                uint32_t bits = PICKED_MARK;
-                if (inside) bits = atomicExch(reinterpret_cast<uint32_t *>(&lds_row[t]), PICKED_MARK);
-                x = __uint_as_float(bits);
-                if (bits == PICKED_MARK) {                    // out of range, or picked before: counted, then read again
-                    bad = 1;
-                    t = t < 0 ? 0 : (t >= N ? N - 1 : t);
-                    x = row[t];
-                    x = (x != x) ? -INFINITY : x;
-                    if (!inside) pt.t[i] = -2;
-                }
-                pt.d[i] = x - smax;
-                pt.e[i] = exp_shifted(pt.d[i]);
-                mass += pt.e[i];
+                for (int u = 0; u < 4; ++u) pt.t[i + u] = v[u];
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (j_lo + i + u < K) pt.t[i + u] = sig[j_lo + i + u];
             }
         }
+    }
+    // Four items; those past the end repeat the first.
+    auto load_quad = [&](int q) -> f32x4 {
+        const float *p = row + 4 * q;
+        if (4 * q + 4 <= N) return *reinterpret_cast<const f32x4_any *>(p);
+        f32x4 x = {p[0], p[0], p[0], p[0]};
+#pragma unroll
+        for (int u = 1; u < 3; ++u)
+            if (4 * q + u < N) x[u] = p[u];
+        return x;
+    };
+    // body(q, x): x is the registers' copy where the row is held, otherwise read by load(q)
+    auto each_quad = [&](auto load, auto body) {
+        if (pt.held) {
+#pragma unroll
+            for (int i = 0; i < QUADS; ++i)
+                if (4 * i * THREADS < N)                      // uniform
+                    if (4 * (i * THREADS + tid) < N) body(i * THREADS + tid, pt.row[i]);
+        } else {
+            for (int q = tid; 4 * q < N; q += THREADS) {
+                f32x4 x = load(q);
+                body(q, x);
+            }
+        }
+    };
+    if (pt.held) {
+#pragma unroll
+        for (int i = 0; i < QUADS; ++i)
+            if (4 * i * THREADS < N)
+                if (4 * (i * THREADS + tid) < N) pt.row[i] = load_quad(i * THREADS + tid);
+    }
+    // a row that is not held waits in LDS for the maximum
+    auto staged_quad = [&](int q) { return reinterpret_cast<const f32x4 *>(lds_row)[q]; };
+    if (tid < SPARE_ITEMS) lds_row[row_cap + tid] = PICKED;
+    // Largest and smallest logit.  These maxima and minima are NaN if one of the logits is; such rows and those with masked
+    // entries look again, at the others alone.
+    float smax = -INFINITY, smin = INFINITY;
+    each_quad(load_quad, [&](int q, f32x4 &x) {
+        if (!pt.held) reinterpret_cast<f32x4 *>(lds_row)[q] = x;
+        smax = max_or_nan(max_or_nan(x[0], x[1]), smax);
+        smax = max_or_nan(max_or_nan(x[2], x[3]), smax);
+        smin = min_or_nan(min_or_nan(x[0], x[1]), smin);
+        smin = min_or_nan(min_or_nan(x[2], x[3]), smin);
+    });
+    block_max_min<THREADS>(smax, smin, fmisc);
+    smax = scalar(smax);                                      // uniform, and everything that follows from them
+    smin = scalar(smin);
+    const bool masked = !(smin > -INFINITY);
+    if (masked) {
+        float neg_smin = -INFINITY;
+        smax = -INFINITY;
+        each_quad(staged_quad, [&](int, f32x4 &x) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (x[u] == x[u]) smax = fmaxf(smax, x[u]);
+                if (x[u] > -INFINITY) neg_smin = fmaxf(neg_smin, -x[u]);
+            }
+        });
+        block_max2_f<THREADS>(smax, neg_smin, fmisc);
+        smax = scalar(smax);
+        smin = -scalar(neg_smin);
+    }
+    if (smax > -INFINITY && smax - smin > NGC_WIDE_SPREAD) return false;
+    if (smax == -INFINITY) smax = 0.f;                        // every entry masked: all weights are 0
+    // Masked entries get a difference that no other has (and whose exponential is 0).
+    constexpr float MASKED_D = -300.0f;
+    auto difference = [&](float x) {
+        float d = x - smax;
+        if (masked && !(x > -INFINITY)) d = MASKED_D;
+        return d;
+    };
+    each_quad(staged_quad, [&](int q, f32x4 &x) {
+        f32x4 e;
+        if (masked) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = difference(x[u]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] -= smax;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) e[u] = exp_shifted_finite(x[u]);
+        if (4 * q + 4 > N) {                                  // past the end: no weight
+#pragma unroll
+            for (int u = 1; u < 4; ++u)
+                if (4 * q + u >= N) e[u] = 0.f;
+        }
+        reinterpret_cast<f32x4 *>(lds_row)[q] = e;
+    });
+    __syncthreads();
+    float mass = 0.f, extra = 0.f;
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < PICKS; ++i) pt.e[i] = 0.f;
+    if (pt.count > 0) {
+#pragma unroll
+        for (int i = 0; i < PICKS; ++i)
+            if (i < per) {                                    // uniform
+                const int t = pt.t[i];
+                const bool inside = (uint32_t)t < (uint32_t)N;
+                const int at = inside ? t : row_cap + lane_id();       // (no pick: -1)
+                pt.e[i] = __uint_as_float(atomicExch(reinterpret_cast<uint32_t *>(&lds_row[at]), __float_as_uint(PICKED)));
+            }
+#pragma unroll
+        for (int i = 0; i < PICKS; ++i)
+            if (i < per) {
+                if (pt.e[i] < 0.f) {                          // no pick, out of range, or picked before
+                    pt.e[i] = 0.f;
+                    if (i < pt.count) {                       // counted, then taken from the row again
+                        bad = true;
+                        int t = pt.t[i];
+                        if (t < 0 || t >= N) pt.t[i] = -2;
+                        t = t < 0 ? 0 : (t >= N ? N - 1 : t);
+                        const float d = difference(row[t]);
+                        extra += d == MASKED_D ? -INFINITY : d;
+                        pt.e[i] = exp_shifted_finite(d);
+                    } else {
+                        pt.t[i] = -1;
+                    }
+                }
+                mass += pt.e[i];
+            }
     }
     if (bad) atomicAdd(&status[NGC_STATUS_BAD_SIGMA], 1);
     __syncthreads();                                          // every pick has marked its item
     float unpicked = 0.f;
-    for (int i = tid; i < N; i += THREADS) {
-        const uint32_t bits = __float_as_uint(lds_row[i]);
-        if (bits != PICKED_MARK) {
-            const float e = exp_shifted(__uint_as_float(bits) - smax);
-            unpicked += e;
-            if (KEEP_ROW) lds_row[i] = e;
-        } else if (KEEP_ROW) {
-            lds_row[i] = -1.f;
+    auto load_unless_kept = [&](int q) { return KEEP_ROW ? f32x4{} : load_quad(q); };
+    each_quad(load_unless_kept, [&](int q, f32x4 &x) {
+        const f32x4 v = reinterpret_cast<const f32x4 *>(lds_row)[q];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float weight = max_no_nan(v[u], 0.f);
+            unpicked += weight;
+            if (!KEEP_ROW) {
+                const float d = pt.held ? x[u] : difference(x[u]);
+                extra = __builtin_fmaf(weight - v[u], d, extra);                // the factor is 1 for a pick, else 0
+            }
         }
-    }
+        if (!KEEP_ROW && masked) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float d = pt.held ? x[u] : difference(x[u]);
+                if (d == MASKED_D && v[u] < 0.f) extra = -INFINITY;             // a masked pick makes log p = -inf
+            }
+        }
+        if (KEEP_ROW) x = v;
+    });
+    pt.logits = extra;
     // one exchange for the scan of the picked masses and the sum of the others
-    constexpr int NW = THREADS / NGC_WAVE;
     const float incl = wave_incl_scan_f(mass);
     const float others = wave_sum_f(unpicked);
     if (lane_id() == NGC_WAVE - 1) { fmisc[2 * wave_id()] = incl; fmisc[2 * wave_id() + 1] = others; }
     __syncthreads();
-    float base = 0.f, never = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        if (w < wave_id()) base += fmisc[2 * w];
-        never += fmisc[2 * w + 1];
-    }
+    float all;
+    const float base = below_waves<NW, 2>(fmisc, &all);
+    pt.unpicked = across_waves<NW, 2>(fmisc + 1, OpAdd{});
     __syncthreads();
-    float prev = __shfl_up(incl, 1, NGC_WAVE);                // sum of the lanes below, no subtraction
-    if (lane_id() == 0) prev = 0.f;
-    pt.after = base + prev;
-    pt.unpicked = never;
+    pt.after = base + lane_below_f(incl);                     // sum of the lanes below, no subtraction
     return true;
 }
 
 // One workgroup per segment; on the general route an LDS bitmap of picked items (65536 bits).
-template <int THREADS, int PICKS>
+template <int THREADS, int PICKS, int QUADS>
 __global__ __launch_bounds__(THREADS) void subset_logprob_kernel(LogprobArgs a)
 {
-    extern __shared__ __align__(16) float staged[];   // max(row_cap, stage_cap) floats
-    __shared__ uint32_t picked[2048];
-    __shared__ float fmisc[32];
+    // row_cap + SPARE_ITEMS floats or, on the general route, PICKED_WORDS of the bitmap and stage_cap floats
+    extern __shared__ __align__(16) float dynamic_lds[];
+    __shared__ __align__(16) float fmisc[32];
+    uint32_t *picked = reinterpret_cast<uint32_t *>(dynamic_lds);
+    float *staged = dynamic_lds + PICKED_WORDS;
     const int tid = threadIdx.x;
     const int seg = blockIdx.x;
     int N = a.n_items[seg];
@@ -201,23 +314,34 @@ __global__ __launch_bounds__(THREADS) void subset_logprob_kernel(LogprobArgs a)
         return;
     }
     {
-        PickedTerms<THREADS, PICKS> pt;
-        if (gather_picked<THREADS, PICKS, false>(row, sig, N, K, a.row_cap, staged, fmisc, a.status, pt)) {
-            float acc = 0.f, R = pt.unpicked + pt.after;
-            LogProduct prod;
+        PickedTerms<THREADS, PICKS, QUADS> pt;
+        if (gather_picked<THREADS, PICKS, QUADS, false>(row, sig, N, K, a.row_cap, dynamic_lds, fmisc, a.status, pt)) {
+            float R = pt.unpicked + pt.after, acc = pt.logits;
+            if (pt.count > 0) {
+                LogProduct prod;
 #pragma unroll
-            for (int i = PICKS - 1; i >= 0; --i)
-                if (i < pt.count) {
-                    R += pt.e[i];
-                    acc += pt.d[i];                           // a masked pick (logit -inf) makes log p = -inf,
-                    prod.times(R > 0.f ? R : 1.0f);           // also where nothing unmasked is left (R == 0)
-                }
-            const float lp = block_sum_f<THREADS>(acc - prod.log(), fmisc);
-            if (tid == 0) a.logp_out[seg] = lp;
+                for (int i = PICKS - 1; i >= 0; --i)
+                    if (i < pt.per) {                          // uniform
+                        R += pt.e[i];
+                        // (0 only where nothing unmasked is left: such a pick is masked, and pt.logits -inf)
+                        if (i < pt.count) prod.times(max_no_nan(R, 1.0e-37f));
+                    }
+                acc -= prod.log();
+            }
+            // (thousands for a long sequence: rounded once)
+            double *totals = reinterpret_cast<double *>(fmisc);
+            const double total = wave_sum_d((double)acc);
+            if (lane_id() == 0) totals[wave_id()] = total;
+            __syncthreads();
+            if (tid < NGC_WAVE) {
+                const double lp = wave_sum_d(tid < THREADS / NGC_WAVE ? totals[tid] : 0.0);
+                if (tid == 0) a.logp_out[seg] = (float)lp;
+            }
             return;
         }
     }
-    for (int i = tid; i < 2048; i += THREADS) picked[i] = 0;
+    __syncthreads();
+    for (int i = tid; i < PICKED_WORDS; i += THREADS) picked[i] = 0;
     __syncthreads();
     int bad = 0;
     for (int j = tid; j < K; j += THREADS) {
@@ -312,12 +436,14 @@ struct LogprobBwdArgs {
     int row_cap;
 };
 
-template <int THREADS, int PICKS>
+template <int THREADS, int PICKS, int QUADS>
 __global__ __launch_bounds__(THREADS) void subset_logprob_backward_kernel(LogprobBwdArgs a)
 {
-    extern __shared__ __align__(16) float inv_r[];   // max(row_cap, keep_cap) floats
-    __shared__ uint32_t picked[2048];
-    __shared__ float fmisc[32];
+    // row_cap + SPARE_ITEMS floats or, on the general route, PICKED_WORDS of the bitmap and keep_cap floats
+    extern __shared__ __align__(16) float dynamic_lds[];
+    __shared__ __align__(16) float fmisc[32];
+    uint32_t *picked = reinterpret_cast<uint32_t *>(dynamic_lds);
+    float *inv_r = dynamic_lds + PICKED_WORDS;
     const int tid = threadIdx.x;
     const int seg = blockIdx.x;
     int N = a.n_items[seg];
@@ -339,8 +465,9 @@ __global__ __launch_bounds__(THREADS) void subset_logprob_backward_kernel(Logpro
         return;
     }
     {
-        PickedTerms<THREADS, PICKS> pt;
-        if (gather_picked<THREADS, PICKS, true>(row, sig, N, K, a.row_cap, inv_r, fmisc, a.status, pt)) {
+        PickedTerms<THREADS, PICKS, QUADS> pt;
+        float *lds_row = dynamic_lds;
+        if (gather_picked<THREADS, PICKS, QUADS, true>(row, sig, N, K, a.row_cap, lds_row, fmisc, a.status, pt)) {
             // 1 / R_j from the last pick backwards, then C_j = sum_{i <= j} 1 / R_i: the picks before a thread's own
             // are those of the threads ABOVE it
             float inv[PICKS], part = 0.f;
@@ -349,9 +476,9 @@ __global__ __launch_bounds__(THREADS) void subset_logprob_backward_kernel(Logpro
 #pragma unroll
                 for (int i = PICKS - 1; i >= 0; --i) {
                     inv[i] = 0.f;
-                    if (i < pt.count) {
+                    if (i < pt.per) {                          // uniform
                         R += pt.e[i];
-                        inv[i] = 1.0f / R;
+                        if (i < pt.count) inv[i] = reciprocal(R);
                     }
                 }
             }
@@ -359,31 +486,50 @@ __global__ __launch_bounds__(THREADS) void subset_logprob_backward_kernel(Logpro
             for (int i = 0; i < PICKS; ++i) part += inv[i];
             float c_all;
             float C = block_above_scan_f<THREADS>(part, fmisc, &c_all);
-            // every item's gradient into the LDS row, then the row goes out in order
-            for (int i = tid; i < N; i += THREADS) {
-                const float e = inv_r[i];
-                if (e != -1.f) inv_r[i] = -g * e * c_all;
+            const float never = -g * c_all;                    // an item that was never picked: its weight times this
+            if (!pt.held) {
+                for (int i = tid; i < N; i += THREADS) {
+                    const float e = lds_row[i];
+                    if (e >= 0.f) lds_row[i] = e * never;
+                }
+                __syncthreads();
             }
-            __syncthreads();
+            // the picks' gradients into the LDS row, then the row goes out in order
 #pragma unroll
             for (int i = 0; i < PICKS; ++i)
-                if (i < pt.count) {
+                if (i < pt.per) {
                     C += inv[i];
-                    if (pt.t[i] >= 0) inv_r[pt.t[i]] = g * (1.0f - pt.e[i] * C);
+                    if (pt.t[i] >= 0) lds_row[pt.t[i]] = g * __builtin_fmaf(-pt.e[i], C, 1.0f);
                 }
             __syncthreads();
-            if ((reinterpret_cast<uintptr_t>(grow) & 15u) == 0) {
-                const int quads = N >> 2;
-                for (int i = tid; i < quads; i += THREADS)
-                    reinterpret_cast<f32x4 *>(grow)[i] = reinterpret_cast<const f32x4 *>(inv_r)[i];
-                for (int i = 4 * quads + tid; i < N; i += THREADS) grow[i] = inv_r[i];
+            auto store_quad = [&](int q, f32x4 w) {
+                if (4 * q + 4 <= N) {
+                    *reinterpret_cast<f32x4_any *>(grow + 4 * q) = w;
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 3; ++u)
+                        if (4 * q + u < N) grow[4 * q + u] = w[u];
+                }
+            };
+            if (pt.held) {
+#pragma unroll
+                for (int i = 0; i < QUADS; ++i) {
+                    const int q = i * THREADS + tid;
+                    if (4 * q < N) {
+                        f32x4 w = reinterpret_cast<const f32x4 *>(lds_row)[q];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) w[u] = pt.row[i][u] >= 0.f ? pt.row[i][u] * never : w[u];
+                        store_quad(q, w);
+                    }
+                }
             } else {
-                for (int i = tid; i < N; i += THREADS) grow[i] = inv_r[i];
+                for (int q = tid; 4 * q < N; q += THREADS) store_quad(q, reinterpret_cast<const f32x4 *>(lds_row)[q]);
             }
             return;
         }
     }
-    for (int i = tid; i < 2048; i += THREADS) picked[i] = 0;
+    __syncthreads();
+    for (int i = tid; i < PICKED_WORDS; i += THREADS) picked[i] = 0;
     __syncthreads();
     int bad = 0;
     for (int j = tid; j < K; j += THREADS) {
@@ -582,6 +728,99 @@ __global__ __launch_bounds__(LMEM_THREADS) void lmem_layer_kernel(LmemArgs a)
         __syncthreads();
     }
     if (tid == 0) a.loss_layer[l] = (float)(-red[0] / (double)a.B);
+}
+
+// Advantages, layers, total and upstream weights in one launch by one workgroup, where there is little to add up or few
+// layers to spread it over: 3 + 0.33 us per 1024 terms, while the two kernels take 7 us and another 1 us per 1024 terms of a
+// layer (call after call: 2 rounds x 7 layers x 128 rollouts x 4 heads 6.9 -> 6.0 us; 3 x 28 x 16 x 2 7.1 -> 5.8; 1 x 1 x
+// 1024 x 32 38 -> 14; 5 x 28 x 64 x 2 would take 10.3 instead of 7.5).  A wave adds one layer's terms or, with fewer
+// layers than waves, an equal share of them.
+constexpr int LMEM_ONE_THREADS = 1024;
+constexpr int LMEM_ONE_WAVES = LMEM_ONE_THREADS / NGC_WAVE;
+constexpr int LMEM_ONE_MAX_B = 1024;
+constexpr int LMEM_ONE_MAX_L = 128;
+constexpr int LMEM_ONE_MAX_TERMS = 32768;
+
+// x / d by a multiplication, exact for x and d up to 2^16: m = floor(2^32 / d) + 1 (0 stands for d = 1) is off by at most d,
+// x m / 2^32 by less than 1 / d.  (One CU does all the work: with three integer divisions and one of floats per term the
+// kernel took 8.5 us.)
+inline uint32_t divide_by(uint32_t d) { return d > 1 ? (uint32_t)((1ull << 32) / d + 1) : 0; }
+__device__ __forceinline__ int divided(int x, uint32_t m) { return m ? (int)__umulhi((uint32_t)x, m) : x; }
+
+__global__ __launch_bounds__(LMEM_ONE_THREADS) void lmem_one_kernel(LmemArgs a, uint32_t by_h, uint32_t by_bh, float *loss)
+{
+    __shared__ float reward[LMEM_ONE_MAX_B], weight[LMEM_ONE_MAX_B], upstream[LMEM_ONE_MAX_B];
+    __shared__ int nrounds[LMEM_ONE_MAX_B];
+    __shared__ double share[LMEM_ONE_MAX_L > LMEM_ONE_WAVES ? LMEM_ONE_MAX_L : LMEM_ONE_WAVES];
+    __shared__ float of_layer[LMEM_ONE_MAX_L];
+    const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
+    // Terms x = 0 .. terms - 1 of a layer: (round x / BH, rollout and head x % BH).  Share `part` of a layer has those with
+    // x / 64 % parts = part; lane k of a wave x = 64 (part + i parts) + k, BATCH values of i at a time.  The first
+    // batch is asked for before the weights are known.
+    constexpr int BATCH = 8;
+    const int BH = a.B * a.H, terms = a.R * BH;
+    const int parts = a.L < LMEM_ONE_WAVES ? LMEM_ONE_WAVES / a.L : 1;
+    float lp[BATCH];
+    auto load_batch = [&](int l, int x0) {
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i) {
+            int x = x0 + i * parts * NGC_WAVE;
+            x = x < terms ? x : terms - 1;
+            const int t = divided(x, by_bh);
+            lp[i] = a.logp[((size_t)t * a.L + l) * BH + (x - t * BH)];
+        }
+    };
+    if (wv < a.L * parts) load_batch(wv / parts, (wv % parts) * NGC_WAVE + lane);
+    int n = 0;
+    if (tid < a.B) {
+        reward[tid] = a.reward[tid];
+        n = a.rounds[tid];
+    }
+    __syncthreads();
+    if (tid < a.B) {
+        const int g0 = (tid / a.group) * a.group;
+        double mean = 0.0;
+        for (int j = 0; j < a.group; ++j) mean += (double)reward[g0 + j];
+        mean /= (double)a.group;
+        const double adv = (double)reward[tid] - mean;
+        n = n < 0 ? 0 : (n > a.R ? a.R : n);
+        nrounds[tid] = n;
+        weight[tid] = n > 0 ? (float)(adv / (double)n) : 0.f;
+        upstream[tid] = -weight[tid] / (float)a.B;
+        if (a.adv_out) a.adv_out[tid] = (float)adv;
+    }
+    __syncthreads();
+    for (int idx = wv; idx < a.L * parts; idx += LMEM_ONE_WAVES) {
+        const int l = idx / parts, part = idx - l * parts;
+        double acc = 0.0;
+        for (int x0 = part * NGC_WAVE + lane; x0 < terms; x0 += BATCH * parts * NGC_WAVE) {
+            if (idx != wv || x0 >= BATCH * parts * NGC_WAVE) load_batch(l, x0);
+#pragma unroll
+            for (int i = 0; i < BATCH; ++i) {
+                const int x = x0 + i * parts * NGC_WAVE;
+                if (x >= terms) break;
+                const int t = divided(x, by_bh), e = x - t * BH, b = divided(e, by_h);
+                const bool live = t < nrounds[b];
+                if (live) acc += (double)lp[i] * (double)weight[b];
+                if (a.gout) a.gout[((size_t)t * a.L + l) * BH + e] = live ? upstream[b] : 0.f;
+            }
+        }
+        acc = wave_sum_d(acc);
+        if (lane == 0) share[idx] = acc;
+    }
+    __syncthreads();
+    if (tid < a.L) {
+        double acc = 0.0;
+        for (int i = 0; i < parts; ++i) acc += share[tid * parts + i];
+        of_layer[tid] = (float)(-acc / (double)a.B);
+        a.loss_layer[tid] = of_layer[tid];
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double s = 0.0;
+        for (int l = 0; l < a.L; ++l) s += (double)of_layer[l];
+        *loss = (float)s;
+    }
 }
 
 // One wave: 64 layers' losses per load, added in layer order.
@@ -1225,8 +1464,10 @@ int resident_workgroups(const void *fn, int threads, size_t lds, int items)
 // of the rows (no row that keeps to its own is longer), an upper bound on the picks, and the number of segments; a row or
 // a sequence too long for the choice takes the general route.
 //   - Strides up to 8192: by the stride.  Two rounds of Eq. 2 and its gradient, us: 2048 segments of 700-1400 items 53
-//     with 256 threads, 67 with 512; of 1000-2000 items 69 and 76; 3584 segments of 2150-3789 items 174 with 256 threads,
-//     163 with 512.
+//     with 256 threads, 67 with 512; of 1000-2000 items 69 and 76 (before the weights were computed once per item).  From
+//     2049 to 4096 items a workgroup of 256 threads with 16 picks each runs fewer instructions in all but is a longer chain:
+//     Eq. 2 of 512 segments of 2150-3789 items 7.2 us, 6.0 with 512 threads, of 2048 15.4 and 15.1, of 3584 22.4 and 24.3; the
+//     gradient, whose 16 picks cost registers, 8.9 and 7.5, 20.1 and 19.2, 29.4 and 29.2.
 //   - Strides up to 16384, as in a cache of that capacity: the rows in it are often far shorter, and with a whole stride in
 //     LDS only two workgroups share a CU, so the picks decide.  Eq. 2 / gradient at a stride of 16384, us (one of 512
 //     threads on the general route alone, then threads x picks per thread):
@@ -1247,6 +1488,7 @@ int resident_workgroups(const void *fn, int threads, size_t lds, int items)
 constexpr int LOGPROB_MAX_ROW = 16384;
 constexpr int LOGPROB_ROW_OF_FOUR = 8064;
 constexpr int LOGPROB_FEW = 512;
+constexpr int LOGPROB_MANY = 2048;
 
 struct LogprobShape {
     int threads, picks, row_cap;
@@ -1263,6 +1505,7 @@ LogprobShape logprob_shape(int64_t stride, int64_t most_picks, int nseg, bool gr
     most_picks = most_picks < stride ? most_picks : stride;
     if (row_cap <= 1024) return {256, 4, row_cap};
     if (row_cap <= 2048) return {256, 8, row_cap};
+    if (row_cap <= 4096 && !gradient && nseg > LOGPROB_MANY) return {256, 16, row_cap};
     if (row_cap <= 8192) return {512, most_picks <= 4096 ? 8 : 16, row_cap};
     if (nseg > LOGPROB_FEW) {
         if (most_picks <= 1024) return {256, 4, row_cap};
@@ -1275,11 +1518,18 @@ LogprobShape logprob_shape(int64_t stride, int64_t most_picks, int nseg, bool gr
 
 // One of the five instantiations of a kernel by its workgroup.
 #define NGC_PICK_SHAPE(KERNEL, shape) \
-    ((shape).picks == 4       ? reinterpret_cast<const void *>(&KERNEL<256, 4>) \
-     : (shape).threads == 256 ? reinterpret_cast<const void *>(&KERNEL<256, 8>) \
-     : (shape).picks == 8     ? reinterpret_cast<const void *>(&KERNEL<512, 8>) \
-     : (shape).threads == 512 ? reinterpret_cast<const void *>(&KERNEL<512, 16>) \
-                              : reinterpret_cast<const void *>(&KERNEL<1024, 16>))
+    ((shape).picks == 4       ? reinterpret_cast<const void *>(&KERNEL<256, 4, 1>) \
+     : (shape).threads == 256 ? reinterpret_cast<const void *>(&KERNEL<256, 8, 2>) \
+     : (shape).picks == 8     ? reinterpret_cast<const void *>(&KERNEL<512, 8, 4>) \
+     : (shape).threads == 512 ? reinterpret_cast<const void *>(&KERNEL<512, 16, 4>) \
+                              : reinterpret_cast<const void *>(&KERNEL<1024, 16, 4>))
+
+// A segment's row and the spare words behind it or, on the general route, the bitmap and a value per pick.
+size_t logprob_lds_bytes(const LogprobShape &shape, int picks)
+{
+    const int row = shape.row_cap + SPARE_ITEMS, general = PICKED_WORDS + picks;
+    return (size_t)(row > general ? row : general) * sizeof(float);
+}
 
 }  // namespace
 
@@ -1430,8 +1680,10 @@ extern "C" int ngc_subset_logprob(const float *logits, const int32_t *n_items,
     const LogprobShape shape = logprob_shape(logit_stride, sigma_stride > 0 ? sigma_stride : 65536, nseg, false);
     LogprobArgs la{logits, n_items, sigma, keep, logp_out, reinterpret_cast<int32_t *>(ws),
                    logit_stride, sigma_stride, stage_cap, shape.row_cap};
-    const size_t lds = (size_t)(stage_cap > shape.row_cap ? stage_cap : shape.row_cap) * sizeof(float);
-    const void *fn = NGC_PICK_SHAPE(subset_logprob_kernel, shape);
+    const size_t lds = logprob_lds_bytes(shape, stage_cap);
+    const void *fn = shape.threads == 256 && shape.picks == 16
+                         ? reinterpret_cast<const void *>(&subset_logprob_kernel<256, 16, 4>)      // (Eq. 2 alone)
+                         : NGC_PICK_SHAPE(subset_logprob_kernel, shape);
     if (lds > 48 * 1024)
         NGC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     void *kargs[] = {&la};
@@ -1453,7 +1705,7 @@ extern "C" int ngc_subset_logprob_backward(const float *logits, const int32_t *n
     const LogprobShape shape = logprob_shape(logit_stride, max_keep, nseg, true);
     LogprobBwdArgs la{logits, n_items, sigma, keep, gout, grad_out, reinterpret_cast<int32_t *>(ws),
                       logit_stride, sigma_stride, max_keep, shape.row_cap};
-    const size_t lds = (size_t)(max_keep > shape.row_cap ? max_keep : shape.row_cap) * sizeof(float);
+    const size_t lds = logprob_lds_bytes(shape, max_keep);
     const void *fn = NGC_PICK_SHAPE(subset_logprob_backward_kernel, shape);
     if (lds > 48 * 1024)
         NGC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -1492,6 +1744,13 @@ extern "C" int ngc_lmem(const float *logp, const int32_t *rounds, const float *r
     if (B > LMEM_MAX_B) return NGC_EUNSUPPORTED;
     LmemArgs la{logp, rounds, reward, adv_out, loss_layer, gout, R, L, B, Hkv, group};
     hipStream_t st = (hipStream_t)stream;
+    const long long terms = (long long)R * L * B * Hkv;
+    if (B <= LMEM_ONE_MAX_B && L <= LMEM_ONE_MAX_L && terms <= LMEM_ONE_MAX_TERMS && terms * (L - 3) <= 9200LL * L) {
+        hipLaunchKernelGGL(lmem_one_kernel, dim3(1), dim3(LMEM_ONE_THREADS), 0, st, la,
+                           divide_by((uint32_t)Hkv), divide_by((uint32_t)(B * Hkv)), loss);
+        NGC_HIP_CHECK(hipGetLastError());
+        return NGC_OK;
+    }
     hipLaunchKernelGGL(lmem_layer_kernel, dim3(L), dim3(LMEM_THREADS), 0, st, la);
     NGC_HIP_CHECK(hipGetLastError());
     hipLaunchKernelGGL(lmem_total_kernel, dim3(1), dim3(64), 0, st, (const float *)loss_layer, (int)L, loss);

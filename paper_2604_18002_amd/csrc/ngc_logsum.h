@@ -20,16 +20,25 @@ namespace ngc {
 
 constexpr float NGC_WIDE_SPREAD = 80.0f;   // e^-80 ~ 1.8e-35: still a normal fp32 number, with room for sums
 
-// e^d for d in [-NGC_WIDE_SPREAD - a little, 0] or -inf (a masked entry): the hardware 2^x with the rounding of the
-// product d * log2(e) put back, without the range handling of the library function (11 instructions there, 7 here).
-__device__ __forceinline__ float exp_shifted(float d)
+// e^d for a finite d in [-1000, 0] (2^-1443 is 0): the hardware's 2^t at t = d log2(e), rounded, times e^(d - t ln 2),
+// which is 1 + (d - t ln 2) to within its square, 1e-11 (LN2 + LN2_LO = ln 2).
+__device__ __forceinline__ float exp_shifted_finite(float d)
 {
-    constexpr float L2E = 1.44269504f, L2E_LO = 1.92596299e-8f, LN2 = 0.693147181f;   // L2E + L2E_LO = log2(e)
-    const float x = d < -200.0f ? -200.0f : d;      // -inf: 2^-288 is 0 (a NaN stays one)
-    const float t = x * L2E;
-    const float lo = __builtin_fmaf(x, L2E_LO, __builtin_fmaf(x, L2E, -t));
+    constexpr float L2E = 1.44269504f, LN2 = 0.693147182f, LN2_LO = -1.90465421e-9f;
+    const float t = d * L2E;
     const float r = fast_exp2(t);
-    return __builtin_fmaf(r, lo * LN2, r);
+    const float c = __builtin_fmaf(t, -LN2_LO, __builtin_fmaf(t, -LN2, d));
+    return __builtin_fmaf(r, c, r);
+}
+// The same with -inf (a masked entry; 0) among the d (a NaN stays one).
+__device__ __forceinline__ float exp_shifted(float d) { return exp_shifted_finite(d < -200.0f ? -200.0f : d); }
+
+// 1 / x for a normal x in [1e-36, 1e36]: the hardware's reciprocal and one Newton step (within an ulp; 3 instructions
+// instead of the division's 11).
+__device__ __forceinline__ float reciprocal(float x)
+{
+    const float r = __builtin_amdgcn_rcpf(x);
+    return __builtin_fmaf(r, __builtin_fmaf(-x, r, 1.0f), r);
 }
 
 // A sum of logarithms taken as the logarithm of a product: mantissas multiply (at most a few dozen before log() is

@@ -160,3 +160,72 @@ def test_workgroups_chosen_by_the_picks(stride, kmax, nseg):
             assert np.all(np.abs(g[s, :n] - gout[s] * want) <= 1e-4 * np.abs(gout[s] * want) + 2e-6 * max(1.0, abs(gout[s]))), (s, n, k)
             assert np.isnan(g[s, n:]).all()
     assert all(v == 0 for v in ngc.read_status(ws))
+
+
+@pytest.mark.parametrize("stride,nseg", [(2049, 2049), (4096, 2049), (4096, 2048), (4097, 2049), (700, 5), (1500, 5), (4096, 5),
+                                         (8192, 5), (8200, 600)])
+def test_rows_held_in_registers(stride, nseg):
+    """Rows as long as the threads hold and one item longer, either side of the number of segments that changes the
+    workgroup: the last segments' rows end inside a group of four items, are picked to the last item, have masked and NaN
+    entries (picked or not) or repeated and outlying picks; all other segments are empty."""
+    import torch
+    ngc = _ngc()
+    rng = np.random.default_rng(stride * 7 + nseg)
+    kinds = ["all", "few", "masked", "masked pick", "repeated"]
+    n_items, keep = np.zeros(nseg, np.int32), np.zeros(nseg, np.int32)
+    logits = np.full((nseg, stride), np.nan, np.float32)
+    sigma = np.full((nseg, stride), -7, np.int32)
+    first = nseg - len(kinds)
+    for i, kind in enumerate(kinds):
+        s, n = first + i, stride - i
+        x = rng.standard_normal(n).astype(np.float32)
+        x[rng.integers(n)] -= 60.0
+        if "masked" in kind:
+            x[rng.choice(n, 9, replace=False)] = [-np.inf] * 5 + [np.nan] * 4
+        order = rng.permutation(n)
+        finite = order[np.isfinite(x[order])]
+        k = {"all": n, "few": 3, "masked": n // 2}.get(kind, n // 3)
+        sigma[s, :k] = (finite if "masked" in kind else order)[:k]
+        if kind == "masked pick":
+            sigma[s, k // 2] = order[~np.isfinite(x[order])][0]
+        if kind == "repeated":
+            sigma[s, 1], sigma[s, k - 1] = sigma[s, 0], stride + 3
+        n_items[s], keep[s], logits[s, :n] = n, k, x
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    gout = rng.standard_normal(nseg).astype(np.float32)
+    d_n, d_s, d_k, d_g = d(n_items), d(sigma), d(keep), d(gout)
+    for shift in (0, 3):
+        flat = torch.full((nseg * stride + 4,), float("nan"), device="cuda")
+        x = flat[shift:shift + nseg * stride].view(nseg, stride)
+        x.copy_(d(logits))
+        out = torch.full((nseg,), float("nan"), device="cuda")
+        grad = torch.full((nseg, stride), float("nan"), device="cuda")
+        ws = torch.zeros(ngc.STATUS_WORDS * 4, dtype=torch.uint8, device="cuda")
+        print(f"[logprob-rows] held stride={stride} nseg={nseg} shift={shift}", flush=True)
+        ngc.ngc_subset_logprob(x, d_n, d_s, d_k, nseg, stride, stride, out, ws)
+        assert ngc.read_status(ws)[ngc.STATUS_BAD_SIGMA] == 2
+        ngc.ngc_subset_logprob_backward(x, d_n, d_s, d_k, nseg, stride, stride, stride, d_g, grad, ws)
+        lp, g = out.cpu().numpy(), grad.cpu().numpy()
+        assert (lp[:first] == 0).all() and np.isnan(g[:first]).all()
+        for i, kind in enumerate(kinds):
+            s = first + i
+            n, k = int(n_items[s]), int(keep[s])
+            assert np.isnan(g[s, n:]).all()
+            if kind == "repeated":
+                assert np.isfinite(lp[s]) and np.isfinite(g[s, :n]).all()
+                continue
+            if kind == "masked pick":
+                assert lp[s] == -np.inf
+                continue
+            row = logits[s, :n].astype(np.float64)
+            row[np.isnan(row)] = -np.inf
+            e = np.exp(row - row.max())
+            sig = sigma[s, :k]
+            rest = np.cumsum(e[sig][::-1])[::-1] + np.delete(e, sig).sum()
+            want = np.sum(row[sig] - row.max() - np.log(rest))
+            # one rounding of the total; a term is off by a few 2^-24 of up to 70
+            assert abs(lp[s] - want) <= 1e-6 * abs(want) + 1e-4, (kind, n, k)
+            c = np.cumsum(1.0 / rest)
+            w = -e * c[-1]
+            w[sig] = 1.0 - e[sig] * c
+            assert np.all(np.abs(g[s, :n] - gout[s] * w) <= abs(gout[s]) * (1e-5 * np.abs(w) + 2e-6)), (kind, n, k)
