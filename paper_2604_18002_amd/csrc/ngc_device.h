@@ -222,17 +222,22 @@ __device__ __forceinline__ float wave_above_scan_f(float v)
 // What the NW <= 16 waves of a workgroup have left in tmp[0], tmp[STRIDE], ... combined by every wave: a lane takes one
 // of the values, data-parallel steps within the row of 16 do the rest (2 to 4 of them; a loop over the values costs
 // every wave two or three instructions for each).
-template <int NW, int STRIDE, class T, class Op>
-__device__ __forceinline__ T across_waves(const T *tmp, Op op)
+template <int NW, class T, class Op>
+__device__ __forceinline__ T lanes_reduce(T v, Op op)      // of lanes that hold the NW values again and again
 {
     static_assert(NW == 4 || NW == 8 || NW == 16, "whole rows of lanes");
-    uint32_t u = __builtin_bit_cast(uint32_t, tmp[(lane_id() & (NW - 1)) * STRIDE]);
+    uint32_t u = __builtin_bit_cast(uint32_t, v);
     auto step = [&](uint32_t w) { u = __builtin_bit_cast(uint32_t, op(__builtin_bit_cast(T, u), __builtin_bit_cast(T, w))); };
     step(dpp::swapped<dpp::QUAD_XOR1>(u));
     step(dpp::swapped<dpp::QUAD_XOR2>(u));
     if constexpr (NW > 4) step(dpp::swapped<dpp::HALF_MIRROR>(u));
     if constexpr (NW > 8) step(dpp::swapped<dpp::MIRROR>(u));
     return __builtin_bit_cast(T, u);
+}
+template <int NW, int STRIDE, class T, class Op>
+__device__ __forceinline__ T across_waves(const T *tmp, Op op)
+{
+    return lanes_reduce<NW>(tmp[(lane_id() & (NW - 1)) * STRIDE], op);
 }
 // The sum of the values of the waves below this one, *total: of all.  ABOVE: of the waves above this one.
 template <int NW, int STRIDE, bool ABOVE = false, class T>

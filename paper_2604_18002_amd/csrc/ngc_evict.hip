@@ -841,26 +841,24 @@ __global__ __launch_bounds__(64) void lmem_total_kernel(const float *loss_layer,
 // In place: the row that ends at slot j comes from a slot >= j, and once one
 // kept row has moved every later one moves too (the kept list is ascending).
 // A workgroup walks the rows from the first one that moves (row_start) to the
-// end in tiles of TILE_ROWS destination rows.  The stores of a tile may only
-// follow a workgroup barrier that every wave reached after issuing its loads of
-// that tile (a row of the tile can be the source of another row of the same
-// tile); they never touch a row that a later tile still has to read (the
-// sources of tile i+1 lie at or beyond its first row), and earlier tiles are
-// done with their reads.  So the loop is software-pipelined over two register
-// buffers: after the barrier of tile i the loads of tile i+1 are issued, then
-// the index fetches of tile i+2, then the stores of tile i.  Every memory
-// operation inside the loop is unconditional (indices are clamped to the last
-// row, so a tile past the end re-reads rows that exist; full tiles store all
-// their rows), which lets the wait before the stores leave the younger loads in
-// flight: loads, index fetches and stores of three tiles overlap.  Only the
-// last, partial tile is stored under a row test.  16-byte accesses, one full
+// end in tiles of TILE_ROWS destination rows: all of a tile's reads, a barrier, all of
+// its writes, a barrier.  The first barrier is what correctness asks for (a row of the
+// tile can be the source of another row of the same tile; the sources of tile
+// i+1 lie at or beyond its first row, so earlier tiles' writes never touch them).  The second one is
+// what the memory asks for: a CU that reads and writes in turns, in bursts of a whole
+// tile, moves more than one whose waves mix both.  2048 segments of 4096-8192 rows, us per round: loads of tile i+1
+// and stores of tile i in flight together (two register buffers) 956; stores held back until those loads have arrived 951, and
+// with a barrier after that 934; this loop 923, without its second barrier 970.  It holds half the registers, so the
+// 512-thread workgroups take 8 rows a thread (896 segments of 700 rows 78.6 -> 74.0; 3584 of 4096 rows, now in 1024-thread
+// workgroups, 946 -> 900).  The row indices come from LDS.  16-byte accesses, one full
 // row per ROW_BYTES/16 consecutive lanes, K and V together; all of them carry
 // the nontemporal hint (every row is touched once).  Offsets inside a segment
 // are 32-bit (the host checks cap * ROW_BYTES < 2^31).
-
-template <int ROW_BYTES, int THREADS, int UNROLL>
+//
+// POWER_OF_TWO: `block` is one, and the item of a row a shift instead of a division (20 instructions a row).
+template <int ROW_BYTES, int THREADS, int UNROLL, bool POWER_OF_TWO, class Index>
 __device__ __forceinline__ void compact_kv_inplace(unsigned char *kbase, unsigned char *vbase,
-                                                   const int32_t *kept, int rows_new, int row_start, int block)
+                                                   const Index *kept, int rows_new, int row_start, int block)
 {
     constexpr int PIECES = ROW_BYTES / 16;           // 16-byte pieces per row
     constexpr int ROWS_PER_STEP = THREADS / PIECES;  // rows covered by one load per thread
@@ -869,6 +867,7 @@ __device__ __forceinline__ void compact_kv_inplace(unsigned char *kbase, unsigne
     const uint32_t col = (uint32_t)(threadIdx.x % PIECES) * 16u;
     const int last = rows_new - 1;
     if (row_start >= rows_new) return;   // workgroup-uniform
+    const int shift = __builtin_ctz(block);
 
     // source rows of this thread's rows of a tile; rows past the end take the last row's source
     auto sources = [&](int tile, int (&src)[UNROLL]) {
@@ -876,8 +875,12 @@ __device__ __forceinline__ void compact_kv_inplace(unsigned char *kbase, unsigne
         for (int u = 0; u < UNROLL; ++u) {
             int r = tile + u * ROWS_PER_STEP + rsub;
             r = r < last ? r : last;
-            const int item = r / block;
-            src[u] = kept[item] * block + (r - item * block);
+            if constexpr (POWER_OF_TWO) {
+                src[u] = ((int)kept[r >> shift] << shift) + (r & (block - 1));
+            } else {
+                const int item = r / block;
+                src[u] = (int)kept[item] * block + (r - item * block);
+            }
         }
     };
     auto load = [&](const int (&src)[UNROLL], u32x4 (&kb)[UNROLL], u32x4 (&vb)[UNROLL]) {
@@ -909,25 +912,20 @@ __device__ __forceinline__ void compact_kv_inplace(unsigned char *kbase, unsigne
     };
 
     int src[UNROLL];
-    int tile = row_start;
-    u32x4 ka[UNROLL], va[UNROLL], kb[UNROLL], vb[UNROLL];
-    sources(tile, src);
-    load(src, ka, va);
-    sources(tile + TILE_ROWS, src);
-    // one copy of the step per buffer, so that each buffer is named by constants and stays in registers
-    while (true) {
-        __syncthreads();                       // every wave has issued its loads of `tile`
-        if (tile + TILE_ROWS > rows_new) { store_tail(tile, ka, va); break; }
-        load(src, kb, vb);                     // tile + 1
-        sources(tile + 2 * TILE_ROWS, src);    // tile + 2
-        store_full(tile, ka, va);
-        tile += TILE_ROWS;
-        __syncthreads();
-        if (tile + TILE_ROWS > rows_new) { store_tail(tile, kb, vb); break; }
-        load(src, ka, va);
-        sources(tile + 2 * TILE_ROWS, src);
+    u32x4 kb[UNROLL], vb[UNROLL];
+    sources(row_start, src);
+    for (int tile = row_start; ; tile += TILE_ROWS) {
+        load(src, kb, vb);
+        sources(tile + TILE_ROWS, src);
+        __builtin_amdgcn_sched_barrier(0);
+        __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();                       // the whole tile has arrived, in every wave
+        if (tile + TILE_ROWS >= rows_new) {
+            store_tail(tile, kb, vb);
+            break;
+        }
         store_full(tile, kb, vb);
-        tile += TILE_ROWS;
+        __syncthreads();                       // all of it is on its way before the next tile is asked for
     }
 }
 
@@ -1217,7 +1215,7 @@ __global__ __launch_bounds__(POOL_THREADS) void evict_pooled_kernel(SelectArgs a
         Kh = Kh < a.max_keep ? Kh : a.max_keep;
         const size_t seg_off = (size_t)(seg_first + h) * cap * ROW_BYTES;
         const int32_t *kept = a.kept_out + (size_t)(seg_first + h) * a.max_keep;
-        compact_kv_inplace<ROW_BYTES, THREADS, 4>(reinterpret_cast<unsigned char *>(a.k) + seg_off,
+        compact_kv_inplace<ROW_BYTES, THREADS, 4, true>(reinterpret_cast<unsigned char *>(a.k) + seg_off,
                                                   reinterpret_cast<unsigned char *>(a.v) + seg_off,
                                                   kept, Kh, 0, 1);
         if (a.pos) compact_pos_inplace<THREADS>(a.pos + (size_t)(seg_first + h) * cap, kept, Kh, 0, 1);
@@ -1231,37 +1229,34 @@ __global__ __launch_bounds__(POOL_THREADS) void evict_pooled_kernel(SelectArgs a
 template <int THREADS, int ROW_BYTES, int UNROLL>
 __device__ __forceinline__ void evict_segment(const SelectArgs &a, int seg, unsigned char *smem_raw, int *misc)
 {
-    select_segment<THREADS, ROW_BYTES>(a, seg, smem_raw);
-    if (a.k == nullptr) return;   // selection only
-
-    if (threadIdx.x == 0) misc[MISC_FIRST] = 0x7FFFFFFF;
-    __syncthreads();   // publishes misc[] and this workgroup's kept_out writes
-    const int K = misc[MISC_KEPT];
-    const int rows_new = misc[MISC_ROWS];
-    const int32_t *kept = a.kept_out + (size_t)seg * a.max_keep;
-    if (a.unordered) {   // rows were moved right after the kept list was known
+    Selected sel;
+    select_keep<THREADS, ROW_BYTES>(a, seg, smem_raw, sel);
+    if (a.k != nullptr) {
+        __syncthreads();   // publishes misc[], the ascending list and this workgroup's kept_out writes
+        const int rows_new = misc[MISC_ROWS], first = misc[MISC_FIRST];   // kept is ascending, kept[j] >= j
         if (threadIdx.x == 0) a.len_out[seg] = rows_new;
-        return;
+        if (first < sel.K) {
+            const size_t seg_off = (size_t)seg * a.g.cap * ROW_BYTES;
+            unsigned char *kbase = reinterpret_cast<unsigned char *>(a.k) + seg_off;
+            unsigned char *vbase = reinterpret_cast<unsigned char *>(a.v) + seg_off;
+            int32_t *pos = a.pos ? a.pos + (size_t)seg * a.g.cap : nullptr;
+            if (a.unordered) {
+                fill_holes_inplace<ROW_BYTES, THREADS, 4>(kbase, vbase, pos, sel.ascending, sel.K);
+            } else {
+                const int row_start = first * a.g.block;
+                if ((a.g.block & (a.g.block - 1)) == 0)
+                    compact_kv_inplace<ROW_BYTES, THREADS, UNROLL, true>(kbase, vbase, sel.ascending, rows_new, row_start,
+                                                                         a.g.block);
+                else
+                    compact_kv_inplace<ROW_BYTES, THREADS, UNROLL, false>(kbase, vbase, sel.ascending, rows_new, row_start,
+                                                                          a.g.block);
+                if (pos)
+                    compact_pos_inplace<THREADS>(pos, a.kept_out + (size_t)seg * a.max_keep, rows_new, row_start, a.g.block);
+            }
+        }
     }
-    // first item that changes place (kept is ascending and kept[j] >= j)
-    {
-        int mine = K;
-        for (int j = threadIdx.x; j < K; j += THREADS)
-            if (kept[j] != j) { mine = j; break; }
-        if (mine < K) atomicMin(&misc[MISC_FIRST], mine);
-    }
-    __syncthreads();
-    const int first = misc[MISC_FIRST];
-    if (first < K) {
-        const int row_start = first * a.g.block;
-        const size_t seg_off = (size_t)seg * a.g.cap * ROW_BYTES;
-        compact_kv_inplace<ROW_BYTES, THREADS, UNROLL>(reinterpret_cast<unsigned char *>(a.k) + seg_off,
-                                                       reinterpret_cast<unsigned char *>(a.v) + seg_off,
-                                                       kept, rows_new, row_start, a.g.block);
-        if (a.pos)
-            compact_pos_inplace<THREADS>(a.pos + (size_t)seg * a.g.cap, kept, rows_new, row_start, a.g.block);
-    }
-    if (threadIdx.x == 0) a.len_out[seg] = rows_new;
+    __syncthreads();       // the ascending list is free to be sorted
+    select_score<THREADS>(a, seg, smem_raw, sel);
 }
 
 // The 1024-thread kernel (the host picks it for large segments, see ngc_evict) is persistent: one workgroup fills a CU, the grid
@@ -1618,11 +1613,12 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
     keep_cap = (keep_cap + 7) & ~7;
     const int items_cap_al = (items_cap + 3) & ~3;
     // Workgroup size and rows in flight per thread, all measured.  A round that moves rows in order is a copy with a
-    // selection in front: the copy wants as many bytes in flight per compute unit as registers allow, which is one
-    // 1024-thread workgroup per CU from 4097 rows per segment up (2048 segments of 4096-8192 rows: 975 us, 1046 with
-    // 512 threads; the size follows the rows of a segment, not its items: with blocks of rows as items the selection is
-    // small and the copy is all there is), 512 threads from 513 rows up (1024 segments of 1500 rows: 171 us, 177 with
-    // 256; 16 of 1500: 26.7, 30.8) and 256 below (1024 of 300: 42, 47 with 512).  A round that only selects, or fills
+    // selection in front, and the size follows the rows of a segment, not its items.  One 1024-thread workgroup per CU, whose
+    // reads and writes take turns, copies best, but has nothing beside it while it selects: it is taken beyond 4096 rows
+    // and, where there are more segments than CUs to spread them over twice, from 1281 rows up (us with 512 and 1024
+    // threads: 2048 segments of 4096-8192 rows 1023 and 924, 3584 of 4096 940 and 900, 3584 of 1800 649 and 600, 1024 of 1500 169 and
+    // 165, of 1200 138 and 141; 512 of 2000 120 and 120; 400 of 3000 140 and 140; 64 of 3000 46 and 49).  512 threads from
+    // 513 rows up (896 of 700: 74, 77 with 256), 256 below (896 of 300: 35 and 38).  A round that only selects, or fills
     // holes (few rows move), is bound by the selection's waits; two 512-thread workgroups per CU cover each other's up to
     // the 8192 rows at which two of them still fit in LDS (1024 segments of 8192: 96 us, 135 with 1024 threads), 256
     // threads up to 2048 rows (1024 of 1500: 25 us, 28 with 512) unless there are too few segments to fill the chip
@@ -1630,7 +1626,8 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
     const bool move_rows = !(p->flags & NGC_EVICT_SELECT_ONLY);
     const bool copy_bound = move_rows && !(p->flags & NGC_EVICT_UNORDERED);
     const int few = (copy_bound || nseg <= 512) ? 512 : 2048;
-    const int threads = c->cap > (copy_bound ? 4096 : 8192) ? 1024 : (c->cap > few ? 512 : 256);
+    const int many = !copy_bound ? 8192 : nseg > 512 ? 1280 : 4096;
+    const int threads = c->cap > many ? 1024 : (c->cap > few ? 512 : 256);
     const int rank_cap = rank_capacity(threads, items_cap_al, keep_cap);
     const size_t lds = select_lds_bytes(threads, items_cap_al, keep_cap, rank_cap);
     if (lds > 160 * 1024) return NGC_EUNSUPPORTED;
@@ -1654,8 +1651,8 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
 #define NGC_PICK(T, U) ((c->D == 128) ? reinterpret_cast<const void *>(&evict_kernel<T, 256, U>) \
                                       : reinterpret_cast<const void *>(&evict_kernel<T, 128, U>))
     if (threads == 1024) fn = NGC_PICK(1024, 4);
-    else if (threads == 512) fn = NGC_PICK(512, 2);
-    else fn = NGC_PICK(256, 4);
+    else if (threads == 512) fn = NGC_PICK(512, 8);
+    else fn = NGC_PICK(256, 6);
 #undef NGC_PICK
     if (lds > 64 * 1024)
         NGC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));

@@ -46,7 +46,10 @@ __global__ __launch_bounds__(THREADS) void paged_evict_kernel(SelectArgs a, Page
     int *misc = reinterpret_cast<int *>(reinterpret_cast<uint32_t *>(smem_raw) + a.items_cap + HIST);
     const int seg = a.seg0 + blockIdx.x;
 
-    select_segment<THREADS, 256>(a, seg, smem_raw);   // a.k == nullptr: the row size is not used
+    Selected sel;
+    select_keep<THREADS, 256>(a, seg, smem_raw, sel);   // a.k == nullptr: the row size is not used
+    __syncthreads();
+    select_score<THREADS>(a, seg, smem_raw, sel);
     if (pa.table == nullptr) return;                  // selection only
     __syncthreads();   // misc[], this workgroup's kept_out writes, and the end of all reads of the codes
 

@@ -504,13 +504,10 @@ __device__ __forceinline__ bool rank_items(const uint32_t *code, int N, int K, u
     biggest = wave_reduce(biggest, OpMaxU{});
     if (lane_id() == NGC_WAVE - 1) { tmp[2 * wave_id()] = upto; tmp[2 * wave_id() + 1] = biggest; }
     __syncthreads();
-    uint32_t run = upto - sum, unmasked = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        if (w < wave_id()) run += tmp[2 * w];
-        unmasked += tmp[2 * w];
-        biggest = tmp[2 * w + 1] > biggest ? tmp[2 * w + 1] : biggest;
-    }
+    uint32_t unmasked;
+    uint32_t run = below_waves<NW, 2>(tmp, &unmasked) + (upto - sum);
+    biggest = across_waves<NW, 2>(tmp + 1, OpMaxU{});
+    biggest = (uint32_t)__builtin_amdgcn_readfirstlane((int)biggest);
     if (biggest > (uint32_t)BUCKET_LIMIT || (uint32_t)K > unmasked) return false;
 #pragma unroll
     for (int i = 0; i < PER / 4; ++i) {
@@ -552,15 +549,15 @@ __device__ __forceinline__ bool rank_items(const uint32_t *code, int N, int K, u
     return true;
 }
 
-// Log-probability of the kept items in sampled order (Eq. 2) from their logits x(j) (any order of calls, -inf for a masked
-// pick), U = this thread's share of the mass never picked.  stage: K floats of LDS.  Whole workgroup; every thread gets it.
-template <int THREADS, class Logit>
-__device__ __forceinline__ float sigma_logprob(Logit x, int K, float smax, float unpicked, float *stage, float *tmp)
+// Log-probability of the kept items in sampled order (Eq. 2) from their weights e(j) = exp(logit - largest logit) in LDS (0
+// for a masked pick), U = this thread's share of the mass never picked.  Whole workgroup; every thread gets it.
+constexpr int LOGPROB_CHUNK = 8;   // picks a thread keeps in registers between its two passes
+
+template <int THREADS, class Weight>
+__device__ __forceinline__ float sigma_logprob(Weight weight, int K, float unpicked, float *tmp)
 {
     constexpr int NW = THREADS / NGC_WAVE;
     const int tid = fresh_thread_index<THREADS>();
-    for (int j = tid; j < K; j += THREADS) stage[j] = exp_shifted(x(j) - smax);
-    __syncthreads();
     const int chunk = (K + THREADS - 1) / THREADS;
     const int nchunks = (K + chunk - 1) / chunk;
     // thread 0 owns the LAST chunk, so an ordinary exclusive scan over threads yields the mass of everything picked
@@ -568,39 +565,57 @@ __device__ __forceinline__ float sigma_logprob(Logit x, int K, float smax, float
     const int cidx = nchunks - 1 - tid;
     const int j_lo = cidx * chunk;
     const int j_hi = (cidx >= 0) ? ((j_lo + chunk < K) ? j_lo + chunk : K) : 0;
-    float mass = 0.f;
-    if (cidx >= 0)
-        for (int j = j_lo; j < j_hi; ++j) mass += stage[j];
+    float mass = 0.f, e[LOGPROB_CHUNK];
+    if (cidx >= 0) {
+        if (chunk <= LOGPROB_CHUNK) {              // uniform; all reads at once
+#pragma unroll
+            for (int i = 0; i < LOGPROB_CHUNK; ++i)
+                if (i < chunk) e[i] = weight(j_lo + i < K ? j_lo + i : K - 1);
+#pragma unroll
+            for (int i = 0; i < LOGPROB_CHUNK; ++i)
+                if (i < chunk) {
+                    if (j_lo + i >= K) e[i] = 0.f;
+                    mass += e[i];
+                }
+        } else {
+            for (int j = j_lo; j < j_hi; ++j) mass += weight(j);
+        }
+    }
     const float incl = wave_incl_scan_f(mass);
     const float others = wave_sum_f(unpicked);
     if (lane_id() == NGC_WAVE - 1) { tmp[2 * wave_id()] = incl; tmp[2 * wave_id() + 1] = others; }
     __syncthreads();
-    float R = 0.f, never = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-        if (w < wave_id()) R += tmp[2 * w];
-        never += tmp[2 * w + 1];
-    }
+    float picked;
+    const float below = below_waves<NW, 2>(tmp, &picked);
+    const float never = across_waves<NW, 2>(tmp + 1, OpAdd{});
     __syncthreads();
-    float prev = __shfl_up(incl, 1, NGC_WAVE);   // sum of the lanes below, no subtraction
-    if (lane_id() == 0) prev = 0.f;
-    R = never + (R + prev);
+    float R = never + (below + lane_below_f(incl));   // (sum of the lanes below, no subtraction)
     LogRatio ratio;
     float logs = 0.f;
     if (cidx >= 0) {
-        int n = 0;
-        for (int j = j_hi - 1; j >= j_lo; --j) {
-            R += stage[j];
-            ratio.times(stage[j], R);            // a masked pick makes log p = -inf
-            if (++n == LogRatio::MAX_PICKS) { logs += ratio.log(); ratio = LogRatio{}; n = 0; }
+        if (chunk <= LOGPROB_CHUNK) {
+#pragma unroll
+            for (int i = LOGPROB_CHUNK - 1; i >= 0; --i)
+                if (i < chunk) {
+                    R += e[i];
+                    if (j_lo + i < K) ratio.times(e[i], R);      // a masked pick makes log p = -inf
+                }
+        } else {
+            int n = 0;
+            for (int j = j_hi - 1; j >= j_lo; --j) {
+                const float w = weight(j);
+                R += w;
+                ratio.times(w, R);
+                if (++n == LogRatio::MAX_PICKS) { logs += ratio.log(); ratio = LogRatio{}; n = 0; }
+            }
         }
+        logs += ratio.log();
     }
-    const float share = wave_sum_f(logs + ratio.log());
+    const float share = wave_sum_f(logs);
     if (lane_id() == 0) tmp[wave_id()] = share;
     __syncthreads();
-    double total = 0.0;      // thousands for a long sequence: rounded once
-#pragma unroll
-    for (int w = 0; w < NW; ++w) total += (double)tmp[w];
+    // thousands for a long sequence: rounded once
+    const double total = wave_sum_d(lane_id() < NW ? (double)tmp[lane_id()] : 0.0);
     __syncthreads();
     return (float)total;
 }
@@ -610,21 +625,36 @@ constexpr int MISC_KEPT = 35;   // items kept in this segment
 constexpr int MISC_ROWS = 36;   // rows in use after compaction
 constexpr int MISC_FIRST = 37;  // first item that changes place
 
-// Selection of one segment by the whole workgroup.  Leaves the kept count and
-// the new row count in misc[MISC_KEPT], misc[MISC_ROWS] (valid after the next
-// barrier).  Every thread of the workgroup returns at the same point.
+// The selection of one segment by the whole workgroup, in two parts: select_keep() decides which items stay, writes their
+// list and leaves what the second part goes on with; select_score() brings the kept items into sampled order where that is
+// not known yet, writes it and its log-probability.  What moves rows stands between the two: a workgroup's copy then starts
+// before its sums and logarithms, and these run while the last rows are on their way.
+struct Selected {
+    int K;                  // items kept (0: everything has been written)
+    uint16_t *ascending;    // LDS: their indices, ascending (before select_score())
+    uint16_t *sampled;      // LDS: in sampled order, or nullptr: to be sorted
+    uint32_t cmax, thr;     // largest code and that of the last kept item (to be sorted)
+    bool weighted;          // the code array holds exp(logit - smax) of every item instead of its code
+    bool wide;              // the logits take the wide-range arithmetic
+    float smax;             // largest logit
+    float unpicked;         // this thread's share of the sum of exp(logit - smax) over the items not kept
+    LogSum unpicked_w;      // the same on the wide-range route
+};
+
+// Besides, it leaves the kept count, the new row count and the first item that changes place in misc[MISC_KEPT],
+// misc[MISC_ROWS], misc[MISC_FIRST] (valid after the next barrier).  Every thread of the workgroup returns at the same point.
 template <int THREADS, int ROW_BYTES>
-__device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, unsigned char *smem_raw)
+__device__ __forceinline__ void select_keep(const SelectArgs &a, int seg, unsigned char *smem_raw, Selected &out)
 {
     constexpr int NW = THREADS / NGC_WAVE;
     constexpr int HIST = (SEL_BINS > SORT_BINS * NW) ? SEL_BINS : SORT_BINS * NW;
+    constexpr int HELD = 2;      // groups of four logits a thread keeps until the kept items are known
     uint32_t *code = reinterpret_cast<uint32_t *>(smem_raw);
     uint32_t *hist = code + a.items_cap;
     int *misc = reinterpret_cast<int *>(hist + HIST);            // 64 ints
     uint16_t *idxA = reinterpret_cast<uint16_t *>(misc + 64);
     uint16_t *idxB = idxA + a.keep_cap;                           // max(keep_cap, rank_cap) entries
     uint32_t *kept_bits = reinterpret_cast<uint32_t *>(idxB + (a.rank_cap > a.keep_cap ? a.rank_cap : a.keep_cap));
-    float *fmisc = reinterpret_cast<float *>(misc);
 
     const int tid = fresh_thread_index<THREADS>(), lane = tid & (NGC_WAVE - 1), wv = tid >> 6;
     int l, b, h;
@@ -642,12 +672,13 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
     const float *row = a.logits + (size_t)seg * a.logit_stride;
     const bool want_logp = a.logp_out != nullptr;
     const bool want_sort = want_logp || a.sigma_out != nullptr;
-    const bool fill_holes = a.unordered && a.k != nullptr;
 
+    out.K = K;
     if (K == 0) {
         if (tid == 0) {
             misc[MISC_KEPT] = 0;
             misc[MISC_ROWS] = 0;
+            misc[MISC_FIRST] = 0x7FFFFFFF;
             if (want_logp) a.logp_out[seg] = 0.f;
         }
         return;
@@ -662,9 +693,14 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
     // ---- 1. keys ----------------------------------------------------------
     float smax = -INFINITY, neg_smin = -INFINITY;   // over the unmasked entries (a NaN compares false everywhere)
     uint32_t cmax = 0, neg_cmin = 0;                // largest code; complement of the smallest code of a finite key
-    for (int quad = tid; 4 * quad < N; quad += THREADS) {
+    f32x4 held[HELD] = {};
+    int group = 0;
+#pragma unroll 1
+    for (int quad = tid; 4 * quad < N; quad += THREADS, ++group) {
         float s[4], key[4];
         keys_of_quad(row, N, quad, a.na, l, b, h, s, key);
+        if (group == 0) held[0] = f32x4{s[0], s[1], s[2], s[3]};
+        if (group == 1) held[1] = f32x4{s[0], s[1], s[2], s[3]};
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             if (4 * quad + i < N) {
@@ -688,14 +724,11 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
         if (lane == 0)
             reinterpret_cast<u32x4 *>(umisc)[wv] = u32x4{__float_as_uint(smax), __float_as_uint(neg_smin), cmax, neg_cmin};
         __syncthreads();
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const u32x4 m = reinterpret_cast<const u32x4 *>(umisc)[w];
-            smax = fmaxf(smax, __uint_as_float(m[0]));
-            neg_smin = fmaxf(neg_smin, __uint_as_float(m[1]));
-            cmax = m[2] > cmax ? m[2] : cmax;
-            neg_cmin = m[3] > neg_cmin ? m[3] : neg_cmin;
-        }
+        const u32x4 m = reinterpret_cast<const u32x4 *>(umisc)[lane & (NW - 1)];
+        smax = lanes_reduce<NW>(__uint_as_float(m[0]), OpMaxF{});
+        neg_smin = lanes_reduce<NW>(__uint_as_float(m[1]), OpMaxF{});
+        cmax = lanes_reduce<NW>(m[2], OpMaxU{});
+        neg_cmin = lanes_reduce<NW>(m[3], OpMaxU{});
         __syncthreads();
         if (want_logp) {
             wide = smax > -INFINITY && smax + neg_smin > NGC_WIDE_SPREAD;
@@ -703,11 +736,23 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
         }
     }
 
+    if (tid == 0) misc[MISC_FIRST] = 0x7FFFFFFF;       // (a barrier follows on every route)
+    int first_moved = -1;                              // of this wave's items (uniform)
+    auto note_moved = [&](bool sel, int slot, int t) {
+        if (first_moved >= 0) return;
+        const uint64_t moved = __ballot(sel && slot != t);
+        if (moved) first_moved = __builtin_amdgcn_readlane(slot, __builtin_ctzll(moved));
+    };
+
     // Ranking by buckets where it applies (steps 2''-4'').  Otherwise -- many equal keys, masked items kept, sigma not
     // wanted, no room in LDS -- radix select, ballot compaction, sort (steps 2-4), or up to SMALL_ITEMS items ranking by all pairs (2'-4').
     // Selection only, 896 segments, microseconds with (without) the buckets: 64 items 11.6 (11.6), 128: 11.7 (13.5),
     // 256: 12.0 (19.8), 300: 13.4 (21.2), 700: 17.2 (22.2); 3584 segments of 4096: 119 (148).
-    uint16_t *src = idxA;   // the kept items in sampled order, once known
+    out.ascending = idxA;
+    out.sampled = nullptr;
+    out.cmax = cmax;
+    out.thr = 0;
+    out.weighted = false;
     float unpicked = 0.f;   // sum of exp(s - smax) over items not kept (for logp)
     LogSum unpicked_w = ls_empty();   // the same sum on the wide-range route
     if (try_rank && rank_items<THREADS>(code, N, K, cmax, ~neg_cmin, hist, reinterpret_cast<uint32_t *>(misc), idxB, idxA,
@@ -730,33 +775,49 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
             const uint64_t sel_bits = ((uint64_t)m[1] << 32) | m[0];
             const int t = w * 64 + lane;
             const bool sel = (sel_bits >> lane) & 1u;
+            const int slot = base + popc_below(sel_bits);
             if (sel) {
-                const int slot = base + popc_below(sel_bits);
                 kept_row[slot] = t;
-                if (fill_holes) ascending[slot] = (uint16_t)t;
+                ascending[slot] = (uint16_t)t;
                 if (slot == K - 1) misc[34] = t;   // highest kept index
-            } else if (t < N && want_logp) {
-                float x = row[t];
-                if (x != x) x = -INFINITY;
-                if (wide) unpicked_w = ls_add_term(unpicked_w, x);
-                else unpicked += exp_shifted(x - smax);
             }
+            note_moved(sel, slot, t);
             base += __popcll(sel_bits);
         }
+        // The weights of all items where their codes stood (nobody reads those any more), from the logits in registers; the
+        // groups beyond those are read again.
+        if (want_logp) {
+            group = 0;
+#pragma unroll 1
+            for (int quad = tid; 4 * quad < N; quad += THREADS, ++group) {
+                f32x4 x = group == 0 ? held[0] : held[1];
+                if (group >= HELD) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        x[i] = 4 * quad + i < N ? row[4 * quad + i] : -INFINITY;
+                        if (x[i] != x[i]) x[i] = -INFINITY;
+                    }
+                }
+                const uint32_t sel_bits = kept_bits[quad >> 3] >> ((quad & 7) * 4);
+                if (wide) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (!(sel_bits >> i & 1u)) unpicked_w = ls_add_term(unpicked_w, x[i]);
+                } else {
+                    f32x4 e;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        e[i] = exp_shifted(x[i] - smax);
+                        unpicked += (sel_bits >> i & 1u) ? 0.f : e[i];
+                    }
+                    reinterpret_cast<f32x4 *>(code)[quad] = e;
+                }
+            }
+            out.weighted = !wide;
+        }
         __syncthreads();
-        if (tid == 0) {
-            const int last_item = misc[34];
-            const int last_rows = (last_item == N - 1) ? (n - (N - 1) * a.g.block) : a.g.block;
-            misc[MISC_KEPT] = K;
-            misc[MISC_ROWS] = (K - 1) * a.g.block + last_rows;
-        }
-        if (fill_holes) {
-            const size_t seg_off = (size_t)seg * a.g.cap * ROW_BYTES;
-            fill_holes_inplace<ROW_BYTES, THREADS, 4>(reinterpret_cast<unsigned char *>(a.k) + seg_off,
-                                                      reinterpret_cast<unsigned char *>(a.v) + seg_off,
-                                                      a.pos ? a.pos + (size_t)seg * a.g.cap : nullptr, ascending, K);
-        }
-        src = idxA;
+        out.ascending = ascending;
+        out.sampled = idxA;
     } else if (N > SMALL_ITEMS) {
         // ---- 2. radix select of the K-th largest code -------------------------
         int need;   // items equal to the threshold that are kept
@@ -779,7 +840,7 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
         __syncthreads();
         int gt_base = 0, eq_base = 0;
         for (int w = 0; w < wv; ++w) { gt_base += misc[w]; eq_base += misc[16 + w]; }
-        unpicked = 0.f;
+        out.thr = thr;
         int32_t *kept_row = a.kept_out + (size_t)seg * a.max_keep;
         for (int t0 = w_begin; t0 < w_end; t0 += NGC_WAVE) {
             const int t = t0 + lane;
@@ -790,10 +851,11 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
             const int gt_before = gt_base + popc_below(bgt);
             const int eq_before = eq_base + popc_below(beq);
             const bool sel = is_gt || (is_eq && eq_before < need);
+            const int slot = gt_before + (eq_before < need ? eq_before : need);
+            note_moved(sel, slot, t);
             if (sel) {
-                const int slot = gt_before + (eq_before < need ? eq_before : need);
                 kept_row[slot] = t;
-                if (want_sort || fill_holes) idxA[slot] = (uint16_t)t;
+                idxA[slot] = (uint16_t)t;
                 if (slot == K - 1) misc[34] = t;   // highest kept index
             } else if (in && want_logp) {
                 float x = row[t];
@@ -805,24 +867,6 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
             eq_base += __popcll(beq);
         }
         __syncthreads();
-        if (tid == 0) {
-            const int last_item = misc[34];
-            const int last_rows = (last_item == N - 1) ? (n - (N - 1) * a.g.block) : a.g.block;
-            misc[MISC_KEPT] = K;
-            misc[MISC_ROWS] = (K - 1) * a.g.block + last_rows;
-        }
-        if (fill_holes) {
-            // idxA still holds the kept list in ascending order (the sort below permutes it)
-            const size_t seg_off = (size_t)seg * a.g.cap * ROW_BYTES;
-            fill_holes_inplace<ROW_BYTES, THREADS, 4>(reinterpret_cast<unsigned char *>(a.k) + seg_off,
-                                                      reinterpret_cast<unsigned char *>(a.v) + seg_off,
-                                                      a.pos ? a.pos + (size_t)seg * a.g.cap : nullptr, idxA, K);
-        }
-        if (want_sort) {
-
-            // ---- 4. sigma: stable sort of the kept indices by descending code ------
-            src = sort_by_code_desc<THREADS>([&](uint16_t t) { return code[t]; }, K, cmax, thr, idxA, idxB, hist, misc);
-        }
     } else {
         // ---- 2'-4'. few items: rank every key by counting ---------------------
         // rank_t = number of keys that precede key t in the total order (larger code, or equal code and
@@ -854,10 +898,11 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
                 if (w < wv) before += c;
                 total += c;
             }
+            const int slot = before + popc_below(bal);
+            note_moved(sel, slot, t);
             if (sel) {
-                const int slot = before + popc_below(bal);
                 kept_row[slot] = t;
-                idxA[slot] = (uint16_t)t;        // ascending (the unordered arrangement reads it)
+                idxA[slot] = (uint16_t)t;        // ascending
                 idxB[rank] = (uint16_t)t;        // sampled order
                 if (slot == K - 1) misc[34] = t; // highest kept index
             } else if (in && want_logp) {
@@ -869,22 +914,43 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
             kept_so_far += total;
             __syncthreads();
         }
-        if (tid == 0) {
-            const int last_item = misc[34];
-            const int last_rows = (last_item == N - 1) ? (n - (N - 1) * a.g.block) : a.g.block;
-            misc[MISC_KEPT] = K;
-            misc[MISC_ROWS] = (K - 1) * a.g.block + last_rows;
-        }
-        if (fill_holes) {
-            const size_t seg_off = (size_t)seg * a.g.cap * ROW_BYTES;
-            fill_holes_inplace<ROW_BYTES, THREADS, 4>(reinterpret_cast<unsigned char *>(a.k) + seg_off,
-                                                      reinterpret_cast<unsigned char *>(a.v) + seg_off,
-                                                      a.pos ? a.pos + (size_t)seg * a.g.cap : nullptr, idxA, K);
-        }
-        src = idxB;
+        out.sampled = idxB;
     }
-    if (!want_sort) return;
-    // the sorted list is in `src` (idxA or idxB, depending on the number of passes)
+    if (first_moved >= 0 && lane == 0) atomicMin(&misc[MISC_FIRST], first_moved);
+    if (tid == 0) {
+        const int last_item = misc[34];
+        const int last_rows = (last_item == N - 1) ? (n - (N - 1) * a.g.block) : a.g.block;
+        misc[MISC_KEPT] = K;
+        misc[MISC_ROWS] = (K - 1) * a.g.block + last_rows;
+    }
+    out.wide = wide;
+    out.smax = smax;
+    out.unpicked = unpicked;
+    out.unpicked_w = unpicked_w;
+}
+
+// The second part.  A barrier stands between the last use of `ascending` and this.  Returns at once if nothing was kept or
+// neither sigma nor its log-probability is wanted.
+template <int THREADS>
+__device__ __forceinline__ void select_score(const SelectArgs &a, int seg, unsigned char *smem_raw, const Selected &kept)
+{
+    constexpr int NW = THREADS / NGC_WAVE;
+    constexpr int HIST = (SEL_BINS > SORT_BINS * NW) ? SEL_BINS : SORT_BINS * NW;
+    const bool want_logp = a.logp_out != nullptr;
+    const int K = kept.K;
+    if (K == 0 || (!want_logp && a.sigma_out == nullptr)) return;
+    uint32_t *code = reinterpret_cast<uint32_t *>(smem_raw);
+    uint32_t *hist = code + a.items_cap;
+    int *misc = reinterpret_cast<int *>(hist + HIST);
+    float *fmisc = reinterpret_cast<float *>(misc);
+    const int tid = fresh_thread_index<THREADS>();
+    const uint16_t *src = kept.sampled;
+    if (src == nullptr) {
+        // ---- 4. sigma: stable sort of the kept indices by descending code ------
+        uint16_t *idxA = reinterpret_cast<uint16_t *>(misc + 64);
+        src = sort_by_code_desc<THREADS>([&](uint16_t t) { return code[t]; }, K, kept.cmax, kept.thr, idxA,
+                                         idxA + a.keep_cap, hist, misc);
+    }
     if (a.sigma_out) {
         int32_t *sig_row = a.sigma_out + (size_t)seg * a.max_keep;
         for (int j = tid; j < K; j += THREADS) sig_row[j] = (int32_t)src[j];
@@ -892,22 +958,28 @@ __device__ __forceinline__ void select_segment(const SelectArgs &a, int seg, uns
     if (!want_logp) return;
 
     // ---- 5. log-probability of sigma (Eq. 2) -------------------------------
-    // The terms of the picked items are gathered into LDS first (over the key codes, which are no longer needed), all
-    // loads in flight at once: the serial chunk loops then never wait for a gather.
     float *ds = reinterpret_cast<float *>(code);
-    auto logit = [&](int j) {
-        const float x = row[src[j]];
-        return (x != x) ? -INFINITY : x;
-    };
-    if (wide) {                          // that route works on the logits as they came
-        for (int j = tid; j < K; j += THREADS) ds[j] = logit(j);
+    float lp;
+    if (kept.weighted) {
+        lp = sigma_logprob<THREADS>([&](int j) { return ds[src[j]]; }, K, kept.unpicked, fmisc);
+    } else {
+        // The terms of the picked items are gathered into LDS first (over the key codes, which are no longer needed), all
+        // loads in flight at once: the serial chunk loops then never wait for a gather.
+        const float *row = a.logits + (size_t)seg * a.logit_stride;
+        auto logit = [&](int j) {
+            const float x = row[src[j]];
+            return (x != x) ? -INFINITY : x;
+        };
+        // (the wide-range route works on the logits as they came)
+        for (int j = tid; j < K; j += THREADS) ds[j] = kept.wide ? logit(j) : exp_shifted(logit(j) - kept.smax);
         __syncthreads();
-        const LogSum Uw = block_sum_ls<THREADS>(unpicked_w, fmisc);
-        const float lpw = sigma_logprob_wide<THREADS>([&](int j) { return ds[j]; }, K, Uw, fmisc);
-        if (tid == 0) a.logp_out[seg] = lpw;
-        return;
+        if (kept.wide) {
+            const LogSum Uw = block_sum_ls<THREADS>(kept.unpicked_w, fmisc);
+            lp = sigma_logprob_wide<THREADS>([&](int j) { return ds[j]; }, K, Uw, fmisc);
+        } else {
+            lp = sigma_logprob<THREADS>([&](int j) { return ds[j]; }, K, kept.unpicked, fmisc);
+        }
     }
-    const float lp = sigma_logprob<THREADS>(logit, K, smax, unpicked, ds, fmisc);
     if (tid == 0) a.logp_out[seg] = lp;
 }
 
