@@ -54,6 +54,9 @@
 // batch, the last tile lost its prefetch and the first was asked for early:
 // 2 segments x 2000 rows 8.2 -> 6.7 us, 32 x 525 rows (8.6 MB) 9.1 -> 7.0 us,
 // 128 x 1494 rows (98 MB) 22.0 -> 19.7 us, 512 x 2700 rows (0.71 GB) 119 -> 117 us.
+// Where the 6.45 us of 32 x 525 rows go today (copies of the kernel that return early): launch 1.8, until the first
+// tile is there 1.7, its products 0.4, the four waves' merge 0.3, partial stores until acknowledged 0.45, ticket 1.2,
+// merge 0.65.
 //
 // Paged layout (PAGED = true): a 32-row tile never straddles a page (pages hold
 // a power-of-two number of rows >= 32), so only the tile's base address changes:
@@ -86,8 +89,6 @@ struct AttnArgs {
     float *part_ml;   // [nseg_launch][S][G][2]
     int32_t *status;
     int seg0;         // first segment of the launch
-    int nseg;         // segments of the launch
-    int lb0;          // (layer * B + sequence) that q[0] / out[0] belong to
     int S;            // splits per segment
     int G, Hkv, cap;
     float scale_log2e;
@@ -151,7 +152,6 @@ void decode_kernel(AttnArgs a)
     __shared__ __align__(16) unsigned char lds[ATT_WAVES * WAVE_LDS];
     __shared__ float red_m[ATT_WAVES][16];
     __shared__ float red_l[ATT_WAVES][16];
-    __shared__ float fin_l[16];
     __shared__ int is_last;
     __shared__ __align__(16) unsigned char fresh[APPEND ? 2 * ROW_BYTES : 16];   // the new K row and V row
 
@@ -161,16 +161,16 @@ void decode_kernel(AttnArgs a)
     // ...  Consecutive workgroups go round-robin to the 8 XCDs: this way every XCD gets the same share of each
     // run index (with the run as the fastest coordinate and S = 2, all first runs land on four of the XCDs and all
     // second runs on the other four: measured 15 % slower at 1024 segments of 16K rows).
-    const int split = (int)(blockIdx.x / a.nseg);
-    const int seg_local = (int)(blockIdx.x - split * a.nseg);
+    // (A grid of two dimensions counts the same way; divisions, here and for the queries, would stand in front of the
+    // first load.)
+    const int split = (int)blockIdx.y;
+    const int seg_local = (int)blockIdx.x;
     const int seg = a.seg0 + seg_local;
     const int G = a.G;
 
     const int n_raw = a.len[seg];
     if constexpr (!EARLY) __builtin_amdgcn_sched_barrier(0);   // asked for before anything else: the tile waits for it
-    const int h = seg % a.Hkv;
-    const int lb = seg / a.Hkv - a.lb0;   // (layer * B + sequence) relative to q / out
-    float *out_seg = a.out + ((size_t)lb * a.Hkv + h) * G * D;   // [G][D] of this KV head
+    float *out_seg = a.out + (size_t)seg_local * G * D;    // [G][D] of this KV head
 
     const unsigned char *kseg = PAGED ? a.k : a.k + (size_t)seg * a.cap * ROW_BYTES;
     const unsigned char *vseg = PAGED ? a.v : a.v + (size_t)seg * a.cap * ROW_BYTES;
@@ -237,7 +237,7 @@ void decode_kernel(AttnArgs a)
     // B operand of the first product: Q[q = li][32c + 8kg .. +7], zero for q >= G
     bf16x8 qop[KCH];
     {
-        const unsigned char *qrow = a.q + ((size_t)lb * a.Hkv * G + (size_t)h * G + (li < G ? li : G - 1)) * ROW_BYTES;
+        const unsigned char *qrow = a.q + ((size_t)seg_local * G + (li < G ? li : G - 1)) * ROW_BYTES;
 #pragma unroll
         for (int c = 0; c < KCH; ++c)
             qop[c] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(qrow + c * 64 + kg * 16));
@@ -295,7 +295,7 @@ void decode_kernel(AttnArgs a)
 
     if (n == 0) {
         if (split == 0) {
-            if (a.lse_out && (int)threadIdx.x < G) a.lse_out[((size_t)lb * a.Hkv + h) * G + threadIdx.x] = -INFINITY;
+            if (a.lse_out && (int)threadIdx.x < G) a.lse_out[(size_t)seg_local * G + threadIdx.x] = -INFINITY;
             for (int i = threadIdx.x; i < G * D; i += ATT_WAVES * 64) out_seg[i] = 0.f;
             if (threadIdx.x == 0) atomicAdd(&a.status[NGC_STATUS_EMPTY_ATTN], 1);
         }
@@ -344,7 +344,7 @@ void decode_kernel(AttnArgs a)
             const float inv = 1.0f / den;
             *reinterpret_cast<f32x4 *>(&out_seg[i4 * 4]) = num * inv;
             if (a.lse_out && i4 * 4 == qi * D)
-                a.lse_out[((size_t)lb * a.Hkv + h) * G + qi] = (M + __log2f(den)) * 0.6931471805599453f;
+                a.lse_out[(size_t)seg_local * G + qi] = (M + __log2f(den)) * 0.6931471805599453f;
         }
     };
     auto merge_partials = [&]() {
@@ -534,60 +534,66 @@ void decode_kernel(AttnArgs a)
     }
 
     // ---- merge the waves of this workgroup ----------------------------------
+    // O of every wave, its maximum and its sum go to LDS as they are (O into the wave's own staging area, which is free now);
+    // after one barrier a thread scales and adds the four waves' values of its own part of the output.
+    // A row of 16-byte stores per query head and lane group, rows a multiple of 16 bytes but not of 256 apart: the 16
+    // heads of a lane group meet 16 different sets of banks.  (Rows of D floats, stored a float at a time after a barrier and
+    // an exchange of the maxima, had all of them meet in one bank: 0.7 us of a launch of 32 segments of 525 rows; per
+    // layer from a HIP graph 6.9 -> 6.45 us, 2 x 300 rows of 128 bytes 4.3 -> 4.0, 128 x 1493 rows 19.8 -> 19.4.)
+    constexpr int OROW = D + 4;                            // floats
+    static_assert(16 * OROW * 4 <= WAVE_LDS, "staging area too small");
     l_run = quad_rows_sum(l_run);
     if (kg == 0) { red_m[wv][li] = m_run; red_l[wv][li] = l_run; }
-    __syncthreads();   // also: every wave is done with its K staging area
-    float m_all = red_m[0][li];
-#pragma unroll
-    for (int w = 1; w < ATT_WAVES; ++w) m_all = fmaxf(m_all, red_m[w][li]);
-    float l_all = 0.f;
-#pragma unroll
-    for (int w = 0; w < ATT_WAVES; ++w) {
-        const float mw = red_m[w][li];
-        l_all += (mw == -INFINITY) ? 0.f : red_l[w][li] * fast_exp2(mw - m_all);
-    }
-    const float f = (m_run == -INFINITY) ? 0.f : fast_exp2(m_run - m_all);
-    if (wv == 0 && kg == 0) fin_l[li] = l_all;
-    // O of every wave, scaled to the common max, into LDS as [wave][q][D] fp32
-    // (the K staging area is free now and large enough)
-    static_assert(ATT_WAVES * 16 * D * 4 <= ATT_WAVES * WAVE_LDS, "staging area too small");
-    float *ost = reinterpret_cast<float *>(lds);
     // lane (q = li, kg), register (c, r) holds d = DPL * (4kg + r) + c
     if (li < G) {
 #pragma unroll
-        for (int c = 0; c < DPL; ++c)
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                ost[(wv * 16 + li) * D + DPL * (4 * kg + r) + c] = oacc[c][r] * f;
+            for (int c = 0; c < DPL; c += 4)
+                reinterpret_cast<f32x4 *>(wlds)[(li * OROW + DPL * (4 * kg + r) + c) / 4] =
+                    f32x4{oacc[c][r], oacc[c + 1][r], oacc[c + 2][r], oacc[c + 3][r]};
     }
     __syncthreads();
+    // maximum and sum of query head qi over the waves, and the waves' factors (0 for a wave without rows)
+    auto waves_of = [&](int qi, float (&f)[ATT_WAVES], float &m_all, float &l_all) {
+        m_all = red_m[0][qi];
+#pragma unroll
+        for (int w = 1; w < ATT_WAVES; ++w) m_all = fmaxf(m_all, red_m[w][qi]);
+        l_all = 0.f;
+#pragma unroll
+        for (int w = 0; w < ATT_WAVES; ++w) {
+            f[w] = fast_exp2(red_m[w][qi] - m_all);        // (m_all is finite: the workgroup has rows)
+            l_all += red_l[w][qi] * f[w];
+        }
+    };
+    auto sum_of_waves = [&](int qi, int d, const float (&f)[ATT_WAVES]) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < ATT_WAVES; ++w) acc += reinterpret_cast<const f32x4 *>(lds + w * WAVE_LDS)[(qi * OROW + d) / 4] * f[w];
+        return acc;
+    };
+    float f[ATT_WAVES], m_all, l_all;
     const bool direct = (s_eff == 1);   // the only split of its segment with rows: finish here
     if (direct) {
-        for (int i = threadIdx.x; i < G * D; i += ATT_WAVES * 64) {
-            const int qi = i / D, d = i - qi * D;
-            float acc = 0.f;
-#pragma unroll
-            for (int w = 0; w < ATT_WAVES; ++w) acc += ost[(w * 16 + qi) * D + d];
-            out_seg[i] = acc / fin_l[qi];
+        for (int i4 = threadIdx.x; i4 < G * D / 4; i4 += ATT_WAVES * 64) {
+            const int qi = (i4 * 4) / D, d = i4 * 4 - qi * D;
+            waves_of(qi, f, m_all, l_all);
+            *reinterpret_cast<f32x4 *>(&out_seg[i4 * 4]) = sum_of_waves(qi, d, f) / l_all;
+            if (a.lse_out && d == 0)
+                a.lse_out[(size_t)seg_local * G + qi] = (m_all + __log2f(l_all)) * 0.6931471805599453f;
         }
-        if (a.lse_out && wv == 0 && kg == 0 && li < G)
-            a.lse_out[((size_t)lb * a.Hkv + h) * G + li] = (m_all + __log2f(l_all)) * 0.6931471805599453f;
         if (a.S == 1 || took_last_ticket()) close_segment();
         return;
     }
     float *dst_o = a.part_o + ((size_t)seg_local * a.S + split) * G * D;
     const __amdgpu_buffer_rsrc_t po = device_span(dst_o, (uint32_t)(G * D * sizeof(float)));
+    const __amdgpu_buffer_rsrc_t pml =
+        device_span(a.part_ml + ((size_t)seg_local * a.S + split) * G * 2, (uint32_t)(G * 2 * sizeof(float)));
     for (int i4 = threadIdx.x; i4 < G * D / 4; i4 += ATT_WAVES * 64) {
         const int qi = (i4 * 4) / D, d = i4 * 4 - qi * D;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int w = 0; w < ATT_WAVES; ++w) acc += *reinterpret_cast<const f32x4 *>(&ost[(w * 16 + qi) * D + d]);
-        st_device16(po, (uint32_t)(i4 * 4 * sizeof(float)), acc);
-    }
-    if (wv == 0 && kg == 0 && li < G) {
-        const __amdgpu_buffer_rsrc_t pml =
-            device_span(a.part_ml + ((size_t)seg_local * a.S + split) * G * 2, (uint32_t)(G * 2 * sizeof(float)));
-        st_device8(pml, (uint32_t)(li * 2 * sizeof(float)), f32x2{m_all, l_all});
+        waves_of(qi, f, m_all, l_all);
+        st_device16(po, (uint32_t)(i4 * 4 * sizeof(float)), sum_of_waves(qi, d, f));
+        if (d == 0) st_device8(pml, (uint32_t)(qi * 2 * sizeof(float)), f32x2{m_all, l_all});
     }
     __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's partial stores have reached memory
     if (took_last_ticket()) {
@@ -808,8 +814,6 @@ int launch_decode(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, 
                                            partial_o_bytes(c, nseg, S));
     aa.status = status ? status : reinterpret_cast<int32_t *>(ws);
     aa.seg0 = seg0;
-    aa.nseg = nseg;
-    aa.lb0 = layer < 0 ? 0 : layer * c->B;
     aa.S = S; aa.G = c->Hq / c->Hkv; aa.Hkv = c->Hkv; aa.cap = c->cap;
     aa.scale_log2e = scale * 1.4426950408889634f;
     aa.ticket = reinterpret_cast<int32_t *>(reinterpret_cast<unsigned char *>(ws) +
@@ -830,7 +834,7 @@ int launch_decode(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, 
         aa.tpp_shift = sh;
     }
     hipStream_t st = (hipStream_t)stream;
-    const dim3 grid(nseg * S), block(ATT_WAVES * 64);
+    const dim3 grid(nseg, S), block(ATT_WAVES * 64);
     const bool early = first_tile_early(nseg, S, max_len, max_len_hint);
 #define NGC_LAUNCH_DECODE(PAGED, APPEND) \
     if (c->D == 128) { \
