@@ -4,7 +4,8 @@
 // (optionally) averaged over KV heads and over blocks of consecutive keys.
 //
 // One workgroup of 4 waves per (layer, sequence, KV head), several where there are
-// few of those and the normalisers are given.  The w*G query rows
+// few of those and the normalisers are given (those kernels ask for everything
+// at once, the queries and normalisers before the length is known, and compare a key with what a query sees only at a segment's end).  The w*G query rows
 // are padded to QT tiles of 16 and both passes run on the matrix cores:
 //   pass 1  S^T = K Q^T   (queries on lane%16): running max / sum per query row
 //   pass 2  S   = Q K^T   (keys on lane%16):    p = 2^(x - m) / l, summed over
@@ -15,6 +16,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "../../include/ngc.h"
 #include "ngc_device.h"
@@ -32,7 +35,8 @@ struct ScoreArgs {
     float *psi_out;           // fp32 [seg][cap], one value per key
     int32_t *status;
     int seg0, nseg, lb0;
-    int S;                    // workgroups per segment (1 unless lse is given)
+    int S;                    // workgroups per segment (1 unless lse is given) ...
+    int share_rows;           // ... of at least so many rows; shorter ones are left to their first
     int w, G, Hkv, cap, causal;
     float scale_log2e;
     // paged layout: k is the pool and a tile's base comes from the page table
@@ -42,7 +46,8 @@ struct ScoreArgs {
 
 // Up to three query tiles the kernel fits 168 registers per thread without spilling, i.e. three waves per SIMD
 // (three workgroups per CU) instead of the two the compiler settles for by itself; with four tiles it does not.
-template <int D, int QT>
+// GIVEN: the normalisers are (lse); one pass.
+template <int D, int QT, bool GIVEN>
 __global__ __launch_bounds__(SC_WAVES * 64) __attribute__((amdgpu_waves_per_eu(QT <= 3 ? 3 : 2)))
 void score_keys_kernel(ScoreArgs a)
 {
@@ -66,34 +71,19 @@ void score_keys_kernel(ScoreArgs a)
     // of share (t / 4) % S.
     const int share = (int)(blockIdx.x / a.nseg);
     const int seg = a.seg0 + (int)(blockIdx.x - share * a.nseg);
-    const int first_tile = share * SC_WAVES, tile_step = a.S * SC_WAVES;
+    const int first_tile = share * SC_WAVES;
     const int G = a.G, w = a.w, R = w * G;
-    int n = a.len[seg];
-    if (n < 0 || n > a.cap) {
-        if (threadIdx.x == 0 && share == 0) atomicAdd(&a.status[NGC_STATUS_LEN_CLAMPED], 1);
-        n = n < 0 ? 0 : a.cap;
-    }
-    if (first_tile * SC_TILE >= n) return;
+    // Asked for first, none of it waits for the length: the query operands -- row r = qt*16 + li  ->  (recent query
+    // j = r / G, head g = r % G) -- and the normaliser of row threadIdx.x.
     const int h = seg % a.Hkv;
     const int lb = seg / a.Hkv - a.lb0;
     const int Hq = a.Hkv * G;
-    const unsigned char *kseg = a.table ? a.k : a.k + (size_t)seg * a.cap * ROW_BYTES;
-    const int32_t *tab = a.table ? a.table + (size_t)seg * a.max_pages : nullptr;
-    float *psi = a.psi_out + (size_t)seg * a.cap;
-    const int tiles = (n + SC_TILE - 1) / SC_TILE;
-    const int last_row = n - 1;
-
-    // query operands: row r = qt*16 + li  ->  (recent query j = r / G, head g = r % G)
     bf16x8 qop[QT][KCH];
-    int vis_q[QT];   // number of rows the query row of this lane can see
 #pragma unroll
     for (int qt = 0; qt < QT; ++qt) {
         const int r = qt * 16 + li;
         const int j = r / G, g = r - j * G;
         const bool ok = r < R;
-        int vis = a.causal ? (n - w + j + 1) : n;
-        vis = vis > n ? n : vis;
-        vis_q[qt] = ok ? (vis > 0 ? vis : 0) : 0;
         const unsigned char *qrow = a.q + (((size_t)lb * w + j) * Hq + (size_t)h * G + g) * ROW_BYTES;
 #pragma unroll
         for (int c = 0; c < KCH; ++c) {
@@ -102,6 +92,26 @@ void score_keys_kernel(ScoreArgs a)
             qop[qt][c] = __builtin_bit_cast(bf16x8, v);
         }
     }
+    float given = -INFINITY;
+    if constexpr (GIVEN) {
+        if ((int)threadIdx.x < R) {
+            const int j = threadIdx.x / G, g = threadIdx.x - j * G;
+            given = a.lse[((size_t)lb * w + j) * Hq + (size_t)h * G + g] * 1.4426950408889634f;
+        }
+    }
+    int n = a.len[seg];
+    if (n < 0 || n > a.cap) {
+        if (threadIdx.x == 0 && share == 0) atomicAdd(&a.status[NGC_STATUS_LEN_CLAMPED], 1);
+        n = n < 0 ? 0 : a.cap;
+    }
+    const int shares = n < a.share_rows ? 1 : a.S;
+    const int tile_step = shares * SC_WAVES;
+    if (share >= shares || first_tile * SC_TILE >= n) return;
+    const unsigned char *kseg = a.table ? a.k : a.k + (size_t)seg * a.cap * ROW_BYTES;
+    const int32_t *tab = a.table ? a.table + (size_t)seg * a.max_pages : nullptr;
+    float *psi = a.psi_out + (size_t)seg * a.cap;
+    const int tiles = (n + SC_TILE - 1) / SC_TILE;
+    const int last_row = n - 1;
 
     unsigned char *wlds = lds + wv * WAVE_LDS;
     u32x4 kbuf[K_LOADS];
@@ -135,24 +145,26 @@ void score_keys_kernel(ScoreArgs a)
         }
     };
 
+    if constexpr (GIVEN) load_tile(first_tile + wv);
     // ------------------------------------------------ pass 1: max and sum ---
     // (skipped when the caller hands over the log-sum-exp that decode attention
     // already computed for these very queries: then K is read only once)
-    if (a.lse != nullptr) {
-        for (int r = threadIdx.x; r < QT * 16; r += SC_WAVES * 64) {
-            float m2 = -INFINITY;
-            if (r < R) {
-                const int j = r / G, g = r - j * G;
-                m2 = a.lse[((size_t)lb * w + j) * Hq + (size_t)h * G + g] * 1.4426950408889634f;
-            }
-            fin_m[r] = m2;
-            fin_il[r] = (m2 > -INFINITY) ? 1.0f : 0.f;
-        }
+    if constexpr (GIVEN) {
+        static_assert(QT * 16 <= SC_WAVES * 64, "a thread per query row");
+        if (threadIdx.x < QT * 16) fin_m[threadIdx.x] = given;
         __syncthreads();
     } else {
     float m_run[QT], l_run[QT];
+    int vis_q[QT];   // number of rows the query row of this lane can see
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) { m_run[qt] = -INFINITY; l_run[qt] = 0.f; }
+    for (int qt = 0; qt < QT; ++qt) {
+        m_run[qt] = -INFINITY;
+        l_run[qt] = 0.f;
+        const int r = qt * 16 + li, j = r / G;
+        int vis = a.causal ? (n - w + j + 1) : n;
+        vis = vis > n ? n : vis;
+        vis_q[qt] = r < R && vis > 0 ? vis : 0;
+    }
     {
         int tile = wv;
         load_tile(tile);
@@ -234,48 +246,62 @@ void score_keys_kernel(ScoreArgs a)
         for (int r = 0; r < 4; ++r) {
             const int row = qt * 16 + 4 * kg + r;
             m_row[qt][r] = fin_m[row];
-            il_row[qt][r] = fin_il[row];
+            if constexpr (!GIVEN) il_row[qt][r] = fin_il[row];
             const int j = row / G;
             int vis = a.causal ? (n - w + j + 1) : n;
             vis = vis > n ? n : vis;
             vis_row[qt][r] = (row < R && vis > 0) ? vis : 0;
         }
     const float inv_rows = 1.0f / (float)R;
+    // Rows that every query sees: all but the last w - 1.  There only the rows that pad the last query tile are left out, and
+    // the comparisons with what a query sees (two instructions for every probability) are not needed.  A wave with a few
+    // tiles does without that copy of the loop body: fetching a second one costs it more (64 segments, 8 workgroups each: 0.5 us of 12).
+    const int seen_by_all = tiles <= 8 * tile_step ? 0 : a.causal ? n - w + 1 : n;
+    auto scores_of_tile = [&](int row0, auto all_seen) {
+        bf16x8 kop[2][KCH];
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+            for (int c = 0; c < KCH; ++c)
+                kop[nt][c] = __builtin_bit_cast(
+                    bf16x8, *reinterpret_cast<const u32x4 *>(wlds + (nt * 16 + li) * LROW + c * 64 + kg * 16));
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            const int t = row0 + nt * 16 + li;   // the key of this lane
+            float acc = 0.f;
+#pragma unroll
+            for (int qt = 0; qt < QT; ++qt) {
+                f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int c = 0; c < KCH; ++c)
+                    s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qop[qt][c], kop[nt][c], s, 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float p = fast_exp2(s[r] * a.scale_log2e - m_row[qt][r]);
+                    if constexpr (!GIVEN) p *= il_row[qt][r];
+                    if constexpr (decltype(all_seen)::value) {
+                        if (qt < QT - 1 || vis_row[qt][r] > 0) acc += p;
+                    } else {
+                        if (t < vis_row[qt][r]) acc += p;
+                    }
+                }
+            }
+            acc = quad_rows_sum(acc);
+            if (kg == 0 && t < n) psi[t] = acc * inv_rows;
+        }
+    };
     {
         int tile = first_tile + wv;
-        load_tile(tile);
+        if constexpr (!GIVEN) load_tile(tile);
         for (; tile < tiles; tile += tile_step) {
             stage_tile();
             const int row0 = tile * SC_TILE;
             load_tile(tile + tile_step);
             __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_wave_barrier();
-            bf16x8 kop[2][KCH];
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-                for (int c = 0; c < KCH; ++c)
-                    kop[nt][c] = __builtin_bit_cast(
-                        bf16x8, *reinterpret_cast<const u32x4 *>(wlds + (nt * 16 + li) * LROW + c * 64 + kg * 16));
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                const int t = row0 + nt * 16 + li;   // the key of this lane
-                float acc = 0.f;
-#pragma unroll
-                for (int qt = 0; qt < QT; ++qt) {
-                    f32x4 s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int c = 0; c < KCH; ++c)
-                        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qop[qt][c], kop[nt][c], s, 0, 0, 0);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (t < vis_row[qt][r])
-                            acc += fast_exp2(s[r] * a.scale_log2e - m_row[qt][r]) * il_row[qt][r];
-                }
-                acc = quad_rows_sum(acc);
-                if (kg == 0 && t < n) psi[t] = acc * inv_rows;
-            }
+            if (row0 + SC_TILE <= seen_by_all) scores_of_tile(row0, std::true_type{});
+            else scores_of_tile(row0, std::false_type{});
         }
     }
 }
@@ -358,14 +384,25 @@ namespace {
 //       128 x 8000       85.2  52.5  46.2  48.8  49.3  52.5
 //       400 x 2000       38.7  43.6  41.7  43.7  54.6  54.4
 //      2048 x 2150-3789   284   282   294   327   382   470
-// i.e. about two workgroups per CU, four at D = 64 (512 x 2000-6000: 64.9, 55.7 with two each).
-int score_shares(int nseg, int cap, int D, bool have_lse)
+// i.e. about two workgroups per CU, four at D = 64 (512 x 2000-6000: 64.9, 55.7 with two each).  From there to 1536
+// segments, two rounds of resident workgroups, a second workgroup evens out what the last ones leave idle, if the segments are
+// long (both libraries in turns on the same buffers: 1024 x 2150-3789 155 -> 142, 600 x 2150-3789 88.6 -> 86.4; 2048 of equal
+// length 274 -> 278, of 2150-3789 278 -> 272; 512 x 1000 24.8 -> 26.7).  The host does not know the lengths, so it launches the
+// second one where the capacity permits and the kernel has it leave at once if the segment has fewer than SHARE_ROWS rows.
+constexpr int SHARE_ROWS = 2048;
+
+struct Shares {
+    int S, rows;
+};
+
+Shares score_shares(int nseg, int cap, int D, bool have_lse)
 {
-    if (!have_lse) return 1;
+    if (!have_lse) return {1, 0};
     const int rounds = (cap + SC_TILE * SC_WAVES - 1) / (SC_TILE * SC_WAVES);
     const int fill = (D == 128 ? 512 : 1024) / nseg;
+    if (fill < 2 && nseg > 512 && nseg <= 1536 && cap >= SHARE_ROWS) return {2, SHARE_ROWS};
     const int s = rounds < fill ? rounds : fill;
-    return s > 1 ? s : 1;
+    return {s > 1 ? s : 1, 0};
 }
 
 int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, const void *q_recent,
@@ -397,7 +434,9 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     sa.psi_out = scores_out;
     sa.status = reinterpret_cast<int32_t *>(ws);
     sa.seg0 = seg0; sa.nseg = nseg;
-    sa.S = score_shares(nseg, c->cap, c->D, lse_recent != nullptr);   // nseg * S <= max(nseg, 1024)
+    const Shares shares = score_shares(nseg, c->cap, c->D, lse_recent != nullptr);   // nseg * S <= max(nseg, 3072)
+    sa.S = shares.S;
+    sa.share_rows = shares.rows;
     sa.lb0 = layer < 0 ? 0 : layer * c->B;
     sa.w = w; sa.G = G; sa.Hkv = c->Hkv; sa.cap = c->cap;
     sa.causal = (flags & NGC_SCORE_NO_CAUSAL) ? 0 : 1;
@@ -412,13 +451,14 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     hipStream_t st = (hipStream_t)stream;
     const int qt = (R + 15) / 16;
 #define NGC_LAUNCH_SCORE(DD, QQ) \
-    hipLaunchKernelGGL((score_keys_kernel<DD, QQ>), dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), 0, st, sa)
+    if (lse_recent) hipLaunchKernelGGL((score_keys_kernel<DD, QQ, true>), dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), 0, st, sa); \
+    else            hipLaunchKernelGGL((score_keys_kernel<DD, QQ, false>), dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), 0, st, sa)
     if (c->D == 128) {
-        if (qt == 1) NGC_LAUNCH_SCORE(128, 1); else if (qt == 2) NGC_LAUNCH_SCORE(128, 2);
-        else if (qt == 3) NGC_LAUNCH_SCORE(128, 3); else NGC_LAUNCH_SCORE(128, 4);
+        if (qt == 1) { NGC_LAUNCH_SCORE(128, 1); } else if (qt == 2) { NGC_LAUNCH_SCORE(128, 2); }
+        else if (qt == 3) { NGC_LAUNCH_SCORE(128, 3); } else { NGC_LAUNCH_SCORE(128, 4); }
     } else {
-        if (qt == 1) NGC_LAUNCH_SCORE(64, 1); else if (qt == 2) NGC_LAUNCH_SCORE(64, 2);
-        else if (qt == 3) NGC_LAUNCH_SCORE(64, 3); else NGC_LAUNCH_SCORE(64, 4);
+        if (qt == 1) { NGC_LAUNCH_SCORE(64, 1); } else if (qt == 2) { NGC_LAUNCH_SCORE(64, 2); }
+        else if (qt == 3) { NGC_LAUNCH_SCORE(64, 3); } else { NGC_LAUNCH_SCORE(64, 4); }
     }
 #undef NGC_LAUNCH_SCORE
     NGC_HIP_CHECK(hipGetLastError());

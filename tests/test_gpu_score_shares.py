@@ -81,3 +81,40 @@ def test_shared_segments(B, cap, D, Hq, block):
                 if block == 1:
                     assert (got[0, b, h, m:] == -1.0).all()
     assert all(v == 0 for v in ngc.read_status(ws))
+
+
+@pytest.mark.parametrize("B,cap", [(257, 2048), (768, 2050), (769, 2048)])
+def test_second_workgroup_of_long_segments(B, cap):
+    """More segments than CUs twice over: those of 2048 rows and more are shared by two workgroups (up to 1536 segments),
+    shorter ones are not; the last rows are not seen by all queries.  Only a few segments are compared."""
+    import torch
+    ngc = _ngc()
+    H, Hq, D, w = 2, 4, 64, 4
+    scale = D ** -0.5
+    g = torch.Generator().manual_seed(B + cap)
+    lens = torch.full((1, B, H), 5, dtype=torch.int32)
+    rows = {0: (2048, 2047), 1: (cap, 33), B - 1: (2045, 2048)}
+    k = torch.zeros(1, B, H, cap, D, dtype=torch.bfloat16, device="cuda")
+    q = torch.randn(B, w, Hq, D, generator=g).to(torch.bfloat16)
+    lse = torch.zeros(B, w, Hq)
+    refs = {}
+    for b, n in rows.items():
+        kb = torch.randn(H, cap, D, generator=g).to(torch.bfloat16)
+        refs[b], e = _reference(kb.double(), q[b].double(), n, w, scale)
+        lse[b] = e.float()
+        for h in range(H):
+            lens[0, b, h] = n[h]
+            kb[h, n[h]:] = float("nan")
+        k[0, b] = kb.cuda()
+    c = ngc.Cache(k, k, lens.cuda(), None, Hq)
+    ws = ngc.allocate_workspace(c, 1)
+    scores = torch.full((1, B, H, cap), -1.0, device="cuda")
+    print(f"[score-shares] second workgroup B={B} cap={cap}", flush=True)
+    ngc.ngc_score_keys(c, 0, q.cuda(), w, scale, 0, 1, scores, ws, lse_recent=lse.cuda())
+    got = scores.cpu().double()[0]
+    for b, n in rows.items():
+        for h in range(H):
+            want = refs[b][h]
+            assert torch.all((got[b, h, :n[h]] - want).abs() <= 2e-4 * want.abs() + 1e-9), (b, h)
+            assert torch.all(got[b, h, n[h]:] == -1.0)
+    assert torch.all(got[2:B - 1, :, 5:] == -1.0) and torch.isfinite(got).all()
