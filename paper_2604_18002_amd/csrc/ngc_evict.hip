@@ -1614,10 +1614,11 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
     const int items_cap_al = (items_cap + 3) & ~3;
     // Workgroup size and rows in flight per thread, all measured.  A round that moves rows in order is a copy with a
     // selection in front, and the size follows the rows of a segment, not its items.  One 1024-thread workgroup per CU, whose
-    // reads and writes take turns, copies best, but has nothing beside it while it selects: it is taken beyond 4096 rows
-    // and, where there are more segments than CUs to spread them over twice, from 1281 rows up (us with 512 and 1024
-    // threads: 2048 segments of 4096-8192 rows 1023 and 924, 3584 of 4096 940 and 900, 3584 of 1800 649 and 600, 1024 of 1500 169 and
-    // 165, of 1200 138 and 141; 512 of 2000 120 and 120; 400 of 3000 140 and 140; 64 of 3000 46 and 49).  512 threads from
+    // reads and writes take turns, copies best, but has nothing beside it while it selects, and half a round of 256 of them
+    // counts as a whole one: it is taken beyond 4096 rows and, with many segments or most rows kept, from fewer (512 over
+    // 1024 threads, times; half kept: 640 segments of 1400 rows 0.98, of 1800 1.00, of 4096 1.03; 1024: 0.99, 1.04, 1.06;
+    // 1152: 1.01, 1.07, 1.02; 2048: 1.06, 1.08, 1.08; nine tenths of 2500 rows 1.05-1.09 for all; a third kept of 2500 and 4096
+    // rows: 1024 segments 0.97 and 0.97, 1536 0.99 and 0.99, 1792 1.00 and 1.01, 3584 of 4096 1.02).  512 threads from
     // 513 rows up (896 of 700: 74, 77 with 256), 256 below (896 of 300: 35 and 38).  A round that only selects, or fills
     // holes (few rows move), is bound by the selection's waits; two 512-thread workgroups per CU cover each other's up to
     // the 8192 rows at which two of them still fit in LDS (1024 segments of 8192: 96 us, 135 with 1024 threads), 256
@@ -1626,7 +1627,10 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
     const bool move_rows = !(p->flags & NGC_EVICT_SELECT_ONLY);
     const bool copy_bound = move_rows && !(p->flags & NGC_EVICT_UNORDERED);
     const int few = (copy_bound || nseg <= 512) ? 512 : 2048;
-    const int many = !copy_bound ? 8192 : nseg > 512 ? 1280 : 4096;
+    const bool mostly_kept = 2LL * max_keep * p->block >= c->cap;
+    int many = copy_bound ? 4096 : 8192;
+    if (copy_bound && (nseg > 1536 || (nseg > 1024 && mostly_kept))) many = 1280;
+    else if (copy_bound && nseg > 512 && mostly_kept) many = 1536;
     const int threads = c->cap > many ? 1024 : (c->cap > few ? 512 : 256);
     const int rank_cap = rank_capacity(threads, items_cap_al, keep_cap);
     const size_t lds = select_lds_bytes(threads, items_cap_al, keep_cap, rank_cap);
