@@ -62,6 +62,7 @@
 // a power-of-two number of rows >= 32), so only the tile's base address changes:
 // it comes from the segment's page table.  Table entries are fetched two tiles
 // ahead of their use so that the lookup never sits in front of the K/V loads.
+#include <float.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -543,7 +544,7 @@ void decode_kernel(AttnArgs a)
     constexpr int OROW = D + 4;                            // floats
     static_assert(16 * OROW * 4 <= WAVE_LDS, "staging area too small");
     l_run = quad_rows_sum(l_run);
-    if (kg == 0) { red_m[wv][li] = m_run; red_l[wv][li] = l_run; }
+    if (kg == 0) { red_m[wv][li] = m_run; red_l[wv][li] = m_run == -INFINITY ? 0.f : l_run; }   // (rows that all score -inf sum to NaN)
     // lane (q = li, kg), register (c, r) holds d = DPL * (4kg + r) + c
     if (li < G) {
 #pragma unroll
@@ -559,10 +560,11 @@ void decode_kernel(AttnArgs a)
         m_all = red_m[0][qi];
 #pragma unroll
         for (int w = 1; w < ATT_WAVES; ++w) m_all = fmaxf(m_all, red_m[w][qi]);
+        const float m_ref = fmaxf(m_all, -FLT_MAX);        // (a segment whose rows all score -inf: factors 0, not NaN)
         l_all = 0.f;
 #pragma unroll
         for (int w = 0; w < ATT_WAVES; ++w) {
-            f[w] = fast_exp2(red_m[w][qi] - m_all);        // (m_all is finite: the workgroup has rows)
+            f[w] = fast_exp2(red_m[w][qi] - m_ref);
             l_all += red_l[w][qi] * f[w];
         }
     };

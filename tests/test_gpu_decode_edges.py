@@ -209,3 +209,27 @@ def test_first_tile_before_and_after_the_length(B, hint, D, Hq):
     print(f"[decode-edges] early paged B={B} hint={hint} D={D}", flush=True)
     ngc.ngc_paged_decode_attn(pc, 0, q.cuda(), scale, hint, out, ngc.allocate_paged_workspace(pc), lse_out=lse)
     check(out, lse, k, v, n, "paged")
+
+
+@pytest.mark.parametrize("B", [2, 130])           # several workgroups a segment, one
+@pytest.mark.parametrize("D,Hq", [(64, 8), (128, 12)])
+def test_wave_whose_rows_all_score_minus_infinity(B, D, Hq):
+    """One wave in four sees only rows that score -inf: the log-sum-exp is that of the other rows (2e-5 as above)."""
+    import torch
+    ngc = _ngc()
+    H, cap, scale = 2, 500, D ** -0.5
+    g = torch.Generator().manual_seed(B + D)
+    n = torch.full((1, B, H), cap, dtype=torch.int32)
+    k = torch.randn(1, B, H, cap, D, generator=g).to(torch.bfloat16)
+    v = torch.randn(1, B, H, cap, D, generator=g).to(torch.bfloat16)
+    q = torch.randn(B, Hq, D, generator=g).to(torch.bfloat16)
+    q[..., 0] = 1
+    lost = torch.arange(cap) // 32 % 4 == 1
+    want = torch.logsumexp(q.double().view(B, H, -1, D) @ k[0, :, :, ~lost].double().transpose(-1, -2) * scale, -1)
+    k[..., lost, 0] = float("-inf")
+    out, lse = torch.zeros(B, Hq, D, device="cuda"), torch.zeros(B, Hq, device="cuda")
+    c = ngc.Cache(k.cuda(), v.cuda(), n.cuda(), None, Hq)
+    ws = ngc.allocate_workspace(c, 1)
+    print(f"[decode-edges] -inf B={B} D={D}", flush=True)
+    ngc.ngc_decode_attn(c, 0, q.cuda(), scale, cap, out, ws, lse_out=lse)
+    assert (lse.cpu().double().view_as(want) - want).abs().max() <= 2e-5
