@@ -56,7 +56,7 @@ struct LogprobArgs {
 // Both kernels below (Eq. 2 for given actions, and its gradient) read a segment's row and its sigma once.  The row's
 // weights exp(s - max s) are computed once, by the threads that read the row, and stand in LDS; a pick takes its item's
 // weight from there and leaves a mark (an exchange, which also finds repeated picks); what stays unmarked was never
-// picked, and the marks tell the thread that read an item whether its logit belongs to the sum over the picks.
+// picked.
 // Thread i owns PICKS consecutive picks -- thread 0 the LAST ones, so that an ordinary exclusive scan over threads yields
 // the mass of everything picked after a thread's own -- and keeps their weights in registers between the passes.  Rows
 // that do not fit (N > row_cap) and rows whose logits span more than NGC_WIDE_SPREAD take the general route: a bitmap of
@@ -84,13 +84,12 @@ __device__ __forceinline__ float scalar(float x)
 // QUADS: a thread holds the items 4 (i THREADS + tid) .. + 3 of a row of up to 4 QUADS THREADS items in registers.
 template <int THREADS, int PICKS, int QUADS>
 struct PickedTerms {
-    f32x4 row[QUADS];   // held rows: s - max s of those items and, once the picks are marked, exp(s - max s) or PICKED
+    f32x4 row[QUADS];   // held rows: the logits and, with KEEP_ROW once the picks are marked, exp(s - max s) or PICKED
     bool held;
     float e[PICKS];     // exp(s - max s) of this thread's picks (latest pick last); 0 past the end
     int t[PICKS];       // item index; -1 past the end, -2 for an index outside the segment
     float after;        // mass of everything picked after them
     float unpicked;     // mass never picked (U of Eq. 2)
-    float logits;       // this thread's share of the sum of s - max s over all picks (not with KEEP_ROW)
     int count;          // picks of this thread
     int per;            // the most any thread has
 };
@@ -191,24 +190,19 @@ __device__ __forceinline__ bool gather_picked(const float *row, const int32_t *s
     }
     if (smax > -INFINITY && smax - smin > NGC_WIDE_SPREAD) return false;
     if (smax == -INFINITY) smax = 0.f;                        // every entry masked: all weights are 0
-    // Masked entries get a difference that no other has (and whose exponential is 0).
-    constexpr float MASKED_D = -300.0f;
-    auto difference = [&](float x) {
-        float d = x - smax;
-        if (masked && !(x > -INFINITY)) d = MASKED_D;
-        return d;
-    };
+    // (a masked entry's weight is 0)
+    auto difference = [&](float x) { return masked && !(x > -INFINITY) ? -300.0f : x - smax; };
     each_quad(staged_quad, [&](int q, f32x4 &x) {
         f32x4 e;
         if (masked) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = difference(x[u]);
+            for (int u = 0; u < 4; ++u) e[u] = difference(x[u]);
         } else {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] -= smax;
+            for (int u = 0; u < 4; ++u) e[u] = x[u] - smax;
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) e[u] = exp_shifted_finite(x[u]);
+        for (int u = 0; u < 4; ++u) e[u] = exp_shifted_finite(e[u]);
         if (4 * q + 4 > N) {                                  // past the end: no weight
 #pragma unroll
             for (int u = 1; u < 4; ++u)
@@ -217,7 +211,7 @@ __device__ __forceinline__ bool gather_picked(const float *row, const int32_t *s
         reinterpret_cast<f32x4 *>(lds_row)[q] = e;
     });
     __syncthreads();
-    float mass = 0.f, extra = 0.f;
+    float mass = 0.f;
     bool bad = false;
 #pragma unroll
     for (int i = 0; i < PICKS; ++i) pt.e[i] = 0.f;
@@ -240,9 +234,7 @@ __device__ __forceinline__ bool gather_picked(const float *row, const int32_t *s
                         int t = pt.t[i];
                         if (t < 0 || t >= N) pt.t[i] = -2;
                         t = t < 0 ? 0 : (t >= N ? N - 1 : t);
-                        const float d = difference(row[t]);
-                        extra += d == MASKED_D ? -INFINITY : d;
-                        pt.e[i] = exp_shifted_finite(d);
+                        pt.e[i] = exp_shifted_finite(difference(row[t]));
                     } else {
                         pt.t[i] = -1;
                     }
@@ -253,28 +245,12 @@ __device__ __forceinline__ bool gather_picked(const float *row, const int32_t *s
     if (bad) atomicAdd(&status[NGC_STATUS_BAD_SIGMA], 1);
     __syncthreads();                                          // every pick has marked its item
     float unpicked = 0.f;
-    auto load_unless_kept = [&](int q) { return KEEP_ROW ? f32x4{} : load_quad(q); };
-    each_quad(load_unless_kept, [&](int q, f32x4 &x) {
+    each_quad([](int) { return f32x4{}; }, [&](int q, f32x4 &x) {
         const f32x4 v = reinterpret_cast<const f32x4 *>(lds_row)[q];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float weight = max_no_nan(v[u], 0.f);
-            unpicked += weight;
-            if (!KEEP_ROW) {
-                const float d = pt.held ? x[u] : difference(x[u]);
-                extra = __builtin_fmaf(weight - v[u], d, extra);                // the factor is 1 for a pick, else 0
-            }
-        }
-        if (!KEEP_ROW && masked) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float d = pt.held ? x[u] : difference(x[u]);
-                if (d == MASKED_D && v[u] < 0.f) extra = -INFINITY;             // a masked pick makes log p = -inf
-            }
-        }
+        for (int u = 0; u < 4; ++u) unpicked += max_no_nan(v[u], 0.f);
         if (KEEP_ROW) x = v;
     });
-    pt.logits = extra;
     // one exchange for the scan of the picked masses and the sum of the others
     const float incl = wave_incl_scan_f(mass);
     const float others = wave_sum_f(unpicked);
@@ -316,17 +292,17 @@ __global__ __launch_bounds__(THREADS) void subset_logprob_kernel(LogprobArgs a)
     {
         PickedTerms<THREADS, PICKS, QUADS> pt;
         if (gather_picked<THREADS, PICKS, QUADS, false>(row, sig, N, K, a.row_cap, dynamic_lds, fmisc, a.status, pt)) {
-            float R = pt.unpicked + pt.after, acc = pt.logits;
+            float R = pt.unpicked + pt.after, acc = 0.f;
             if (pt.count > 0) {
-                LogProduct prod;
+                LogRatio ratio;                                // (a masked pick, weight 0, makes log p = -inf)
+                static_assert(PICKS <= LogRatio::MAX_PICKS);
 #pragma unroll
                 for (int i = PICKS - 1; i >= 0; --i)
                     if (i < pt.per) {                          // uniform
                         R += pt.e[i];
-                        // (0 only where nothing unmasked is left: such a pick is masked, and pt.logits -inf)
-                        if (i < pt.count) prod.times(max_no_nan(R, 1.0e-37f));
+                        if (i < pt.count) ratio.times(pt.e[i], R);
                     }
-                acc -= prod.log();
+                acc = ratio.log();
             }
             // (thousands for a long sequence: rounded once)
             double *totals = reinterpret_cast<double *>(fmisc);
@@ -405,11 +381,15 @@ __global__ __launch_bounds__(THREADS) void subset_logprob_kernel(LogprobArgs a)
     float acc = 0.f;
     if (cidx >= 0) {
         float R = U + after;
+        LogRatio ratio;
+        int n = 0;
         for (int j = j_hi - 1; j >= j_lo; --j) {
-            const float d = term(j);
-            R += expf(d);
-            acc += (d == -INFINITY) ? -INFINITY : d - logf(R);   // a masked pick: probability 0
+            const float e = expf(term(j));
+            R += e;
+            ratio.times(e, R);                                   // a masked pick: probability 0
+            if (++n == LogRatio::MAX_PICKS) { acc += ratio.log(); ratio = LogRatio{}; n = 0; }
         }
+        acc += ratio.log();
     }
     const float lp = block_sum_f<THREADS>(acc, fmisc);
     if (tid == 0) a.logp_out[seg] = lp;

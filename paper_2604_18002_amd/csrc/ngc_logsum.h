@@ -41,20 +41,6 @@ __device__ __forceinline__ float reciprocal(float x)
     return __builtin_fmaf(r, __builtin_fmaf(-x, r, 1.0f), r);
 }
 
-// A sum of logarithms taken as the logarithm of a product: mantissas multiply (at most a few dozen before log() is
-// called: each is in [1/2, 1)), exponents add.  Four instructions per term instead of a logarithm; the product of n
-// mantissas is off by n * 2^-24, n logarithms of ~7 by about 2^-22 each.
-struct LogProduct {
-    float mant = 1.0f;
-    int exponent = 0;
-    __device__ __forceinline__ void times(float x)
-    {
-        mant *= __builtin_amdgcn_frexp_mantf(x);
-        exponent += __builtin_amdgcn_frexp_expf(x);
-    }
-    __device__ __forceinline__ float log() const { return __builtin_fmaf((float)exponent, 0.693147181f, logf(mant)); }
-};
-
 // Sum of log(e_j / R_j) over a few picks, taken as one logarithm: the mantissas of the e_j and of the R_j multiply, the
 // difference of their exponents is an integer.  A pick that is nearly certain (e_j close to R_j) adds an error of a few
 // 2^-24 whatever its logit; d_j - log R_j, two numbers of up to 80 that cancel, adds 80 * 2^-24, and sums of the d_j and of

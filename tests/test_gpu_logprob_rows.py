@@ -229,3 +229,38 @@ def test_rows_held_in_registers(stride, nseg):
             w = -e * c[-1]
             w[sig] = 1.0 - e[sig] * c
             assert np.all(np.abs(g[s, :n] - gout[s] * w) <= abs(gout[s]) * (1e-5 * np.abs(w) + 2e-6)), (kind, n, k)
+
+
+@pytest.mark.parametrize("stride,n,nseg", [(16, 0, 192), (700, 700, 192), (4096, 3000, 192),     # held in registers
+                                           (8200, 1500, 513),                                    # staged in LDS
+                                           (16400, 8100, 96)])                                   # general route
+def test_logprob_of_nearly_certain_given_picks(stride, n, nseg):
+    """Ladders of picks, each far likelier than all that come after it, scattered over the row in a random order (n = 0: the
+    row holds nothing else): log p is a small sum although logits lie up to 75 below the largest.  A pick's term is the
+    logarithm of e_j / R_j, two fp32 numbers (2^-21.6 in all, 16 picks 5e-6), on every route.  1e-4 relative + 1e-5 as for
+    any other row."""
+    import torch
+    ngc = _ngc()
+    rng = np.random.default_rng(stride)
+    ladders = [(8, 10.0), (12, 6.5), (16, 5.0)]
+    n_items, keep = np.zeros(nseg, np.int32), np.zeros(nseg, np.int32)
+    logits, sigma = np.full((nseg, stride), np.nan, np.float32), np.zeros((nseg, 16), np.int32)
+    want = np.zeros(nseg)
+    for s in range(nseg):
+        k, step = ladders[s % 3]
+        m = n or k
+        x = np.full(m, -79.9, np.float32)              # never picked
+        sigma[s, :k] = rng.permutation(m)[:k]
+        x[sigma[s, :k]] = -step * np.arange(k) + 0.01 * rng.random(k)
+        x += np.float32(3.0)
+        n_items[s], keep[s], logits[s, :m] = m, k, x
+        e = np.exp(x.astype(np.float64) - x.max())
+        rest = np.cumsum(e[sigma[s, :k]][::-1])[::-1] + np.delete(e, sigma[s, :k]).sum()
+        want[s] = np.sum(np.log(e[sigma[s, :k]] / rest))
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    out = torch.zeros(nseg, device="cuda")
+    ws = torch.zeros(ngc.STATUS_WORDS * 4, dtype=torch.uint8, device="cuda")
+    print(f"[logprob-rows] ladder stride={stride} n={n} nseg={nseg}", flush=True)
+    ngc.ngc_subset_logprob(d(logits), d(n_items), d(sigma), d(keep), nseg, stride, 16, out, ws)
+    off = np.abs(out.cpu().numpy() - want)
+    assert np.all(off <= 1e-4 * np.abs(want) + 1e-5), (off.max(), int((off > 1e-4 * np.abs(want) + 1e-5).sum()))
