@@ -328,7 +328,7 @@ void decode_kernel(AttnArgs a)
                     o[u] = ld_device16(po, (uint32_t)((sp * G * D + i4 * 4) * sizeof(float)));
                     ml[u] = ld_device8(pml, (uint32_t)((sp * G + qi) * 2 * sizeof(float)));
                 }
-                float top = M;                       // finite: a partial has at least one row
+                float top = M;                       // finite from here on: every partial's maximum is
 #pragma unroll
                 for (int u = 0; u < MERGE; ++u) top = fmaxf(top, ml[u][0]);
                 const float old = fast_exp2(M - top);
@@ -364,7 +364,9 @@ void decode_kernel(AttnArgs a)
     f32x4 oacc[DPL];
 #pragma unroll
     for (int c = 0; c < DPL; ++c) oacc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run = -INFINITY, l_run = 0.f;
+    // The running maximum starts at the smallest finite number: exponents against it are never inf - inf, so rows that score
+    // -inf add 0 to the sum and to O whatever comes before or after them (and a wave without rows has factor 0 in the merges).
+    float m_run = -FLT_MAX, l_run = 0.f;
 
 #pragma unroll
     for (int c = 0; c < KCH; ++c)
@@ -425,7 +427,7 @@ void decode_kernel(AttnArgs a)
 #pragma unroll
         for (int e = 1; e < 8; ++e) tmax = fmaxf(tmax, x[e]);
         tmax = quad_rows_max(tmax);
-        const float m_new = fmaxf(m_run, tmax);           // finite: a tile has a valid row
+        const float m_new = fmaxf(m_run, tmax);
         if (__ballot(m_new != m_run)) {                   // wave-uniform: the running max moved somewhere
             const float alpha = fast_exp2(m_run - m_new); // 0 on the first tile, 1 where nothing changed
             l_run *= alpha;
@@ -544,7 +546,7 @@ void decode_kernel(AttnArgs a)
     constexpr int OROW = D + 4;                            // floats
     static_assert(16 * OROW * 4 <= WAVE_LDS, "staging area too small");
     l_run = quad_rows_sum(l_run);
-    if (kg == 0) { red_m[wv][li] = m_run; red_l[wv][li] = m_run == -INFINITY ? 0.f : l_run; }   // (rows that all score -inf sum to NaN)
+    if (kg == 0) { red_m[wv][li] = m_run; red_l[wv][li] = l_run; }
     // lane (q = li, kg), register (c, r) holds d = DPL * (4kg + r) + c
     if (li < G) {
 #pragma unroll
@@ -560,11 +562,10 @@ void decode_kernel(AttnArgs a)
         m_all = red_m[0][qi];
 #pragma unroll
         for (int w = 1; w < ATT_WAVES; ++w) m_all = fmaxf(m_all, red_m[w][qi]);
-        const float m_ref = fmaxf(m_all, -FLT_MAX);        // (a segment whose rows all score -inf: factors 0, not NaN)
         l_all = 0.f;
 #pragma unroll
         for (int w = 0; w < ATT_WAVES; ++w) {
-            f[w] = fast_exp2(red_m[w][qi] - m_ref);
+            f[w] = fast_exp2(red_m[w][qi] - m_all);
             l_all += red_l[w][qi] * f[w];
         }
     };

@@ -211,10 +211,13 @@ def test_first_tile_before_and_after_the_length(B, hint, D, Hq):
     check(out, lse, k, v, n, "paged")
 
 
+@pytest.mark.parametrize("lost", ["a wave", "first tiles", "a workgroup", "all but a row"])
 @pytest.mark.parametrize("B", [2, 130])           # several workgroups a segment, one
 @pytest.mark.parametrize("D,Hq", [(64, 8), (128, 12)])
-def test_wave_whose_rows_all_score_minus_infinity(B, D, Hq):
-    """One wave in four sees only rows that score -inf: the log-sum-exp is that of the other rows (2e-5 as above)."""
+def test_rows_that_score_minus_infinity(B, D, Hq, lost):
+    """Rows that score -inf for every query add nothing, whether they are all that one wave of four sees, the first that every
+    wave sees, all that a workgroup of a shared segment sees, or nearly all there are: output and log-sum-exp are those of the
+    other rows (tolerances as above).  A row of NaN is not hidden by them."""
     import torch
     ngc = _ngc()
     H, cap, scale = 2, 500, D ** -0.5
@@ -224,12 +227,23 @@ def test_wave_whose_rows_all_score_minus_infinity(B, D, Hq):
     v = torch.randn(1, B, H, cap, D, generator=g).to(torch.bfloat16)
     q = torch.randn(B, Hq, D, generator=g).to(torch.bfloat16)
     q[..., 0] = 1
-    lost = torch.arange(cap) // 32 % 4 == 1
-    want = torch.logsumexp(q.double().view(B, H, -1, D) @ k[0, :, :, ~lost].double().transpose(-1, -2) * scale, -1)
-    k[..., lost, 0] = float("-inf")
-    out, lse = torch.zeros(B, Hq, D, device="cuda"), torch.zeros(B, Hq, device="cuda")
-    c = ngc.Cache(k.cuda(), v.cuda(), n.cuda(), None, Hq)
-    ws = ngc.allocate_workspace(c, 1)
-    print(f"[decode-edges] -inf B={B} D={D}", flush=True)
-    ngc.ngc_decode_attn(c, 0, q.cuda(), scale, cap, out, ws, lse_out=lse)
-    assert (lse.cpu().double().view_as(want) - want).abs().max() <= 2e-5
+    tile = torch.arange(cap) // 32                    # tile t: wave t % 4 of workgroup t / 4 modulo the workgroups
+    gone = {"a wave": tile % 4 == 1, "first tiles": tile < 12, "a workgroup": tile // 4 == 1,
+            "all but a row": torch.arange(cap) != 77}[lost]
+    s = q.double().view(B, H, -1, D) @ k[0][:, :, ~gone].double().transpose(-1, -2) * scale
+    want_lse, want = torch.logsumexp(s, -1), torch.softmax(s, -1) @ v[0][:, :, ~gone].double()
+    k[..., gone, 0] = float("-inf")
+    for nan in (False, True):
+        if nan:
+            k[:, -1, :, 40, 0] = float("nan")
+        out, lse = torch.zeros(B, Hq, D, device="cuda"), torch.zeros(B, Hq, device="cuda")
+        c = ngc.Cache(k.cuda(), v.cuda(), n.cuda(), None, Hq)
+        ws = ngc.allocate_workspace(c, 1)
+        print(f"[decode-edges] -inf {lost} B={B} D={D} nan={nan}", flush=True)
+        ngc.ngc_decode_attn(c, 0, q.cuda(), scale, cap, out, ws, lse_out=lse)
+        got, got_lse = out.cpu().double().view_as(want), lse.cpu().double().view_as(want_lse)
+        m = B - 1 if nan else B
+        assert (got_lse[:m] - want_lse[:m]).abs().max() <= 2e-5
+        assert (got[:m] - want[:m]).abs().max() <= TOL
+        if nan:
+            assert torch.isnan(got[-1]).all() and torch.isnan(got_lse[-1]).all()
