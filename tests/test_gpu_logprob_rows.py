@@ -264,3 +264,37 @@ def test_logprob_of_nearly_certain_given_picks(stride, n, nseg):
     ngc.ngc_subset_logprob(d(logits), d(n_items), d(sigma), d(keep), nseg, stride, 16, out, ws)
     off = np.abs(out.cpu().numpy() - want)
     assert np.all(off <= 1e-4 * np.abs(want) + 1e-5), (off.max(), int((off > 1e-4 * np.abs(want) + 1e-5).sum()))
+
+
+@pytest.mark.parametrize("stride,n,nseg", [(64, 64, 4), (8200, 1500, 513)])        # held in registers, staged in LDS
+def test_gradient_with_large_upstream_weights(stride, n, nseg):
+    """Upstream weights as a loss scale makes them, over rows whose last items lie just under 80 below the largest: the sum of
+    1 / R_j reaches e^80, its product with the weight leaves fp32's range, the gradient (weight times a share) does not.
+    Masked items that nobody picks get 0.  1e-4 of an entry plus 2e-6 of the weight as elsewhere."""
+    import torch
+    ngc = _ngc()
+    rng = np.random.default_rng(n)
+    first, k = nseg - 3, n // 2
+    weights = np.array([65536.0, -1.0e6, 1.0e-3], np.float32)
+    n_items, keep, gout = np.zeros(nseg, np.int32), np.zeros(nseg, np.int32), np.zeros(nseg, np.float32)
+    logits, sigma = np.full((nseg, stride), np.nan, np.float32), np.zeros((nseg, k), np.int32)
+    for s in range(first, nseg):
+        order = rng.permutation(n)
+        x = np.full(n, -79.5, np.float32) + 0.1 * rng.random(n).astype(np.float32)
+        x[order[0]] = 0.0
+        x[order[-3:]] = -np.inf
+        n_items[s], keep[s], gout[s], logits[s, :n], sigma[s] = n, k, weights[s - first], x, order[:k]
+    d = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    grad = torch.full((nseg, stride), float("nan"), device="cuda")
+    ws = torch.zeros(ngc.STATUS_WORDS * 4, dtype=torch.uint8, device="cuda")
+    print(f"[logprob-rows] large weights stride={stride} n={n}", flush=True)
+    ngc.ngc_subset_logprob_backward(d(logits), d(n_items), d(sigma), d(keep), nseg, stride, k, k, d(gout), grad, ws)
+    g = grad.cpu().numpy()
+    for s in range(first, nseg):
+        e = np.exp(logits[s, :n].astype(np.float64))
+        picked = e[sigma[s]]
+        inv = np.cumsum(1.0 / (np.cumsum(picked[::-1])[::-1] + np.delete(e, sigma[s]).sum()))
+        want = -e * inv[-1]
+        want[sigma[s]] = 1.0 - picked * inv
+        assert np.all(np.abs(g[s, :n] - gout[s] * want) <= abs(gout[s]) * (1e-4 * np.abs(want) + 2e-6)), s
+        assert (g[s, :n][np.isinf(logits[s, :n])] == 0).all() and np.isnan(g[s, n:]).all()
