@@ -727,10 +727,9 @@ __global__ __launch_bounds__(LMEM_THREADS) void lmem_layer_kernel(LmemArgs a)
 }
 
 // Advantages, layers, total and upstream weights in one launch by one workgroup, where there is little to add up or few
-// layers to spread it over: 3 + 0.33 us per 1024 terms, while the two kernels take 7 us and another 1 us per 1024 terms of a
-// layer (call after call: 2 rounds x 7 layers x 128 rollouts x 4 heads 6.9 -> 6.0 us; 3 x 28 x 16 x 2 7.1 -> 5.8; 1 x 1 x
-// 1024 x 32 38 -> 14; 5 x 28 x 64 x 2 would take 10.3 instead of 7.5).  A wave adds one layer's terms or, with fewer
-// layers than waves, an equal share of them.
+// layers to spread it over (lmem_in_one(): call after call 2 rounds x 7 layers x 128 rollouts x 4 heads 6.9 -> 5.9 us;
+// 3 x 28 x 16 x 2 7.3 -> 5.8; 1 x 1 x 1024 x 32 38 -> 14).  A wave adds one layer's terms or, with fewer layers than waves,
+// an equal share of them; with more, it takes one after another.
 constexpr int LMEM_ONE_THREADS = 1024;
 constexpr int LMEM_ONE_WAVES = LMEM_ONE_THREADS / NGC_WAVE;
 constexpr int LMEM_ONE_MAX_B = 1024;
@@ -1507,6 +1506,25 @@ LogprobShape logprob_shape(int64_t stride, int64_t most_picks, int nseg, bool gr
     return {1024, 16, row_cap};
 }
 
+// Whether Eq. 4 goes to one workgroup.  Nanoseconds, call after call: it takes about 3700 + 0.32 a term and, beyond the 16
+// layers that its waves hold at once, 1.3 L^2; the two kernels 5900 + 240 for every 256 rollouts and heads of every round + 20
+// a layer.  Microseconds of two kernels and of one (* where it is taken):
+//      1 layer,   16 rounds, 8192 terms  14.6   5.7 *      20 layers,  1 round,  10240 terms   6.5   7.0
+//      4 layers,   8 rounds, 16384        9.9   8.6 *      28 layers,  9 rounds,  8064         9.0   7.0 *
+//      8 layers,   3 rounds, 12288        7.2   7.6        28 layers,  1 round,  14336         6.8   8.1
+//     16 layers,   1 round,  8192         6.5   5.7 *      40 layers,  1 round,   1280         7.0   6.3 *
+//     16 layers,   2 rounds, 16384        6.9   8.4        48 layers,  1 round,   1536         7.2   7.3
+//     17 layers,   1 round,  8704         6.5   6.7       128 layers,  1 round,   4096        10.7  15.7
+bool lmem_in_one(int64_t R, int64_t L, int64_t B, int64_t H)
+{
+    if (B > LMEM_ONE_MAX_B || L > LMEM_ONE_MAX_L || B * H > LMEM_ONE_MAX_TERMS || R > LMEM_ONE_MAX_TERMS ||
+        R * L * B * H > LMEM_ONE_MAX_TERMS)
+        return false;
+    const int64_t one = 3700 + R * L * B * H * 32 / 100 + (L > LMEM_ONE_WAVES ? L * L * 13 / 10 : 0);
+    const int64_t two = 5900 + 240 * R * ((B * H + LMEM_THREADS - 1) / LMEM_THREADS) + 20 * L;
+    return one <= two;
+}
+
 // One of the five instantiations of a kernel by its workgroup.
 #define NGC_PICK_SHAPE(KERNEL, shape) \
     ((shape).picks == 4       ? reinterpret_cast<const void *>(&KERNEL<256, 4, 1>) \
@@ -1741,8 +1759,7 @@ extern "C" int ngc_lmem(const float *logp, const int32_t *rounds, const float *r
     if (B > LMEM_MAX_B) return NGC_EUNSUPPORTED;
     LmemArgs la{logp, rounds, reward, adv_out, loss_layer, gout, R, L, B, Hkv, group};
     hipStream_t st = (hipStream_t)stream;
-    const long long terms = (long long)R * L * B * Hkv;
-    if (B <= LMEM_ONE_MAX_B && L <= LMEM_ONE_MAX_L && terms <= LMEM_ONE_MAX_TERMS && terms * (L - 3) <= 9200LL * L) {
+    if (lmem_in_one(R, L, B, Hkv)) {
         hipLaunchKernelGGL(lmem_one_kernel, dim3(1), dim3(LMEM_ONE_THREADS), 0, st, la,
                            divide_by((uint32_t)Hkv), divide_by((uint32_t)(B * Hkv)), loss);
         NGC_HIP_CHECK(hipGetLastError());

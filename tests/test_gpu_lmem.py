@@ -18,7 +18,8 @@ def _ngc():
                                        # waves, shares of a layer that are not whole batches, one head and many
                                        (1, 16, 352, 2, 16), (1, 16, 354, 2, 6), (1, 3, 1024, 10, 4), (1, 128, 4, 3, 2), (1, 129, 4, 3, 2),
                                        (5, 17, 3, 7, 3), (1, 1, 1024, 32, 8), (1, 1, 1040, 31, 8), (2, 5, 1, 3000, 1),
-                                       (2, 7, 128, 4, 16)])
+                                       (2, 7, 128, 4, 16), (1, 16, 316, 2, 4), (1, 16, 318, 2, 6), (120, 128, 1, 2, 1),
+                                       (9, 28, 16, 2, 16), (1, 40, 16, 2, 16), (1, 48, 16, 2, 16)])
 def test_loss_advantages_and_weights(R, L, B, H, G):
     import torch
     ngc = _ngc()
