@@ -1637,7 +1637,9 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
     // holes (few rows move), is bound by the selection's waits; two 512-thread workgroups per CU cover each other's up to
     // the 8192 rows at which two of them still fit in LDS (1024 segments of 8192: 96 us, 135 with 1024 threads), 256
     // threads up to 2048 rows (1024 of 1500: 25 us, 28 with 512) unless there are too few segments to fill the chip
-    // that way (16 of 1500: 14.6 us with 512 threads, 17.2 with 256).
+    // that way (16 of 1500: 14.6 us with 512 threads, 17.2 with 256).  Their 512-thread kernel is the one with 2 rows a thread in
+    // the ordered copy, which they do not run: 63 registers instead of the 113 that 8 rows cost, three workgroups a CU instead
+    // of two (2048 segments of 4096 rows, kept lists only: 56 us, 66 with the other; 1024: 31.7 and 34.8).
     const bool move_rows = !(p->flags & NGC_EVICT_SELECT_ONLY);
     const bool copy_bound = move_rows && !(p->flags & NGC_EVICT_UNORDERED);
     const int few = (copy_bound || nseg <= 512) ? 512 : 2048;
@@ -1669,6 +1671,7 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
 #define NGC_PICK(T, U) ((c->D == 128) ? reinterpret_cast<const void *>(&evict_kernel<T, 256, U>) \
                                       : reinterpret_cast<const void *>(&evict_kernel<T, 128, U>))
     if (threads == 1024) fn = NGC_PICK(1024, 4);
+    else if (threads == 512 && !copy_bound) fn = NGC_PICK(512, 2);
     else if (threads == 512) fn = NGC_PICK(512, 8);
     else fn = NGC_PICK(256, 6);
 #undef NGC_PICK
