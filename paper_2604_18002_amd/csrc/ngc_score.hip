@@ -4,8 +4,8 @@
 // (optionally) averaged over KV heads and over blocks of consecutive keys.
 //
 // One workgroup of 4 waves per (layer, sequence, KV head), several where there are
-// few of those and the normalisers are given (those kernels ask for everything
-// at once, the queries and normalisers before the length is known, and compare a key with what a query sees only at a segment's end).  The w*G query rows
+// few of those and the normalisers are given (those kernels ask for the queries and
+// normalisers before the length is known).  The w*G query rows
 // are padded to QT tiles of 16 and both passes run on the matrix cores:
 //   pass 1  S^T = K Q^T   (queries on lane%16): running max / sum per query row
 //   pass 2  S   = Q K^T   (keys on lane%16):    p = 2^(x - m) / l, summed over
@@ -16,8 +16,6 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
-
-#include <type_traits>
 
 #include "../../include/ngc.h"
 #include "ngc_device.h"
@@ -73,6 +71,7 @@ void score_keys_kernel(ScoreArgs a)
     const int seg = a.seg0 + (int)(blockIdx.x - share * a.nseg);
     const int first_tile = share * SC_WAVES;
     const int G = a.G, w = a.w, R = w * G;
+    if (GIVEN && share > 0 && a.share_rows > 0 && a.len[seg] < a.share_rows) return;   // nothing to share
     // Asked for first, none of it waits for the length: the query operands -- row r = qt*16 + li  ->  (recent query
     // j = r / G, head g = r % G) -- and the normaliser of row threadIdx.x.
     const int h = seg % a.Hkv;
@@ -145,7 +144,11 @@ void score_keys_kernel(ScoreArgs a)
         }
     };
 
-    if constexpr (GIVEN) load_tile(first_tile + wv);
+    // The first tile before the normalisers are there, except with one query tile, where the launches that are resident at
+    // once (up to 512 segments) got slower for it: 400 segments of 2150-3789 keys 52.0 -> 55.0 us, 512 63.8 -> 65.6; with two
+    // tiles 512 68.7 -> 67.9, 300 51.9 -> 49.9.
+    constexpr bool ASK_EARLY = GIVEN && QT > 1;
+    if constexpr (ASK_EARLY) load_tile(first_tile + wv);
     // ------------------------------------------------ pass 1: max and sum ---
     // (skipped when the caller hands over the log-sum-exp that decode attention
     // already computed for these very queries: then K is read only once)
@@ -253,55 +256,43 @@ void score_keys_kernel(ScoreArgs a)
             vis_row[qt][r] = (row < R && vis > 0) ? vis : 0;
         }
     const float inv_rows = 1.0f / (float)R;
-    // Rows that every query sees: all but the last w - 1.  There only the rows that pad the last query tile are left out, and
-    // the comparisons with what a query sees (two instructions for every probability) are not needed.  A wave with a few
-    // tiles does without that copy of the loop body: fetching a second one costs it more (64 segments, 8 workgroups each: 0.5 us of 12).
-    const int seen_by_all = tiles <= 8 * tile_step ? 0 : a.causal ? n - w + 1 : n;
-    auto scores_of_tile = [&](int row0, auto all_seen) {
-        bf16x8 kop[2][KCH];
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int c = 0; c < KCH; ++c)
-                kop[nt][c] = __builtin_bit_cast(
-                    bf16x8, *reinterpret_cast<const u32x4 *>(wlds + (nt * 16 + li) * LROW + c * 64 + kg * 16));
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            const int t = row0 + nt * 16 + li;   // the key of this lane
-            float acc = 0.f;
-#pragma unroll
-            for (int qt = 0; qt < QT; ++qt) {
-                f32x4 s = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int c = 0; c < KCH; ++c)
-                    s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qop[qt][c], kop[nt][c], s, 0, 0, 0);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    float p = fast_exp2(s[r] * a.scale_log2e - m_row[qt][r]);
-                    if constexpr (!GIVEN) p *= il_row[qt][r];
-                    if constexpr (decltype(all_seen)::value) {
-                        if (qt < QT - 1 || vis_row[qt][r] > 0) acc += p;
-                    } else {
-                        if (t < vis_row[qt][r]) acc += p;
-                    }
-                }
-            }
-            acc = quad_rows_sum(acc);
-            if (kg == 0 && t < n) psi[t] = acc * inv_rows;
-        }
-    };
     {
         int tile = first_tile + wv;
-        if constexpr (!GIVEN) load_tile(tile);
+        if constexpr (!ASK_EARLY) load_tile(tile);
         for (; tile < tiles; tile += tile_step) {
             stage_tile();
             const int row0 = tile * SC_TILE;
             load_tile(tile + tile_step);
             __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_wave_barrier();
-            if (row0 + SC_TILE <= seen_by_all) scores_of_tile(row0, std::true_type{});
-            else scores_of_tile(row0, std::false_type{});
+            bf16x8 kop[2][KCH];
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+                for (int c = 0; c < KCH; ++c)
+                    kop[nt][c] = __builtin_bit_cast(
+                        bf16x8, *reinterpret_cast<const u32x4 *>(wlds + (nt * 16 + li) * LROW + c * 64 + kg * 16));
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                const int t = row0 + nt * 16 + li;   // the key of this lane
+                float acc = 0.f;
+#pragma unroll
+                for (int qt = 0; qt < QT; ++qt) {
+                    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int c = 0; c < KCH; ++c)
+                        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qop[qt][c], kop[nt][c], s, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        float p = fast_exp2(s[r] * a.scale_log2e - m_row[qt][r]);
+                        if constexpr (!GIVEN) p *= il_row[qt][r];
+                        if (t < vis_row[qt][r]) acc += p;
+                    }
+                }
+                acc = quad_rows_sum(acc);
+                if (kg == 0 && t < n) psi[t] = acc * inv_rows;
+            }
         }
     }
 }
@@ -384,11 +375,12 @@ namespace {
 //       128 x 8000       85.2  52.5  46.2  48.8  49.3  52.5
 //       400 x 2000       38.7  43.6  41.7  43.7  54.6  54.4
 //      2048 x 2150-3789   284   282   294   327   382   470
-// i.e. about two workgroups per CU, four at D = 64 (512 x 2000-6000: 64.9, 55.7 with two each).  From there to 1536
-// segments, two rounds of resident workgroups, a second workgroup evens out what the last ones leave idle, if the segments are
-// long (both libraries in turns on the same buffers: 1024 x 2150-3789 155 -> 142, 600 x 2150-3789 88.6 -> 86.4; 2048 of equal
-// length 274 -> 278, of 2150-3789 278 -> 272; 512 x 1000 24.8 -> 26.7).  The host does not know the lengths, so it launches the
-// second one where the capacity permits and the kernel has it leave at once if the segment has fewer than SHARE_ROWS rows.
+// i.e. about two workgroups per CU, four at D = 64 (512 x 2000-6000: 64.9, 55.7 with two each).  Just beyond that, up to 640
+// segments at D = 128, a second workgroup evens out what the last ones leave idle, if the segments are long (S = 1 -> 2:
+// 520 x 2150-3789 78.5 -> 72.4, 640 x 2150-3789 92.7 -> 89.0; 768 x 4096 136 -> 138, 1536 x 4096 273 -> 279; at D = 64
+// 640 x 2150-3789 45.5 -> 43.0, but 520 x 100-300 in a capacity of 2500 4.9 -> 5.2: not there).  The host does not know the
+// lengths, so it launches the second one where the capacity permits; if the segment has fewer than SHARE_ROWS rows that
+// leaves before it asks for anything else (640 x 100-300 in a capacity of 4096 9.8, 10.4 before there was one).
 constexpr int SHARE_ROWS = 2048;
 
 struct Shares {
@@ -400,7 +392,7 @@ Shares score_shares(int nseg, int cap, int D, bool have_lse)
     if (!have_lse) return {1, 0};
     const int rounds = (cap + SC_TILE * SC_WAVES - 1) / (SC_TILE * SC_WAVES);
     const int fill = (D == 128 ? 512 : 1024) / nseg;
-    if (fill < 2 && nseg > 512 && nseg <= 1536 && cap >= SHARE_ROWS) return {2, SHARE_ROWS};
+    if (D == 128 && nseg > 512 && nseg <= 640 && cap >= SHARE_ROWS) return {2, SHARE_ROWS};
     const int s = rounds < fill ? rounds : fill;
     return {s > 1 ? s : 1, 0};
 }
@@ -434,7 +426,7 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     sa.psi_out = scores_out;
     sa.status = reinterpret_cast<int32_t *>(ws);
     sa.seg0 = seg0; sa.nseg = nseg;
-    const Shares shares = score_shares(nseg, c->cap, c->D, lse_recent != nullptr);   // nseg * S <= max(nseg, 3072)
+    const Shares shares = score_shares(nseg, c->cap, c->D, lse_recent != nullptr);   // nseg * S <= max(nseg, 1280)
     sa.S = shares.S;
     sa.share_rows = shares.rows;
     sa.lb0 = layer < 0 ? 0 : layer * c->B;
@@ -450,18 +442,20 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     }
     hipStream_t st = (hipStream_t)stream;
     const int qt = (R + 15) / 16;
-#define NGC_LAUNCH_SCORE(DD, QQ) \
-    if (lse_recent) hipLaunchKernelGGL((score_keys_kernel<DD, QQ, true>), dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), 0, st, sa); \
-    else            hipLaunchKernelGGL((score_keys_kernel<DD, QQ, false>), dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), 0, st, sa)
-    if (c->D == 128) {
-        if (qt == 1) { NGC_LAUNCH_SCORE(128, 1); } else if (qt == 2) { NGC_LAUNCH_SCORE(128, 2); }
-        else if (qt == 3) { NGC_LAUNCH_SCORE(128, 3); } else { NGC_LAUNCH_SCORE(128, 4); }
-    } else {
-        if (qt == 1) { NGC_LAUNCH_SCORE(64, 1); } else if (qt == 2) { NGC_LAUNCH_SCORE(64, 2); }
-        else if (qt == 3) { NGC_LAUNCH_SCORE(64, 3); } else { NGC_LAUNCH_SCORE(64, 4); }
-    }
-#undef NGC_LAUNCH_SCORE
-    NGC_HIP_CHECK(hipGetLastError());
+#define NGC_PICK_QT(DD, GIVEN) \
+    (qt == 1   ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 1, GIVEN>) \
+     : qt == 2 ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 2, GIVEN>) \
+     : qt == 3 ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 3, GIVEN>) \
+               : reinterpret_cast<const void *>(&score_keys_kernel<DD, 4, GIVEN>))
+    const void *fn = c->D == 128 ? (lse_recent ? NGC_PICK_QT(128, true) : NGC_PICK_QT(128, false))
+                                 : (lse_recent ? NGC_PICK_QT(64, true) : NGC_PICK_QT(64, false));
+#undef NGC_PICK_QT
+    // With two query tiles at D = 128 and the normalisers given four workgroups fit a CU.  Between 1024 and 1536 segments two
+    // rounds of three are fuller than two of four: LDS that nobody uses keeps the fourth out (1536 x 1366-1800 keys 110 -> 107.5
+    // us, 1030 77.4 -> 75.8; with four 1024 x 2150-3789 147 -> 139, 896 x 700 30.2 -> 29.0).
+    const size_t keep_out = c->D == 128 && qt == 2 && lse_recent && nseg > 1024 && nseg <= 1536 ? 8192 : 0;
+    void *kargs[] = {&sa};
+    NGC_HIP_CHECK(hipLaunchKernel(fn, dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), kargs, keep_out, st));
     if (pool || block > 1) {
         // scores_out is indexed by the global segment; the reduce kernel gets the global base
         ReduceArgs ra{scores_out, c->len, seg0 / c->Hkv, c->Hkv, c->cap, block, pool ? 1 : 0};

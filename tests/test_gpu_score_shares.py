@@ -83,13 +83,16 @@ def test_shared_segments(B, cap, D, Hq, block):
     assert all(v == 0 for v in ngc.read_status(ws))
 
 
-@pytest.mark.parametrize("B,cap", [(257, 2048), (768, 2050), (769, 2048)])
-def test_second_workgroup_of_long_segments(B, cap):
-    """More segments than CUs twice over: those of 2048 rows and more are shared by two workgroups (up to 1536 segments),
-    shorter ones are not; the last rows are not seen by all queries.  Only a few segments are compared."""
+@pytest.mark.parametrize("B,cap,D,w", [(257, 2048, 64, 4), (768, 2050, 64, 4), (769, 2048, 64, 4), (257, 2048, 128, 4),
+                                       (320, 2050, 128, 9), (321, 2048, 128, 4), (512, 2048, 128, 9), (513, 2048, 128, 9),
+                                       (768, 2050, 128, 9), (769, 2048, 128, 9)])
+def test_second_workgroup_of_long_segments(B, cap, D, w):
+    """More segments than CUs twice over: at D = 128 those of 2048 rows and more are shared by two workgroups (up to 640
+    segments), shorter ones are not; the last rows are not seen by all queries.  Either side of that, and of the numbers of
+    segments between which launches with two query tiles keep to three workgroups a CU.  Only a few segments are compared."""
     import torch
     ngc = _ngc()
-    H, Hq, D, w = 2, 4, 64, 4
+    H, Hq = 2, 4
     scale = D ** -0.5
     g = torch.Generator().manual_seed(B + cap)
     lens = torch.full((1, B, H), 5, dtype=torch.int32)
