@@ -837,26 +837,15 @@ int launch_decode(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, 
         aa.tpp_shift = sh;
     }
     hipStream_t st = (hipStream_t)stream;
-    const dim3 grid(nseg, S), block(ATT_WAVES * 64);
     const bool early = first_tile_early(nseg, S, max_len, max_len_hint);
-#define NGC_LAUNCH_DECODE(PAGED, APPEND) \
-    if (c->D == 128) { \
-        if (early) hipLaunchKernelGGL((decode_kernel<128, PAGED, APPEND, true>), grid, block, 0, st, aa); \
-        else       hipLaunchKernelGGL((decode_kernel<128, PAGED, APPEND, false>), grid, block, 0, st, aa); \
-    } else { \
-        if (early) hipLaunchKernelGGL((decode_kernel<64, PAGED, APPEND, true>), grid, block, 0, st, aa); \
-        else       hipLaunchKernelGGL((decode_kernel<64, PAGED, APPEND, false>), grid, block, 0, st, aa); \
-    }
-    if (pc) {
-        NGC_LAUNCH_DECODE(true, false)
-    } else if (nr) {
-        NGC_LAUNCH_DECODE(false, true)
-    } else {
-        NGC_LAUNCH_DECODE(false, false)
-    }
-#undef NGC_LAUNCH_DECODE
-    NGC_HIP_CHECK(hipGetLastError());
-    return NGC_OK;
+#define NGC_PICK_DECODE(PAGED, APPEND) \
+    (c->D == 128 ? (early ? reinterpret_cast<const void *>(&decode_kernel<128, PAGED, APPEND, true>) \
+                          : reinterpret_cast<const void *>(&decode_kernel<128, PAGED, APPEND, false>)) \
+                 : (early ? reinterpret_cast<const void *>(&decode_kernel<64, PAGED, APPEND, true>) \
+                          : reinterpret_cast<const void *>(&decode_kernel<64, PAGED, APPEND, false>)))
+    const void *fn = pc ? NGC_PICK_DECODE(true, false) : nr ? NGC_PICK_DECODE(false, true) : NGC_PICK_DECODE(false, false);
+#undef NGC_PICK_DECODE
+    return launch(fn, dim3(nseg, S), dim3(ATT_WAVES * 64), 0, st, aa);
 }
 }  // namespace
 

@@ -454,8 +454,8 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     // rounds of three are fuller than two of four: LDS that nobody uses keeps the fourth out (1536 x 1366-1800 keys 110 -> 107.5
     // us, 1030 77.4 -> 75.8; with four 1024 x 2150-3789 147 -> 139, 896 x 700 30.2 -> 29.0).
     const size_t keep_out = c->D == 128 && qt == 2 && lse_recent && nseg > 1024 && nseg <= 1536 ? 8192 : 0;
-    void *kargs[] = {&sa};
-    NGC_HIP_CHECK(hipLaunchKernel(fn, dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), kargs, keep_out, st));
+    const int rc = launch(fn, dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), keep_out, st, sa);
+    if (rc) return rc;
     if (pool || block > 1) {
         // scores_out is indexed by the global segment; the reduce kernel gets the global base
         ReduceArgs ra{scores_out, c->len, seg0 / c->Hkv, c->Hkv, c->cap, block, pool ? 1 : 0};
