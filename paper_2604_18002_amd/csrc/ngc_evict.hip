@@ -1629,10 +1629,21 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
     // Workgroup size and rows in flight per thread, all measured.  A round that moves rows in order is a copy with a
     // selection in front, and the size follows the rows of a segment, not its items.  One 1024-thread workgroup per CU, whose
     // reads and writes take turns, copies best, but has nothing beside it while it selects, and half a round of 256 of them
-    // counts as a whole one: it is taken beyond 4096 rows and, with many segments or most rows kept, from fewer (512 over
-    // 1024 threads, times; half kept: 640 segments of 1400 rows 0.98, of 1800 1.00, of 4096 1.03; 1024: 0.99, 1.04, 1.06;
-    // 1152: 1.01, 1.07, 1.02; 2048: 1.06, 1.08, 1.08; nine tenths of 2500 rows 1.05-1.09 for all; a third kept of 2500 and 4096
-    // rows: 1024 segments 0.97 and 0.97, 1536 0.99 and 0.99, 1792 1.00 and 1.01, 3584 of 4096 1.02).  512 threads from
+    // counts as a whole one: it is taken beyond 4096 rows and, with many segments and enough rows kept, from fewer.  Times of
+    // 512 over 1024 threads by the share kept:
+    //     segments x rows      a tenth  a fifth  a quarter  a third  0.4   half  nine tenths
+    //        640 x 1600          0.81     0.84                0.93          0.98     1.04
+    //       1152 x 1600          0.80     0.88     0.95       0.97  1.00    1.02     1.06
+    //       1536 x 1300          0.69     0.82     0.85       0.95  0.95    1.00     1.05
+    //       1792 x 3300          0.86     0.97     0.89       0.98  1.00    1.02     1.07
+    //       2048 x 2048          0.77     0.90     0.94       0.99  1.00    1.05     1.06
+    //       3584 x 1300          0.65     0.81     0.86       0.99  0.99    1.07     1.09
+    //       3584 x 2304          0.78     0.98     0.98       1.05  1.08    1.09     1.11
+    //       3584 x 4096          0.73     0.89     0.98       1.04  1.05    1.06     1.06
+    // i.e. from half kept up and, beyond 2048 segments, from a third.  (Machines differ: where a plain copy runs at 5.9 instead
+    // of 5.0 TB/s the right half of the table is 0.94-1.02.)  What is kept is on the device; max_keep is its bound.
+    // Uneven budgets under a loose bound are taken for more than they are: 1536 x 1300 rows, a fifth kept of a bound of half,
+    // 114 us where 512 threads take 102; a third of a bound of 0.83, 152 and 155.  512 threads from
     // 513 rows up (896 of 700: 74, 77 with 256), 256 below (896 of 300: 35 and 38).  A round that only selects, or fills
     // holes (few rows move), is bound by the selection's waits; two 512-thread workgroups per CU cover each other's up to
     // the 8192 rows at which two of them still fit in LDS (1024 segments of 8192: 96 us, 135 with 1024 threads), 256
@@ -1643,10 +1654,10 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
     const bool move_rows = !(p->flags & NGC_EVICT_SELECT_ONLY);
     const bool copy_bound = move_rows && !(p->flags & NGC_EVICT_UNORDERED);
     const int few = (copy_bound || nseg <= 512) ? 512 : 2048;
-    const bool mostly_kept = 2LL * max_keep * p->block >= c->cap;
+    const long long kept_rows = (long long)max_keep * p->block;              // at most, of a segment
     int many = copy_bound ? 4096 : 8192;
-    if (copy_bound && (nseg > 1536 || (nseg > 1024 && mostly_kept))) many = 1280;
-    else if (copy_bound && nseg > 512 && mostly_kept) many = 1536;
+    if (copy_bound && ((nseg > 2048 && 3 * kept_rows >= c->cap) || (nseg > 1024 && 2 * kept_rows >= c->cap))) many = 1280;
+    else if (copy_bound && nseg > 512 && 2 * kept_rows >= c->cap) many = 1536;
     const int threads = c->cap > many ? 1024 : (c->cap > few ? 512 : 256);
     const int rank_cap = rank_capacity(threads, items_cap_al, keep_cap);
     const size_t lds = select_lds_bytes(threads, items_cap_al, keep_cap, rank_cap);

@@ -34,7 +34,11 @@ def _round(ngc, L, B, Hkv, cap, D, block, n, keep, max_keep, logits, flags, k, v
     # 1024 threads beyond 4096 rows, and below with many segments or most rows kept
     (3, 4097, 1, 128, 256, 4097), (3, 4500, 7, 64, 1, 2), (3, 9000, 1, 128, 2, 5), (514, 1537, 1, 64, 1, 2),
     (514, 1536, 1, 64, 1, 2), (1026, 1281, 1, 64, 1, 2), (1026, 1281, 1, 64, 1, 3), (1538, 1281, 1, 64, 1, 3),
-    (1538, 1280, 1, 64, 1, 3)])
+    (1538, 1280, 1, 64, 1, 3),
+    # either side of the kept share that decides: half of the rows, a third beyond 2048 segments
+    (514, 1537, 1, 64, 769, 1537), (514, 1537, 1, 64, 768, 1537), (1026, 1281, 1, 64, 641, 1281),
+    (1026, 1281, 1, 64, 640, 1281), (2050, 1281, 1, 64, 427, 1281), (2050, 1281, 1, 64, 426, 1281),
+    (2048, 1281, 1, 64, 427, 1281), (2050, 1290, 3, 128, 143, 430), (514, 1540, 4, 128, 193, 385)])
 def test_rows_follow_the_kept_list(nseg, cap, block, D, num, den):
     import torch
     ngc = _ngc()
@@ -49,12 +53,13 @@ def test_rows_follow_the_kept_list(nseg, cap, block, D, num, den):
     n = torch.full((L, B, Hkv), cap, dtype=torch.int32, device="cuda")
     n[0, B // 2:, -1] -= cap // 3 + 1                       # some end inside a block
     items_cap = -(-cap // block)
+    max_keep = -(-items_cap * num // den)                   # the bound that the workgroup is chosen by
+    n[0, -1, -1] = block * max_keep // 2 + 1
     items = (n + block - 1) // block
     keep = torch.minimum((items * num + den - 1) // den, items).clamp(min=1).to(torch.int32)
     keep[0, 0, 0] = 1
     keep[0, -1, -1] = items[0, -1, -1]                      # nothing moves
-    max_keep = -(-items_cap * num // den)
-    max_keep = max(max_keep, int(keep.max()))
+    assert int(keep.max()) <= max_keep
     logits = torch.randn(L, B, Hkv, cap, generator=g, device="cuda")
     print(f"[evict-tiles] nseg={nseg} cap={cap} block={block} D={D} {num}/{den}", flush=True)
     args = (L, B, Hkv, cap, D, block, n, keep, max_keep, logits)
