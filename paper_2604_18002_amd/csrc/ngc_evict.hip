@@ -264,9 +264,11 @@ __device__ __forceinline__ bool gather_picked(const float *row, const int32_t *s
     return true;
 }
 
-// One workgroup per segment; on the general route an LDS bitmap of picked items (65536 bits).
+// One workgroup per segment; on the general route an LDS bitmap of picked items (65536 bits).  Scalar registers: beyond 80 a
+// SIMD holds seven waves instead of eight, i.e. a CU three workgroups of 512 threads instead of four (896 segments of
+// 18000-20000 items, 5999 picks, general route: 95 us, 82 with at most 80).
 template <int THREADS, int PICKS, int QUADS>
-__global__ __launch_bounds__(THREADS) void subset_logprob_kernel(LogprobArgs a)
+__global__ __launch_bounds__(THREADS) __attribute__((amdgpu_num_sgpr(80))) void subset_logprob_kernel(LogprobArgs a)
 {
     // row_cap + SPARE_ITEMS floats or, on the general route, PICKED_WORDS of the bitmap and stage_cap floats
     extern __shared__ __align__(16) float dynamic_lds[];
