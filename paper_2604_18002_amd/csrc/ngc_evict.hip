@@ -1464,13 +1464,18 @@ int resident_workgroups(const void *fn, int threads, size_t lds, int items)
 //     LDS only two workgroups share a CU, so the picks decide.  Eq. 2 / gradient at a stride of 16384, us (one of 512
 //     threads on the general route alone, then threads x picks per thread):
 //         segments x items, picks       general     256 x 4/8     512 x 8/16    1024 x 16
-//         3584 x 150-300,    240       21.7 / 24.6  19.4 / 24.4   22.7 / 28.8       -
-//         2048 x 700-1400,   1120      19.5 / 26.5  18.2 / 23.9   17.1 / 22.8   37.8 / 49.2
-//         896 x 12000-16000, 1919      40.6 / 85.3  34.0 / 48.5   24.1 / 35.6   33.3 / 48.6
-//         3584 x 2150-3789,  3144      58.5 / 97        -         39.3 / 53.1   76.8 / 104
-//         896 x 6000-7000,   5599      38.6 / 92        -         21.0 / 28.7   29.2 / 40.6
-//         16 x 12000-16000,  7128      26.6 / 40.8      -         12.7 / 17.3   11.3 / 14.6
-//     Up to 2048 picks 256 threads are never the slowest; up to 512 segments, all resident at once, the larger
+//         3584 x 150-300,    240       15.2 / 17.2  17.3 / 20.0   20.6 / 24.8   42.9 / 60.2
+//         3584 x 300-600,    480       18.2 / 21.2  17.3 / 20.9   21.2 / 25.3   43.8 / 61.5
+//         3584 x 2150-3789, 1000       37.1 / 55.2  34.1 / 46.9   28.5 / 34.5   56.5 / 72.7
+//         2048 x 700-1400,  1120       15.5 / 21.8  14.1 / 17.2   14.2 / 17.0   28.8 / 37.6
+//         896 x 12000-16000, 1919      38.3 / 83.6  25.3 / 40.5   19.0 / 29.8   25.2 / 34.9
+//         3584 x 2150-3789, 3144       52.3 / 93.6       -        33.6 / 39.4   59.9 / 76.6
+//         896 x 6000-7000,  5599       34.6 / 95.4       -        16.3 / 21.4   23.1 / 30.1
+//         400 x 6000-7000,  2000       12.0 / 19.9   7.2 / 11.4    6.0 /  8.2    9.6 / 13.0
+//         16 x 12000-16000, 7128       23.6 / 38.0       -         8.4 / 12.2    7.1 /  8.6
+//     Up to 1024 picks the rows may be short or long, and 256 threads are the slowest for neither; beyond, rows are as long
+//     as their picks and 512 are never the slower ones (before the weights were computed once per item, 256 were, up to
+//     2048 picks).  Up to 512 segments, all resident at once, the larger
 //     workgroup is faster: it works through a row in fewer steps.
 //   - Longer strides, or one row for all segments (stride 0): rows may be longer than any LDS row or far shorter (blocks of
 //     rows as items).  LOGPROB_ROW_OF_FOUR items leave room for four workgroups of 512 threads, what the general route
@@ -1499,10 +1504,7 @@ LogprobShape logprob_shape(int64_t stride, int64_t most_picks, int nseg, bool gr
     if (row_cap <= 2048) return {256, 8, row_cap};
     if (row_cap <= 4096 && !gradient && nseg > LOGPROB_MANY) return {256, 16, row_cap};
     if (row_cap <= 8192) return {512, most_picks <= 4096 ? 8 : 16, row_cap};
-    if (nseg > LOGPROB_FEW) {
-        if (most_picks <= 1024) return {256, 4, row_cap};
-        if (most_picks <= 2048) return {256, 8, row_cap};
-    }
+    if (nseg > LOGPROB_FEW && most_picks <= 1024) return {256, 4, row_cap};
     if (most_picks <= 4096) return {512, 8, row_cap};
     if (most_picks <= 8192 && nseg > LOGPROB_FEW) return {512, 16, row_cap};
     return {1024, 16, row_cap};
