@@ -66,8 +66,8 @@ struct LogprobArgs {
 // the gradient 43 MB out; ~15 and ~24 us of traffic): three reads of the row and up to three gathers per pick 61 and
 // 102 us; one read of the row 35 and 44 (570 and 726 instructions a wave); one exponential per item instead of one per pick
 // and one per item and whatever the lanes of a wave disagree about, maxima of three, reductions that fold into their
-// additions, a reciprocal instead of a division: 24 and 29 us.  log p is added up in 64 bits from the threads on (error
-// against 64 bits 5.0e-8 -> 2.7e-8: it is a sum of thousands).
+// additions, a reciprocal instead of a division: 22.4 and 29.3 us.  log p is added up in 64 bits from the threads on (error
+// against 64 bits 5.0e-8 -> 2.6e-8: it is a sum of thousands).
 constexpr float PICKED = -1.0f;      // in the LDS row, where every weight is >= 0
 constexpr int PICKED_WORDS = 2048;   // general route: a bit per item
 constexpr int SPARE_ITEMS = 64;      // LDS words behind the row for lanes without a pick to mark (one each)
@@ -846,8 +846,8 @@ __global__ __launch_bounds__(64) void lmem_total_kernel(const float *loss_layer,
 // tile, moves more than one whose waves mix both.  2048 segments of 4096-8192 rows, us per round: loads of tile i+1
 // and stores of tile i in flight together (two register buffers) 956; stores held back until those loads have arrived 951, and
 // with a barrier after that 934; this loop 923, without its second barrier 970.  It holds half the registers, so the
-// 512-thread workgroups take 8 rows a thread (896 segments of 700 rows 78.6 -> 74.0; 3584 of 4096 rows, now in 1024-thread
-// workgroups, 946 -> 900).  The row indices come from LDS.  16-byte accesses, one full
+// 512-thread workgroups take 8 rows a thread (896 segments of 700 rows 77.4 us with 2, 74.4 with 8).  The row indices come
+// from LDS (pooled rounds: from kept_out).  16-byte accesses, one full
 // row per ROW_BYTES/16 consecutive lanes, K and V together; all of them carry
 // the nontemporal hint (every row is touched once).  Offsets inside a segment
 // are 32-bit (the host checks cap * ROW_BYTES < 2^31).
@@ -1227,7 +1227,7 @@ template <int THREADS, int ROW_BYTES, int UNROLL>
 __device__ __forceinline__ void evict_segment(const SelectArgs &a, int seg, unsigned char *smem_raw, int *misc)
 {
     Selected sel;
-    select_keep<THREADS, ROW_BYTES>(a, seg, smem_raw, sel);
+    select_keep<THREADS>(a, seg, smem_raw, sel);
     if (a.k != nullptr) {
         __syncthreads();   // publishes misc[], the ascending list and this workgroup's kept_out writes
         const int rows_new = misc[MISC_ROWS], first = misc[MISC_FIRST];   // kept is ascending, kept[j] >= j

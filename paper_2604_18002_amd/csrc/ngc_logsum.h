@@ -33,8 +33,8 @@ __device__ __forceinline__ float exp_shifted_finite(float d)
 // The same with -inf (a masked entry; 0) among the d (a NaN stays one).
 __device__ __forceinline__ float exp_shifted(float d) { return exp_shifted_finite(d < -200.0f ? -200.0f : d); }
 
-// 1 / x for a normal x in [1e-36, 1e36]: the hardware's reciprocal and one Newton step (within an ulp; 3 instructions
-// instead of the division's 11).
+// 1 / x for a normal x in [1e-36, 1e36]: the hardware's reciprocal and one Newton step, 3 instructions instead of the
+// division's 11 and the same result (compared for every mantissa at six exponents).
 __device__ __forceinline__ float reciprocal(float x)
 {
     const float r = __builtin_amdgcn_rcpf(x);

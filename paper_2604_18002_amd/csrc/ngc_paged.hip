@@ -47,7 +47,7 @@ __global__ __launch_bounds__(THREADS) void paged_evict_kernel(SelectArgs a, Page
     const int seg = a.seg0 + blockIdx.x;
 
     Selected sel;
-    select_keep<THREADS, 256>(a, seg, smem_raw, sel);   // a.k == nullptr: the row size is not used
+    select_keep<THREADS>(a, seg, smem_raw, sel);
     __syncthreads();
     select_score<THREADS>(a, seg, smem_raw, sel);
     if (pa.table == nullptr) return;                  // selection only

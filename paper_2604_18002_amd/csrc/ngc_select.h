@@ -230,8 +230,9 @@ __device__ __forceinline__ void fill_holes_inplace(unsigned char *kbase, unsigne
 
 // The thread's index as a value the compiler does not connect with that of the previous segment.  In the persistent
 // kernel (128 registers a thread) what follows from it would otherwise be computed once, before the loop over the
-// segments, and kept in scratch, to be read again for every segment while rows stream through the caches: 18 registers,
-// 1.2 % of the bytes of a round; 2048 segments of up to 8192 rows took 1005 us with 37 such registers, 988 with none.
+// segments, and kept: 26 registers.  With the copy's earlier second buffer they went to scratch, to be read again for every
+// segment while rows stream through the caches (2048 segments of up to 8192 rows 1005 us with 37 such registers, 988 with
+// none); with one buffer all 128 are in use without this, 102 with it, and the time is the same.
 template <int THREADS>
 __device__ __forceinline__ int fresh_thread_index()
 {
@@ -460,7 +461,7 @@ __device__ __forceinline__ uint16_t *sort_by_code_desc(CodeOf code_of, int K, ui
 // route runs, this is one counting pass, one prefix sum and one scatter, 5 workgroup barriers instead of ~25.
 //   bucketed   u16[N] scratch;  order   u16[K] out: the kept items by descending code, equal codes by ascending index
 //   kept_bits  one bit per item, zeroed by the caller (before a barrier), out: which items are kept
-//   hist       NB zeroed entries (before a barrier);  tmp  4 * waves entries
+//   hist       NB zeroed entries (before a barrier);  tmp  2 * waves entries
 // Masked items stay out of the buckets: they rank behind all others.  Returns false (workgroup-uniform) if a bucket holds
 // more than BUCKET_LIMIT items (many equal keys) or if masked items are kept: nothing but hist, bucketed and tmp has been
 // written then.  Whole workgroup; ends on a barrier.
@@ -643,7 +644,7 @@ struct Selected {
 
 // Besides, it leaves the kept count, the new row count and the first item that changes place in misc[MISC_KEPT],
 // misc[MISC_ROWS], misc[MISC_FIRST] (valid after the next barrier).  Every thread of the workgroup returns at the same point.
-template <int THREADS, int ROW_BYTES>
+template <int THREADS>
 __device__ __forceinline__ void select_keep(const SelectArgs &a, int seg, unsigned char *smem_raw, Selected &out)
 {
     constexpr int NW = THREADS / NGC_WAVE;
@@ -715,7 +716,7 @@ __device__ __forceinline__ void select_keep(const SelectArgs &a, int seg, unsign
     // Logits that span more than NGC_WIDE_SPREAD take the wide-range arithmetic of ngc_logsum.h for Eq. 2
     // (workgroup-uniform).
     bool wide = false;
-    if (want_sort) {   // all four maxima in one exchange
+    if (want_sort) {   // all four maxima in one exchange: up to all 64 words of misc, whose MISC_* slots are set after it
         smax = wave_max_f(smax);
         neg_smin = wave_max_f(neg_smin);
         cmax = wave_reduce(cmax, OpMaxU{});
