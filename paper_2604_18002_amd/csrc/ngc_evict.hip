@@ -294,7 +294,8 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_num_sgpr(80))) void 
     {
         PickedTerms<THREADS, PICKS, QUADS> pt;
         if (gather_picked<THREADS, PICKS, QUADS, false>(row, sig, N, K, a.row_cap, dynamic_lds, fmisc, a.status, pt)) {
-            float R = pt.unpicked + pt.after, acc = 0.f;
+            float R = pt.unpicked + pt.after;
+            double acc = 0.0;
             if (pt.count > 0) {
                 LogRatio ratio;                                // (a masked pick, weight 0, makes log p = -inf)
                 static_assert(PICKS <= LogRatio::MAX_PICKS);
@@ -304,11 +305,11 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_num_sgpr(80))) void 
                         R += pt.e[i];
                         if (i < pt.count) ratio.times(pt.e[i], R);
                     }
-                acc = ratio.log();
+                acc = ratio.log_d();
             }
             // (thousands for a long sequence: rounded once)
             double *totals = reinterpret_cast<double *>(fmisc);
-            const double total = wave_sum_d((double)acc);
+            const double total = wave_sum_d(acc);
             if (lane_id() == 0) totals[wave_id()] = total;
             __syncthreads();
             if (tid < NGC_WAVE) {

@@ -52,12 +52,18 @@ struct LogRatio {
     int exponent = 0;
     __device__ __forceinline__ void times(float e, float r)
     {
-        r = r > 0.f ? r : 1.0f;      // 0 only where e is
+        r = max_no_nan(r, 1.0e-37f);      // 0 only where e is; otherwise at least e^-80
         num *= __builtin_amdgcn_frexp_mantf(e);
         den *= __builtin_amdgcn_frexp_mantf(r);
         exponent += __builtin_amdgcn_frexp_expf(e) - __builtin_amdgcn_frexp_expf(r);
     }
     __device__ __forceinline__ float log() const { return __builtin_fmaf((float)exponent, 0.693147181f, logf(num / den)); }
+    // in 64 bits where it goes into such a sum: the exponents of thousands of picks add up to tens of thousands, and ln 2 in
+    // 32 bits alone is off by 2.7e-9 of itself
+    __device__ __forceinline__ double log_d() const
+    {
+        return __builtin_fma((double)exponent, 0.69314718055994531, (double)logf(num / den));
+    }
 };
 
 struct LogSum {
