@@ -1645,8 +1645,9 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
     //       3584 x 1300          0.65     0.81     0.86       0.99  0.99    1.07     1.09
     //       3584 x 2304          0.78     0.98     0.98       1.05  1.08    1.09     1.11
     //       3584 x 4096          0.73     0.89     0.98       1.04  1.05    1.06     1.06
-    // i.e. from half kept up and, beyond 2048 segments, from a third.  (Machines differ: where a plain copy runs at 5.9 instead
-    // of 5.0 TB/s the right half of the table is 0.94-1.02.)  What is kept is on the device; max_keep is its bound.
+    // i.e. from half kept up and, beyond 2048 segments, from a third.  (In one job of ten 512 threads copied faster than
+    // in all others, 2048 x 4096 rows, a third kept, in 478 us instead of 548, and the half-kept rounds were at 0.94-0.98;
+    // the cause was not found.)  What is kept is on the device; max_keep is its bound.
     // Uneven budgets under a loose bound are taken for more than they are: 1536 x 1300 rows, a fifth kept of a bound of half,
     // 114 us where 512 threads take 102; a third of a bound of 0.83, 152 and 155.  512 threads from
     // 513 rows up (896 of 700: 74, 77 with 256), 256 below (896 of 300: 35 and 38).  A round that only selects, or fills

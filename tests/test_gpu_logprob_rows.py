@@ -223,8 +223,9 @@ def test_rows_held_in_registers(stride, nseg):
             sig = sigma[s, :k]
             rest = np.cumsum(e[sig][::-1])[::-1] + np.delete(e, sig).sum()
             want = np.sum(row[sig] - row.max() - np.log(rest))
-            # one rounding of the total; a term is off by a few 2^-24 of up to 70
-            assert abs(lp[s] - want) <= 1e-6 * abs(want) + 1e-4, (kind, n, k)
+            # the total is rounded once; a term is off by 2^-21.6 and the ~40 roundings that R_j goes through one after the
+            # other, 2.7e-6 at most.  Over many picks terms are ~log n - 1 >= 5 in the mean (5e-7 of them), three picks 8e-6
+            assert abs(lp[s] - want) <= 1e-6 * abs(want) + 1e-5, (kind, n, k)
             c = np.cumsum(1.0 / rest)
             w = -e * c[-1]
             w[sig] = 1.0 - e[sig] * c
