@@ -98,7 +98,8 @@ struct AttnArgs {
     int max_pages;
     int num_pages;
     int tpp_shift;          // log2(tiles per page)
-    int32_t *ticket;        // [segments of the launch] workgroups of a segment that are done; 0 between launches
+    int32_t *ticket;        // [segments of the launch][ticket_step] workgroups of a segment that are done (the first word of
+    int ticket_step;        // each); 0 between launches
     // fused append (APPEND kernels only)
     unsigned char *k_rw;    // the cache again, writable
     unsigned char *v_rw;
@@ -279,7 +280,7 @@ void decode_kernel(AttnArgs a)
     auto took_last_ticket = [&]() -> bool {
         __syncthreads();   // this workgroup's partial stores have been waited for by their threads
         if (threadIdx.x == 0) {
-            const int old = __hip_atomic_fetch_add(&a.ticket[seg_local], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int old = __hip_atomic_fetch_add(&a.ticket[seg_local * a.ticket_step], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             is_last = (old == a.S - 1) ? 1 : 0;
         }
         __syncthreads();
@@ -289,7 +290,7 @@ void decode_kernel(AttnArgs a)
     // the appended row becomes part of the segment.
     auto close_segment = [&]() {
         if (threadIdx.x == 0) {
-            if (a.S > 1) __hip_atomic_store(&a.ticket[seg_local], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (a.S > 1) __hip_atomic_store(&a.ticket[seg_local * a.ticket_step], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (APPEND && grew) a.len_rw[seg] = n;
         }
     };
@@ -734,6 +735,21 @@ int static_limit_splits(int nseg_launch, int max_len, int row_bytes)
 // on the geometry (a ticket region that moved with the geometry would land on an earlier call's partials).
 constexpr size_t FIXED_TICKET_OFFSET = STATUS_BYTES;      // COMPUTE_UNITS tickets: only launches of at most
 constexpr size_t FIXED_PARTIAL_OFFSET = 4096;             // COMPUTE_UNITS / 2 segments are ever split
+constexpr size_t FIXED_TICKETS = (FIXED_PARTIAL_OFFSET - FIXED_TICKET_OFFSET) / sizeof(int32_t);
+
+// Words between the tickets of two segments.  Atomics on one cache line are served one after the other, so a launch's
+// tickets lie as far apart as the words at hand allow, up to a line of 128 bytes.  A workspace has a word for every
+// segment of the cache, so the launches of a model of L layers, one layer each, have L words for a segment; a launch
+// over all layers has one, as does a cache of a single layer.  Microseconds per layer from a HIP graph of 28 layers, words
+// next to each other -> 28 apart, D = 128 (no difference below 16 segments, where at most 64 atomics meet):
+//     16 x 1500 rows   8.27 -> 6.69      32 x 1500   8.83 -> 8.11      64 x 1500        11.56 -> 11.06
+//     32 x  300        5.70 -> 5.47      64 x  525   8.06 -> 7.79      128 x 525        10.18 ->  9.55
+//     32 x  525        6.31 -> 5.74      48 x 676-1352 8.91 -> 8.64    64 x 3000-10000  41.18 -> 39.89
+int ticket_step(size_t words, int nseg_launch)
+{
+    const size_t apart = words / (size_t)nseg_launch;
+    return apart > 32 ? 32 : apart > 1 ? (int)apart : 1;
+}
 
 bool fits_static(const ngc_cache *c, int nseg_launch, int S)
 {
@@ -821,6 +837,7 @@ int launch_decode(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, 
     aa.scale_log2e = scale * 1.4426950408889634f;
     aa.ticket = reinterpret_cast<int32_t *>(reinterpret_cast<unsigned char *>(ws) +
                                             (fixed_layout ? FIXED_TICKET_OFFSET : ticket_offset(c)));
+    aa.ticket_step = ticket_step(fixed_layout ? FIXED_TICKETS : (size_t)c->L * per_layer, nseg);
     aa.k_rw = reinterpret_cast<unsigned char *>(c->k);
     aa.v_rw = reinterpret_cast<unsigned char *>(c->v);
     aa.len_rw = c->len;
