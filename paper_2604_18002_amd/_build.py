@@ -1,6 +1,7 @@
 """Build the HIP libraries in-tree for gfx950: ``paper_2604_18002_amd/libngc.so`` (the method) and
 ``paper_2604_18002_amd/libngc_probe.so`` (streaming probes for the measurement harness); with the host compiler
-``paper_2604_18002_amd/_ngc_host.so`` (the Python front of the C ABI)."""
+``paper_2604_18002_amd/_ngc_host.so`` (the Python front of the C ABI) and ``paper_2604_18002_amd/libngc_torch.so`` (its reader
+of torch tensors)."""
 from __future__ import annotations
 
 import os
@@ -13,6 +14,7 @@ _CSRC = os.path.join(_PKG, "csrc")
 LIB_PATH = os.path.join(_PKG, "libngc.so")
 PROBE_LIB_PATH = os.path.join(_PKG, "libngc_probe.so")   # measurement probes, not part of the method
 HOST_LIB_PATH = os.path.join(_PKG, "_ngc_host.so")       # CPython front of the C ABI (no device code)
+TORCH_LIB_PATH = os.path.join(_PKG, "libngc_torch.so")   # the front's reader of torch tensors (no device code)
 
 _COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
            # packed fp32 instructions stay off on the test machines
@@ -61,11 +63,17 @@ def build(verbose: bool = False) -> str:
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
         raise RuntimeError("no host C++ compiler found; the Python front cannot be built")
-    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
-           "-I", sysconfig.get_paths()["include"], os.path.join(_CSRC, "ngc_host.cpp"), "-o", HOST_LIB_PATH, "-ldl"]
-    r = subprocess.run(cmd, capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"{cxx} failed on ngc_host.cpp:\n{r.stderr}")
+    import torch
+    from torch.utils.cpp_extension import include_paths, library_paths
+    python = ["-I", sysconfig.get_paths()["include"]]
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall"]
+    abi = f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"
+    torch_flags = [abi, *(f"-isystem{d}" for d in include_paths()), *(f"-L{d}" for d in library_paths()),
+                   "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    for src, lib, flags in (("ngc_host.cpp", HOST_LIB_PATH, ["-ldl"]), ("ngc_torch.cpp", TORCH_LIB_PATH, torch_flags)):
+        r = subprocess.run([*cmd, *python, os.path.join(_CSRC, src), "-o", lib, *flags], capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(f"{cxx} failed on {src}:\n{r.stderr}")
     return LIB_PATH
 
 

@@ -13,10 +13,11 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import sys
 from dataclasses import dataclass
 from typing import Optional
 
-from ._build import HOST_LIB_PATH, LIB_PATH
+from ._build import HOST_LIB_PATH, LIB_PATH, TORCH_LIB_PATH
 
 NGC_OK = 0
 NGC_EINVAL = -1
@@ -148,9 +149,18 @@ def load_library(path: Optional[str] = None) -> C.CDLL:
         from . import _ngc_host
         _ngc_host.open(path)
         _ngc_host.types(ArgumentError, Cache, PagedCache, ngc_cache, ngc_paged_cache, ngc_evict_params, C._SimpleCData)
+        if "torch" in sys.modules:
+            _read_tensors_directly(_ngc_host)
         _host = _ngc_host
         _lib = lib
     return lib
+
+
+def _read_tensors_directly(host) -> None:
+    """From now on the front reads plain tensors itself (torch has been imported)."""
+    if not os.path.exists(TORCH_LIB_PATH):
+        raise RuntimeError(f"{TORCH_LIB_PATH} is missing: build it first (python -m paper_2604_18002_amd._build)")
+    host.torch_reader(TORCH_LIB_PATH)
 
 
 def _front():
@@ -194,7 +204,10 @@ def _stream(stream) -> Optional[int]:
         # the current stream of the current device, without the Stream object where torch has its own way to that
         get, device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
         if get and device:
-            _current_raw_stream = lambda: get(device())     # noqa: E731
+            host = _front()
+            _read_tensors_directly(host)        # (torch may have been imported after the library)
+            host.stream_readers(device, get)
+            _current_raw_stream = host.current_stream
         else:
             _current_raw_stream = lambda: torch.cuda.current_stream().cuda_stream     # noqa: E731
     return _current_raw_stream()

@@ -1,8 +1,8 @@
 // CPython front of the C ABI: turns tensors into the plain pointers and structs of ngc.h and calls the entry point.
 //
 // The Python binding used ctypes for this: building an ngc_cache out of a dozen attribute reads and converting a dozen
-// arguments took ~6 us of the 8.5 us a decode step cost on the host, more than the kernel runs for a small cache.  Here
-// it takes ~1.5 us.  Marshalling only: no state is kept between calls, nothing is remembered about a tensor, and every
+// arguments took ~6 us of the 8.5 us a decode step cost on the host, more than the kernel runs for a small cache.  Here it took
+// 1.1 us through the tensors' methods, and takes 0.3 us with plain tensors read directly (ngc_torch.cpp).  Marshalling only: no state is kept between calls, nothing is remembered about a tensor, and every
 // check is the C ABI's own (plus the contiguity the binding always asked for).  What it takes is what ctypes took: a cache
 // with a view() of its own is asked for it, a structure must be of its type, a number may be a ctypes one.
 #define PY_SSIZE_T_CLEAN
@@ -11,6 +11,7 @@
 #include <stdint.h>
 
 #include "../../include/ngc.h"
+#include "ngc_torch.h"
 
 namespace {
 
@@ -31,6 +32,11 @@ struct Names {
     PyObject *k, *v, *len, *pos, *Hq, *k_pool, *v_pool, *pos_pool, *table, *free_stack, *free_count, *shape, *data_ptr,
         *numel, *is_contiguous, *view, *value;
 } names;
+
+// reads plain tensors directly; null until torch_reader() (torch may be imported later, or never)
+ngc_read_tensor_fn read_tensor = nullptr;
+// what stream_readers() was given: the current device, and the raw stream of a device
+PyObject *device_of = nullptr, *stream_of = nullptr;
 
 // what types() was given: the binding's own classes and functions
 struct Types {
@@ -54,6 +60,8 @@ struct Ref {   // a new reference, released at the end of the scope
 void *ptr(PyObject *t)
 {
     if (t == Py_None || PyErr_Occurred()) return nullptr;
+    ngc_tensor x;
+    if (read_tensor && read_tensor(t, &x)) return x.data;
     const Ref r(PyObject_CallMethodNoArgs(t, names.data_ptr));
     return r.o ? PyLong_AsVoidPtr(r.o) : nullptr;
 }
@@ -87,6 +95,8 @@ float f32(PyObject *o) { return number<float>(o, "float", PyFloat_AsDouble); }
 size_t bytes(PyObject *t)   // elements of a uint8 workspace tensor
 {
     if (PyErr_Occurred()) return 0;
+    ngc_tensor x;
+    if (read_tensor && read_tensor(t, &x)) return (size_t)x.numel;
     const Ref r(PyObject_CallMethodNoArgs(t, names.numel));
     return r.o ? PyLong_AsSize_t(r.o) : 0;
 }
@@ -109,6 +119,8 @@ void *attr_ptr(const Object &o, PyObject *name, bool contiguous)
     if (PyErr_Occurred()) return nullptr;
     const Ref t(o.get(name));
     if (!t.o) return nullptr;
+    ngc_tensor x;
+    if (read_tensor && read_tensor(t.o, &x) && (x.contiguous || !contiguous)) return x.data;
     if (contiguous) {
         const Ref c(PyObject_CallMethodNoArgs(t.o, names.is_contiguous));
         if (!c.o) return nullptr;
@@ -126,6 +138,11 @@ void sizes(const Object &o, PyObject *name, int32_t *d, Py_ssize_t count)
     if (PyErr_Occurred()) return;
     const Ref t(o.get(name));
     if (!t.o) return;
+    ngc_tensor x;
+    if (read_tensor && read_tensor(t.o, &x) && x.dims == count) {
+        for (Py_ssize_t i = 0; i < count; ++i) d[i] = (int32_t)x.sizes[i];
+        return;
+    }
     const Ref s(PyObject_GetAttr(t.o, names.shape));
     if (!s.o) return;
     if (!PyTuple_Check(s.o) || PyTuple_GET_SIZE(s.o) != count) {
@@ -346,6 +363,39 @@ PyObject *open_(PyObject *, PyObject *path)
     Py_RETURN_NONE;
 }
 
+// torch_reader(path): plain tensors are read by this library from now on (torch has been imported).
+PyObject *torch_reader(PyObject *, PyObject *path)
+{
+    const char *p = PyUnicode_AsUTF8(path);
+    if (!p) return nullptr;
+    void *h = dlopen(p, RTLD_NOW | RTLD_LOCAL);
+    if (!h) return PyErr_Format(PyExc_RuntimeError, "%s", dlerror());
+    const auto fn = reinterpret_cast<ngc_read_tensor_fn>(dlsym(h, "ngc_read_tensor"));
+    if (!fn) return PyErr_Format(PyExc_RuntimeError, "%s: no ngc_read_tensor", p);
+    read_tensor = fn;
+    Py_RETURN_NONE;
+}
+
+// stream_readers(device, stream): torch's own functions for the current device and a device's current raw stream.
+ENTRY(stream_readers, 2)
+    Py_INCREF(a[0]);
+    Py_XSETREF(device_of, a[0]);
+    Py_INCREF(a[1]);
+    Py_XSETREF(stream_of, a[1]);
+    Py_RETURN_NONE;
+END
+
+// current_stream() -> the raw stream as an int
+PyObject *current_stream(PyObject *, PyObject *)
+{
+    if (!device_of || !stream_of) {
+        PyErr_SetString(PyExc_RuntimeError, "stream_readers() has not been called");
+        return nullptr;
+    }
+    const Ref device(PyObject_CallNoArgs(device_of));
+    return device.o ? PyObject_CallOneArg(stream_of, device.o) : nullptr;
+}
+
 // types(ArgumentError, Cache, PagedCache, ngc_cache, ngc_paged_cache, ngc_evict_params, _SimpleCData)
 ENTRY(types, 7)
     PyObject **const to[] = {&types.argument_error, &types.cache_class, &types.paged_class, &types.cache, &types.paged,
@@ -362,7 +412,8 @@ END
 
 #define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(&name##_)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
-    {"open", open_, METH_O, nullptr}, FAST(types),
+    {"open", open_, METH_O, nullptr}, {"torch_reader", torch_reader, METH_O, nullptr},
+    {"current_stream", current_stream, METH_NOARGS, nullptr}, FAST(stream_readers), FAST(types),
     FAST(perturbed_keys), FAST(keep_counts), FAST(evict), FAST(subset_logprob), FAST(subset_logprob_backward), FAST(lmem),
     FAST(cache_append), FAST(decode_attn), FAST(decode_step), FAST(decode_attn_static), FAST(score_keys),
     FAST(replay_attn), FAST(paged_evict), FAST(paged_append), FAST(paged_decode_attn), FAST(paged_score_keys),

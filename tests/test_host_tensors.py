@@ -1,0 +1,92 @@
+"""What the front reads of a tensor directly is what the tensor's methods say; every other object is left to its methods, and
+a torch error comes out of them as it did (no GPU)."""
+import ctypes as C
+
+import pytest
+import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
+from torch.overrides import TorchFunctionMode
+
+from paper_2604_18002_amd import binding as ngc
+from paper_2604_18002_amd._build import TORCH_LIB_PATH
+
+
+class Read(C.Structure):
+    _fields_ = [("data", C.c_void_p), ("sizes", C.POINTER(C.c_int64)), ("numel", C.c_int64), ("dims", C.c_int32),
+                ("contiguous", C.c_int32)]
+
+
+def _read(o):
+    """The reader's answer, or None where it leaves the object to its methods."""
+    fn = C.PyDLL(TORCH_LIB_PATH).ngc_read_tensor        # (a Python error it left would surface here)
+    fn.argtypes, fn.restype = [C.py_object, C.POINTER(Read)], C.c_int
+    r = Read()
+    return (r.data or 0, list(r.sizes[:r.dims]), r.numel, bool(r.contiguous)) if fn(o, C.byref(r)) else None
+
+
+class Own(torch.Tensor):
+    def data_ptr(self):
+        return 64
+
+
+class Mode(TorchFunctionMode):
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        return func(*args, **(kwargs or {}))
+
+
+@pytest.mark.parametrize("t", [
+    torch.zeros(2, 3, 4, dtype=torch.bfloat16), torch.zeros(4, 6).t(), torch.zeros(8, 8)[2:, 1:5], torch.zeros(7)[3:],
+    torch.zeros(0, 5), torch.tensor(3), torch.zeros(3, 1, 2).expand(3, 4, 2), torch.nn.Parameter(torch.zeros(5)),
+    torch.zeros(6, dtype=torch.uint8).view(torch.int16), torch.zeros(3, requires_grad=True) * 2, torch.zeros(2, device="meta"),
+    torch.randn(3, dtype=torch.complex64).conj()], ids=str)
+def test_plain_tensors_are_read_as_their_methods_say(t):
+    assert _read(t) == (t.data_ptr(), list(t.shape), t.numel(), t.is_contiguous())
+
+
+def test_everything_else_is_left_to_its_methods():
+    plain = torch.zeros(4, 4)
+    for o in (None, 3, 2.5, "x", object(), [plain], torch.zeros(3).as_subclass(Own), torch.eye(3).to_sparse(),
+              torch.nested.nested_tensor([torch.zeros(2), torch.zeros(3)])):
+        assert _read(o) is None
+    with FakeTensorMode():
+        assert _read(torch.zeros(3)) is None
+    with Mode():
+        assert _read(plain) is None
+    assert _read(plain) is not None
+    seen = []
+    torch.vmap(lambda x: (seen.append(_read(x)), x)[1])(plain)
+    torch.func.grad(lambda x: (seen.append(_read(x)), x.sum())[1])(plain)
+    torch.func.functionalize(lambda x: (seen.append(_read(x)), x + 1)[1])(plain)
+    assert seen == [None, None, None]
+
+
+def test_errors_come_from_the_methods():
+    c = ngc.Cache.allocate(1, 1, 2, 8, 64, 32, device="cpu")
+    q, out, ws = torch.zeros(1, 8, 64, dtype=torch.bfloat16), torch.zeros(1, 8, 64), torch.zeros(1 << 16, dtype=torch.uint8)
+
+    def call(cache=c, q=q, ws=ws):
+        ngc.ngc_decode_attn(cache, 0, q, 0.1, 0, out, ws, stream=0)
+    with pytest.raises(RuntimeError) as want:
+        torch.vmap(lambda x: (x.data_ptr(), x)[1])(q)
+    with pytest.raises(RuntimeError) as got:
+        torch.vmap(lambda x: (call(q=x), x)[1])(q)
+    assert str(got.value) == str(want.value)
+    with pytest.raises(AttributeError):
+        call(q=3)
+    with pytest.raises(AssertionError, match="k must be contiguous"):
+        call(cache=ngc.Cache(c.k.transpose(3, 4), c.v, c.len, None, 8))
+    with pytest.raises(ValueError, match="k must have 5 dimensions"):
+        call(cache=ngc.Cache(c.k[0], c.v, c.len, None, 8))
+    with pytest.raises(ngc.NgcError) as e:          # a subclass is asked: 64 is aligned, 3 would not be
+        call(q=torch.zeros(1, 8, 64).as_subclass(Own), ws=ws[:16])
+    assert e.value.code == ngc.NGC_ENOSPC
+
+
+def test_stream_readers():
+    front = ngc._front()
+    front.stream_readers(lambda: 5, lambda device: device + 70)
+    assert front.current_stream() == 75
+    with pytest.raises(ZeroDivisionError):
+        front.stream_readers(lambda: 1 // 0, lambda device: device)
+        front.current_stream()
+    ngc._forget_stream_reader()
