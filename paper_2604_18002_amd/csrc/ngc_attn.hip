@@ -54,9 +54,9 @@
 // batch, the last tile lost its prefetch and the first was asked for early:
 // 2 segments x 2000 rows 8.2 -> 6.7 us, 32 x 525 rows (8.6 MB) 9.1 -> 7.0 us,
 // 128 x 1494 rows (98 MB) 22.0 -> 19.7 us, 512 x 2700 rows (0.71 GB) 119 -> 117 us.
-// Where the 6.45 us of 32 x 525 rows go today (copies of the kernel that return early): launch 1.8, until the first
-// tile is there 1.7, its products 0.4, the four waves' merge 0.3, partial stores until acknowledged 0.45, ticket 1.2,
-// merge 0.65.
+// Where the 5.75 us of 32 x 525 rows go (copies of the kernel that return early): launch 1.8, until the first
+// tile is there 1.7, its products 0.4, the four waves' merge 0.3, partial stores until acknowledged 0.45, ticket 0.5
+// (1.2 with the tickets of all segments on one cache line), merge 0.65.
 //
 // Paged layout (PAGED = true): a 32-row tile never straddles a page (pages hold
 // a power-of-two number of rows >= 32), so only the tile's base address changes:
@@ -615,31 +615,32 @@ using namespace ngc;
 namespace {
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 constexpr size_t STATUS_BYTES = NGC_STATUS_WORDS * sizeof(int32_t);
-// How many workgroups share a segment.  Microseconds per launch (MI355X, one launch per layer from a HIP graph, D = 128)
+// How many workgroups share a segment.  Microseconds per launch (MI355X, one launch per layer of 28 from a HIP graph, D = 128)
 // against S, best in brackets:
-//     segments x rows      S=1    2     3     4     5     6     8    10    12    16    24    32
-//         2 x  300         6.6   6.6 [ 5.7]  5.7   5.7   5.7   5.7
-//         2 x  525         8.4   7.7   7.2   6.6 [ 5.9]  6.0   6.0
-//         2 x 2000        20.7  13.8  11.4   9.6   9.4   8.6   7.7   8.2   8.2 [ 6.7]  6.7   6.7
-//         4 x 4000        37.6  22.4  17.0  14.2  12.9  11.9  10.2  10.4   9.4 [ 8.5]  9.6   8.9
-//         4 x 3-10K       53.6  30.2  22.4  18.5  16.2  14.5  12.4  11.7  10.9 [ 9.6] 10.0   9.8
-//        16 x 1.5K        17.4  12.5  10.4   9.2   9.2   8.6 [ 8.3]  8.9   9.0   9.0   9.4  10.8
-//        16 x 3-10K       88.3  47.9  34.3  27.7  23.8  20.7  17.8  16.5  15.4 [14.2] 18.0  16.8
-//        32 x  300         7.2   7.3 [ 6.3]  6.3   6.3   6.3   6.7   6.7
-//        32 x  525         9.4   8.5   7.9   7.4 [ 6.8]  6.9   6.8   6.9   6.9   6.9   8.3   9.9
-//        32 x 1.5K        17.9  12.9  10.9   9.6   9.8   9.4 [ 9.4] 11.2   9.9   9.8  11.5  13.0
-//        32 x 3-10K       89.6  49.4  36.2  30.0  26.2  24.0 [22.8] 28.5  27.0  24.1  26.4  26.5
-//        64 x  525        10.0   9.1   8.8 [ 8.5]  8.9   8.9   8.9   9.2  10.0  11.1
-//        64 x 1.5K        20.3  14.8  13.0 [12.3] 14.5  13.5  13.4  13.8  14.6  15.2
-//        64 x 3-10K       93.6  54.7  43.4 [41.2] 52.6  47.9  43.2  45.3  44.9  43.6
-//       128 x  525        11.1 [10.9] 11.3  11.0  12.4  12.4  12.5
-//       128 x 1.5K        22.2 [20.0] 21.8  20.3  21.9  21.0  21.6
-//       128 x 3-10K      106.4 [78.5] 91.5  80.5  87.4  82.2  78.5
-//       256 x 1.5K       [33.8] 35.7  36.2  37.0
+//     segments x rows      S=1    2     3     4     5     6     7     8    10    12    16    24    32
+//         2 x  525         8.0   6.8   6.4   5.8 [ 5.1]
+//         2 x 2000        20.5  13.0  10.8   9.0   8.8   7.9         6.9   7.5   7.4 [ 6.0]
+//         2 x 4000        37.8  22.0  16.5  13.6  12.3  11.3         9.5   9.8   8.7   7.7   8.7 [ 7.2]
+//        16 x  525         8.5   7.5   6.9   6.1 [ 5.5]
+//        16 x 2000        21.7  14.1  11.6   9.7   9.5   8.5         7.8   8.4   8.5 [ 7.5]
+//        16 x 8000        74.7  41.2  29.4  24.1  20.7  18.5        16.0  16.0  16.0 [15.1]
+//        32 x  300         6.2   6.3 [ 5.5]
+//        32 x  800        11.0   9.0   7.7   7.2   7.5   6.7 [ 6.1]
+//        32 x 2000        22.1  14.7  12.3  10.5  10.5 [ 9.7]        9.9
+//        48 x  525         8.9   7.9   7.2   6.9 [ 6.2]
+//        64 x  400         7.8   7.3   6.9 [ 6.1]
+//        64 x 2000        24.5  15.9  15.2 [14.7]
+//        64 x 8000        81.8  49.1 [42.4] 42.8
+//       128 x  525         9.6 [ 9.5]
+//       128 x 2000        26.6 [23.8]
 // What they say: a launch should have no more workgroups than the chip has CUs, S <= 256 / segments.  Below that a
-// workgroup works through rounds of four tiles (one per wave), ~0.95 us each (0.58 at D = 64), so only the S that
-// lower the number of rounds are worth their cost: sharing a segment at all costs ~1.2 us (partial, ticket, merge:
-// three memory round trips), every 16 partials more another such trip, and workgroups beyond 128 ~0.01 us each.
+// workgroup works through rounds of four tiles (one per wave), so only the S that lower the number of rounds are worth
+// their cost: sharing a segment at all (partial, ticket, merge: three memory round trips), a further such trip for every
+// 16 partials more, and a little for workgroups beyond 128.  What these cost depends on how far apart the tickets lie
+// (ticket_step()): the prices of a launch over words next to each other, 4 or more words apart, and half a line.  With one
+// price for all, the one of the first row: 32 x 800 rows 7.2 us at S = 4 instead of 6.1 at 7, 48 x 525 7.2 (S = 3) instead of
+// 6.2, 64 x 400 7.3 (2) and 6.1, 32 x 800 rows of 128 bytes 5.5 (4) and 5.0; with the last row's over tickets next to each other
+// 16 x 2000 rows 9.6 us (S = 16) instead of 8.5 (8), 8 x 8000 12.9 (32) instead of 11.6 (16).
 constexpr int COMPUTE_UNITS = 256;
 
 int most_splits(int nseg_launch, int max_len)
@@ -651,18 +652,32 @@ int most_splits(int nseg_launch, int max_len)
     return s > 1 ? s : 1;
 }
 
-int splits_for(int nseg_launch, int max_len, int row_bytes)
+struct SplitPrice {
+    float round, share, more, beyond;      // us: a round of tiles, sharing a segment, 16 partials more, a workgroup beyond 128
+};
+
+SplitPrice split_price(int row_bytes, int apart)
+{
+    const bool wide = row_bytes == 256;
+    if (apart < 4) return wide ? SplitPrice{0.95f, 1.2f, 1.2f, 0.01f} : SplitPrice{0.58f, 1.2f, 1.2f, 0.01f};
+    if (apart < 16) return wide ? SplitPrice{0.8f, 1.05f, 0.9f, 0.007f} : SplitPrice{0.45f, 1.1f, 0.9f, 0.004f};
+    return wide ? SplitPrice{0.8f, 1.05f, 0.55f, 0.005f} : SplitPrice{0.45f, 1.1f, 0.6f, 0.003f};
+}
+
+// apart: words between the tickets of a workspace's launch (the static entry point splits the same way).
+int splits_for(int nseg_launch, int max_len, int row_bytes, int apart)
 {
     const int most = most_splits(nseg_launch, max_len);
     const int tiles = (max_len + ATT_TILE - 1) / ATT_TILE;
-    const float per_round = row_bytes == 256 ? 0.95f : 0.58f;
+    const SplitPrice price = split_price(row_bytes, apart);
     int best = 1;
     float best_us = 3.0e38f;
     for (int s = most; s >= 1; --s) {
         const int rounds = (tiles + ATT_WAVES * s - 1) / (ATT_WAVES * s);
         if (s > 1 && (tiles + ATT_WAVES * (s - 1) - 1) / (ATT_WAVES * (s - 1)) == rounds) continue;   // one fewer does as well
         const int beyond = s * nseg_launch > 128 ? s * nseg_launch - 128 : 0;
-        const float us = per_round * (float)rounds + (s > 1 ? 1.2f * (float)((s + 15) / 16) + 0.01f * (float)beyond : 0.f);
+        const float us = price.round * (float)rounds +
+                         (s > 1 ? price.share + price.more * (float)((s - 1) / 16) + price.beyond * (float)beyond : 0.f);
         if (us < best_us) { best_us = us; best = s; }
     }
     return best;
@@ -810,7 +825,8 @@ int launch_decode(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, 
     const int seg0 = layer < 0 ? 0 : layer * per_layer;
     const int nseg = layer < 0 ? c->L * per_layer : per_layer;
     const int max_len = (max_len_hint > 0 && max_len_hint < c->cap) ? max_len_hint : c->cap;
-    int S = splits_for(nseg, max_len, c->D * 2);
+    const int apart = ticket_step((size_t)c->L * per_layer, nseg);
+    int S = splits_for(nseg, max_len, c->D * 2, apart);
     if (nseg > COMPUTE_UNITS) S = 1;   // (what splits_for() returns anyway: the fixed ticket region relies on it)
     // A call that the fixed array serves is split the same way with a workspace: both return the same bits.
     const bool static_ok = fits_static(c, nseg, static_limit_splits(nseg, max_len, c->D * 2));
@@ -837,7 +853,7 @@ int launch_decode(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, 
     aa.scale_log2e = scale * 1.4426950408889634f;
     aa.ticket = reinterpret_cast<int32_t *>(reinterpret_cast<unsigned char *>(ws) +
                                             (fixed_layout ? FIXED_TICKET_OFFSET : ticket_offset(c)));
-    aa.ticket_step = ticket_step(fixed_layout ? FIXED_TICKETS : (size_t)c->L * per_layer, nseg);
+    aa.ticket_step = fixed_layout ? ticket_step(FIXED_TICKETS, nseg) : apart;
     aa.k_rw = reinterpret_cast<unsigned char *>(c->k);
     aa.v_rw = reinterpret_cast<unsigned char *>(c->v);
     aa.len_rw = c->len;

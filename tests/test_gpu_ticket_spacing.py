@@ -2,20 +2,21 @@
 cache) or of the fixed array allow, up to 32 words.  Caches of one layer (next to each other), a few (between), more than
 32 (a whole line apart), segment counts that do not divide the words.
 
-The same rows as a cache of one layer are the same kernel with the same split: the bits have to agree; fp64 attention on the
-CPU checks one layer of each.  1e-4 absolute: the probabilities enter the second product with 2^-16 relative error against
-values of at most ~5, the rest is fp32."""
+The entry point without a workspace splits the same way and returns the same bits; a cache of one layer holding the same rows
+may be split another way (the split follows the spacing).  1e-4 absolute, there and against fp64 attention on the CPU: the
+probabilities enter the second product with 2^-16 relative error against values of at most ~5, the rest is fp32."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("L,B,H", [(1, 3, 2), (2, 5, 3), (7, 9, 1), (28, 16, 2), (33, 2, 2), (40, 21, 3)])
-def test_layers_agree_with_caches_of_one_layer(L, B, H):
+@pytest.mark.parametrize("L,B,H,D", [(1, 3, 2, 64), (2, 5, 3, 64), (7, 9, 1, 64), (28, 16, 2, 64), (33, 2, 2, 64), (40, 21, 3, 64),
+                                     (5, 8, 2, 128), (28, 24, 2, 128)])
+def test_layers_agree_with_caches_of_one_layer(L, B, H, D):
     import torch
     from paper_2604_18002_amd import binding as ngc
     ngc.load_library()
-    D, G, cap = 64, 4, 660
+    G, cap = 4, 660
     g = torch.Generator(device="cuda").manual_seed(L * 100 + B)
     k, v = (torch.randn(L, B, H, cap, D, generator=g, device="cuda").to(torch.bfloat16) for _ in range(2))
     q = torch.randn(L, B, H * G, D, generator=g, device="cuda").to(torch.bfloat16)
@@ -31,7 +32,8 @@ def test_layers_agree_with_caches_of_one_layer(L, B, H):
             ngc.ngc_decode_attn_static(cache, l, q[l], scale, 0, static)
             one = ngc.Cache(k[l:l + 1], v[l:l + 1], n[l:l + 1], None, H * G)
             ngc.ngc_decode_attn(one, 0, q[l], scale, 0, want, ngc.allocate_workspace(one, 1))
-            assert torch.equal(got, want) and torch.equal(static, want)
+            assert torch.equal(static, got)
+            assert (got - want).abs().max() <= 1e-4
     tickets = ws[ngc.STATUS_WORDS * 4:ngc.STATUS_WORDS * 4 + 12 * L * B * H].view(torch.int32)
     assert int(tickets.abs().sum()) == 0 and all(x == 0 for x in ngc.read_status(ws))
     for b in range(B):
