@@ -175,6 +175,7 @@ struct PagedAppendArgs {
     int32_t *status;
     int seg0, src_seg0;
     int B, Hkv, page_rows, max_pages, num_pages;
+    int page_shift;          // log2(page_rows)
 };
 
 // One wave per segment: lanes [0, PIECES) copy the K row, the next PIECES the V row.
@@ -186,7 +187,7 @@ __global__ __launch_bounds__(64) void paged_append_kernel(PagedAppendArgs a)
     const int lane = threadIdx.x;
     const int n = a.len[seg];
     int page = -1;
-    if (n >= 0 && n < a.page_rows * a.max_pages) page = a.table[(size_t)seg * a.max_pages + n / a.page_rows];
+    if (n >= 0 && n < a.page_rows * a.max_pages) page = a.table[(size_t)seg * a.max_pages + (n >> a.page_shift)];
     if (page < 0 || page >= a.num_pages) {
         if (lane == 0) {
             atomicAdd(&a.status[NGC_STATUS_APPEND_FULL], 1);
@@ -211,19 +212,25 @@ __global__ __launch_bounds__(64) void paged_append_kernel(PagedAppendArgs a)
 }
 
 // Grant and append in one launch, by one workgroup, for a layer of a small batch.  The two kernels above take 4.6 us
-// together whatever the number of segments (HIP graph; plus a launch on the host); this one 3.1 us at 32 segments, 3.8
-// at 128, 5.2 at 256 of 256-byte rows and 3.0, 3.3, 3.8, 4.5 (384) of 128-byte rows: it is the copy by one workgroup
+// together whatever the number of segments (HIP graph; plus a launch on the host); this one 2.3 us at 32 segments, 3.4
+// at 128, 5.2 at 256 of 256-byte rows and 2.1, 3.3, 3.8, 4.5 (384) of 128-byte rows: it is the copy by one workgroup
 // that grows, hence the limit on the rows' bytes.  Segment i belongs to thread i for the grant; then 2 * PIECES
 // consecutive threads copy a segment's K and V row.  The new rows are asked for first: they wait for nothing.
+// Half the threads where a thread then still copies at most two pieces and one wave does the grant (microseconds per layer from
+// a HIP graph, 512 / 1024 threads: 8 segments of 256-byte rows 2.03 / 2.19, 32 2.26 / 2.36, 64 2.68 / 2.65; 32 of 128-byte rows 2.07 /
+// 2.23; 1024 threads, a scan by all of them and a division by the page size, before: 2.41, 2.58, 2.87, 2.44).
+constexpr int SMALL_GROW_THREADS = 512;
+constexpr int SMALL_GROW_BYTES = 8 * 1024;                     // of new K rows
 constexpr int ONE_LAUNCH_BYTES = 48 * 1024;                    // of new K rows
 constexpr int ONE_LAUNCH_SEGMENTS = ONE_LAUNCH_BYTES / 128;    // at the smaller row
 static_assert(ONE_LAUNCH_SEGMENTS <= POOL_SCAN_THREADS, "a thread per segment");
 
-template <int ROW_BYTES>
-__global__ __launch_bounds__(POOL_SCAN_THREADS) void paged_grow_kernel(PagedArgs pa, PagedAppendArgs a)
+// ONE_WAVE: at most 64 segments, a wave's threads; no exchange to find their order.
+template <int ROW_BYTES, int THREADS, bool ONE_WAVE>
+__global__ __launch_bounds__(THREADS) void paged_grow_kernel(PagedArgs pa, PagedAppendArgs a)
 {
     constexpr int PIECES = ROW_BYTES / 16;
-    constexpr int SEGS_PER_STEP = POOL_SCAN_THREADS / (2 * PIECES);
+    constexpr int SEGS_PER_STEP = THREADS / (2 * PIECES);
     constexpr int PREFETCH = 4;                                        // steps whose rows are asked for in advance
     __shared__ int tmp[32];
     __shared__ int page_of[ONE_LAUNCH_SEGMENTS];                       // page of the new row, -1: no room
@@ -247,11 +254,17 @@ __global__ __launch_bounds__(POOL_SCAN_THREADS) void paged_grow_kernel(PagedArgs
     if (tid < pa.nseg) n = pa.len[pa.seg0 + tid];
     const bool fits = n >= 0 && n < cap;
     const bool needs = fits && (n & (pa.page_rows - 1)) == 0;
-    int32_t *entry = pa.table + (size_t)(pa.seg0 + (tid < pa.nseg ? tid : 0)) * pa.max_pages + (fits ? n / pa.page_rows : 0);
+    int32_t *entry = pa.table + (size_t)(pa.seg0 + (tid < pa.nseg ? tid : 0)) * pa.max_pages + (fits ? n >> a.page_shift : 0);
     int page = -1;
     if (fits && !needs) page = *entry;
-    int total;
-    const int rank = block_excl_scan_i<POOL_SCAN_THREADS>(needs ? 1 : 0, tmp, &total);   // every thread has read the count
+    int total, rank;         // the segments that take a page before this one; all
+    if constexpr (ONE_WAVE) {
+        const uint64_t takers = __ballot(needs);
+        rank = popc_below(takers);
+        total = __popcll(takers);
+    } else {
+        rank = block_excl_scan_i<THREADS>(needs ? 1 : 0, tmp, &total);   // every thread has read the count
+    }
     if (needs) {
         page = rank < count ? pa.free_stack[count - 1 - rank] : -1;
         *entry = page;
@@ -432,12 +445,19 @@ extern "C" int ngc_paged_append(const ngc_paged_cache *pc, int32_t layer, const 
     aa.seg0 = seg0; aa.src_seg0 = seg0;
     aa.B = pc->B; aa.Hkv = pc->Hkv;
     aa.page_rows = pc->page_rows; aa.max_pages = pc->max_pages; aa.num_pages = pc->num_pages;
+    aa.page_shift = __builtin_ctz((unsigned)pc->page_rows);
     if ((long long)nseg * pc->D * 2 <= ONE_LAUNCH_BYTES) {
-        if (pc->D == 128)
-            hipLaunchKernelGGL(paged_grow_kernel<256>, dim3(1), dim3(POOL_SCAN_THREADS), 0, st, pa, aa);
-        else
-            hipLaunchKernelGGL(paged_grow_kernel<128>, dim3(1), dim3(POOL_SCAN_THREADS), 0, st, pa, aa);
-        NGC_HIP_CHECK(hipGetLastError());
+        const bool one_wave = nseg <= NGC_WAVE;
+        const bool small = one_wave && (long long)nseg * pc->D * 2 <= SMALL_GROW_BYTES;
+        const dim3 threads(small ? SMALL_GROW_THREADS : POOL_SCAN_THREADS);
+#define NGC_PICK_GROW(ROW_BYTES) \
+    (small      ? reinterpret_cast<const void *>(&paged_grow_kernel<ROW_BYTES, SMALL_GROW_THREADS, true>) \
+     : one_wave ? reinterpret_cast<const void *>(&paged_grow_kernel<ROW_BYTES, POOL_SCAN_THREADS, true>) \
+                : reinterpret_cast<const void *>(&paged_grow_kernel<ROW_BYTES, POOL_SCAN_THREADS, false>))
+        const void *fn = pc->D == 128 ? NGC_PICK_GROW(256) : NGC_PICK_GROW(128);
+#undef NGC_PICK_GROW
+        void *kargs[] = {&pa, &aa};
+        NGC_HIP_CHECK(hipLaunchKernel(fn, dim3(1), threads, kargs, 0, st));
         return NGC_OK;
     }
     hipLaunchKernelGGL(paged_grant_kernel, dim3(1), dim3(POOL_SCAN_THREADS), 0, st, pa);
