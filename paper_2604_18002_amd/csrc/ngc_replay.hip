@@ -4,12 +4,13 @@
 //
 // Instead of the paper's dense T x T boolean mask per layer, visibility is one
 // int per key: death[j] = first query position that no longer sees key j, so
-// visible(i, j) = (j <= i < death[j]).  A small first kernel compacts, for every
-// tile of 128 query positions, the list of keys that at least one of its
-// queries can see (j not after its last query, death[j] after its first); the
-// attention kernel then only ever loads those rows: the work follows the
-// retained cache, not the T x T triangle.  The lists are shared by all query
-// heads that share the decisions.
+// visible(i, j) = (j <= i < death[j]).  For every tile of 128 query positions
+// the keys that at least one of its queries can see are compacted into a list
+// (j not after its last query, death[j] after its first); the attention kernel
+// then only ever loads those rows: the work follows the retained cache, not the
+// T x T triangle.  Over long trajectories a small first kernel makes the lists,
+// shared by all query heads that share the decisions; over short ones every
+// workgroup makes its own.
 //
 // Flash-attention forward on the matrix cores (S^T = K Q^T, O^T = V^T P, mfma 32x32x16: one query per lane % 32, so all
 // soft-max state is lane local and crosses lanes once, between the two halves; P as bf16 head + remainder).  A workgroup
@@ -63,6 +64,21 @@ struct ReplayArgs {
     int B, T, Hq, Hkv, Hd;     // Hd = Hkv (a death row per KV head) or 1 (shared by the heads)
     float scale_log2e;
 };
+
+// What a wave-wide step of the list means for the tile's waves, from its first and last key and its earliest death.
+__device__ __forceinline__ uint32_t step_of(int i0, int T, int first, int last, int lives_until)
+{
+    int after = 0, from = 0, until = 0;
+#pragma unroll
+    for (int w = 0; w < RP_WAVES; ++w) {
+        const int q0 = i0 + w * RP_QW;                                   // the wave's first query and its last real one
+        const int q1 = q0 + RP_QW - 1 < T - 1 ? q0 + RP_QW - 1 : T - 1;
+        after += first > q1;
+        from += last > q0;
+        until += lives_until > q1;
+    }
+    return step_word(after, from, until);
+}
 
 // Ordered compaction, LIST_PASS keys per pass (one pass up to 4096 positions: its keys' death positions are all asked
 // for at once).  Key j0 + 256 i + tid belongs to thread tid's i-th bit: ballots give the counts of every (i, wave),
@@ -129,21 +145,88 @@ __global__ __launch_bounds__(LIST_THREADS) void replay_lists_kernel(ReplayArgs a
     if (tid == 0) a.kcount[(size_t)row * nqt + qt] = n_list;
     uint32_t *steps = a.steps + ((size_t)row * nqt + qt) * ((T + RP_MT - 1) / RP_MT);
     for (int s = tid; s * RP_MT < n_list; s += LIST_THREADS) {
-        const int first = first_key[s], last = last_key[s], lives_until = min_death[s];
-        int after = 0, from = 0, until = 0;
-#pragma unroll
-        for (int w = 0; w < RP_WAVES; ++w) {
-            const int q0 = i0 + w * RP_QW;                                   // the wave's first query and its last real one
-            const int q1 = q0 + RP_QW - 1 < T - 1 ? q0 + RP_QW - 1 : T - 1;
-            after += first > q1;
-            from += last > q0;
-            until += lives_until > q1;
-        }
-        steps[s] = step_word(after, from, until);
+        steps[s] = step_of(i0, T, first_key[s], last_key[s], min_death[s]);
     }
 }
 
-template <int D>
+// The key list of one query tile in LDS, made by the workgroup itself, for trajectories of up to OWN_MAX positions.  A kernel of its
+// own for the lists pays where many workgroups share a long one; over short trajectories it is mostly a launch and two
+// memory round trips in front of the attention.  Microseconds, lists by a kernel -> by the workgroups:
+//     B  heads         T = 130          350            600           1050            1500            2000
+//     2  28/4      13.1 -> 10.0   15.7 -> 12.6   18.5 -> 15.1   26.3 -> 22.8    41.0 -> 37.8    50.8 -> 48.1
+//    16  12/2      14.5 -> 11.0   25.5 -> 24.1   39.5 -> 36.1   75.8 -> 73.4   133.3 -> 132.0    197 -> 197
+// i.e. nothing to gain beyond, where a list also no longer fits beside the tiles of two workgroups a CU.
+constexpr int OWN_BITS = 8;
+constexpr int OWN_MAX = LIST_THREADS * OWN_BITS;
+static_assert(LIST_THREADS == RP_WAVES * NGC_WAVE, "a workgroup of the attention kernel makes its list");
+template <bool OWN>
+struct OwnList {
+    static constexpr int SLOTS = 1, STEPS = 1;
+    uint16_t key[1], death[1];
+    uint32_t steps[1];
+};
+template <>
+struct OwnList<true> {
+    static constexpr int SLOTS = OWN_MAX + RP_KT;           // the list, padded to a whole tile
+    static constexpr int STEPS = SLOTS / RP_MT;
+    __align__(16) uint16_t key[SLOTS], death[SLOTS];        // padding: key 0, which nobody sees
+    uint32_t steps[STEPS];
+    int min_death[STEPS];
+    uint16_t first_key[STEPS], last_key[STEPS];
+    int counts[OWN_BITS * LIST_WAVES];
+};
+
+// Returns the length of the list.  Whole workgroup; ends on a barrier.
+__device__ __forceinline__ int replay_own_list(OwnList<true> &own, const int32_t *death, int i0, int T)
+{
+    const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
+    const int last_pos = (i0 + RP_QT - 1 < T - 1) ? i0 + RP_QT - 1 : T - 1;
+    int d[OWN_BITS];
+#pragma unroll
+    for (int i = 0; i < OWN_BITS; ++i) {
+        const int j = i * LIST_THREADS + tid;
+        d[i] = j <= last_pos ? death[j] : -1;                            // (a key no query of the tile sees)
+    }
+    if (tid < OwnList<true>::STEPS) {
+        own.min_death[tid] = 0x7FFFFFFF;
+        own.last_key[tid] = NO_KEY;
+    }
+    uint64_t seen[OWN_BITS];
+#pragma unroll
+    for (int i = 0; i < OWN_BITS; ++i) {
+        seen[i] = __ballot(d[i] > i0);
+        if (lane == 0) own.counts[i * LIST_WAVES + wv] = __popcll(seen[i]);
+    }
+    __syncthreads();
+    const int mine = lane < OWN_BITS * LIST_WAVES ? own.counts[lane] : 0;
+    const int upto = wave_incl_scan_i(mine);
+#pragma unroll
+    for (int i = 0; i < OWN_BITS; ++i) {
+        if (i * LIST_THREADS > last_pos) break;                          // uniform
+        const int before = __builtin_amdgcn_readlane(upto - mine, i * LIST_WAVES + wv);
+        if (d[i] > i0) {
+            const int j = i * LIST_THREADS + tid;
+            const int slot = before + popc_below(seen[i]);
+            own.key[slot] = (uint16_t)j;
+            own.death[slot] = (uint16_t)(d[i] < 0xFFFF ? d[i] : 0xFFFF);
+            atomicMin(&own.min_death[slot / RP_MT], d[i]);
+            if (slot % RP_MT == 0) own.first_key[slot / RP_MT] = (uint16_t)j;
+            if (slot % RP_MT == RP_MT - 1) own.last_key[slot / RP_MT] = (uint16_t)j;
+        }
+    }
+    const int n_list = __builtin_amdgcn_readlane(upto, NGC_WAVE - 1);
+    if (tid < RP_KT) {
+        own.key[n_list + tid] = 0;
+        own.death[n_list + tid] = 0;
+    }
+    __syncthreads();
+    if (tid * RP_MT < n_list) own.steps[tid] = step_of(i0, T, own.first_key[tid], own.last_key[tid], own.min_death[tid]);
+    __syncthreads();
+    return n_list;
+}
+
+// OWN: trajectories of up to OWN_MAX positions; a workgroup makes its key list itself, in LDS (see replay_own_list()).
+template <int D, bool OWN>
 __global__ __launch_bounds__(RP_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2)))
 void replay_attn_kernel(ReplayArgs a)
 {
@@ -157,8 +240,9 @@ void replay_attn_kernel(ReplayArgs a)
     constexpr int STEPS = RP_KT / RP_MT;
 
     __shared__ __align__(16) unsigned char lds_k0[TILE_LDS], lds_k1[TILE_LDS], lds_v0[TILE_LDS], lds_v1[TILE_LDS];
-    __shared__ __align__(16) int32_t lds_death[2][RP_KT];
-    __shared__ __align__(16) int32_t lds_kidx[2][RP_KT];
+    __shared__ __align__(16) int32_t lds_death[2][OWN ? 1 : RP_KT];
+    __shared__ __align__(16) int32_t lds_kidx[2][OWN ? 1 : RP_KT];
+    __shared__ OwnList<OWN> own;
 
     const int tid = threadIdx.x, lane = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id());
     const int li = lane & 31, half = lane >> 5;
@@ -186,9 +270,11 @@ void replay_attn_kernel(ReplayArgs a)
     const unsigned char *kbase = a.k + ((size_t)b * T * a.Hkv + hkv) * ROW_BYTES;
     const unsigned char *vbase = a.v + ((size_t)b * T * a.Hkv + hkv) * ROW_BYTES;
     const size_t list = ((size_t)b * a.Hd + hd) * nqt + qt;
-    const uint16_t *klist = a.klist + list * T;
-    const uint32_t *info = a.steps + list * ((T + RP_MT - 1) / RP_MT);
-    const int n_list = a.kcount[list];
+    const uint16_t *klist = OWN ? nullptr : a.klist + list * T;
+    const uint32_t *info = OWN ? nullptr : a.steps + list * ((T + RP_MT - 1) / RP_MT);
+    int n_list;
+    if constexpr (OWN) n_list = replay_own_list(own, death, i0, T);
+    else n_list = a.kcount[list];
     const int t_end = (n_list + RP_KT - 1) / RP_KT;
 
     // Rows of a tile go straight from memory to LDS: a wave-wide load brings LOAD_ROWS whole rows, lane after lane.
@@ -208,12 +294,18 @@ void replay_attn_kernel(ReplayArgs a)
 #pragma unroll
         for (int r = 0; r < LOADS; ++r) {
             int slot = s0 + (wv * LOADS + r) * LOAD_ROWS + lrow;
-            slot = slot < T ? slot : T - 1;             // a list row has T slots
-            ix.key[r] = (int)klist[slot];
+            if constexpr (OWN) {
+                ix.key[r] = (int)own.key[slot < OwnList<OWN>::SLOTS ? slot : 0];
+            } else {
+                slot = slot < T ? slot : T - 1;         // a list row has T slots
+                ix.key[r] = (int)klist[slot];
+            }
         }
-        int sl = s0 + (tid & (RP_KT - 1));
-        sl = sl < T ? sl : T - 1;
-        ix.mine = (int)klist[sl];
+        if constexpr (!OWN) {
+            int sl = s0 + (tid & (RP_KT - 1));
+            sl = sl < T ? sl : T - 1;
+            ix.mine = (int)klist[sl];
+        }
     };
     auto load_rows = [&](const IdxStage &ix, unsigned char *dk, unsigned char *dv) {
 #pragma unroll
@@ -233,10 +325,12 @@ void replay_attn_kernel(ReplayArgs a)
         int d, i;
     };
     auto load_mask = [&](const IdxStage &ix, MaskStage &ms) {
+        if constexpr (OWN) return;
         ms.i = ix.mine;
         ms.d = death[ix.mine < T ? ix.mine : T - 1];
     };
     auto store_mask = [&](int t, int buf, const MaskStage &ms) {
+        if constexpr (OWN) return;
         const bool inside = t * RP_KT + tid < n_list;
         if (tid < RP_KT) {
             lds_death[buf][tid] = inside ? ms.d : 0;
@@ -253,6 +347,10 @@ void replay_attn_kernel(ReplayArgs a)
 #pragma unroll
         for (int st = 0; st < STEPS; ++st) {
             const int at = t * STEPS + st;
+            if constexpr (OWN) {
+                ti.step[st] = (uint32_t)__builtin_amdgcn_readfirstlane((int)own.steps[at < OwnList<OWN>::STEPS ? at : 0]);
+                continue;
+            }
             ti.step[st] = reinterpret_cast<const __attribute__((address_space(4))) uint32_t *>(
                 (uintptr_t)info)[at < last_step ? at : last_step];
         }
@@ -302,8 +400,9 @@ void replay_attn_kernel(ReplayArgs a)
         }
     }
 
+    // `slot`: where the step's keys stand in the list (OWN)
     auto compute_step = [&](const unsigned char *lk, const unsigned char *lv, const int32_t *ldeath, const int32_t *lkidx,
-                            bool full) {
+                            int slot, bool full) {
         f32x16 sc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) sc[r] = 0.f;
@@ -331,8 +430,16 @@ void replay_attn_kernel(ReplayArgs a)
         if (!full) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const int4 d = *reinterpret_cast<const int4 *>(&ldeath[8 * g + 4 * half]);
-                const int4 j = *reinterpret_cast<const int4 *>(&lkidx[8 * g + 4 * half]);
+                int4 d, j;
+                if constexpr (OWN) {
+                    const u32x2 dd = *reinterpret_cast<const u32x2 *>(&own.death[slot + 8 * g + 4 * half]);
+                    const u32x2 jj = *reinterpret_cast<const u32x2 *>(&own.key[slot + 8 * g + 4 * half]);
+                    d = int4{(int)(dd[0] & 0xFFFFu), (int)(dd[0] >> 16), (int)(dd[1] & 0xFFFFu), (int)(dd[1] >> 16)};
+                    j = int4{(int)(jj[0] & 0xFFFFu), (int)(jj[0] >> 16), (int)(jj[1] & 0xFFFFu), (int)(jj[1] >> 16)};
+                } else {
+                    d = *reinterpret_cast<const int4 *>(&ldeath[8 * g + 4 * half]);
+                    j = *reinterpret_cast<const int4 *>(&lkidx[8 * g + 4 * half]);
+                }
                 sc[4 * g + 0] = ((j.x <= qpos) & (qpos < d.x)) ? sc[4 * g + 0] : -INFINITY;
                 sc[4 * g + 1] = ((j.y <= qpos) & (qpos < d.y)) ? sc[4 * g + 1] : -INFINITY;
                 sc[4 * g + 2] = ((j.z <= qpos) & (qpos < d.z)) ? sc[4 * g + 2] : -INFINITY;
@@ -388,13 +495,13 @@ void replay_attn_kernel(ReplayArgs a)
 #pragma unroll
         for (int st = 0; st < STEPS; ++st) {
             const int at = t * STEPS + st;
-            if (at * RP_MT >= n_list) break;
+            if (at * RP_MT >= n_list || wave_q0 >= T) break;       // (a last tile may have waves without queries)
             const int after = (int)(ti.step[st] & 0xFFu), from = (int)((ti.step[st] >> 8) & 0xFFu);
             const int until = (int)(ti.step[st] >> 16);
             if (wv < after) break;                                 // the list ascends: all later keys come after them too
             const bool full = wv >= from && wv < until;            // no mask
-            compute_step(lk + st * RP_MT * ROW_BYTES, lv + st * RP_MT * ROW_BYTES, &lds_death[buf][st * RP_MT],
-                         &lds_kidx[buf][st * RP_MT], full);
+            compute_step(lk + st * RP_MT * ROW_BYTES, lv + st * RP_MT * ROW_BYTES, &lds_death[buf][OWN ? 0 : st * RP_MT],
+                         &lds_kidx[buf][OWN ? 0 : st * RP_MT], at * RP_MT, full);
         }
     };
 
@@ -513,12 +620,15 @@ extern "C" int ngc_replay_attn(const void *q, const void *k, const void *v, cons
     size_t counts = (size_t)B * ra.Hd * nqt * sizeof(int32_t);
     counts = (counts + 255) & ~(size_t)255;
     ra.steps = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(ws) + 256 + lists + counts);
-    hipLaunchKernelGGL(replay_lists_kernel, dim3(nqt, B * ra.Hd), dim3(LIST_THREADS), 0, st, ra);
-    NGC_HIP_CHECK(hipGetLastError());
-    if (D == 128)
-        hipLaunchKernelGGL(replay_attn_kernel<128>, dim3((unsigned)(nqt * Hq * B)), dim3(RP_WAVES * 64), 0, st, ra);
-    else
-        hipLaunchKernelGGL(replay_attn_kernel<64>, dim3((unsigned)(nqt * Hq * B)), dim3(RP_WAVES * 64), 0, st, ra);
-    NGC_HIP_CHECK(hipGetLastError());
-    return NGC_OK;
+    const bool own = T <= OWN_MAX;       // (the list needs 8 KB beside the tiles: two workgroups still share a CU)
+    if (!own) {
+        hipLaunchKernelGGL(replay_lists_kernel, dim3(nqt, B * ra.Hd), dim3(LIST_THREADS), 0, st, ra);
+        NGC_HIP_CHECK(hipGetLastError());
+    }
+    const void *fn = D == 128 ? (own ? reinterpret_cast<const void *>(&replay_attn_kernel<128, true>)
+                                     : reinterpret_cast<const void *>(&replay_attn_kernel<128, false>))
+                              : (own ? reinterpret_cast<const void *>(&replay_attn_kernel<64, true>)
+                                     : reinterpret_cast<const void *>(&replay_attn_kernel<64, false>));
+    return launch(fn, dim3((unsigned)(nqt * Hq * B)), dim3(RP_WAVES * 64), 0, st, ra);
 }
+
