@@ -962,72 +962,50 @@ __device__ __forceinline__ void compact_pos_inplace(int32_t *pos, const int32_t 
 // One selection problem per (layer, sequence): the items of all its KV heads
 // compete for one budget, so heads whose logits are larger keep more rows.
 // Item order (for ties and for the sampled sequence) is (head, row); the noise
-// of item (head, row) is the one the per-head mode draws for it.  Up to
-// Hkv * cap = 65536 items: their key codes live in a workspace in global
-// memory (read in order by the select passes), the kept items' codes, logits
-// and item indices in three dense arrays next to them (K entries each, served
-// by the L2 cache to the sort and to the log-probability), the index buffers
-// of the sort in LDS.  Select and sort are the
-// shared routines of ngc_select.h.
+// of item (head, row) is the one the per-head mode draws for it.
+//
+// What bounds it: one workgroup selects for all heads of a sequence, a chain of waits as long as its items are many, and
+// the chip has as many workgroups to hide it as there are (layer, sequence) pairs.  Where LDS has room for a code and a
+// bucket entry per item (about 17000), they are ranked by value buckets as in the per-head mode, every head's items filled
+// up to a multiple of four so that a thread's four codes stay one access.  Beyond, and where ranking does not apply
+// (masked items kept, many equal keys, a wide spread, no sequence wanted), pooled_general() selects by radix: up to
+// Hkv * cap = 65536 items, their codes in a workspace in global memory.
+// The rows are moved by the same workgroup or, for few sequences, by a launch of one workgroup per head (see ngc_evict).
+// Rounds of half the rows, us, before (radix always, one launch) and now:
+//     sequences x heads x rows   16 x 2 x 500     16 x 8 x 300     16 x 8 x 2000   64 x 4 x 1500   128 x 2 x 4000
+//                                25.9   18.1      53.7   24.7     217.5  100.0    103.3   67.5    144.8  134.1
+//                              256 x 2 x 4000  448 x 4 x 500    896 x 4 x 1500   896 x 8 x 300
+//                               240.3  225.6    128.7  107.0     618.0  564.1    335.9  250.4
 
-constexpr int POOL_THREADS = 1024;
 constexpr int POOL_MAX_HEADS = 16;
+constexpr int POOL_FEW = 128;            // (layer, sequence) pairs up to which the rows take a second launch
+constexpr int POOL_MANY = 256;           // beyond, with few items each, 512 threads
+constexpr int POOL_SMALL_ITEMS = 2560;
 // misc slots of the pooled kernel
 constexpr int PM_N = 40;      // rows per head        [40, 56)
 constexpr int PM_OFF = 56;    // item offset per head [56, 73)
 constexpr int PM_BASE = 73;   // kept slots before each head [73, 90)
+constexpr int PM_QUAD = 90;   // groups of four items before each head, every head's last one filled up [90, 107)
+constexpr int PM_WORDS = 128;
+constexpr int PM_MAXIMA = 64; // behind misc, where items are ranked: four words a wave
 
-template <int ROW_BYTES>
-__global__ __launch_bounds__(POOL_THREADS) void evict_pooled_kernel(SelectArgs a)
+// Selection by radix.  The codes of all items are read in order by the select passes; the kept items' codes, logits and
+// item indices stand in three dense arrays next to them (K entries each, served by the L2 cache to the sort and to the
+// log-probability), the index buffers of the sort in LDS.  Writes the kept lists, sigma and its log-probability, and
+// leaves the kept slots before each head in misc.
+template <int THREADS>
+__device__ void pooled_general(const SelectArgs &a, int seg_first, int l, int b, int N, int K, uint32_t *hist, int *misc,
+                               uint16_t *idxA, uint16_t *idxB)
 {
-    constexpr int THREADS = POOL_THREADS;
     constexpr int NW = THREADS / NGC_WAVE;
-    constexpr int HIST = (SEL_BINS > SORT_BINS * NW) ? SEL_BINS : SORT_BINS * NW;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    uint32_t *hist = reinterpret_cast<uint32_t *>(smem_raw);
-    int *misc = reinterpret_cast<int *>(hist + HIST);   // 128 ints
-    uint16_t *idxA = reinterpret_cast<uint16_t *>(misc + 128);
-    uint16_t *idxB = idxA + a.keep_cap;
-    float *fmisc = reinterpret_cast<float *>(misc);
-
     const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
-    const int Hkv = a.g.Hkv, cap = a.g.cap;
-    const int lb = a.seg0 / Hkv + blockIdx.x;     // layer * B + sequence
-    const int l = lb / a.g.B, b = lb - l * a.g.B;
-    const int seg_first = lb * Hkv;
+    const int Hkv = a.g.Hkv, cap = a.g.cap, lb = seg_first / Hkv;
+    float *fmisc = reinterpret_cast<float *>(misc);
     // per (layer, sequence): [codes of all items][codes | logits | item indices of the kept items]
     uint32_t *code = a.pool_codes + (size_t)lb * Hkv * cap * 4;
     uint32_t *kcode = code + (size_t)Hkv * cap;
     float *klogit = reinterpret_cast<float *>(kcode + (size_t)Hkv * cap);
     uint16_t *items = reinterpret_cast<uint16_t *>(klogit + (size_t)Hkv * cap);
-
-    // ---- 0. geometry of the pooled item space ------------------------------
-    if (tid == 0) {
-        int off = 0, ktot = 0;
-        for (int h = 0; h < Hkv; ++h) {
-            int n = a.len[seg_first + h];
-            if (n < 0 || n > cap) {
-                atomicAdd(&a.status[NGC_STATUS_LEN_CLAMPED], 1);
-                n = n < 0 ? 0 : cap;
-            }
-            int kh = a.keep[seg_first + h];
-            if (kh < 0) { atomicAdd(&a.status[NGC_STATUS_KEEP_CLAMPED], 1); kh = 0; }
-            misc[PM_N + h] = n;
-            misc[PM_OFF + h] = off;
-            off += n;
-            ktot += kh;
-        }
-        misc[PM_OFF + Hkv] = off;
-        int lim = off < a.keep_cap ? off : a.keep_cap;
-        if (ktot > lim) {
-            atomicAdd(&a.status[NGC_STATUS_KEEP_CLAMPED], 1);
-            ktot = lim;
-        }
-        misc[MISC_KEPT] = ktot;
-    }
-    __syncthreads();
-    const int N = misc[PM_OFF + Hkv];
-    const int K = misc[MISC_KEPT];
     const bool want_logp = a.logp_out != nullptr;
     const bool want_sort = want_logp || a.sigma_out != nullptr;
     auto head_of = [&](int i) {
@@ -1035,13 +1013,6 @@ __global__ __launch_bounds__(POOL_THREADS) void evict_pooled_kernel(SelectArgs a
         while (h + 1 < Hkv && i >= misc[PM_OFF + h + 1]) ++h;
         return h;
     };
-    if (K == 0) {
-        if (tid < Hkv) {
-            if (a.k) a.len_out[seg_first + tid] = 0;
-            if (want_logp) a.logp_out[seg_first + tid] = 0.f;
-        }
-        return;
-    }
 
     // ---- 1. keys (and the first histogram of the radix select) -------------
     for (int i = tid; i < SEL_BINS; i += THREADS) hist[i] = 0;
@@ -1154,8 +1125,6 @@ __global__ __launch_bounds__(POOL_THREADS) void evict_pooled_kernel(SelectArgs a
         const int slot = j - misc[PM_BASE + h];
         if (slot < a.max_keep) a.kept_out[(size_t)(seg_first + h) * a.max_keep + slot] = (int)items[j] - misc[PM_OFF + h];
     }
-    if (tid < Hkv && misc[PM_BASE + tid + 1] - misc[PM_BASE + tid] > a.max_keep)
-        atomicAdd(&a.status[NGC_STATUS_KEEP_CLAMPED], 1);
 
     if (want_sort) {
         // ---- 4. sigma: the slots sorted by descending code ---------------------
@@ -1204,21 +1173,230 @@ __global__ __launch_bounds__(POOL_THREADS) void evict_pooled_kernel(SelectArgs a
             }
         }
     }
-    if (a.k == nullptr) return;
+}
 
-    // ---- 6. per-head compaction ---------------------------------------------
-    __syncthreads();   // kept_out of this workgroup is complete and visible
-    for (int h = 0; h < Hkv; ++h) {
-        int Kh = misc[PM_BASE + h + 1] - misc[PM_BASE + h];
-        Kh = Kh < a.max_keep ? Kh : a.max_keep;
-        const size_t seg_off = (size_t)(seg_first + h) * cap * ROW_BYTES;
-        const int32_t *kept = a.kept_out + (size_t)(seg_first + h) * a.max_keep;
-        compact_kv_inplace<ROW_BYTES, THREADS, 4, true>(reinterpret_cast<unsigned char *>(a.k) + seg_off,
-                                                  reinterpret_cast<unsigned char *>(a.v) + seg_off,
-                                                  kept, Kh, 0, 1);
-        if (a.pos) compact_pos_inplace<THREADS>(a.pos + (size_t)(seg_first + h) * cap, kept, Kh, 0, 1);
-        if (tid == 0) a.len_out[seg_first + h] = Kh;
+template <int THREADS, int ROW_BYTES, int UNROLL>
+__global__ __launch_bounds__(THREADS) void evict_pooled_kernel(SelectArgs a)
+{
+    constexpr int NW = THREADS / NGC_WAVE;
+    constexpr int HIST = (SEL_BINS > SORT_BINS * NW) ? SEL_BINS : SORT_BINS * NW;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    uint32_t *hist = reinterpret_cast<uint32_t *>(smem_raw);
+    int *misc = reinterpret_cast<int *>(hist + HIST);
+    u32x4 *maxima = reinterpret_cast<u32x4 *>(misc + PM_WORDS);
+    // ranking: rank_cap codes, then as many bits
+    uint32_t *rank_code = reinterpret_cast<uint32_t *>(misc + PM_WORDS + (a.rank_cap > 0 ? PM_MAXIMA : 0));
+    uint32_t *kept_bits = rank_code + a.rank_cap;
+    uint16_t *idxA = reinterpret_cast<uint16_t *>(kept_bits + (a.rank_cap + 63) / 64 * 2);
+    uint16_t *idxB = idxA + a.keep_cap;                                      // max(keep_cap, rank_cap) entries
+    float *fmisc = reinterpret_cast<float *>(misc);
+
+    const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
+    const int Hkv = a.g.Hkv, cap = a.g.cap;
+    const int lb = a.seg0 / Hkv + blockIdx.x;     // layer * B + sequence
+    const int l = lb / a.g.B, b = lb - l * a.g.B;
+    const int seg_first = lb * Hkv;
+
+    // ---- 0. geometry of the pooled item space ------------------------------
+    if (tid == 0) {
+        int off = 0, ktot = 0, quads = 0;
+        for (int h = 0; h < Hkv; ++h) {
+            int n = a.len[seg_first + h];
+            if (n < 0 || n > cap) {
+                atomicAdd(&a.status[NGC_STATUS_LEN_CLAMPED], 1);
+                n = n < 0 ? 0 : cap;
+            }
+            int kh = a.keep[seg_first + h];
+            if (kh < 0) { atomicAdd(&a.status[NGC_STATUS_KEEP_CLAMPED], 1); kh = 0; }
+            misc[PM_N + h] = n;
+            misc[PM_OFF + h] = off;
+            misc[PM_QUAD + h] = quads;
+            off += n;
+            quads += (n + 3) / 4;
+            ktot += kh;
+        }
+        misc[PM_OFF + Hkv] = off;
+        misc[PM_QUAD + Hkv] = quads;
+        int lim = off < a.keep_cap ? off : a.keep_cap;
+        if (ktot > lim) {
+            atomicAdd(&a.status[NGC_STATUS_KEEP_CLAMPED], 1);
+            ktot = lim;
+        }
+        misc[MISC_KEPT] = ktot;
     }
+    __syncthreads();
+    const int N = misc[PM_OFF + Hkv];
+    const int K = misc[MISC_KEPT];
+    const bool want_logp = a.logp_out != nullptr;
+    const bool want_sort = want_logp || a.sigma_out != nullptr;
+    if (K == 0) {
+        if (tid < Hkv) {
+            if (a.len_out) a.len_out[seg_first + tid] = 0;
+            if (want_logp) a.logp_out[seg_first + tid] = 0.f;
+        }
+        return;
+    }
+
+    // ---- 1. ranking, where LDS holds a code and a bucket entry for every item (groups of four are dealt to the threads
+    // over all heads: a head of few rows leaves none idle) ----
+    const int quads = misc[PM_QUAD + Hkv];
+    auto head_of_quad = [&](int q) {
+        int h = 0;
+        while (h + 1 < Hkv && q >= misc[PM_QUAD + h + 1]) ++h;
+        return h;
+    };
+    bool ranked = false;
+    float unpicked = 0.f, smax = -INFINITY;
+    if (want_sort && 4 * quads <= a.rank_cap) {
+        for (int i = tid; i < HIST / 4; i += THREADS) reinterpret_cast<u32x4 *>(hist)[i] = u32x4{0u, 0u, 0u, 0u};
+        for (int i = tid; i < (4 * quads + 63) / 64 * 2; i += THREADS) kept_bits[i] = 0;
+        float neg_smin = -INFINITY;
+        uint32_t cmax = 0, neg_cmin = 0;
+        constexpr int HELD = 2;      // groups of four logits a thread keeps until the kept items are known
+        f32x4 held[HELD] = {};
+        int group = 0;
+#pragma unroll 1
+        for (int q = tid; q < quads; q += THREADS, ++group) {
+            const int h = head_of_quad(q), quad = q - misc[PM_QUAD + h], n = misc[PM_N + h];
+            float x[4], key[4];
+            keys_of_quad(a.logits + (size_t)(seg_first + h) * cap, n, quad, a.na, l, b, h, x, key);
+            if (group == 0) held[0] = f32x4{x[0], x[1], x[2], x[3]};
+            if (group == 1) held[1] = f32x4{x[0], x[1], x[2], x[3]};
+            u32x4 c;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                c[i] = 4 * quad + i < n ? ordered_code(key[i]) : 0u;          // (0: below every masked item)
+                cmax = c[i] > cmax ? c[i] : cmax;
+                if (c[i] > CODE_MASKED) neg_cmin = ~c[i] > neg_cmin ? ~c[i] : neg_cmin;
+                smax = fmaxf(smax, x[i]);
+                if (x[i] > -INFINITY) neg_smin = fmaxf(neg_smin, -x[i]);
+            }
+            reinterpret_cast<u32x4 *>(rank_code)[q] = c;
+        }
+        smax = wave_max_f(smax);
+        neg_smin = wave_max_f(neg_smin);
+        cmax = wave_reduce(cmax, OpMaxU{});
+        neg_cmin = wave_reduce(neg_cmin, OpMaxU{});
+        if (lane == 0) maxima[wv] = u32x4{__float_as_uint(smax), __float_as_uint(neg_smin), cmax, neg_cmin};
+        __syncthreads();
+        const u32x4 m = maxima[lane & (NW - 1)];
+        smax = lanes_reduce<NW>(__uint_as_float(m[0]), OpMaxF{});
+        neg_smin = lanes_reduce<NW>(__uint_as_float(m[1]), OpMaxF{});
+        cmax = lanes_reduce<NW>(m[2], OpMaxU{});
+        neg_cmin = lanes_reduce<NW>(m[3], OpMaxU{});
+        const bool spread = want_logp && smax > -INFINITY && smax + neg_smin > NGC_WIDE_SPREAD;
+        if (smax == -INFINITY) smax = 0.f;
+        ranked = !spread && rank_items<THREADS>(rank_code, 4 * quads, K, cmax, ~neg_cmin, hist,
+                                                reinterpret_cast<uint32_t *>(misc), idxB, idxA, kept_bits);
+        if (ranked) {
+            // kept slots before each head
+            for (int h = wv; h <= Hkv; h += NW) {
+                const int before = 4 * misc[PM_QUAD + h];
+                int count = 0;
+                for (int w = lane; 32 * w < before; w += NGC_WAVE) {
+                    uint32_t bits = kept_bits[w];
+                    if (32 * w + 32 > before) bits &= (1u << (before - 32 * w)) - 1u;
+                    count += __popc(bits);
+                }
+                count = wave_reduce(count, OpAdd{});
+                if (lane == 0) misc[PM_BASE + h] = count;
+            }
+            __syncthreads();
+            const int words = (4 * quads + 63) / 64;
+            const int per_wave = (words + NW - 1) / NW;
+            const int w_begin = wv * per_wave;
+            const int w_end = (w_begin + per_wave < words) ? (w_begin + per_wave) : words;
+            const u32x2 *bits = reinterpret_cast<const u32x2 *>(kept_bits);
+            int base = 0;
+            for (int w = lane; w < w_begin; w += NGC_WAVE) base += __popc(bits[w][0]) + __popc(bits[w][1]);
+            base = wave_reduce(base, OpAdd{});
+            for (int w = w_begin; w < w_end; ++w) {
+                const u32x2 pair = bits[w];
+                const uint64_t sel_bits = ((uint64_t)pair[1] << 32) | pair[0];
+                const int t = w * 64 + lane;
+                if ((sel_bits >> lane) & 1u) {
+                    const int h = head_of_quad(t >> 2);
+                    const int slot = base + popc_below(sel_bits) - misc[PM_BASE + h];
+                    if (slot < a.max_keep)
+                        a.kept_out[(size_t)(seg_first + h) * a.max_keep + slot] = t - 4 * misc[PM_QUAD + h];
+                }
+                base += __popcll(sel_bits);
+            }
+            if (want_logp) {         // the weights of all items where their codes stood
+                group = 0;
+#pragma unroll 1
+                for (int q = tid; q < quads; q += THREADS, ++group) {
+                    f32x4 x = group == 0 ? held[0] : held[1];
+                    if (group >= HELD) {
+                        const int h = head_of_quad(q), first = 4 * (q - misc[PM_QUAD + h]), n = misc[PM_N + h];
+                        const float *row = a.logits + (size_t)(seg_first + h) * cap;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            x[i] = first + i < n ? row[first + i] : -INFINITY;
+                            if (x[i] != x[i]) x[i] = -INFINITY;
+                        }
+                    }
+                    const uint32_t sel_bits = kept_bits[q >> 3] >> ((q & 7) * 4);
+                    f32x4 e;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        e[i] = exp_shifted(x[i] - smax);
+                        unpicked += (sel_bits >> i & 1u) ? 0.f : e[i];
+                    }
+                    reinterpret_cast<f32x4 *>(rank_code)[q] = e;
+                }
+            }
+        }
+    }
+    if (!ranked) pooled_general<THREADS>(a, seg_first, l, b, N, K, hist, misc, idxA, idxB);
+    if (tid < Hkv) {
+        const int kept = misc[PM_BASE + tid + 1] - misc[PM_BASE + tid];
+        if (kept > a.max_keep) atomicAdd(&a.status[NGC_STATUS_KEEP_CLAMPED], 1);
+        if (a.len_out) a.len_out[seg_first + tid] = kept < a.max_keep ? kept : a.max_keep;
+    }
+    __syncthreads();   // kept_out of this workgroup and the weights are complete and visible
+    // ---- 2. per-head compaction; sums and logarithms come behind it ----
+    if (a.k != nullptr)
+        for (int h = 0; h < Hkv; ++h) {
+            int Kh = misc[PM_BASE + h + 1] - misc[PM_BASE + h];
+            Kh = Kh < a.max_keep ? Kh : a.max_keep;
+            const size_t seg_off = (size_t)(seg_first + h) * cap * ROW_BYTES;
+            const int32_t *kept = a.kept_out + (size_t)(seg_first + h) * a.max_keep;
+            compact_kv_inplace<ROW_BYTES, THREADS, UNROLL, true>(reinterpret_cast<unsigned char *>(a.k) + seg_off,
+                                                                 reinterpret_cast<unsigned char *>(a.v) + seg_off,
+                                                                 kept, Kh, 0, 1);
+            if (a.pos) compact_pos_inplace<THREADS>(a.pos + (size_t)(seg_first + h) * cap, kept, Kh, 0, 1);
+        }
+    if (ranked) {
+        if (a.sigma_out) {
+            // the pooled sequence occupies the Hkv rows of this (layer, sequence) back to back
+            int32_t *sig_row = a.sigma_out + (size_t)seg_first * a.max_keep;
+            const int room = Hkv * a.max_keep;
+            for (int j = tid; j < K && j < room; j += THREADS) {
+                const int t = idxA[j], h = head_of_quad(t >> 2);
+                sig_row[j] = h * cap + (t - 4 * misc[PM_QUAD + h]);
+            }
+        }
+        if (want_logp) {
+            const float *weight = reinterpret_cast<const float *>(rank_code);
+            const float lp = sigma_logprob<THREADS>([&](int j) { return weight[idxA[j]]; }, K, unpicked, fmisc);
+            if (tid < Hkv) a.logp_out[seg_first + tid] = (tid == 0) ? lp : 0.f;
+        }
+    }
+}
+
+// The rows of a pooled round, one workgroup per segment: the selection has left each head's list and, as its length, how
+// many it keeps.
+template <int THREADS, int ROW_BYTES, int UNROLL>
+__global__ __launch_bounds__(THREADS) void pooled_copy_kernel(SelectArgs a)
+{
+    const int seg = a.seg0 + (int)blockIdx.x;
+    const int kept = a.len_out[seg];
+    const int32_t *list = a.kept_out + (size_t)seg * a.max_keep;
+    const size_t seg_off = (size_t)seg * a.g.cap * ROW_BYTES;
+    compact_kv_inplace<ROW_BYTES, THREADS, UNROLL, true>(reinterpret_cast<unsigned char *>(a.k) + seg_off,
+                                                         reinterpret_cast<unsigned char *>(a.v) + seg_off, list, kept, 0, 1);
+    if (a.pos) compact_pos_inplace<THREADS>(a.pos + (size_t)seg * a.g.cap, list, kept, 0, 1);
 }
 
 // One segment at a time per workgroup: sample, score, then move the survivors.  While a workgroup is in its
@@ -1595,34 +1773,62 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
         long long kc = (long long)c->Hkv * max_keep;
         if (kc > (long long)c->Hkv * c->cap) kc = (long long)c->Hkv * c->cap;
         int keep_cap = (int)((kc + 7) & ~7LL);
-        const int hist = (SEL_BINS > SORT_BINS * (POOL_THREADS / 64)) ? SEL_BINS : SORT_BINS * (POOL_THREADS / 64);
-        size_t lds = (size_t)hist * 4 + 128 * 4 + (size_t)keep_cap * 2 * 2;
+        const long long quads = (long long)c->Hkv * ((c->cap + 3) / 4);
+        // One workgroup per (layer, sequence) selects.  Up to POOL_FEW of them, half the CUs at most would copy, one head
+        // after another: the rows get a launch of their own, a workgroup per head.  Microseconds with one launch and with two:
+        //     sequences x heads x rows      8 x 4 x 500   32 x 2 x 1500   64 x 4 x 4000   128 x 4 x 1500   128 x 2 x 4000
+        //                                  28.1  21.9     37.5  31.7     217.2  163.2    107.7  107.2     132.6  134.1
+        //                               192 x 4 x 1500  192 x 4 x 4000   256 x 2 x 1500   448 x 4 x 500    896 x 4 x 1500
+        //                                 141.2  146.0   345.5  373.4      91.0   97.9     109.5  119.2    564.1  627.8
+        // 1024 threads; 512 where several workgroups share a CU and have little to select (us of 1024 and of 512: 448 x 2 x
+        // 500 rows 59.2 and 55.8, 896 x 8 x 300 268 and 250, 896 x 2 x 1500 289 and 293, 448 x 8 x 1000 398 and 438; 256 x 4 x
+        // 500 65.3 and 67.8; two launches, 16 x 8 x 300 24.7 and 27.8).
+        const int sequences = nseg / c->Hkv;
+        const bool split = sequences <= POOL_FEW;
+        const int threads = sequences > POOL_MANY && (long long)c->Hkv * c->cap <= POOL_SMALL_ITEMS ? 512 : 1024;
+        const int hist = (SEL_BINS > SORT_BINS * (threads / 64)) ? SEL_BINS : SORT_BINS * (threads / 64);
+        const size_t fixed = (size_t)hist * 4 + PM_WORDS * 4;
+        auto lds_for = [&](long long ranked) {
+            const long long second = ranked > keep_cap ? ranked : keep_cap;
+            return fixed + (ranked > 0 ? PM_MAXIMA * 4 : 0) + (size_t)ranked * 4 + (size_t)((ranked + 63) / 64) * 8 + (size_t)keep_cap * 2 + (size_t)second * 2;
+        };
+        int rank_cap = (int)((4 * quads + 7) & ~7LL);
+        if (lds_for(rank_cap) > 160 * 1024) rank_cap = 0;
+        size_t lds = lds_for(rank_cap);
         if (lds > 160 * 1024) {
             // Hkv * max_keep is only an upper bound of what a (layer, sequence) keeps (max_keep has to cover the
             // largest single head); the budget itself is on the device.  The index buffers take what LDS holds;
             // a budget above that is clamped by the kernel and counted in NGC_STATUS_KEEP_CLAMPED.
-            keep_cap = (int)(((160 * 1024 - (size_t)hist * 4 - 128 * 4) / 4) & ~7u);
-            lds = (size_t)hist * 4 + 128 * 4 + (size_t)keep_cap * 2 * 2;
+            keep_cap = (int)(((160 * 1024 - fixed) / 4) & ~7u);
+            lds = lds_for(0);
         }
         SelectArgs sa;
         sa.logits = logits; sa.len = c->len; sa.keep = keep;
         sa.kept_out = kept_out; sa.sigma_out = sigma_out; sa.logp_out = logp_out;
         sa.status = reinterpret_cast<int32_t *>(ws);
-        const bool move = !(p->flags & NGC_EVICT_SELECT_ONLY);
-        sa.k = move ? c->k : nullptr; sa.v = c->v; sa.pos = c->pos; sa.len_out = c->len;
+        const bool move = !(p->flags & NGC_EVICT_SELECT_ONLY);       // (a second launch finds a.len_out, not a.k, set)
+        sa.k = move && !split ? c->k : nullptr; sa.v = c->v; sa.pos = c->pos; sa.len_out = move ? c->len : nullptr;
         sa.unordered = 0;
-        sa.seg0 = seg0; sa.max_keep = max_keep; sa.items_cap = 0; sa.keep_cap = keep_cap; sa.rank_cap = 0;
+        sa.seg0 = seg0; sa.max_keep = max_keep; sa.items_cap = 0; sa.keep_cap = keep_cap; sa.rank_cap = rank_cap;
         sa.pool_codes = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(ws) + codes_off);
         sa.g = SegGeom{c->B, c->Hkv, c->cap, 1};
         sa.logit_stride = c->cap;
         sa.na = NoiseArgs{p->seed, p->round, p->noise_scale, p->share_heads, p->layer_base, p->seq_base};
-        const void *fn = (c->D == 128) ? reinterpret_cast<const void *>(&evict_pooled_kernel<256>)
-                                       : reinterpret_cast<const void *>(&evict_pooled_kernel<128>);
+#define NGC_PICK(KERNEL, T, U) ((c->D == 128) ? reinterpret_cast<const void *>(&KERNEL<T, 256, U>) \
+                                              : reinterpret_cast<const void *>(&KERNEL<T, 128, U>))
+        const void *select = threads == 1024 ? NGC_PICK(evict_pooled_kernel, 1024, 4) : NGC_PICK(evict_pooled_kernel, 512, 8);
         if (lds > 64 * 1024)
-            NGC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            NGC_HIP_CHECK(hipFuncSetAttribute(select, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         void *kargs[] = {&sa};
-        NGC_HIP_CHECK(hipLaunchKernel(fn, dim3(nseg / c->Hkv), dim3(POOL_THREADS), kargs, lds,
-                                      (hipStream_t)stream));
+        NGC_HIP_CHECK(hipLaunchKernel(select, dim3(sequences), dim3(threads), kargs, lds, (hipStream_t)stream));
+        if (!move || !split) return NGC_OK;
+        sa.k = c->k;
+        const int movers = c->cap > 4096 ? 1024 : (c->cap > 512 ? 512 : 256);    // (as in the per-head mode)
+        const void *copy = movers == 1024  ? NGC_PICK(pooled_copy_kernel, 1024, 4)
+                           : movers == 512 ? NGC_PICK(pooled_copy_kernel, 512, 8)
+                                           : NGC_PICK(pooled_copy_kernel, 256, 6);
+#undef NGC_PICK
+        NGC_HIP_CHECK(hipLaunchKernel(copy, dim3(nseg), dim3(movers), kargs, 0, (hipStream_t)stream));
         return NGC_OK;
     }
 
