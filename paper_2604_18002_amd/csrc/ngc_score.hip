@@ -30,12 +30,14 @@ struct ScoreArgs {
     const int32_t *len;
     const unsigned char *q;   // bf16 [lb][w][Hq][D]
     const float *lse;         // optional fp32 [lb][w][Hq]: log-sum-exp of every query's scaled scores
-    float *psi_out;           // fp32 [seg][cap], one value per key
+    float *psi_out;           // fp32 [seg][cap], one value per key or per tile
     int32_t *status;
     int seg0, nseg, lb0;
     int S;                    // workgroups per segment (1 unless lse is given) ...
     int share_rows;           // ... of at least so many rows; shorter ones are left to their first
     int w, G, Hkv, cap, causal;
+    int block;                // a multiple of SC_TILE (TILES): tile t leaves the sum of its keys, their mean if the block is
+                              // one tile, at psi[t]
     float scale_log2e;
     // paged layout: k is the pool and a tile's base comes from the page table
     const int32_t *table;   // [seg][max_pages] or nullptr (contiguous layout)
@@ -45,7 +47,9 @@ struct ScoreArgs {
 // Up to three query tiles the kernel fits 168 registers per thread without spilling, i.e. three waves per SIMD
 // (three workgroups per CU) instead of the two the compiler settles for by itself; with four tiles it does not.
 // GIVEN: the normalisers are (lse); one pass.
-template <int D, int QT, bool GIVEN>
+// TILES: `block` is a multiple of a tile, and a tile leaves one value (their own kernels: the choice at run time costs the
+// others four registers and with them a workgroup per CU).
+template <int D, int QT, bool GIVEN, bool TILES>
 __global__ __launch_bounds__(SC_WAVES * 64) __attribute__((amdgpu_waves_per_eu(QT <= 3 ? 3 : 2)))
 void score_keys_kernel(ScoreArgs a)
 {
@@ -273,6 +277,7 @@ void score_keys_kernel(ScoreArgs a)
                     kop[nt][c] = __builtin_bit_cast(
                         bf16x8, *reinterpret_cast<const u32x4 *>(wlds + (nt * 16 + li) * LROW + c * 64 + kg * 16));
             __builtin_amdgcn_wave_barrier();
+            float tile_sum = 0.f;
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) {
                 const int t = row0 + nt * 16 + li;   // the key of this lane
@@ -291,23 +296,39 @@ void score_keys_kernel(ScoreArgs a)
                     }
                 }
                 acc = quad_rows_sum(acc);
-                if (kg == 0 && t < n) psi[t] = acc * inv_rows;
+                if constexpr (TILES) tile_sum += t < n ? acc : 0.f;
+                else if (kg == 0 && t < n) psi[t] = acc * inv_rows;
+            }
+            if constexpr (TILES) {
+                tile_sum = lanes_reduce<16>(tile_sum, OpAdd{}) * inv_rows;
+                if (a.block == SC_TILE) tile_sum /= (float)(n - row0 < SC_TILE ? n - row0 : SC_TILE);
+                if (lane == 0) psi[tile] = tile_sum;
             }
         }
     }
 }
 
-// Block means and head pooling, in place over the per-key scores: item j of a
-// segment becomes the mean of the scores of its rows; with pooling, the mean of
-// that over the KV heads of the (layer, sequence) that have item j.  One
-// workgroup per (layer, sequence); items are processed in ascending tiles and
-// an item only reads rows at or beyond its own index, so reading a tile,
-// waiting, then writing it never clobbers what a later tile still reads.
+// Block means and head pooling, in place over the per-key scores or the tiles' sums: item j of a segment becomes the mean
+// over its rows; with pooling, the mean of that over the KV heads of the (layer, sequence) that have item j.
+//
+// Where an item's mean already stands at its own offset -- blocks of one tile, or of one key -- only the pooling is left, and
+// every item of a (layer, sequence) is a thread's of its own, wherever it runs: pool_heads_kernel.  Before, a thread made the
+// mean of 32 keys from memory, one after another, and one workgroup per (layer, sequence) went through all its items.
+// Microseconds, before and now (normalisers given but in the last):
+//     blocks of 32, pooled: 48 x 4 segments of 416 keys 20.0 and 11.6, 35 x 2 of 1692 at D = 64 13.6 and 8.5, 16 x 2 of 8000
+//     23.7 and 14.6, 512 x 4 of 3000 290 and 238; not pooled: 3472 x 4 of 333 259 and 200, 512 x 2 of 3000 at D = 64 83 and 60;
+//     blocks of 64, pooled: 40 x 2 of 3000 25.3 and 14.4; pooled per key: 128 x 8 of 2000 121 and 97; two passes: blocks of 32,
+//     pooled, 20 x 8 of 447 31.6 and 13.1
+//
+// Otherwise (score_reduce_kernel) one workgroup per (layer, sequence); items are processed in ascending tiles and an item
+// only reads values at or beyond its own index, so reading a tile, waiting, then writing it never clobbers what a later tile
+// still reads.
 struct ReduceArgs {
     float *scores;      // [lb][Hkv][cap]
     const int32_t *len;
     int lb0_seg;        // first (layer*B + sequence) of the launch
     int Hkv, cap, block, pool;
+    int unit;           // rows per value: 1, or SC_TILE where the tiles' sums are reduced
 };
 
 __global__ __launch_bounds__(256) void score_reduce_kernel(ReduceArgs a)
@@ -330,7 +351,7 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(ReduceArgs a)
         const int lo = j * block;
         const int hi = (lo + block < n) ? lo + block : n;
         float acc = 0.f;
-        for (int t = lo; t < hi; ++t) acc += base[(size_t)h * a.cap + t];
+        for (int t = lo; t < hi; t += a.unit) acc += base[(size_t)h * a.cap + t / a.unit];
         return acc / (float)(hi - lo);
     };
     for (int tile = 0; tile < max_items; tile += 256) {
@@ -356,6 +377,29 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(ReduceArgs a)
                 __syncthreads();
             }
         }
+    }
+}
+
+__global__ __launch_bounds__(256) void pool_heads_kernel(ReduceArgs a)
+{
+    const int lb = a.lb0_seg + blockIdx.x;
+    float *base = a.scores + (size_t)lb * a.Hkv * a.cap;
+    const int items = (a.cap + a.block - 1) / a.block;
+    for (int j = (int)(blockIdx.y * 256 + threadIdx.x); j < items; j += (int)gridDim.y * 256) {
+        auto has_item = [&](int h) {
+            int n = a.len[lb * a.Hkv + h];
+            n = n > a.cap ? a.cap : n;
+            return j * a.block < n;
+        };
+        float pooled = 0.f;
+        int heads = 0;
+#pragma unroll 4
+        for (int h = 0; h < a.Hkv; ++h)
+            if (has_item(h)) { pooled += base[(size_t)h * a.cap + j]; ++heads; }
+        pooled /= (float)heads;
+#pragma unroll 4
+        for (int h = 0; h < a.Hkv; ++h)
+            if (has_item(h)) base[(size_t)h * a.cap + j] = pooled;
     }
 }
 
@@ -432,6 +476,8 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     sa.lb0 = layer < 0 ? 0 : layer * c->B;
     sa.w = w; sa.G = G; sa.Hkv = c->Hkv; sa.cap = c->cap;
     sa.causal = (flags & NGC_SCORE_NO_CAUSAL) ? 0 : 1;
+    const bool tiles = block % SC_TILE == 0;
+    sa.block = block;
     sa.scale_log2e = scale * 1.4426950408889634f;
     sa.table = nullptr; sa.max_pages = 0; sa.num_pages = 0; sa.tpp_shift = 0;
     if (pc) {
@@ -442,13 +488,15 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     }
     hipStream_t st = (hipStream_t)stream;
     const int qt = (R + 15) / 16;
-#define NGC_PICK_QT(DD, GIVEN) \
-    (qt == 1   ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 1, GIVEN>) \
-     : qt == 2 ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 2, GIVEN>) \
-     : qt == 3 ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 3, GIVEN>) \
-               : reinterpret_cast<const void *>(&score_keys_kernel<DD, 4, GIVEN>))
-    const void *fn = c->D == 128 ? (lse_recent ? NGC_PICK_QT(128, true) : NGC_PICK_QT(128, false))
-                                 : (lse_recent ? NGC_PICK_QT(64, true) : NGC_PICK_QT(64, false));
+#define NGC_PICK_QT(DD, GIVEN, TILES) \
+    (qt == 1   ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 1, GIVEN, TILES>) \
+     : qt == 2 ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 2, GIVEN, TILES>) \
+     : qt == 3 ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 3, GIVEN, TILES>) \
+               : reinterpret_cast<const void *>(&score_keys_kernel<DD, 4, GIVEN, TILES>))
+#define NGC_PICK_GIVEN(DD, TILES) (lse_recent ? NGC_PICK_QT(DD, true, TILES) : NGC_PICK_QT(DD, false, TILES))
+    const void *fn = c->D == 128 ? (tiles ? NGC_PICK_GIVEN(128, true) : NGC_PICK_GIVEN(128, false))
+                                 : (tiles ? NGC_PICK_GIVEN(64, true) : NGC_PICK_GIVEN(64, false));
+#undef NGC_PICK_GIVEN
 #undef NGC_PICK_QT
     // With two query tiles at D = 128 and the normalisers given four workgroups fit a CU.  Between 1024 and 1536 segments two
     // rounds of three are fuller than two of four: LDS that nobody uses keeps the fourth out (1536 x 1366-1800 keys 110 -> 107.5
@@ -456,12 +504,17 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     const size_t keep_out = c->D == 128 && qt == 2 && lse_recent && nseg > 1024 && nseg <= 1536 ? 8192 : 0;
     const int rc = launch(fn, dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), keep_out, st, sa);
     if (rc) return rc;
-    if (pool || block > 1) {
-        // scores_out is indexed by the global segment; the reduce kernel gets the global base
-        ReduceArgs ra{scores_out, c->len, seg0 / c->Hkv, c->Hkv, c->cap, block, pool ? 1 : 0};
-        hipLaunchKernelGGL(score_reduce_kernel, dim3(nseg / c->Hkv), dim3(256), 0, st, ra);
-        NGC_HIP_CHECK(hipGetLastError());
+    // scores_out is indexed by the global segment; what follows gets the global base
+    const int sequences = nseg / c->Hkv;
+    ReduceArgs ra{scores_out, c->len, seg0 / c->Hkv, c->Hkv, c->cap, block, pool ? 1 : 0, tiles ? SC_TILE : 1};
+    const bool whole = block == 1 || block == SC_TILE;       // an item's mean stands at its offset
+    if (whole && pool) {
+        const int columns = ((c->cap + block - 1) / block + 255) / 256;
+        return launch(reinterpret_cast<const void *>(&pool_heads_kernel),
+                      dim3((unsigned)sequences, (unsigned)(columns < 4096 ? columns : 4096)), dim3(256), 0, st, ra);
     }
+    if (!whole) return launch(reinterpret_cast<const void *>(&score_reduce_kernel), dim3((unsigned)sequences), dim3(256), 0,
+                               st, ra);
     return NGC_OK;
 }
 }  // namespace
