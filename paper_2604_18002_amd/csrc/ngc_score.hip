@@ -3,9 +3,9 @@
 // averaged over the query heads of a KV head and over the w queries, then
 // (optionally) averaged over KV heads and over blocks of consecutive keys.
 //
-// One workgroup of 4 waves per (layer, sequence, KV head), several where there are
-// few of those and the normalisers are given (those kernels ask for the queries and
-// normalisers before the length is known).  The w*G query rows
+// One workgroup of 4 waves per (layer, sequence, KV head), several (or of 8 waves)
+// where there are few of those (they ask for the queries, and for normalisers that
+// are given, before the length is known).  The w*G query rows
 // are padded to QT tiles of 16 and both passes run on the matrix cores:
 //   pass 1  S^T = K Q^T   (queries on lane%16): running max / sum per query row
 //   pass 2  S   = Q K^T   (keys on lane%16):    p = 2^(x - m) / l, summed over
@@ -24,6 +24,7 @@ namespace ngc {
 
 constexpr int SC_WAVES = 4;
 constexpr int SC_TILE = 32;
+constexpr int MOST_SHARES = 32;
 
 struct ScoreArgs {
     const unsigned char *k;
@@ -33,7 +34,8 @@ struct ScoreArgs {
     float *psi_out;           // fp32 [seg][cap], one value per key or per tile
     int32_t *status;
     int seg0, nseg, lb0;
-    int S;                    // workgroups per segment (1 unless lse is given) ...
+    f32x2 *parts;             // SCORE_FIRST, SCORE_SECOND: [segment of the launch][share][w * G]: maximum and sum of a query row
+    int S;                    // workgroups per segment (1 for SCORE_BOTH) ...
     int share_rows;           // ... of at least so many rows; shorter ones are left to their first
     int w, G, Hkv, cap, causal;
     int block;                // a multiple of SC_TILE (TILES): tile t leaves the sum of its keys, their mean if the block is
@@ -46,13 +48,17 @@ struct ScoreArgs {
 
 // Up to three query tiles the kernel fits 168 registers per thread without spilling, i.e. three waves per SIMD
 // (three workgroups per CU) instead of the two the compiler settles for by itself; with four tiles it does not.
-// GIVEN: the normalisers are (lse); one pass.
+// MODE: the normalisers are given (lse), one pass; both passes; or the two passes as launches of their own, which the
+// workgroups of a segment share: the first leaves every share's maximum and sum of each query row, the second merges them.
 // TILES: `block` is a multiple of a tile, and a tile leaves one value (their own kernels: the choice at run time costs the
 // others four registers and with them a workgroup per CU).
-template <int D, int QT, bool GIVEN, bool TILES>
-__global__ __launch_bounds__(SC_WAVES * 64) __attribute__((amdgpu_waves_per_eu(QT <= 3 ? 3 : 2)))
+enum { SCORE_GIVEN, SCORE_BOTH, SCORE_FIRST, SCORE_SECOND };
+
+template <int D, int QT, int MODE, bool TILES, int WAVES = SC_WAVES>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(WAVES == SC_WAVES && QT <= 3 ? 3 : 2)))
 void score_keys_kernel(ScoreArgs a)
 {
+    constexpr bool GIVEN = MODE == SCORE_GIVEN, FIRST = MODE == SCORE_FIRST, SECOND = MODE == SCORE_SECOND;
     constexpr int ROW_BYTES = D * 2;
     constexpr int KCH = D / 32;
     constexpr int LROW = ROW_BYTES + 16;
@@ -61,9 +67,9 @@ void score_keys_kernel(ScoreArgs a)
     constexpr int K_ROWS_PER_LOAD = 64 / K_PIECES;
     constexpr int WAVE_LDS = SC_TILE * LROW;
 
-    __shared__ __align__(16) unsigned char lds[SC_WAVES * WAVE_LDS];
-    __shared__ float red_m[SC_WAVES][QT * 16];
-    __shared__ float red_l[SC_WAVES][QT * 16];
+    __shared__ __align__(16) unsigned char lds[WAVES * WAVE_LDS];
+    __shared__ float red_m[WAVES][QT * 16];
+    __shared__ float red_l[WAVES][QT * 16];
     __shared__ float fin_m[QT * 16];
     __shared__ float fin_il[QT * 16];
 
@@ -73,7 +79,7 @@ void score_keys_kernel(ScoreArgs a)
     // of share (t / 4) % S.
     const int share = (int)(blockIdx.x / a.nseg);
     const int seg = a.seg0 + (int)(blockIdx.x - share * a.nseg);
-    const int first_tile = share * SC_WAVES;
+    const int first_tile = share * WAVES;
     const int G = a.G, w = a.w, R = w * G;
     if (GIVEN && share > 0 && a.share_rows > 0 && a.len[seg] < a.share_rows) return;   // nothing to share
     // Asked for first, none of it waits for the length: the query operands -- row r = qt*16 + li  ->  (recent query
@@ -104,11 +110,11 @@ void score_keys_kernel(ScoreArgs a)
     }
     int n = a.len[seg];
     if (n < 0 || n > a.cap) {
-        if (threadIdx.x == 0 && share == 0) atomicAdd(&a.status[NGC_STATUS_LEN_CLAMPED], 1);
+        if (!SECOND && threadIdx.x == 0 && share == 0) atomicAdd(&a.status[NGC_STATUS_LEN_CLAMPED], 1);
         n = n < 0 ? 0 : a.cap;
     }
     const int shares = n < a.share_rows ? 1 : a.S;
-    const int tile_step = shares * SC_WAVES;
+    const int tile_step = shares * WAVES;
     if (share >= shares || first_tile * SC_TILE >= n) return;
     const unsigned char *kseg = a.table ? a.k : a.k + (size_t)seg * a.cap * ROW_BYTES;
     const int32_t *tab = a.table ? a.table + (size_t)seg * a.max_pages : nullptr;
@@ -151,14 +157,41 @@ void score_keys_kernel(ScoreArgs a)
     // The first tile before the normalisers are there, except with one query tile, where the launches that are resident at
     // once (up to 512 segments) got slower for it: 400 segments of 2150-3789 keys 52.0 -> 55.0 us, 512 63.8 -> 65.6; with two
     // tiles 512 68.7 -> 67.9, 300 51.9 -> 49.9.
-    constexpr bool ASK_EARLY = GIVEN && QT > 1;
+    constexpr bool ASK_EARLY = (GIVEN && QT > 1) || SECOND;
     if constexpr (ASK_EARLY) load_tile(first_tile + wv);
     // ------------------------------------------------ pass 1: max and sum ---
     // (skipped when the caller hands over the log-sum-exp that decode attention
     // already computed for these very queries: then K is read only once)
     if constexpr (GIVEN) {
-        static_assert(QT * 16 <= SC_WAVES * 64, "a thread per query row");
+        static_assert(QT * 16 <= WAVES * 64, "a thread per query row");
         if (threadIdx.x < QT * 16) fin_m[threadIdx.x] = given;
+        __syncthreads();
+    } else if constexpr (SECOND) {
+        // four threads a row, each with every fourth share
+        static_assert(WAVES == 4 && QT <= 4, "up to 64 query rows");
+        const int r = threadIdx.x >> 2;
+        const int used = (tiles + WAVES - 1) / WAVES < a.S ? (tiles + WAVES - 1) / WAVES : a.S;
+        const f32x2 *part = a.parts + (size_t)(seg - a.seg0) * a.S * R + r;
+        float M = -INFINITY, L = 0.f;
+        if (r < R) {
+            f32x2 own[MOST_SHARES / 4];
+#pragma unroll
+            for (int i = 0; i < MOST_SHARES / 4; ++i) {
+                const int x = 4 * i + (threadIdx.x & 3);
+                own[i] = f32x2{-INFINITY, 0.f};
+                if (x < used) own[i] = part[(size_t)x * R];
+            }
+#pragma unroll
+            for (int i = 0; i < MOST_SHARES / 4; ++i) M = fmaxf(M, own[i][0]);
+            M = lanes_reduce<4>(M, OpMaxF{});
+#pragma unroll
+            for (int i = 0; i < MOST_SHARES / 4; ++i) L += own[i][0] == -INFINITY ? 0.f : own[i][1] * fast_exp2(own[i][0] - M);
+            L = lanes_reduce<4>(L, OpAdd{});
+        }
+        if ((threadIdx.x & 3) == 0 && r < QT * 16) {
+            fin_m[r] = M;
+            fin_il[r] = (L > 0.f) ? 1.0f / L : 0.f;
+        }
         __syncthreads();
     } else {
     float m_run[QT], l_run[QT];
@@ -173,12 +206,13 @@ void score_keys_kernel(ScoreArgs a)
         vis_q[qt] = r < R && vis > 0 ? vis : 0;
     }
     {
-        int tile = wv;
+        const int step = FIRST ? tile_step : WAVES;
+        int tile = FIRST ? first_tile + wv : wv;
         load_tile(tile);
-        for (; tile < tiles; tile += SC_WAVES) {
+        for (; tile < tiles; tile += step) {
             stage_tile();
             const int row0 = tile * SC_TILE;
-            load_tile(tile + SC_WAVES);
+            load_tile(tile + step);
             __builtin_amdgcn_sched_barrier(0);
             __builtin_amdgcn_wave_barrier();
             bf16x8 kop[2][KCH];
@@ -227,19 +261,23 @@ void score_keys_kernel(ScoreArgs a)
         if (kg == 0) { red_m[wv][qt * 16 + li] = m_run[qt]; red_l[wv][qt * 16 + li] = l; }
     }
     __syncthreads();
-    for (int r = threadIdx.x; r < QT * 16; r += SC_WAVES * 64) {
+    for (int r = threadIdx.x; r < QT * 16; r += WAVES * 64) {
         float M = red_m[0][r];
 #pragma unroll
-        for (int x = 1; x < SC_WAVES; ++x) M = fmaxf(M, red_m[x][r]);
+        for (int x = 1; x < WAVES; ++x) M = fmaxf(M, red_m[x][r]);
         float L = 0.f;
 #pragma unroll
-        for (int x = 0; x < SC_WAVES; ++x) {
+        for (int x = 0; x < WAVES; ++x) {
             const float mw = red_m[x][r];
             L += (mw == -INFINITY) ? 0.f : red_l[x][r] * fast_exp2(mw - M);
+        }
+        if constexpr (FIRST) {
+            if (r < R) a.parts[((size_t)(seg - a.seg0) * a.S + share) * R + r] = f32x2{M, L};
         }
         fin_m[r] = M;
         fin_il[r] = (L > 0.f) ? 1.0f / L : 0.f;
     }
+    if constexpr (FIRST) return;
     __syncthreads();
     }
 
@@ -409,8 +447,7 @@ using namespace ngc;
 
 namespace {
 // Workgroups per segment.  With the normalisers given, a key's score needs nothing from the other keys, so a segment can be
-// shared freely; without them every workgroup would first have to read all of K.  Microseconds against the number S of
-// workgroups per segment (D = 128, w = 5, 6 heads per KV head):
+// shared freely.  Microseconds against the number S of workgroups per segment (D = 128, w = 5, 6 heads per KV head):
 //     segments x keys     S=1     2     4     8    16    32
 //         8 x 2000       17.6  10.8   7.5   6.5   5.8   5.9
 //         8 x 8000       55.7  30.7  17.7  11.1   7.9   6.4
@@ -427,6 +464,13 @@ namespace {
 // leaves before it asks for anything else (640 x 100-300 in a capacity of 4096 9.8, 10.4 before there was one).
 constexpr int SHARE_ROWS = 2048;
 
+// Where a workspace's scratch begins: behind the status words and the tickets of decode attention (which stay zero).
+size_t score_parts_offset(const ngc_cache *c)
+{
+    const size_t tickets = (size_t)c->L * c->B * c->Hkv * 12;
+    return (NGC_STATUS_WORDS * sizeof(int32_t) + tickets + 255) & ~(size_t)255;
+}
+
 struct Shares {
     int S, rows;
 };
@@ -439,6 +483,32 @@ Shares score_shares(int nseg, int cap, int D, bool have_lse)
     if (D == 128 && nseg > 512 && nseg <= 640 && cap >= SHARE_ROWS) return {2, SHARE_ROWS};
     const int s = rounds < fill ? rounds : fill;
     return {s > 1 ? s : 1, 0};
+}
+
+// Workgroups per segment where the normalisers are not given: the two passes as two launches, two workgroups per CU in all,
+// a share's maxima and sums in the workspace (if it has the room that decode attention's partials take, and the segments four
+// shares or more); otherwise, up to a workgroup per CU, one with eight waves.  Microseconds (D = 128, 6 heads per KV head, w
+// queries) of one workgroup of four waves, of eight, and of two launches with S shares:
+//     segments x keys, w     4      8     S=2    S=4    S=8    S=16   S=32
+//         8 x  500, 3      10.6    9.0   10.7    8.8    8.4
+//         8 x 3000, 3      43.6   30.6   26.0   16.7   11.5   10.1    9.0
+//        32 x  700, 3      14.3   11.6   12.0   10.6    9.0
+//        64 x  500, 5      10.8    9.8   10.7    9.2   10.2
+//        64 x 3000, 3      49.6   36.8   30.1   20.0   18.2   23.1   25.1
+//       160 x  447, 1      13.4   12.2   15.2   14.2
+//       160 x 3000, 3      56.4   42.9
+//       256 x 3000, 3      65.1   59.1
+//       512 x 3000, 3     120.3  122.3
+// (16 waves spill with two query tiles.)
+constexpr int MORE_WAVES_SEGMENTS = 256;
+
+int passes_shares(int nseg, int cap)
+{
+    const int rounds = (cap + SC_TILE * SC_WAVES - 1) / (SC_TILE * SC_WAVES);
+    int S = 512 / nseg;
+    if (S > rounds) S = rounds;
+    if (S > MOST_SHARES) S = MOST_SHARES;
+    return S >= 4 ? S : 1;
 }
 
 int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, const void *q_recent,
@@ -470,7 +540,17 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     sa.psi_out = scores_out;
     sa.status = reinterpret_cast<int32_t *>(ws);
     sa.seg0 = seg0; sa.nseg = nseg;
-    const Shares shares = score_shares(nseg, c->cap, c->D, lse_recent != nullptr);   // nseg * S <= max(nseg, 1280)
+    Shares shares = score_shares(nseg, c->cap, c->D, lse_recent != nullptr);   // nseg * S <= max(nseg, 1280)
+    sa.parts = nullptr;
+    if (!lse_recent) {
+        const int S = passes_shares(nseg, c->cap);
+        const size_t parts_at = score_parts_offset(c), parts_bytes = (size_t)nseg * S * R * sizeof(f32x2);
+        if (S > 1 && (reinterpret_cast<uintptr_t>(ws) & 7) == 0 && ws_bytes >= parts_at + parts_bytes) {
+            shares = {S, 0};
+            sa.parts = reinterpret_cast<f32x2 *>(reinterpret_cast<unsigned char *>(ws) + parts_at);
+        }
+    }
+    const bool more_waves = !lse_recent && !sa.parts && nseg <= MORE_WAVES_SEGMENTS;
     sa.S = shares.S;
     sa.share_rows = shares.rows;
     sa.lb0 = layer < 0 ? 0 : layer * c->B;
@@ -488,12 +568,20 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     }
     hipStream_t st = (hipStream_t)stream;
     const int qt = (R + 15) / 16;
-#define NGC_PICK_QT(DD, GIVEN, TILES) \
-    (qt == 1   ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 1, GIVEN, TILES>) \
-     : qt == 2 ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 2, GIVEN, TILES>) \
-     : qt == 3 ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 3, GIVEN, TILES>) \
-               : reinterpret_cast<const void *>(&score_keys_kernel<DD, 4, GIVEN, TILES>))
-#define NGC_PICK_GIVEN(DD, TILES) (lse_recent ? NGC_PICK_QT(DD, true, TILES) : NGC_PICK_QT(DD, false, TILES))
+#define NGC_PICK_QT(DD, ...) \
+    (qt == 1   ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 1, __VA_ARGS__>) \
+     : qt == 2 ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 2, __VA_ARGS__>) \
+     : qt == 3 ? reinterpret_cast<const void *>(&score_keys_kernel<DD, 3, __VA_ARGS__>) \
+               : reinterpret_cast<const void *>(&score_keys_kernel<DD, 4, __VA_ARGS__>))
+#define NGC_PICK_GIVEN(DD, TILES) \
+    (lse_recent ? NGC_PICK_QT(DD, SCORE_GIVEN, TILES) \
+     : sa.parts ? NGC_PICK_QT(DD, SCORE_SECOND, TILES) \
+     : more_waves ? NGC_PICK_QT(DD, SCORE_BOTH, TILES, 2 * SC_WAVES) : NGC_PICK_QT(DD, SCORE_BOTH, TILES))
+    if (sa.parts) {
+        const void *first = c->D == 128 ? NGC_PICK_QT(128, SCORE_FIRST, false) : NGC_PICK_QT(64, SCORE_FIRST, false);
+        const int rc = launch(first, dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), 0, st, sa);
+        if (rc) return rc;
+    }
     const void *fn = c->D == 128 ? (tiles ? NGC_PICK_GIVEN(128, true) : NGC_PICK_GIVEN(128, false))
                                  : (tiles ? NGC_PICK_GIVEN(64, true) : NGC_PICK_GIVEN(64, false));
 #undef NGC_PICK_GIVEN
@@ -502,7 +590,7 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     // rounds of three are fuller than two of four: LDS that nobody uses keeps the fourth out (1536 x 1366-1800 keys 110 -> 107.5
     // us, 1030 77.4 -> 75.8; with four 1024 x 2150-3789 147 -> 139, 896 x 700 30.2 -> 29.0).
     const size_t keep_out = c->D == 128 && qt == 2 && lse_recent && nseg > 1024 && nseg <= 1536 ? 8192 : 0;
-    const int rc = launch(fn, dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), keep_out, st, sa);
+    const int rc = launch(fn, dim3((unsigned)(nseg * sa.S)), dim3((more_waves ? 2 : 1) * SC_WAVES * 64), keep_out, st, sa);
     if (rc) return rc;
     // scores_out is indexed by the global segment; what follows gets the global base
     const int sequences = nseg / c->Hkv;
