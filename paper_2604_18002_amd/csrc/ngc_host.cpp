@@ -2,8 +2,8 @@
 //
 // The Python binding used ctypes for this: building an ngc_cache out of a dozen attribute reads and converting a dozen
 // arguments took ~6 us of the 8.5 us a decode step cost on the host, more than the kernel runs for a small cache.  Here it took
-// 1.1 us through the tensors' methods, and takes 0.3 us with plain tensors read directly (ngc_torch.cpp).  Marshalling only: no state is kept between calls, nothing is remembered about a tensor, and every
-// check is the C ABI's own (plus the contiguity the binding always asked for).  What it takes is what ctypes took: a cache
+// 1.1 us through the tensors' methods, and takes 0.3 us with plain tensors read directly (ngc_torch.cpp).  Marshalling only: no
+// state is kept between calls, nothing is remembered about a tensor, and every check is the C ABI's own (plus the contiguity the binding always asked for).  What it takes is what ctypes took: a cache
 // with a view() of its own is asked for it, a structure must be of its type, a number may be a ctypes one.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>

@@ -19,7 +19,7 @@
 //
 // What bounds it: matrix and vector work of two waves per SIMD that overlap only in part, then the output.  B = 8,
 // T = 4096, 28/4 heads, 27 % of the causal pairs visible (the issued products are worth 390 GFLOP): 546-557 us with
-// 16-wide tiles and rows staged through registers, now 440-460 us; B = 16, T = 1050, 12/2 heads 123 -> 81-84 us.  On the
+// 16-wide tiles and rows staged through registers, now 440-460 us; B = 16, T = 1050, 12/2 heads 123 -> 79 us.  On the
 // way, at the first shape (552 us before): 32-wide tiles and loads straight to LDS 511 us; a reference for the
 // exponents that moves only when outgrown by 2^8, and transposing reads of V instead of 32 byte permutes a step, 464 us;
 // the output through LDS in whole lines, nontemporal, and the list kernel in one pass 440 us.  The version before the last
