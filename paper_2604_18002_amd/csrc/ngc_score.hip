@@ -34,16 +34,16 @@ struct ScoreArgs {
     float *psi_out;           // fp32 [seg][cap], one value per key or per tile
     int32_t *status;
     int seg0, nseg, lb0;
-    f32x2 *parts;             // SCORE_FIRST, SCORE_SECOND: [segment of the launch][share][w * G]: maximum and sum of a query row
     int S;                    // workgroups per segment (1 for SCORE_BOTH) ...
     int share_rows;           // ... of at least so many rows; shorter ones are left to their first
     int w, G, Hkv, cap, causal;
-    int block;                // a multiple of SC_TILE (TILES): tile t leaves the sum of its keys, their mean if the block is
-                              // one tile, at psi[t]
     float scale_log2e;
     // paged layout: k is the pool and a tile's base comes from the page table
     const int32_t *table;   // [seg][max_pages] or nullptr (contiguous layout)
     int max_pages, num_pages, tpp_shift;
+    int block;                // a multiple of SC_TILE (TILES): tile t leaves the sum of its keys, their mean if the block is
+                              // one tile, at psi[t]
+    f32x2 *parts;             // SCORE_FIRST, SCORE_SECOND: [segment of the launch][share][w * G]: maximum and sum of a query row
 };
 
 // Up to three query tiles the kernel fits 168 registers per thread without spilling, i.e. three waves per SIMD
