@@ -1,7 +1,7 @@
 """Build the HIP libraries in-tree for gfx950: ``paper_2604_18002_amd/libngc.so`` (the method) and
 ``paper_2604_18002_amd/libngc_probe.so`` (streaming probes for the measurement harness); with the host compiler
-``paper_2604_18002_amd/_ngc_host.so`` (the Python front of the C ABI) and ``paper_2604_18002_amd/libngc_torch.so`` (its reader
-of torch tensors)."""
+``paper_2604_18002_amd/_ngc_host.so`` (the Python front of the C ABI) and, where torch is there to compile against,
+``paper_2604_18002_amd/libngc_torch.so`` (its reader of torch tensors)."""
 from __future__ import annotations
 
 import os
@@ -39,6 +39,11 @@ def _hipcc() -> str:
     return exe
 
 
+def torch_identity(torch) -> str:
+    """Names the torch that the reader of tensors is compiled against; it serves no other."""
+    return f"{torch.__version__} {getattr(torch.version, 'git_version', None)}"
+
+
 def build(verbose: bool = False) -> str:
     """Compile every translation unit and link the shared library.  Always
     recompiles (this is the 'does it build' check)."""
@@ -63,14 +68,20 @@ def build(verbose: bool = False) -> str:
     cxx = shutil.which("g++") or shutil.which("c++")
     if cxx is None:
         raise RuntimeError("no host C++ compiler found; the Python front cannot be built")
-    import torch
-    from torch.utils.cpp_extension import include_paths, library_paths
     python = ["-I", sysconfig.get_paths()["include"]]
     cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall"]
-    abi = f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"
-    torch_flags = [abi, *(f"-isystem{d}" for d in include_paths()), *(f"-L{d}" for d in library_paths()),
-                   "-ltorch_python", "-ltorch_cpu", "-lc10"]
-    for src, lib, flags in (("ngc_host.cpp", HOST_LIB_PATH, ["-ldl"]), ("ngc_torch.cpp", TORCH_LIB_PATH, torch_flags)):
+    host_units = [("ngc_host.cpp", HOST_LIB_PATH, ["-ldl"])]
+    try:
+        import torch
+    except ImportError:      # the front needs none: without the reader it asks the tensors' methods
+        torch = None
+    if torch is not None:
+        from torch.utils.cpp_extension import include_paths, library_paths
+        host_units.append(("ngc_torch.cpp", TORCH_LIB_PATH, [
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DNGC_TORCH_IDENTITY="{torch_identity(torch)}"',
+            *(f"-isystem{d}" for d in include_paths()), *(f"-L{d}" for d in library_paths()),
+            "-ltorch_python", "-ltorch_cpu", "-lc10"]))
+    for src, lib, flags in host_units:
         r = subprocess.run([*cmd, *python, os.path.join(_CSRC, src), "-o", lib, *flags], capture_output=True, text=True)
         if r.returncode != 0:
             raise RuntimeError(f"{cxx} failed on {src}:\n{r.stderr}")

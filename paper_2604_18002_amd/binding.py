@@ -17,7 +17,7 @@ import sys
 from dataclasses import dataclass
 from typing import Optional
 
-from ._build import HOST_LIB_PATH, LIB_PATH, TORCH_LIB_PATH
+from ._build import HOST_LIB_PATH, LIB_PATH, TORCH_LIB_PATH, torch_identity
 
 NGC_OK = 0
 NGC_EINVAL = -1
@@ -149,18 +149,19 @@ def load_library(path: Optional[str] = None) -> C.CDLL:
         from . import _ngc_host
         _ngc_host.open(path)
         _ngc_host.types(ArgumentError, Cache, PagedCache, ngc_cache, ngc_paged_cache, ngc_evict_params, C._SimpleCData)
-        if "torch" in sys.modules:
-            _read_tensors_directly(_ngc_host)
+        _read_tensors_directly(_ngc_host)
         _host = _ngc_host
         _lib = lib
     return lib
 
 
-def _read_tensors_directly(host) -> None:
-    """From now on the front reads plain tensors itself (torch has been imported)."""
-    if not os.path.exists(TORCH_LIB_PATH):
-        raise RuntimeError(f"{TORCH_LIB_PATH} is missing: build it first (python -m paper_2604_18002_amd._build)")
-    host.torch_reader(TORCH_LIB_PATH)
+def _read_tensors_directly(host) -> bool:
+    """From now on the front reads plain tensors itself, if torch has been imported and the reader was compiled against
+    this very torch; otherwise it asks the tensors' methods, which takes longer and gives the same."""
+    torch = sys.modules.get("torch")
+    if getattr(torch, "_C", None) is None or not hasattr(torch, "version"):     # (absent, blocked, or still being imported)
+        return False
+    return host.torch_reader(TORCH_LIB_PATH, torch_identity(torch))
 
 
 def _front():

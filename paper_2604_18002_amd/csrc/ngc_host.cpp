@@ -9,6 +9,7 @@
 #include <Python.h>
 #include <dlfcn.h>
 #include <stdint.h>
+#include <string.h>
 
 #include "../../include/ngc.h"
 #include "ngc_torch.h"
@@ -33,7 +34,7 @@ struct Names {
         *numel, *is_contiguous, *view, *value;
 } names;
 
-// reads plain tensors directly; null until torch_reader() (torch may be imported later, or never)
+// reads plain tensors directly; null until torch_reader() (torch may be imported later, or never) and without a reader that fits
 ngc_read_tensor_fn read_tensor = nullptr;
 // what stream_readers() was given: the current device, and the raw stream of a device
 PyObject *device_of = nullptr, *stream_of = nullptr;
@@ -363,18 +364,24 @@ PyObject *open_(PyObject *, PyObject *path)
     Py_RETURN_NONE;
 }
 
-// torch_reader(path): plain tensors are read by this library from now on (torch has been imported).
-PyObject *torch_reader(PyObject *, PyObject *path)
-{
-    const char *p = PyUnicode_AsUTF8(path);
-    if (!p) return nullptr;
-    void *h = dlopen(p, RTLD_NOW | RTLD_LOCAL);
-    if (!h) return PyErr_Format(PyExc_RuntimeError, "%s", dlerror());
+// torch_reader(path, identity) -> whether plain tensors are read by this library from now on.  Not if it cannot be loaded or
+// was compiled against another torch than the one that has been imported, `identity`: then all tensors go by their methods.
+ENTRY(torch_reader, 2)
+    const char *path = PyUnicode_AsUTF8(a[0]);
+    const char *identity = path ? PyUnicode_AsUTF8(a[1]) : nullptr;
+    if (!identity) return nullptr;
+    read_tensor = nullptr;
+    void *h = dlopen(path, RTLD_NOW | RTLD_LOCAL);
+    if (!h) Py_RETURN_FALSE;
+    const auto built_for = reinterpret_cast<ngc_torch_identity_fn>(dlsym(h, "ngc_torch_identity"));
     const auto fn = reinterpret_cast<ngc_read_tensor_fn>(dlsym(h, "ngc_read_tensor"));
-    if (!fn) return PyErr_Format(PyExc_RuntimeError, "%s: no ngc_read_tensor", p);
+    if (!built_for || !fn || strcmp(built_for(), identity) != 0) {
+        dlclose(h);
+        Py_RETURN_FALSE;
+    }
     read_tensor = fn;
-    Py_RETURN_NONE;
-}
+    Py_RETURN_TRUE;
+END
 
 // stream_readers(device, stream): torch's own functions for the current device and a device's current raw stream.
 ENTRY(stream_readers, 2)
@@ -412,7 +419,7 @@ END
 
 #define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(&name##_)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
-    {"open", open_, METH_O, nullptr}, {"torch_reader", torch_reader, METH_O, nullptr},
+    {"open", open_, METH_O, nullptr}, FAST(torch_reader),
     {"current_stream", current_stream, METH_NOARGS, nullptr}, FAST(stream_readers), FAST(types),
     FAST(perturbed_keys), FAST(keep_counts), FAST(evict), FAST(subset_logprob), FAST(subset_logprob_backward), FAST(lmem),
     FAST(cache_append), FAST(decode_attn), FAST(decode_step), FAST(decode_attn_static), FAST(score_keys),

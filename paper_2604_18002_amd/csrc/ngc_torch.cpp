@@ -13,6 +13,8 @@
 
 #include "ngc_torch.h"
 
+extern "C" __attribute__((visibility("default"))) const char *ngc_torch_identity(void) noexcept { return NGC_TORCH_IDENTITY; }
+
 extern "C" __attribute__((visibility("default"))) int ngc_read_tensor(PyObject *o, ngc_tensor *out) noexcept
 {
     try {

@@ -13,3 +13,7 @@ struct ngc_tensor {
 
 // 1: *out is filled.  0: ask the object's methods; no Python error is set.
 typedef int (*ngc_read_tensor_fn)(PyObject *o, ngc_tensor *out);
+
+// The torch that the reader was compiled against, as torch_identity() in _build.py writes it: it reads torch's structures
+// where that one has them, so it serves no other.
+typedef const char *(*ngc_torch_identity_fn)(void);

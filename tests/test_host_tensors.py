@@ -1,6 +1,9 @@
 """What the front reads of a tensor directly is what the tensor's methods say; every other object is left to its methods, and
 a torch error comes out of them as it did (no GPU)."""
 import ctypes as C
+import os
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -8,7 +11,9 @@ from torch._subclasses.fake_tensor import FakeTensorMode
 from torch.overrides import TorchFunctionMode
 
 from paper_2604_18002_amd import binding as ngc
-from paper_2604_18002_amd._build import TORCH_LIB_PATH
+from paper_2604_18002_amd._build import LIB_PATH, TORCH_LIB_PATH, torch_identity
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 class Read(C.Structure):
@@ -90,3 +95,39 @@ def test_stream_readers():
         front.stream_readers(lambda: 1 // 0, lambda device: device)
         front.current_stream()
     ngc._forget_stream_reader()
+
+
+@pytest.fixture
+def front():
+    yield ngc._front()
+    assert ngc._read_tensors_directly(ngc._front())        # the others read directly again
+
+
+@pytest.mark.parametrize("path,identity", [("/nowhere/libngc_torch.so", torch_identity(torch)), (__file__, torch_identity(torch)),
+                                           (LIB_PATH, torch_identity(torch)), (TORCH_LIB_PATH, "2.0.0 another"),
+                                           (TORCH_LIB_PATH, "")], ids=["missing", "no library", "another library", "another torch",
+                                                                       "no torch"])
+def test_without_a_reader_for_this_torch_tensors_go_by_their_methods(front, path, identity, monkeypatch):
+    c = ngc.Cache.allocate(1, 1, 2, 8, 64, 32, device="cpu")
+    q, out = torch.zeros(1, 8, 64, dtype=torch.bfloat16), torch.zeros(1, 8, 64)
+    ws = torch.zeros(16, dtype=torch.uint8)
+    asked = []
+    monkeypatch.setattr(torch.Tensor, "data_ptr", lambda t, own=torch.Tensor.data_ptr: (asked.append(1), own(t))[1])
+
+    def call():
+        asked.clear()
+        with pytest.raises(ngc.NgcError) as e:
+            ngc.ngc_decode_attn(c, 0, q, 0.1, 0, out, ws, stream=0)
+        assert e.value.code == ngc.NGC_ENOSPC             # all pointers and sizes were read: it is the workspace that falls short
+        return len(asked)
+    assert front.torch_reader(TORCH_LIB_PATH, torch_identity(torch)) and call() == 0
+    assert front.torch_reader(path, identity) is False and call() > 0
+
+
+@pytest.mark.parametrize("before", ["", "import sys; sys.modules['torch'] = None",
+                                    "import sys, types; sys.modules['torch'] = types.ModuleType('torch')",
+                                    "import torch; import paper_2604_18002_amd._build as b; b.TORCH_LIB_PATH += '.gone'"])
+def test_the_library_loads_without_torch_and_without_its_reader(before):
+    code = f"{before}\nimport paper_2604_18002_amd.binding as ngc\nngc.load_library(); print(ngc._front() is not None)"
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT)
+    assert r.returncode == 0 and r.stdout.strip() == "True", r.stderr
