@@ -374,9 +374,7 @@ int ngc_decode_attn_static(const ngc_cache *c, int32_t layer, const void *q, flo
  *               layout ngc_evict takes as logits.  Entries past the item count
  *               are unspecified.
  * Limit: w * (Hq/Hkv) <= 64 (NGC_EUNSUPPORTED beyond).
- * ws needs NGC_STATUS_WORDS * 4 bytes (status).  Without lse_recent, and with
- * the bytes that ngc_workspace_bytes() asks for, up to 128 segments are shared
- * among workgroups, whose partial sums stand there as decode attention's do. */
+ * ws needs NGC_STATUS_WORDS * 4 bytes (status only). */
 #define NGC_SCORE_NO_CAUSAL  1u
 #define NGC_SCORE_POOL_HEADS 2u
 int ngc_score_keys(const ngc_cache *c, int32_t layer, const void *q_recent,

@@ -35,7 +35,8 @@ struct ScoreArgs {
     int32_t *status;
     int seg0, nseg, lb0;
     int S;                    // workgroups per segment (1 for SCORE_BOTH) ...
-    int share_rows;           // ... of at least so many rows; shorter ones are left to their first
+    int share_rows;           // ... of at least so many rows; shorter ones are left to their first (SCORE_FIRST, SCORE_SECOND:
+                              // as many of them as shares_of() says)
     int w, G, Hkv, cap, causal;
     float scale_log2e;
     // paged layout: k is the pool and a tile's base comes from the page table
@@ -43,13 +44,47 @@ struct ScoreArgs {
     int max_pages, num_pages, tpp_shift;
     int block;                // a multiple of SC_TILE (TILES): tile t leaves the sum of its keys, their mean if the block is
                               // one tile, at psi[t]
-    f32x2 *parts;             // SCORE_FIRST, SCORE_SECOND: [segment of the launch][share][w * G]: maximum and sum of a query row
 };
+
+// Where the shares of a segment leave their maxima and sums between the two launches: in the segment's own row of the scores,
+// below its length, where every entry is either written again by the second launch or past the items.  (The workspace
+// has no room to give: a call may bring the status words alone, or the workspace of another cache, whose tickets have to
+// stay zero.)  Tiles' values end at the number of tiles, so one copy of all shares' parts fits behind them.  With a value
+// per key a share reads its copy from the entries that itself will overwrite, so every share writes one for each of them:
+// word e of the copy of share x stands in the e / 128-th of the rounds of 128 keys that x owns.
+constexpr int SC_ROUND = SC_WAVES * SC_TILE;
+
+template <bool TILES>
+__host__ __device__ __forceinline__ bool parts_fit(int n, int shares, int R)
+{
+    const int words = 2 * R * shares;
+    if (TILES) return words <= n - (n + SC_TILE - 1) / SC_TILE;
+    return shares * ((words + SC_ROUND - 1) / SC_ROUND) * SC_ROUND <= n;
+}
+
+// The shares of a segment of n rows, `most` if their parts fit.  One: it leaves no parts, and its first workgroup does all
+// of it in the first launch.
+template <bool TILES>
+__host__ __device__ __forceinline__ int shares_of(int n, int most, int R)
+{
+    const int rounds = TILES ? (n + SC_ROUND - 1) / SC_ROUND : n / SC_ROUND;      // (each share has a round)
+    int shares = most < rounds ? most : rounds;
+    while (shares > 1 && !parts_fit<TILES>(n, shares, R)) --shares;
+    return shares > 1 ? shares : 1;
+}
+
+template <bool TILES>
+__device__ __forceinline__ int part_at(int n, int shares, int reader, int word)
+{
+    if (TILES) return (n + SC_TILE - 1) / SC_TILE + word;
+    return (word / SC_ROUND * shares + reader) * SC_ROUND + word % SC_ROUND;
+}
 
 // Up to three query tiles the kernel fits 168 registers per thread without spilling, i.e. three waves per SIMD
 // (three workgroups per CU) instead of the two the compiler settles for by itself; with four tiles it does not.
 // MODE: the normalisers are given (lse), one pass; both passes; or the two passes as launches of their own, which the
-// workgroups of a segment share: the first leaves every share's maximum and sum of each query row, the second merges them.
+// workgroups of a segment share: the first leaves every share's maximum and sum of each query row, the second merges them;
+// segments of one share are done by the first alone.
 // TILES: `block` is a multiple of a tile, and a tile leaves one value (their own kernels: the choice at run time costs the
 // others four registers and with them a workgroup per CU).
 enum { SCORE_GIVEN, SCORE_BOTH, SCORE_FIRST, SCORE_SECOND };
@@ -113,7 +148,8 @@ void score_keys_kernel(ScoreArgs a)
         if (!SECOND && threadIdx.x == 0 && share == 0) atomicAdd(&a.status[NGC_STATUS_LEN_CLAMPED], 1);
         n = n < 0 ? 0 : a.cap;
     }
-    const int shares = n < a.share_rows ? 1 : a.S;
+    const int shares = FIRST || SECOND ? shares_of<TILES>(n, a.S, R) : n < a.share_rows ? 1 : a.S;
+    if (SECOND && shares == 1) return;
     const int tile_step = shares * WAVES;
     if (share >= shares || first_tile * SC_TILE >= n) return;
     const unsigned char *kseg = a.table ? a.k : a.k + (size_t)seg * a.cap * ROW_BYTES;
@@ -170,8 +206,6 @@ void score_keys_kernel(ScoreArgs a)
         // four threads a row, each with every fourth share
         static_assert(WAVES == 4 && QT <= 4, "up to 64 query rows");
         const int r = threadIdx.x >> 2;
-        const int used = (tiles + WAVES - 1) / WAVES < a.S ? (tiles + WAVES - 1) / WAVES : a.S;
-        const f32x2 *part = a.parts + (size_t)(seg - a.seg0) * a.S * R + r;
         float M = -INFINITY, L = 0.f;
         if (r < R) {
             f32x2 own[MOST_SHARES / 4];
@@ -179,7 +213,10 @@ void score_keys_kernel(ScoreArgs a)
             for (int i = 0; i < MOST_SHARES / 4; ++i) {
                 const int x = 4 * i + (threadIdx.x & 3);
                 own[i] = f32x2{-INFINITY, 0.f};
-                if (x < used) own[i] = part[(size_t)x * R];
+                if (x < shares) {
+                    const float *part = psi + part_at<TILES>(n, shares, share, 2 * (x * R + r));
+                    own[i] = f32x2{part[0], part[1]};
+                }
             }
 #pragma unroll
             for (int i = 0; i < MOST_SHARES / 4; ++i) M = fmaxf(M, own[i][0]);
@@ -272,12 +309,17 @@ void score_keys_kernel(ScoreArgs a)
             L += (mw == -INFINITY) ? 0.f : red_l[x][r] * fast_exp2(mw - M);
         }
         if constexpr (FIRST) {
-            if (r < R) a.parts[((size_t)(seg - a.seg0) * a.S + share) * R + r] = f32x2{M, L};
+            if (shares > 1 && r < R)
+                for (int x = 0; x < (TILES ? 1 : shares); ++x) {
+                    float *part = psi + part_at<TILES>(n, shares, x, 2 * (share * R + r));
+                    part[0] = M;
+                    part[1] = L;
+                }
         }
         fin_m[r] = M;
         fin_il[r] = (L > 0.f) ? 1.0f / L : 0.f;
     }
-    if constexpr (FIRST) return;
+    if (FIRST && shares > 1) return;
     __syncthreads();
     }
 
@@ -464,13 +506,6 @@ namespace {
 // leaves before it asks for anything else (640 x 100-300 in a capacity of 4096 9.8, 10.4 before there was one).
 constexpr int SHARE_ROWS = 2048;
 
-// Where a workspace's scratch begins: behind the status words and the tickets of decode attention (which stay zero).
-size_t score_parts_offset(const ngc_cache *c)
-{
-    const size_t tickets = (size_t)c->L * c->B * c->Hkv * 12;
-    return (NGC_STATUS_WORDS * sizeof(int32_t) + tickets + 255) & ~(size_t)255;
-}
-
 struct Shares {
     int S, rows;
 };
@@ -486,9 +521,9 @@ Shares score_shares(int nseg, int cap, int D, bool have_lse)
 }
 
 // Workgroups per segment where the normalisers are not given: the two passes as two launches, two workgroups per CU in all,
-// a share's maxima and sums in the workspace (if it has the room that decode attention's partials take, and the segments four
-// shares or more); otherwise, up to a workgroup per CU, one with eight waves.  Microseconds (D = 128, 6 heads per KV head, w
-// queries) of one workgroup of four waves, of eight, and of two launches with S shares:
+// if the capacity has room for the parts of four shares or more; otherwise, up to a workgroup per CU, one with eight waves.
+// Microseconds (D = 128, 6 heads per KV head, w queries) of one workgroup of four waves, of eight, and of two launches
+// with S shares (measured with the parts in memory of their own, where any number fits):
 //     segments x keys, w     4      8     S=2    S=4    S=8    S=16   S=32
 //         8 x  500, 3      10.6    9.0   10.7    8.8    8.4
 //         8 x 3000, 3      43.6   30.6   26.0   16.7   11.5   10.1    9.0
@@ -502,12 +537,11 @@ Shares score_shares(int nseg, int cap, int D, bool have_lse)
 // (16 waves spill with two query tiles.)
 constexpr int MORE_WAVES_SEGMENTS = 256;
 
-int passes_shares(int nseg, int cap)
+int passes_shares(int nseg, int cap, int R, bool tiles)
 {
-    const int rounds = (cap + SC_TILE * SC_WAVES - 1) / (SC_TILE * SC_WAVES);
     int S = 512 / nseg;
-    if (S > rounds) S = rounds;
     if (S > MOST_SHARES) S = MOST_SHARES;
+    S = tiles ? shares_of<true>(cap, S, R) : shares_of<false>(cap, S, R);
     return S >= 4 ? S : 1;
 }
 
@@ -541,22 +575,15 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     sa.status = reinterpret_cast<int32_t *>(ws);
     sa.seg0 = seg0; sa.nseg = nseg;
     Shares shares = score_shares(nseg, c->cap, c->D, lse_recent != nullptr);   // nseg * S <= max(nseg, 1280)
-    sa.parts = nullptr;
-    if (!lse_recent) {
-        const int S = passes_shares(nseg, c->cap);
-        const size_t parts_at = score_parts_offset(c), parts_bytes = (size_t)nseg * S * R * sizeof(f32x2);
-        if (S > 1 && (reinterpret_cast<uintptr_t>(ws) & 7) == 0 && ws_bytes >= parts_at + parts_bytes) {
-            shares = {S, 0};
-            sa.parts = reinterpret_cast<f32x2 *>(reinterpret_cast<unsigned char *>(ws) + parts_at);
-        }
-    }
-    const bool more_waves = !lse_recent && !sa.parts && nseg <= MORE_WAVES_SEGMENTS;
+    const bool tiles = block % SC_TILE == 0;
+    if (!lse_recent) shares = {passes_shares(nseg, c->cap, R, tiles), 0};
+    const bool two_passes = !lse_recent && shares.S > 1;
+    const bool more_waves = !lse_recent && !two_passes && nseg <= MORE_WAVES_SEGMENTS;
     sa.S = shares.S;
     sa.share_rows = shares.rows;
     sa.lb0 = layer < 0 ? 0 : layer * c->B;
     sa.w = w; sa.G = G; sa.Hkv = c->Hkv; sa.cap = c->cap;
     sa.causal = (flags & NGC_SCORE_NO_CAUSAL) ? 0 : 1;
-    const bool tiles = block % SC_TILE == 0;
     sa.block = block;
     sa.scale_log2e = scale * 1.4426950408889634f;
     sa.table = nullptr; sa.max_pages = 0; sa.num_pages = 0; sa.tpp_shift = 0;
@@ -575,10 +602,11 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
                : reinterpret_cast<const void *>(&score_keys_kernel<DD, 4, __VA_ARGS__>))
 #define NGC_PICK_GIVEN(DD, TILES) \
     (lse_recent ? NGC_PICK_QT(DD, SCORE_GIVEN, TILES) \
-     : sa.parts ? NGC_PICK_QT(DD, SCORE_SECOND, TILES) \
+     : two_passes ? NGC_PICK_QT(DD, SCORE_SECOND, TILES) \
      : more_waves ? NGC_PICK_QT(DD, SCORE_BOTH, TILES, 2 * SC_WAVES) : NGC_PICK_QT(DD, SCORE_BOTH, TILES))
-    if (sa.parts) {
-        const void *first = c->D == 128 ? NGC_PICK_QT(128, SCORE_FIRST, false) : NGC_PICK_QT(64, SCORE_FIRST, false);
+    if (two_passes) {
+        const void *first = c->D == 128 ? (tiles ? NGC_PICK_QT(128, SCORE_FIRST, true) : NGC_PICK_QT(128, SCORE_FIRST, false))
+                                        : (tiles ? NGC_PICK_QT(64, SCORE_FIRST, true) : NGC_PICK_QT(64, SCORE_FIRST, false));
         const int rc = launch(first, dim3((unsigned)(nseg * sa.S)), dim3(SC_WAVES * 64), 0, st, sa);
         if (rc) return rc;
     }
