@@ -521,24 +521,26 @@ Shares score_shares(int nseg, int cap, int D, bool have_lse)
 }
 
 // Workgroups per segment where the normalisers are not given: the two passes as two launches, two workgroups per CU in all,
-// if the capacity has room for the parts of four shares or more; otherwise, up to a workgroup per CU, one with eight waves.
-// Microseconds (D = 128, 6 heads per KV head, w queries) of one workgroup of four waves, of eight, and of two launches
-// with S shares (measured with the parts in memory of their own, where any number fits):
-//     segments x keys, w     4      8     S=2    S=4    S=8    S=16   S=32
-//         8 x  500, 3      10.6    9.0   10.7    8.8    8.4
-//         8 x 3000, 3      43.6   30.6   26.0   16.7   11.5   10.1    9.0
-//        32 x  700, 3      14.3   11.6   12.0   10.6    9.0
-//        64 x  500, 5      10.8    9.8   10.7    9.2   10.2
-//        64 x 3000, 3      49.6   36.8   30.1   20.0   18.2   23.1   25.1
-//       160 x  447, 1      13.4   12.2   15.2   14.2
-//       160 x 3000, 3      56.4   42.9
-//       256 x 3000, 3      65.1   59.1
-//       512 x 3000, 3     120.3  122.3
-// (16 waves spill with two query tiles.)
+// where the capacity has room for the parts of four shares or more and is PASSES_ROWS or more; otherwise, up to a workgroup
+// per CU, one with eight waves.  Microseconds (D = 128, 6 heads per KV head, w = 3) of one workgroup of four waves, of
+// eight, and of two launches, lengths of the capacity:
+//     segments     512           1024              2048              3000              8000 keys
+//            8  10.7  9.1    17.5 13.8 10.0    30.7 22.4 12.1    45.0 32.6 14.4     119   84  17.6
+//           32  10.9  9.4    17.7 14.0 10.6    35.3 26.7 14.4    50.7 37.0 16.8     127   89  25.1
+//           64  12.3 10.5    18.5 14.9 11.1    35.9 26.9 16.6    52.3 38.2 20.4     131   93  44.6
+//          128  12.9 11.1    20.8 16.8 15.6    38.1 29.1 24.8    55.9 42.0 34.6     139  102  85.7
+//          160  13.1 11.2                      4096: 74.9 57.0;  256: 85.2 78.8;  512 x 3000 120 122
+// The host does not know the lengths.  Far below the capacity the second launch only costs, 100 keys in 4096: 8 segments 5.6
+// and 7.4, 64 5.7 and 8.6; 300 in 2048: 8.9, 8.0 (eight waves) and 11.0; 512 in 1024: 64 segments 10.7, 9.4 and 10.1, 128 11.6,
+// 10.3 and 11.9.  So the capacities are those from which half of them still gains, and eight waves start beyond the rows that
+// four have a tile or two each for (256 keys: 7.3 and 7.1, 100 keys 5.6 and 6.2).  (16 waves spill with two query tiles.)
 constexpr int MORE_WAVES_SEGMENTS = 256;
+constexpr int MORE_WAVES_ROWS = 2 * SC_ROUND;        // (more than so many)
+constexpr int PASSES_ROWS = 1024;                    // ... up to 64 segments, twice that beyond
 
 int passes_shares(int nseg, int cap, int R, bool tiles)
 {
+    if (cap < (nseg <= 64 ? PASSES_ROWS : 2 * PASSES_ROWS)) return 1;
     int S = 512 / nseg;
     if (S > MOST_SHARES) S = MOST_SHARES;
     S = tiles ? shares_of<true>(cap, S, R) : shares_of<false>(cap, S, R);
@@ -578,7 +580,7 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     const bool tiles = block % SC_TILE == 0;
     if (!lse_recent) shares = {passes_shares(nseg, c->cap, R, tiles), 0};
     const bool two_passes = !lse_recent && shares.S > 1;
-    const bool more_waves = !lse_recent && !two_passes && nseg <= MORE_WAVES_SEGMENTS;
+    const bool more_waves = !lse_recent && !two_passes && nseg <= MORE_WAVES_SEGMENTS && c->cap > MORE_WAVES_ROWS;
     sa.S = shares.S;
     sa.share_rows = shares.rows;
     sa.lb0 = layer < 0 ? 0 : layer * c->B;

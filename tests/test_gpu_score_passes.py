@@ -1,6 +1,6 @@
 """Key scores without normalisers: the two passes as launches that the workgroups of a segment share, at segments around a
-share of 128 keys and shorter than their shares, and the single launches (eight waves, four) where the workspace holds
-nothing but the status words, the segments are many or short.  Against fp64 attention on the CPU: 2e-4 relative plus 1e-9
+share of 128 keys and shorter than their shares, and the single launches (eight waves, four) where the segments are many or
+the capacity is small; with a whole workspace and with one of the status words alone.  Against fp64 attention on the CPU: 2e-4 relative plus 1e-9
 (means of probabilities, each an exponential of an fp32 sum)."""
 import pytest
 
@@ -42,7 +42,7 @@ def test_two_passes(B, cap, w, G, D, block):
                     want = torch.stack([x.mean() for x in want.split(block)])
                 x = got[0, b, h, :want.numel()]
                 assert (x - want).abs().le(2e-4 * want + 1e-9).all(), (b, h, (x - want).abs().max())
-    # the tickets of decode attention, which the scratch follows, are as they were
+    # the tickets of decode attention are as they were
     assert int(full[:ngc.STATUS_WORDS * 4 + B * H * 12].count_nonzero()) == 0
 
 
