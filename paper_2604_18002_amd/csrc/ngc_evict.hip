@@ -968,14 +968,21 @@ __device__ __forceinline__ void compact_pos_inplace(int32_t *pos, const int32_t 
 // the chip has as many workgroups to hide it as there are (layer, sequence) pairs.  Where LDS has room for a code and a
 // bucket entry per item (about 17000), they are ranked by value buckets as in the per-head mode, every head's items filled
 // up to a multiple of four so that a thread's four codes stay one access.  Beyond, and where ranking does not apply
-// (masked items kept, many equal keys, a wide spread, no sequence wanted), pooled_general() selects by radix: up to
-// Hkv * cap = 65536 items, their codes in a workspace in global memory.
+// (masked items kept, many equal keys, a wide spread, no sequence wanted), pooled_general() selects by radix, from the codes
+// in LDS if they are there; otherwise up to Hkv * cap = 65536 items, their codes in a workspace in global memory.
 // The rows are moved by the same workgroup or, for few sequences, by a launch of one workgroup per head (see ngc_evict).
 // Rounds of half the rows, us, before (radix always, one launch) and now:
 //     sequences x heads x rows   16 x 2 x 500     16 x 8 x 300     16 x 8 x 2000   64 x 4 x 1500   128 x 2 x 4000
 //                                25.9   18.1      53.7   24.7     217.5  100.0    103.3   67.5    144.8  134.1
 //                              256 x 2 x 4000  448 x 4 x 500    896 x 4 x 1500   896 x 8 x 300
 //                               240.3  225.6    128.7  107.0     618.0  564.1    335.9  250.4
+// Selections that are not ranked, us, before ranking was tried, with keys made again after it, and from the codes in LDS
+// (logits in steps of 1/8 at tau = 0; all equal; two thirds masked, some of them kept; a spread of 400):
+//     sequences x heads x rows   quantised            equal                masked               spread
+//               16 x 8 x  300     39.7  43.9  38.4    26.0  29.1  23.8    45.0  51.0  38.7     43.1  48.2  36.6
+//               16 x 8 x 2000    125   137   127      90.0  97.5  82.8   137   159   138      104   124   103
+//              128 x 2 x 4000     65.5  72.8  67.2    45.8  50.0  41.7    69.8  82.0  71.5     54.8  65.2  54.4
+//              896 x 8 x  300    161   117   100     101    82.8  67.6   180   140   102      174   122    85.7
 
 constexpr int POOL_MAX_HEADS = 16;
 constexpr int POOL_FEW = 128;            // (layer, sequence) pairs up to which the rows take a second launch
@@ -989,13 +996,23 @@ constexpr int PM_QUAD = 90;   // groups of four items before each head, every he
 constexpr int PM_WORDS = 128;
 constexpr int PM_MAXIMA = 64; // behind misc, where items are ranked: four words a wave
 
-// Selection by radix.  The codes of all items are read in order by the select passes; the kept items' codes, logits and
-// item indices stand in three dense arrays next to them (K entries each, served by the L2 cache to the sort and to the
-// log-probability), the index buffers of the sort in LDS.  Writes the kept lists, sigma and its log-probability, and
+// What the attempt at ranking has made: the codes in LDS (null: nothing yet), groups of four over all heads, 0 where a head's
+// last one is filled up; the largest code and logit (0: all masked), and whether the logits span more than NGC_WIDE_SPREAD.
+struct PooledKeys {
+    const uint32_t *code;
+    uint32_t cmax;
+    float smax;
+    bool wide;
+};
+
+// Selection by radix.  The codes of all items are read in order by the select passes, from LDS if they have been made there
+// (an item's index then counts the filled-up places too); the kept items' codes, logits and
+// item indices stand in three dense arrays next to those in memory (K entries each, served by the L2 cache to the sort and to
+// the log-probability), the index buffers of the sort in LDS.  Writes the kept lists, sigma and its log-probability, and
 // leaves the kept slots before each head in misc.
 template <int THREADS>
-__device__ void pooled_general(const SelectArgs &a, int seg_first, int l, int b, int N, int K, uint32_t *hist, int *misc,
-                               uint16_t *idxA, uint16_t *idxB)
+__device__ void pooled_general(const SelectArgs &a, int seg_first, int l, int b, int N, int K, const PooledKeys &keys,
+                               uint32_t *hist, int *misc, uint16_t *idxA, uint16_t *idxB)
 {
     constexpr int NW = THREADS / NGC_WAVE;
     const int tid = threadIdx.x, lane = lane_id(), wv = wave_id();
@@ -1015,40 +1032,63 @@ __device__ void pooled_general(const SelectArgs &a, int seg_first, int l, int b,
     };
 
     // ---- 1. keys (and the first histogram of the radix select) -------------
+    const bool in_lds = keys.code != nullptr;
+    if (in_lds) {
+        N = 4 * misc[PM_QUAD + Hkv];
+        if (tid <= Hkv) misc[PM_OFF + tid] = 4 * misc[PM_QUAD + tid];
+    }
     for (int i = tid; i < SEL_BINS; i += THREADS) hist[i] = 0;
     __syncthreads();
-    float smax = -INFINITY, neg_smin = -INFINITY;   // over the unmasked entries
-    uint32_t cmax = 0;
-    for (int h = 0; h < Hkv; ++h) {
-        const int n = misc[PM_N + h], off = misc[PM_OFF + h];
-        const float *row = a.logits + (size_t)(seg_first + h) * cap;
-        for (int quad = tid; 4 * quad < n; quad += THREADS) {
-            float s[4], key[4];
-            keys_of_quad(row, n, quad, a.na, l, b, h, s, key);
+    float smax = keys.smax;
+    uint32_t cmax = keys.cmax;
+    bool wide = keys.wide;   // logits spanning more than NGC_WIDE_SPREAD: wide-range arithmetic for Eq. 2
+    if (in_lds) {
+        for (int q = tid; 4 * q < N; q += THREADS) {
+            const u32x4 c = reinterpret_cast<const u32x4 *>(keys.code)[q];
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                if (4 * quad + i < n) {
-                    const uint32_t c = ordered_code(key[i]);
-                    code[off + 4 * quad + i] = c;
-                    atomicAdd(&hist[c >> 21], 1u);
-                    cmax = c > cmax ? c : cmax;
-                    smax = fmaxf(smax, s[i]);
-                    if (s[i] > -INFINITY) neg_smin = fmaxf(neg_smin, -s[i]);
+                if (c[i] != 0u) {
+                    // what comes here has many equal codes, masked ones or others: the bin of the first lane's is added to at
+                    // once (8 heads of 2000 equal keys 93.7 -> 82.3 us)
+                    const uint32_t bin = c[i] >> 21;
+                    const uint64_t same = __ballot(bin == (uint32_t)__builtin_amdgcn_readfirstlane((int)bin));
+                    const bool in = (same >> lane) & 1u;
+                    if (!in || popc_below(same) == 0) atomicAdd(&hist[bin], in ? (uint32_t)__popcll(same) : 1u);
                 }
         }
+    } else {
+        float neg_smin = -INFINITY;   // over the unmasked entries, as smax
+        for (int h = 0; h < Hkv; ++h) {
+            const int n = misc[PM_N + h], off = misc[PM_OFF + h];
+            const float *row = a.logits + (size_t)(seg_first + h) * cap;
+            for (int quad = tid; 4 * quad < n; quad += THREADS) {
+                float s[4], key[4];
+                keys_of_quad(row, n, quad, a.na, l, b, h, s, key);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (4 * quad + i < n) {
+                        const uint32_t c = ordered_code(key[i]);
+                        code[off + 4 * quad + i] = c;
+                        atomicAdd(&hist[c >> 21], 1u);
+                        cmax = c > cmax ? c : cmax;
+                        smax = fmaxf(smax, s[i]);
+                        if (s[i] > -INFINITY) neg_smin = fmaxf(neg_smin, -s[i]);
+                    }
+            }
+        }
+        if (want_logp) {
+            block_max2_f<THREADS>(smax, neg_smin, fmisc);
+            wide = smax > -INFINITY && smax + neg_smin > NGC_WIDE_SPREAD;
+            if (smax == -INFINITY) smax = 0.f;
+        }
+        if (want_sort) cmax = block_max_u<THREADS>(cmax, reinterpret_cast<uint32_t *>(misc));
     }
-    bool wide = false;   // logits spanning more than NGC_WIDE_SPREAD: wide-range arithmetic for Eq. 2
-    if (want_logp) {
-        block_max2_f<THREADS>(smax, neg_smin, fmisc);
-        wide = smax > -INFINITY && smax + neg_smin > NGC_WIDE_SPREAD;
-        if (smax == -INFINITY) smax = 0.f;
-    }
-    if (want_sort) cmax = block_max_u<THREADS>(cmax, reinterpret_cast<uint32_t *>(misc));
+    auto code_at = [&](int t) { return in_lds ? keys.code[t] : code[t]; };
 
     // ---- 2. radix select (the first histogram was accumulated with the keys) --
     int need;
     __syncthreads();   // publishes the codes and the histogram of step 1
-    const uint32_t thr = radix_select_kth<THREADS>([&](int t) { return code[t]; }, N, K, hist, misc, need, true);
+    const uint32_t thr = radix_select_kth<THREADS>(code_at, N, K, hist, misc, need, true);
 
     // ---- 3. kept items, ascending in (head, row) order ----------------------
     // Slot j of the kept list gets its item index (items[j]) and its code (kcode[j]) in two dense arrays next to
@@ -1061,9 +1101,9 @@ __device__ void pooled_general(const SelectArgs &a, int seg_first, int l, int b,
         int gt = 0, eq = 0;
         for (int t0 = w_begin; t0 < w_end; t0 += NGC_WAVE) {
             const int t = t0 + lane;
-            const uint32_t u = (t < w_end) ? code[t] : 0u;
-            gt += __popcll(__ballot(t < w_end && u > thr));
-            eq += __popcll(__ballot(t < w_end && u == thr));
+            const uint32_t u = (t < w_end) ? code_at(t) : 0u;
+            gt += __popcll(__ballot(u > thr));             // (a kept item's code is never 0)
+            eq += __popcll(__ballot(u == thr));
         }
         if (lane == 0) { misc[wv] = gt; misc[16 + wv] = eq; }
     }
@@ -1074,9 +1114,9 @@ __device__ void pooled_general(const SelectArgs &a, int seg_first, int l, int b,
     LogSum unpicked_w = ls_empty();
     for (int t0 = w_begin; t0 < w_end; t0 += NGC_WAVE) {
         const int t = t0 + lane;
-        const bool in = t < w_end;
-        const uint32_t u = in ? code[t] : 0u;
-        const bool is_gt = in && u > thr, is_eq = in && u == thr;
+        const uint32_t u = t < w_end ? code_at(t) : 0u;
+        const bool in = u != 0u;
+        const bool is_gt = u > thr, is_eq = u == thr;
         const uint64_t bgt = __ballot(is_gt), beq = __ballot(is_eq);
         const int gt_before = gt_base + popc_below(bgt);
         const int eq_before = eq_base + popc_below(beq);
@@ -1247,11 +1287,13 @@ __global__ __launch_bounds__(THREADS) void evict_pooled_kernel(SelectArgs a)
     };
     bool ranked = false;
     float unpicked = 0.f, smax = -INFINITY;
+    PooledKeys keys{nullptr, 0u, -INFINITY, false};
     if (want_sort && 4 * quads <= a.rank_cap) {
         for (int i = tid; i < HIST / 4; i += THREADS) reinterpret_cast<u32x4 *>(hist)[i] = u32x4{0u, 0u, 0u, 0u};
         for (int i = tid; i < (4 * quads + 63) / 64 * 2; i += THREADS) kept_bits[i] = 0;
         float neg_smin = -INFINITY;
         uint32_t cmax = 0, neg_cmin = 0;
+        int unmasked = 0;
         constexpr int HELD = 2;      // groups of four logits a thread keeps until the kept items are known
         f32x4 held[HELD] = {};
         int group = 0;
@@ -1268,6 +1310,7 @@ __global__ __launch_bounds__(THREADS) void evict_pooled_kernel(SelectArgs a)
                 c[i] = 4 * quad + i < n ? ordered_code(key[i]) : 0u;          // (0: below every masked item)
                 cmax = c[i] > cmax ? c[i] : cmax;
                 if (c[i] > CODE_MASKED) neg_cmin = ~c[i] > neg_cmin ? ~c[i] : neg_cmin;
+                unmasked += c[i] > CODE_MASKED;
                 smax = fmaxf(smax, x[i]);
                 if (x[i] > -INFINITY) neg_smin = fmaxf(neg_smin, -x[i]);
             }
@@ -1277,17 +1320,24 @@ __global__ __launch_bounds__(THREADS) void evict_pooled_kernel(SelectArgs a)
         neg_smin = wave_max_f(neg_smin);
         cmax = wave_reduce(cmax, OpMaxU{});
         neg_cmin = wave_reduce(neg_cmin, OpMaxU{});
-        if (lane == 0) maxima[wv] = u32x4{__float_as_uint(smax), __float_as_uint(neg_smin), cmax, neg_cmin};
+        unmasked = wave_reduce(unmasked, OpAdd{});
+        if (lane == 0) {
+            maxima[wv] = u32x4{__float_as_uint(smax), __float_as_uint(neg_smin), cmax, neg_cmin};
+            misc[wv] = unmasked;
+        }
         __syncthreads();
         const u32x4 m = maxima[lane & (NW - 1)];
         smax = lanes_reduce<NW>(__uint_as_float(m[0]), OpMaxF{});
         neg_smin = lanes_reduce<NW>(__uint_as_float(m[1]), OpMaxF{});
         cmax = lanes_reduce<NW>(m[2], OpMaxU{});
         neg_cmin = lanes_reduce<NW>(m[3], OpMaxU{});
+        unmasked = lanes_reduce<NW>(misc[lane & (NW - 1)], OpAdd{});
         const bool spread = want_logp && smax > -INFINITY && smax + neg_smin > NGC_WIDE_SPREAD;
         if (smax == -INFINITY) smax = 0.f;
-        ranked = !spread && rank_items<THREADS>(rank_code, 4 * quads, K, cmax, ~neg_cmin, hist,
-                                                reinterpret_cast<uint32_t *>(misc), idxB, idxA, kept_bits);
+        keys = PooledKeys{rank_code, cmax, smax, spread};
+        ranked = !spread && K <= __builtin_amdgcn_readfirstlane(unmasked) &&
+                 rank_items<THREADS>(rank_code, 4 * quads, K, cmax, ~neg_cmin, hist, reinterpret_cast<uint32_t *>(misc), idxB, idxA,
+                                     kept_bits);
         if (ranked) {
             // kept slots before each head
             for (int h = wv; h <= Hkv; h += NW) {
@@ -1348,7 +1398,7 @@ __global__ __launch_bounds__(THREADS) void evict_pooled_kernel(SelectArgs a)
             }
         }
     }
-    if (!ranked) pooled_general<THREADS>(a, seg_first, l, b, N, K, hist, misc, idxA, idxB);
+    if (!ranked) pooled_general<THREADS>(a, seg_first, l, b, N, K, keys, hist, misc, idxA, idxB);
     if (tid < Hkv) {
         const int kept = misc[PM_BASE + tid + 1] - misc[PM_BASE + tid];
         if (kept > a.max_keep) atomicAdd(&a.status[NGC_STATUS_KEEP_CLAMPED], 1);
