@@ -748,8 +748,10 @@ int static_limit_splits(int nseg_launch, int max_len, int row_bytes)
 // `fixed_layout`: the scratch is not a workspace sized for this cache but the library's own fixed array, which
 // serves caches of any geometry one after the other: tickets and partials then sit at offsets that do not depend
 // on the geometry (a ticket region that moved with the geometry would land on an earlier call's partials).
-constexpr size_t FIXED_TICKET_OFFSET = STATUS_BYTES;      // COMPUTE_UNITS tickets: only launches of at most
-constexpr size_t FIXED_PARTIAL_OFFSET = 4096;             // COMPUTE_UNITS / 2 segments are ever split
+// All words between the two offsets are tickets, ticket_step() apart, and zero between launches: they outnumber the
+// COMPUTE_UNITS / 2 segments that a launch can have and still be split.
+constexpr size_t FIXED_TICKET_OFFSET = STATUS_BYTES;
+constexpr size_t FIXED_PARTIAL_OFFSET = 4096;
 constexpr size_t FIXED_TICKETS = (FIXED_PARTIAL_OFFSET - FIXED_TICKET_OFFSET) / sizeof(int32_t);
 
 // Words between the tickets of two segments.  Atomics on one cache line are served one after the other, so a launch's

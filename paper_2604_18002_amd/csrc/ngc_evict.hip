@@ -966,10 +966,11 @@ __device__ __forceinline__ void compact_pos_inplace(int32_t *pos, const int32_t 
 //
 // What bounds it: one workgroup selects for all heads of a sequence, a chain of waits as long as its items are many, and
 // the chip has as many workgroups to hide it as there are (layer, sequence) pairs.  Where LDS has room for a code and a
-// bucket entry per item (about 17000), they are ranked by value buckets as in the per-head mode, every head's items filled
-// up to a multiple of four so that a thread's four codes stay one access.  Beyond, and where ranking does not apply
-// (masked items kept, many equal keys, a wide spread, no sequence wanted), pooled_general() selects by radix, from the codes
-// in LDS if they are there; otherwise up to Hkv * cap = 65536 items, their codes in a workspace in global memory.
+// bucket entry per item (16032 where all may be kept, 19200 where 6000), they are ranked by value buckets as in the per-head
+// mode, every head's items filled up to a multiple of four so that a thread's four codes stay one access.  Beyond, and where
+// ranking does not apply (masked items kept, many equal keys, a wide spread, no sequence wanted), pooled_general() selects by
+// radix, from the codes in LDS if they are there; otherwise up to Hkv * cap = 65536 items, their codes in a workspace in
+// global memory.
 // The rows are moved by the same workgroup or, for few sequences, by a launch of one workgroup per head (see ngc_evict).
 // Rounds of half the rows, us, before (radix always, one launch) and now:
 //     sequences x heads x rows   16 x 2 x 500     16 x 8 x 300     16 x 8 x 2000   64 x 4 x 1500   128 x 2 x 4000

@@ -110,8 +110,8 @@ void score_keys_kernel(ScoreArgs a)
 
     const int lane = lane_id(), wv = wave_id();
     const int li = lane & 15, kg = lane >> 4;
-    // Workgroup -> (segment, share): the first shares of all segments come first.  Tile t of a segment belongs to wave t % 4
-    // of share (t / 4) % S.
+    // Workgroup -> (segment, share): the first shares of all segments come first.  Tile t of a segment belongs to wave
+    // t % WAVES of share (t / WAVES) % shares.
     const int share = (int)(blockIdx.x / a.nseg);
     const int seg = a.seg0 + (int)(blockIdx.x - share * a.nseg);
     const int first_tile = share * WAVES;

@@ -108,11 +108,15 @@ def test_launches_and_workgroups(L, B, H, cap, D):
     _round(L, B, H, cap, D, lens, keeps, cap, ["normal"])
 
 
-# two heads around what LDS ranks: 16384 items with every row kept, ~17400 with few, and beyond
-@pytest.mark.parametrize("cap,max_keep,share", [(8192, 8192, 1.0), (8191, 3000, 0.25), (8700, 3000, 0.25), (9001, 9001, 0.5)])
-def test_items_in_lds_and_beyond(cap, max_keep, share):
+# two heads: 160 KB hold 33536 bytes of 1024 threads, 6 and a bit for every item that is ranked and 2 for each that may be kept.
+# With all of them kept 16032 items (163800 of 163840 bytes), with 2 x 3000 19200 (163136); the next sizes go by radix.
+@pytest.mark.parametrize("cap,max_keep,share,kinds", [
+    (8016, 8016, 1.0, ["normal"]), (8020, 8020, 1.0, ["normal"]), (9600, 3000, 0.25, ["normal"]), (9700, 3000, 0.25, ["normal"]),
+    (8013, 8013, 0.5, ["equal", "masked"]), (8192, 8192, 1.0, ["normal"]), (8191, 3000, 0.25, ["normal"]),
+    (8700, 3000, 0.25, ["normal"]), (9001, 9001, 0.5, ["normal"])])
+def test_items_in_lds_and_beyond(cap, max_keep, share, kinds):
     lens, keeps = _ragged(np.random.default_rng(cap), 1, 2, 2, cap, share)
-    _round(1, 2, 2, cap, 64, lens, keeps, max_keep, ["normal"])
+    _round(1, 2, 2, cap, 64, lens, keeps, max_keep, kinds)
 
 
 @pytest.mark.parametrize("tau", [0.0, 1.0])
