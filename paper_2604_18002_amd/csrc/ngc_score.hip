@@ -408,9 +408,11 @@ struct ReduceArgs {
     const int32_t *len;
     int lb0_seg;        // first (layer*B + sequence) of the launch
     int Hkv, cap, block, pool;
-    int unit;           // rows per value: 1, or SC_TILE where the tiles' sums are reduced
 };
 
+// UNIT: rows per value, 1, or SC_TILE where the tiles' sums are reduced.  (As an argument it is a division per value: blocks of
+// 48, pooled, 64 x 4 segments of 1000 keys 30.6 -> 39.7 us in all.)
+template <int UNIT>
 __global__ __launch_bounds__(256) void score_reduce_kernel(ReduceArgs a)
 {
     const int lb = a.lb0_seg + blockIdx.x;
@@ -431,7 +433,7 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(ReduceArgs a)
         const int lo = j * block;
         const int hi = (lo + block < n) ? lo + block : n;
         float acc = 0.f;
-        for (int t = lo; t < hi; t += a.unit) acc += base[(size_t)h * a.cap + t / a.unit];
+        for (int t = lo; t < hi; t += UNIT) acc += base[(size_t)h * a.cap + t / UNIT];
         return acc / (float)(hi - lo);
     };
     for (int tile = 0; tile < max_items; tile += 256) {
@@ -624,15 +626,17 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     if (rc) return rc;
     // scores_out is indexed by the global segment; what follows gets the global base
     const int sequences = nseg / c->Hkv;
-    ReduceArgs ra{scores_out, c->len, seg0 / c->Hkv, c->Hkv, c->cap, block, pool ? 1 : 0, tiles ? SC_TILE : 1};
+    ReduceArgs ra{scores_out, c->len, seg0 / c->Hkv, c->Hkv, c->cap, block, pool ? 1 : 0};
     const bool whole = block == 1 || block == SC_TILE;       // an item's mean stands at its offset
     if (whole && pool) {
         const int columns = ((c->cap + block - 1) / block + 255) / 256;
         return launch(reinterpret_cast<const void *>(&pool_heads_kernel),
                       dim3((unsigned)sequences, (unsigned)(columns < 4096 ? columns : 4096)), dim3(256), 0, st, ra);
     }
-    if (!whole) return launch(reinterpret_cast<const void *>(&score_reduce_kernel), dim3((unsigned)sequences), dim3(256), 0,
-                               st, ra);
+    if (!whole)
+        return launch(tiles ? reinterpret_cast<const void *>(&score_reduce_kernel<SC_TILE>)
+                            : reinterpret_cast<const void *>(&score_reduce_kernel<1>),
+                      dim3((unsigned)sequences), dim3(256), 0, st, ra);
     return NGC_OK;
 }
 }  // namespace
