@@ -466,7 +466,13 @@ __global__ __launch_bounds__(256) void pool_heads_kernel(ReduceArgs a)
 {
     const int lb = a.lb0_seg + blockIdx.x;
     float *base = a.scores + (size_t)lb * a.Hkv * a.cap;
-    const int items = (a.cap + a.block - 1) / a.block;
+    int longest = 0;
+    for (int h = 0; h < a.Hkv; ++h) {
+        const int n = a.len[lb * a.Hkv + h];
+        longest = n > longest ? n : longest;
+    }
+    longest = longest < a.cap ? longest : a.cap;
+    const int items = (longest + a.block - 1) / a.block;
     for (int j = (int)(blockIdx.y * 256 + threadIdx.x); j < items; j += (int)gridDim.y * 256) {
         auto has_item = [&](int h) {
             int n = a.len[lb * a.Hkv + h];
@@ -549,6 +555,12 @@ int passes_shares(int nseg, int cap, int R, bool tiles)
     return S >= 4 ? S : 1;
 }
 
+// Workgroups that pool heads: enough for every CU, then more items each.  One per 256 items of the capacity costs as much as the
+// scores where the segments are short: per key, 448 x 2 segments, capacity 4000, us of one workgroup per sequence, of one per
+// 256 items and of 2048: 60 keys 10.6, 17.2 and 10.4, 1000 50.4, 53.6 and 48.3, 4000 189, 179 and 178; 256 x 4, capacity
+// 8000, 60 keys 11.5, 20.1 and 11.2, 2000 115, 109 and 102 (1024 and 4096 the same within 1 %).
+constexpr int POOL_WORKGROUPS = 2048;
+
 int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, const void *q_recent,
                  const float *lse_recent, int32_t w, float scale, uint32_t flags, int32_t block,
                  float *scores_out, void *ws, size_t ws_bytes, void *stream)
@@ -630,8 +642,9 @@ int launch_score(const ngc_cache *c, const ngc_paged_cache *pc, int32_t layer, c
     const bool whole = block == 1 || block == SC_TILE;       // an item's mean stands at its offset
     if (whole && pool) {
         const int columns = ((c->cap + block - 1) / block + 255) / 256;
+        const int most = (POOL_WORKGROUPS + sequences - 1) / sequences;
         return launch(reinterpret_cast<const void *>(&pool_heads_kernel),
-                      dim3((unsigned)sequences, (unsigned)(columns < 4096 ? columns : 4096)), dim3(256), 0, st, ra);
+                      dim3((unsigned)sequences, (unsigned)(columns < most ? columns : most)), dim3(256), 0, st, ra);
     }
     if (!whole)
         return launch(tiles ? reinterpret_cast<const void *>(&score_reduce_kernel<SC_TILE>)

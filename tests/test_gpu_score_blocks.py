@@ -49,3 +49,28 @@ def test_block_means_and_pooling(cap, D, Hq, block, pool, given):
                 if l == 1:
                     assert torch.equal(one[l, b, h, :want.numel()], x), (b, h)
     assert all(v == 0 for v in ngc.read_status(ws))
+
+
+# sequences that share the pooling workgroups: one to a sequence, two (three would be a thread per item), one per 256 items
+@pytest.mark.parametrize("B,H,cap", [(2049, 1, 300), (1100, 2, 700), (40, 3, 1030)])
+def test_pooling_workgroups(B, H, cap):
+    import torch
+    ngc = _ngc()
+    D, G, w = 64, 2, 1
+    g = torch.Generator(device="cuda").manual_seed(cap)
+    k = torch.randn(1, B, H, cap, D, generator=g, device="cuda").to(torch.bfloat16)
+    q = torch.randn(B, w, H * G, D, generator=g, device="cuda").to(torch.bfloat16)
+    n = torch.randint(0, cap + 1, (1, B, H), generator=g, device="cuda", dtype=torch.int32)
+    n[0, 0] = cap
+    n[0, 1] = 0
+    c = ngc.Cache(k, k, n, None, H * G)
+    ws = ngc.allocate_workspace(c, 1)
+    alone, pooled = torch.zeros(1, B, H, cap, device="cuda"), torch.full((1, B, H, cap), -1.0, device="cuda")
+    print(f"[score-blocks] pooling B={B} H={H} cap={cap}", flush=True)
+    ngc.ngc_score_keys(c, 0, q, w, D ** -0.5, 0, 1, alone, ws)
+    ngc.ngc_score_keys(c, 0, q, w, D ** -0.5, ngc.SCORE_POOL_HEADS, 1, pooled, ws)
+    has = torch.arange(cap, device="cuda") < n[..., None]
+    want = (alone.double() * has).sum(2, keepdim=True) / has.sum(2, keepdim=True).clamp(min=1)
+    # up to H fp32 additions and a division
+    assert (torch.where(has, (pooled.double() - want).abs(), 0.0) <= 1e-6 * want + 1e-30).all()
+    assert (pooled[~has] == -1.0).all()
