@@ -1011,7 +1011,7 @@ struct PooledKeys {
 // item indices stand in three dense arrays next to those in memory (K entries each, served by the L2 cache to the sort and to
 // the log-probability), the index buffers of the sort in LDS.  Writes the kept lists, sigma and its log-probability, and
 // leaves the kept slots before each head in misc.
-template <int THREADS>
+template <int THREADS, bool RANK>
 __device__ void pooled_general(const SelectArgs &a, int seg_first, int l, int b, int N, int K, const PooledKeys &keys,
                                uint32_t *hist, int *misc, uint16_t *idxA, uint16_t *idxB)
 {
@@ -1033,7 +1033,7 @@ __device__ void pooled_general(const SelectArgs &a, int seg_first, int l, int b,
     };
 
     // ---- 1. keys (and the first histogram of the radix select) -------------
-    const bool in_lds = keys.code != nullptr;
+    const bool in_lds = RANK && keys.code != nullptr;
     if (in_lds) {
         N = 4 * misc[PM_QUAD + Hkv];
         if (tid <= Hkv) misc[PM_OFF + tid] = 4 * misc[PM_QUAD + tid];
@@ -1216,7 +1216,9 @@ __device__ void pooled_general(const SelectArgs &a, int seg_first, int l, int b,
     }
 }
 
-template <int THREADS, int ROW_BYTES, int UNROLL>
+// RANK: LDS has been given for ranking (a.rank_cap).  Where it has not, a kernel without that code: 896 x 2 x 300 rows without
+// sampled orders 34.8 -> 38.0 us with it, 16 x 2 x 500 10.5 -> 11.0.
+template <int THREADS, int ROW_BYTES, int UNROLL, bool RANK>
 __global__ __launch_bounds__(THREADS) void evict_pooled_kernel(SelectArgs a)
 {
     constexpr int NW = THREADS / NGC_WAVE;
@@ -1226,9 +1228,10 @@ __global__ __launch_bounds__(THREADS) void evict_pooled_kernel(SelectArgs a)
     int *misc = reinterpret_cast<int *>(hist + HIST);
     u32x4 *maxima = reinterpret_cast<u32x4 *>(misc + PM_WORDS);
     // ranking: rank_cap codes, then as many bits
-    uint32_t *rank_code = reinterpret_cast<uint32_t *>(misc + PM_WORDS + (a.rank_cap > 0 ? PM_MAXIMA : 0));
-    uint32_t *kept_bits = rank_code + a.rank_cap;
-    uint16_t *idxA = reinterpret_cast<uint16_t *>(kept_bits + (a.rank_cap + 63) / 64 * 2);
+    const int rank_cap = RANK ? a.rank_cap : 0;
+    uint32_t *rank_code = reinterpret_cast<uint32_t *>(misc + PM_WORDS + (RANK ? PM_MAXIMA : 0));
+    uint32_t *kept_bits = rank_code + rank_cap;
+    uint16_t *idxA = reinterpret_cast<uint16_t *>(kept_bits + (rank_cap + 63) / 64 * 2);
     uint16_t *idxB = idxA + a.keep_cap;                                      // max(keep_cap, rank_cap) entries
     float *fmisc = reinterpret_cast<float *>(misc);
 
@@ -1289,7 +1292,7 @@ __global__ __launch_bounds__(THREADS) void evict_pooled_kernel(SelectArgs a)
     bool ranked = false;
     float unpicked = 0.f, smax = -INFINITY;
     PooledKeys keys{nullptr, 0u, -INFINITY, false};
-    if (want_sort && 4 * quads <= a.rank_cap) {
+    if (RANK && want_sort && 4 * quads <= rank_cap) {
         for (int i = tid; i < HIST / 4; i += THREADS) reinterpret_cast<u32x4 *>(hist)[i] = u32x4{0u, 0u, 0u, 0u};
         for (int i = tid; i < (4 * quads + 63) / 64 * 2; i += THREADS) kept_bits[i] = 0;
         float neg_smin = -INFINITY;
@@ -1399,7 +1402,7 @@ __global__ __launch_bounds__(THREADS) void evict_pooled_kernel(SelectArgs a)
             }
         }
     }
-    if (!ranked) pooled_general<THREADS>(a, seg_first, l, b, N, K, keys, hist, misc, idxA, idxB);
+    if (!ranked) pooled_general<THREADS, RANK>(a, seg_first, l, b, N, K, keys, hist, misc, idxA, idxB);
     if (tid < Hkv) {
         const int kept = misc[PM_BASE + tid + 1] - misc[PM_BASE + tid];
         if (kept > a.max_keep) atomicAdd(&a.status[NGC_STATUS_KEEP_CLAMPED], 1);
@@ -1843,7 +1846,8 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
             const long long second = ranked > keep_cap ? ranked : keep_cap;
             return fixed + (ranked > 0 ? PM_MAXIMA * 4 : 0) + (size_t)ranked * 4 + (size_t)((ranked + 63) / 64) * 8 + (size_t)keep_cap * 2 + (size_t)second * 2;
         };
-        int rank_cap = (int)((4 * quads + 7) & ~7LL);
+        // (without a sequence or its log-probability nothing is ranked, and the LDS for it would keep a second workgroup off the CU)
+        int rank_cap = sigma_out || logp_out ? (int)((4 * quads + 7) & ~7LL) : 0;
         if (lds_for(rank_cap) > 160 * 1024) rank_cap = 0;
         size_t lds = lds_for(rank_cap);
         if (lds > 160 * 1024) {
@@ -1865,9 +1869,12 @@ extern "C" int ngc_evict(const ngc_cache *c, int32_t layer, const float *logits,
         sa.g = SegGeom{c->B, c->Hkv, c->cap, 1};
         sa.logit_stride = c->cap;
         sa.na = NoiseArgs{p->seed, p->round, p->noise_scale, p->share_heads, p->layer_base, p->seq_base};
-#define NGC_PICK(KERNEL, T, U) ((c->D == 128) ? reinterpret_cast<const void *>(&KERNEL<T, 256, U>) \
-                                              : reinterpret_cast<const void *>(&KERNEL<T, 128, U>))
-        const void *select = threads == 1024 ? NGC_PICK(evict_pooled_kernel, 1024, 4) : NGC_PICK(evict_pooled_kernel, 512, 8);
+#define NGC_PICK(KERNEL, T, ...) ((c->D == 128) ? reinterpret_cast<const void *>(&KERNEL<T, 256, __VA_ARGS__>) \
+                                                : reinterpret_cast<const void *>(&KERNEL<T, 128, __VA_ARGS__>))
+        const void *select = rank_cap > 0 ? (threads == 1024 ? NGC_PICK(evict_pooled_kernel, 1024, 4, true)
+                                                             : NGC_PICK(evict_pooled_kernel, 512, 8, true))
+                                          : (threads == 1024 ? NGC_PICK(evict_pooled_kernel, 1024, 4, false)
+                                                             : NGC_PICK(evict_pooled_kernel, 512, 8, false));
         if (lds > 64 * 1024)
             NGC_HIP_CHECK(hipFuncSetAttribute(select, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         void *kargs[] = {&sa};
