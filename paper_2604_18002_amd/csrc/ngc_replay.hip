@@ -155,9 +155,16 @@ __global__ __launch_bounds__(LIST_THREADS) void replay_lists_kernel(ReplayArgs a
 //     B  heads         T = 130          350            600           1050            1500            2000
 //     2  28/4      13.1 -> 10.0   15.7 -> 12.6   18.5 -> 15.1   26.3 -> 22.8    41.0 -> 37.8    50.8 -> 48.1
 //    16  12/2      14.5 -> 11.0   25.5 -> 24.1   39.5 -> 36.1   75.8 -> 73.4   133.3 -> 132.0    197 -> 197
-// i.e. nothing to gain beyond, where a list also no longer fits beside the tiles of two workgroups a CU.
+// i.e. nothing to gain beyond, where a list also no longer fits beside the tiles of two workgroups a CU.  A launch of many
+// workgroups whose lists are shared by query heads hides the list kernel better than each workgroup its own list, beyond some
+// 1600 positions: B = 32, 28/4 at D = 64, one set of decisions, T = 1600 / 1792 / 2048 357 -> 361, 401 -> 413, 477 -> 497; B = 64,
+// 12/2 305 -> 308, 347 -> 357, 416 -> 431; 16, 28/4 at D = 128, a set per KV head, 358 -> 355 and 431 -> 429 (1792, 2048).  Up to 4096
+// workgroups, or with a set of decisions for every query head, it stays the other way: 8, 28/4 at D = 64, T = 2048 129 -> 130 (one
+// set), 16, 12/2 109 -> 110, 256, 4/4 at D = 128 1115 -> 1081 (a set per head).
 constexpr int OWN_BITS = 8;
 constexpr int OWN_MAX = LIST_THREADS * OWN_BITS;
+constexpr int OWN_ALWAYS = 1536;              // positions
+constexpr int OWN_WORKGROUPS = 4096;          // beyond them, where lists are shared
 static_assert(LIST_THREADS == RP_WAVES * NGC_WAVE, "a workgroup of the attention kernel makes its list");
 template <bool OWN>
 struct OwnList {
@@ -620,7 +627,8 @@ extern "C" int ngc_replay_attn(const void *q, const void *k, const void *v, cons
     size_t counts = (size_t)B * ra.Hd * nqt * sizeof(int32_t);
     counts = (counts + 255) & ~(size_t)255;
     ra.steps = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(ws) + 256 + lists + counts);
-    const bool own = T <= OWN_MAX;       // (the list needs 8 KB beside the tiles: two workgroups still share a CU)
+    // (the list needs 8 KB beside the tiles: two workgroups still share a CU)
+    const bool own = T <= OWN_ALWAYS || (T <= OWN_MAX && (ra.Hd == Hq || (long long)nqt * Hq * B <= OWN_WORKGROUPS));
     if (!own) {
         hipLaunchKernelGGL(replay_lists_kernel, dim3(nqt, B * ra.Hd), dim3(LIST_THREADS), 0, st, ra);
         NGC_HIP_CHECK(hipGetLastError());
